@@ -384,7 +384,7 @@ void run_levels_slm(dc_ctx* c, const int32_t* active, int64_t n_active) {
     // 5. start partition of the compacted graph: the parent communities (also
     // when nothing was reduced: then it is the final partition, over the
     // coarse ids, which may permute the level's ids)
-    parent_start(par, Cl, c->cs.rank.as<int32_t>(), g.n, c->first.as<int32_t>(), Cn, st);
+    parent_start(par, Cl, c->cs.rank.as<int32_t>(), g.n, h.n, c->first.as<int32_t>(), Cn, st);
     g = h;
     level++;
     {

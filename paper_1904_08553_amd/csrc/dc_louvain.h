@@ -370,8 +370,9 @@ void apply_pre(const int32_t* list, int64_t cnt, const uint8_t* R, const int32_t
 int64_t induced_subgraph(const LevelView& g, const int32_t* C, int32_t* cnt, int32_t* off_s,
                          DBuf& adj_s, void* host, hipStream_t st);
 // Cnext[rank[R[u]]] = the smallest rank[R[v]] over v with P[v] == P[u]
-// (first: n ints of scratch): the parents' partition over the coarse ids.
-void parent_start(const int32_t* P, const int32_t* R, const int32_t* rank, int32_t n,
+// (first: n ints of scratch; nc coarse ids): the parents' partition over the
+// coarse ids.
+void parent_start(const int32_t* P, const int32_t* R, const int32_t* rank, int32_t n, int32_t nc,
                   int32_t* first, int32_t* Cnext, hipStream_t st);
 // a[X] = sum of k over members of label X, sz[X] = their number.
 void totals_sizes(const int32_t* k, const int32_t* C, int32_t n, int32_t* a, int32_t* sz,

@@ -69,24 +69,45 @@ __global__ void __launch_bounds__(TPB)
   }
 }
 
-// first[P[u]] = min over u of rank[R[u]] (first: filled with INT32_MAX).
-__global__ void k_parent_first(const int32_t* __restrict__ P, const int32_t* __restrict__ R,
-                               const int32_t* __restrict__ rank, int32_t n,
-                               int32_t* __restrict__ first) {
+// par[rank[R[u]]] = P[u]: the parent label of every coarse vertex (each member
+// of a refined community writes the same value).
+__global__ void k_coarse_parent(const int32_t* __restrict__ P, const int32_t* __restrict__ R,
+                                const int32_t* __restrict__ rank, int32_t n,
+                                int32_t* __restrict__ par) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
   for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < n; u += stride)
-    atomicMin(&first[P[u]], rank[R[u]]);
+    par[rank[R[u]]] = P[u];
 }
 
-// Cnext[rank[R[u]]] = first[P[u]]: every member of a refined community
-// writes the same value.
-__global__ void k_parent_start(const int32_t* __restrict__ P, const int32_t* __restrict__ R,
-                               const int32_t* __restrict__ rank,
-                               const int32_t* __restrict__ first, int32_t n,
-                               int32_t* __restrict__ Cnext) {
+// first[par[c]] = min c (first: filled with INT32_MAX): one atomic per
+// distinct parent of a wave's 64 consecutive coarse vertices, from its first
+// (smallest) one.  Bound by same-address atomics: taking the minimum over the
+// level's vertices instead (one atomic each, a parent holding thousands of
+// them) took 363 us for 200,003 vertices in 200 parents, this and the two
+// kernels around it about 10 us.
+__global__ void __launch_bounds__(TPB)
+    k_parent_first(const int32_t* __restrict__ par, int32_t nc, int32_t* __restrict__ first) {
+  const int lane = lane_id();
+  const int64_t stride = int64_t(gridDim.x) * TPB;
+  // whole waves: the loop runs while the wave's first coarse vertex is in range
+  for (int64_t c = int64_t(blockIdx.x) * TPB + threadIdx.x; c - lane < nc; c += stride) {
+    const bool valid = c < nc;
+    const int32_t p = par[valid ? c : nc - 1];
+    for (uint64_t todo = __ballot(valid); todo;) {
+      const int l = __ffsll((unsigned long long)todo) - 1;
+      const int32_t pl = __builtin_amdgcn_readlane(p, l);
+      if (lane == l) atomicMin(&first[p], int32_t(c));
+      todo &= ~__ballot(p == pl);
+    }
+  }
+}
+
+// start[c] = first[start[c]]: from the parent's label to its smallest coarse id.
+__global__ void k_parent_start(const int32_t* __restrict__ first, int32_t nc,
+                               int32_t* __restrict__ start) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < n; u += stride)
-    Cnext[rank[R[u]]] = first[P[u]];
+  for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c < nc; c += stride)
+    start[c] = first[start[c]];
 }
 
 // a[C[x]] += k[x], sz[C[x]] += 1 (a, sz zeroed), pre-combined per block.
@@ -142,13 +163,15 @@ int64_t induced_subgraph(const LevelView& g, const int32_t* C, int32_t* cnt, int
   return nnz;
 }
 
-void parent_start(const int32_t* P, const int32_t* R, const int32_t* rank, int32_t n,
+void parent_start(const int32_t* P, const int32_t* R, const int32_t* rank, int32_t n, int32_t nc,
                   int32_t* first, int32_t* Cnext, hipStream_t st) {
-  if (n <= 0) return;
+  if (n <= 0 || nc <= 0) return;
   fill_i32(first, 0x7fffffff, n, st);
-  k_parent_first<<<grid_for(n), TPB, 0, st>>>(P, R, rank, n, first);
+  k_coarse_parent<<<grid_for(n), TPB, 0, st>>>(P, R, rank, n, Cnext);
   DC_LAUNCH_CHECK();
-  k_parent_start<<<grid_for(n), TPB, 0, st>>>(P, R, rank, first, n, Cnext);
+  k_parent_first<<<grid_for(nc), TPB, 0, st>>>(Cnext, nc, first);
+  DC_LAUNCH_CHECK();
+  k_parent_start<<<grid_for(nc), TPB, 0, st>>>(first, nc, Cnext);
   DC_LAUNCH_CHECK();
 }
 
