@@ -54,10 +54,13 @@ void mark_touched(const int32_t* list, const int32_t* count, int64_t max_count,
 void mlp_forward(const uint16_t* wq, const uint16_t* X, int64_t n, float* logits, hipStream_t st);
 
 // Mean weighted BCE gradient (and loss) into grad[GRAD_SLOTS] (device),
-// deterministic for a given n.  partial: scratch of mlp_partial_floats(n).
+// deterministic for a given n.  partial: scratch of mlp_partial_floats(n);
+// host (may be null): the device address of pinned host memory that receives
+// grad too, to be read after a wait on the stream.
 int64_t mlp_partial_floats(int64_t n);
 void mlp_grad(const uint16_t* wq, const uint16_t* X, const uint8_t* y, int64_t n,
-              float pos_weight, float* partial, float* grad, hipStream_t st);
+              float pos_weight, float* partial, float* grad, hipStream_t st,
+              float* host = nullptr);
 
 // One Adam step on the fp32 master w (moments m, v), refreshing wq.
 void mlp_adam(float* w, float* m, float* v, const float* grad, int step, float lr, uint16_t* wq,

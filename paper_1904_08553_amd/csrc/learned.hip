@@ -33,12 +33,26 @@ constexpr int NW = TPB / WAVE;
 
 typedef short s4v __attribute__((ext_vector_type(4)));
 typedef __bf16 b8v __attribute__((ext_vector_type(8)));
+typedef __bf16 b2v __attribute__((ext_vector_type(2)));
+typedef float f2v __attribute__((ext_vector_type(2)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf16_val(uint32_t b) { return __uint_as_float(b << 16); }
 __device__ __forceinline__ uint32_t pack2(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
+
+// Two fp32 values rounded to bfloat16 (nearest even, as bf16_bits) and packed:
+// one v_cvt_pk_bf16_f32.  The forward pass is bound by vector instruction
+// issue, and the integer form of bf16_bits is four of them a value for 128
+// rounded activations a sample: with the pairs, one-instruction relu and the
+// next tile's features loaded ahead 1,000,003 samples take 28 us, before 38.
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{lo, hi}, b2v));
+}
+// The two values of a pair, exact in fp32.
+__device__ __forceinline__ float pair_lo(uint32_t p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float pair_hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
 
 __device__ __forceinline__ f4v mma16(u2v a, u2v b, f4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4v, a),
@@ -55,6 +69,19 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// max(x, 0), 0 for NaN, in one instruction: the median of x, 0 and inf,
+// where inf comes from big() so that the compiler keeps the median (with a
+// constant it turns it back into fmaxf, which costs a second instruction
+// that quiets a signalling NaN first).
+__device__ __forceinline__ float big() {
+  float x;
+  asm("s_mov_b32 %0, 0x7f800000" : "=s"(x));
+  return x;
+}
+__device__ __forceinline__ float relu(float x, float inf) {
+  return __builtin_amdgcn_fmed3f(x, 0.f, inf);
 }
 
 // K slot (q, j) of block kb of a layer-2 contraction: the hidden unit that
@@ -97,29 +124,32 @@ __device__ __forceinline__ void load_net(const uint16_t* __restrict__ wq, Net& N
 struct Fwd {
   u2v xb;           // X[s][4q .. 4q+3] (q < 2), the layer-1 B operand
   f4v z1[4];        // pre-activations of unit 16mb + 4q + i, sample r
-  uint32_t h1[4][4];
-  u4v hb[2];        // layer-2 B operand (bf16 h1 in K-slot order)
+  u4v hb[2];        // layer-2 B operand: bf16 h1 in K-slot order, so units 2p and
+                    // 2p + 1 of block mb are the pair hb[mb / 2][2 (mb % 2) + p]
   f4v z2[4];
   float h2[4][4];
   float z3;         // logit of sample r (every q)
 };
 
-__device__ __forceinline__ void forward_tile(const Net& N, const uint16_t* __restrict__ X,
-                                             int64_t n, int64_t s0, int q, int r, Fwd& F) {
-  const int64_t s = s0 + r;
-  F.xb = (q < 2 && s < n) ? *reinterpret_cast<const u2v*>(X + s * MLP_IN + 4 * q) : u2v{0u, 0u};
+// The layer-1 operand of tile t (samples 16t + r; zero past n).
+__device__ __forceinline__ u2v load_x(const uint16_t* __restrict__ X, int64_t n, int64_t t, int q,
+                                      int r) {
+  const int64_t s = t * 16 + r;
+  return (q < 2 && s < n) ? *reinterpret_cast<const u2v*>(X + s * MLP_IN + 4 * q) : u2v{0u, 0u};
+}
+
+__device__ __forceinline__ void forward_tile(const Net& N, u2v xb, Fwd& F) {
+  const float inf = big();
+  F.xb = xb;
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) {
     f4v acc = {N.b1[mb][0], N.b1[mb][1], N.b1[mb][2], N.b1[mb][3]};
     F.z1[mb] = mma16(N.w1[mb], F.xb, acc);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) F.h1[mb][i] = bf16_bits(fmaxf(F.z1[mb][i], 0.f));
+    for (int p = 0; p < 2; ++p)
+      F.hb[mb / 2][2 * (mb % 2) + p] =
+          bf16_pair(relu(F.z1[mb][2 * p], inf), relu(F.z1[mb][2 * p + 1], inf));
   }
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-    F.hb[kb] = u4v{pack2(F.h1[2 * kb][0], F.h1[2 * kb][1]), pack2(F.h1[2 * kb][2], F.h1[2 * kb][3]),
-                   pack2(F.h1[2 * kb + 1][0], F.h1[2 * kb + 1][1]),
-                   pack2(F.h1[2 * kb + 1][2], F.h1[2 * kb + 1][3])};
   float part = 0.f;
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) {
@@ -128,27 +158,34 @@ __device__ __forceinline__ void forward_tile(const Net& N, const uint16_t* __res
     acc = mma32(N.w2[mb][1], F.hb[1], acc);
     F.z2[mb] = acc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      F.h2[mb][i] = bf16_val(bf16_bits(fmaxf(acc[i], 0.f)));
-      part += N.w3[mb][i] * F.h2[mb][i];
+    for (int p = 0; p < 2; ++p) {
+      const uint32_t h = bf16_pair(relu(acc[2 * p], inf), relu(acc[2 * p + 1], inf));
+      F.h2[mb][2 * p] = pair_lo(h);
+      F.h2[mb][2 * p + 1] = pair_hi(h);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) part += N.w3[mb][i] * F.h2[mb][i];
   }
   part += __shfl_xor(part, 16, WAVE);
   part += __shfl_xor(part, 32, WAVE);
   F.z3 = part + N.b3;
 }
 
-__global__ void __launch_bounds__(TPB)
+__global__ void __launch_bounds__(TPB, 4)
     k_mlp_forward(const uint16_t* __restrict__ wq, const uint16_t* __restrict__ X, int64_t n,
                   float* __restrict__ logits) {
   const int lane = lane_id(), q = lane >> 4, r = lane & 15;
   const int wid = threadIdx.x / WAVE;
   Net N;
   load_net(wq, N, q, r);
-  const int64_t tiles = ceil_div(n, 16);
-  for (int64_t t = int64_t(blockIdx.x) * NW + wid; t < tiles; t += int64_t(gridDim.x) * NW) {
+  const int64_t tiles = ceil_div(n, 16), step = int64_t(gridDim.x) * NW;
+  int64_t t = int64_t(blockIdx.x) * NW + wid;
+  u2v xb = load_x(X, n, t, q, r);
+  for (; t < tiles; t += step) {
+    const u2v next = load_x(X, n, t + step, q, r);  // in flight during this tile
     Fwd F;
-    forward_tile(N, X, n, t * 16, q, r, F);
+    forward_tile(N, xb, F);
+    xb = next;
     if (q == 0 && t * 16 + r < n) logits[t * 16 + r] = F.z3;
   }
 }
@@ -170,10 +207,15 @@ __global__ void __launch_bounds__(TPB)
     k_mlp_grad(const uint16_t* __restrict__ wq, const uint16_t* __restrict__ X,
                const uint8_t* __restrict__ y, int64_t n, float pw, float inv_n,
                float* __restrict__ partial) {
-  __shared__ float acc[GRAD_SLOTS];
-  __shared__ __align__(16) uint16_t lt[NW][4][MLP_HID * 16];
+  // the waves' tile buffers, then (after the last tile) their sums: one LDS
+  // row per wave and one barrier, where adding wave after wave into one row
+  // took a barrier and a read-modify-write of every slot per wave (8,192
+  // samples, with the packed rounding: 12.9 us, before 21.3)
+  __shared__ union {
+    __align__(16) uint16_t lt[NW][4][MLP_HID * 16];
+    float acc[NW][GRAD_SLOTS];
+  } lds;
   const int wid = threadIdx.x / WAVE, lane = lane_id(), q = lane >> 4, r = lane & 15;
-  for (int p = threadIdx.x; p < GRAD_SLOTS; p += TPB) acc[p] = 0.f;
   Net N;
   load_net(wq, N, q, r);
   // A operand of dh1^T = W2^T dz2^T: row = hidden unit 16mj + r, K slots as
@@ -201,15 +243,15 @@ __global__ void __launch_bounds__(TPB)
     }
   }
   float gb3 = 0.f, gloss = 0.f;
-  uint16_t* Ldz2 = lt[wid][0];  // [unit][sample]
-  uint16_t* Lh1 = lt[wid][1];
-  uint16_t* Ldz1 = lt[wid][2];
-  uint16_t* LX = lt[wid][3];    // [feature (16 rows, 8..15 zero)][sample]
+  uint16_t* Ldz2 = lds.lt[wid][0];  // [unit][sample]
+  uint16_t* Lh1 = lds.lt[wid][1];
+  uint16_t* Ldz1 = lds.lt[wid][2];
+  uint16_t* LX = lds.lt[wid][3];    // [feature (16 rows, 8..15 zero)][sample]
   const int64_t tiles = ceil_div(n, 16);
   for (int64_t t = int64_t(blockIdx.x) * NW + wid; t < tiles; t += int64_t(gridDim.x) * NW) {
     const int64_t s = t * 16 + r;
     Fwd F;
-    forward_tile(N, X, n, t * 16, q, r, F);
+    forward_tile(N, load_x(X, n, t, q, r), F);
     const bool valid = s < n;
     const float yv = valid ? float(y[s]) : 0.f;
     const float z = F.z3;
@@ -219,17 +261,26 @@ __global__ void __launch_bounds__(TPB)
       gloss += pw * yv * softplus(-z) + (1.f - yv) * softplus(z);
       gb3 += dz3;
     }
-    uint32_t d2[4][4];
+    u4v db[2];  // bf16 dz2 in K-slot order, the pairs as in F.hb
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        gw3[mb][i] += dz3 * F.h2[mb][i];
-        d2[mb][i] = bf16_bits(F.z2[mb][i] > 0.f ? dz3 * N.w3[mb][i] : 0.f);
-        gb2[mb][i] += bf16_val(d2[mb][i]);
-        const int u = 16 * mb + 4 * q + i;
-        Ldz2[u * 16 + r] = uint16_t(d2[mb][i]);
-        Lh1[u * 16 + r] = uint16_t(F.h1[mb][i]);
+      for (int p = 0; p < 2; ++p) {
+        float d[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          gw3[mb][2 * p + i] += dz3 * F.h2[mb][2 * p + i];
+          d[i] = F.z2[mb][2 * p + i] > 0.f ? dz3 * N.w3[mb][2 * p + i] : 0.f;
+        }
+        const uint32_t b = bf16_pair(d[0], d[1]), h = F.hb[mb / 2][2 * (mb % 2) + p];
+        db[mb / 2][2 * (mb % 2) + p] = b;
+        gb2[mb][2 * p] += pair_lo(b);
+        gb2[mb][2 * p + 1] += pair_hi(b);
+        const int u = 16 * mb + 4 * q + 2 * p;
+        Ldz2[u * 16 + r] = uint16_t(b);
+        Ldz2[(u + 1) * 16 + r] = uint16_t(b >> 16);
+        Lh1[u * 16 + r] = uint16_t(h);
+        Lh1[(u + 1) * 16 + r] = uint16_t(h >> 16);
       }
     {
       const uint32_t xs[4] = {F.xb.x & 0xffffu, F.xb.x >> 16, F.xb.y & 0xffffu, F.xb.y >> 16};
@@ -248,22 +299,20 @@ __global__ void __launch_bounds__(TPB)
       }
     }
     // dh1^T = W2^T dz2^T, then dz1 = bf16(dh1 * [z1 > 0])
-    u4v db[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-      db[kb] = u4v{pack2(d2[2 * kb][0], d2[2 * kb][1]), pack2(d2[2 * kb][2], d2[2 * kb][3]),
-                   pack2(d2[2 * kb + 1][0], d2[2 * kb + 1][1]),
-                   pack2(d2[2 * kb + 1][2], d2[2 * kb + 1][3])};
 #pragma unroll
     for (int mj = 0; mj < 4; ++mj) {
       f4v h = {0.f, 0.f, 0.f, 0.f};
       h = mma32(w2t[mj][0], db[0], h);
       h = mma32(w2t[mj][1], db[1], h);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t b = bf16_bits(F.z1[mj][i] > 0.f ? h[i] : 0.f);
-        gb1[mj][i] += bf16_val(b);
-        Ldz1[(16 * mj + 4 * q + i) * 16 + r] = uint16_t(b);
+      for (int p = 0; p < 2; ++p) {
+        const uint32_t b = bf16_pair(F.z1[mj][2 * p] > 0.f ? h[2 * p] : 0.f,
+                                     F.z1[mj][2 * p + 1] > 0.f ? h[2 * p + 1] : 0.f);
+        gb1[mj][2 * p] += pair_lo(b);
+        gb1[mj][2 * p + 1] += pair_hi(b);
+        const int u = 16 * mj + 4 * q + 2 * p;
+        Ldz1[u * 16 + r] = uint16_t(b);
+        Ldz1[(u + 1) * 16 + r] = uint16_t(b >> 16);
       }
     }
     wave_sync();
@@ -286,40 +335,60 @@ __global__ void __launch_bounds__(TPB)
     }
   gb3 = wave_sum(gb3);
   gloss = wave_sum(gloss);
-  __syncthreads();  // acc cleared
-  for (int w = 0; w < NW; ++w) {
-    if (wid == w) {
+  __syncthreads();  // every wave is done with its tile buffers
+  {
+    float* const acc = lds.acc[wid];
 #pragma unroll
-      for (int mo = 0; mo < 4; ++mo)
+    for (int mo = 0; mo < 4; ++mo)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int o = 16 * mo + 4 * q + i;
+      for (int i = 0; i < 4; ++i) {
+        const int o = 16 * mo + 4 * q + i;
 #pragma unroll
-          for (int mj = 0; mj < 4; ++mj) acc[OFF_W2 + o * MLP_HID + 16 * mj + r] += gW2[mo][mj][i];
-          if (r < MLP_IN) acc[OFF_W1 + o * MLP_IN + r] += gW1[mo][i];
-          if (r == 0) {
-            acc[OFF_W3 + o] += gw3[mo][i];
-            acc[OFF_B2 + o] += gb2[mo][i];
-            acc[OFF_B1 + o] += gb1[mo][i];
-          }
+        for (int mj = 0; mj < 4; ++mj) acc[OFF_W2 + o * MLP_HID + 16 * mj + r] = gW2[mo][mj][i];
+        if (r < MLP_IN) acc[OFF_W1 + o * MLP_IN + r] = gW1[mo][i];
+        if (r == 0) {
+          acc[OFF_W3 + o] = gw3[mo][i];
+          acc[OFF_B2 + o] = gb2[mo][i];
+          acc[OFF_B1 + o] = gb1[mo][i];
         }
-      if (lane == 0) {
-        acc[OFF_B3] += gb3;
-        acc[MLP_P] += gloss;
       }
+    if (lane == 0) {
+      acc[OFF_B3] = gb3;
+      acc[MLP_P] = gloss;
     }
-    __syncthreads();
   }
-  for (int p = threadIdx.x; p < GRAD_SLOTS; p += TPB)
-    partial[int64_t(blockIdx.x) * GRAD_SLOTS + p] = acc[p];
+  __syncthreads();
+  for (int p = threadIdx.x; p < GRAD_SLOTS; p += TPB) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) s += lds.acc[w][p];
+    partial[int64_t(blockIdx.x) * GRAD_SLOTS + p] = s;
+  }
 }
 
-__global__ void k_grad_reduce(const float* __restrict__ partial, int nblocks, float* grad) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// grad[p] = the blocks' sums in block order, RD_BATCH loads in flight at a
+// time; host (may be null): pinned host memory that receives the same values.
+// Bound by load latency: one dependent load per block took 30 us for 128
+// blocks, the batches 4.7 us.
+constexpr int RD_TPB = 64;
+constexpr int RD_BATCH = 32;
+__global__ void __launch_bounds__(RD_TPB)
+    k_grad_reduce(const float* __restrict__ partial, int nblocks, float* grad, float* host) {
+  const int p = blockIdx.x * RD_TPB + threadIdx.x;
   if (p >= GRAD_SLOTS) return;
+  const float* col = partial + p;
   float s = 0.f;
-  for (int b = 0; b < nblocks; ++b) s += partial[int64_t(b) * GRAD_SLOTS + p];
+  int b = 0;
+  for (; b + RD_BATCH <= nblocks; b += RD_BATCH) {
+    float v[RD_BATCH];
+#pragma unroll
+    for (int j = 0; j < RD_BATCH; ++j) v[j] = col[int64_t(b + j) * GRAD_SLOTS];
+#pragma unroll
+    for (int j = 0; j < RD_BATCH; ++j) s += v[j];
+  }
+  for (; b < nblocks; ++b) s += col[int64_t(b) * GRAD_SLOTS];
   grad[p] = s;
+  if (host) host_store(host + p, s);
 }
 
 __global__ void k_adam(float* w, float* m, float* v, const float* __restrict__ g, float lr,
@@ -479,11 +548,11 @@ void mlp_forward(const uint16_t* wq, const uint16_t* X, int64_t n, float* logits
 int64_t mlp_partial_floats(int64_t n) { return int64_t(grad_blocks(n)) * GRAD_SLOTS; }
 
 void mlp_grad(const uint16_t* wq, const uint16_t* X, const uint8_t* y, int64_t n,
-              float pos_weight, float* partial, float* grad, hipStream_t st) {
+              float pos_weight, float* partial, float* grad, hipStream_t st, float* host) {
   const int nb = grad_blocks(n);
   k_mlp_grad<<<nb, TPB, 0, st>>>(wq, X, y, n, pos_weight, n > 0 ? 1.f / float(n) : 0.f, partial);
   DC_LAUNCH_CHECK();
-  k_grad_reduce<<<int(ceil_div(GRAD_SLOTS, TPB)), TPB, 0, st>>>(partial, nb, grad);
+  k_grad_reduce<<<int(ceil_div(GRAD_SLOTS, RD_TPB)), RD_TPB, 0, st>>>(partial, nb, grad, host);
   DC_LAUNCH_CHECK();
 }
 
@@ -540,6 +609,7 @@ struct dc_mlp {
   hipStream_t st = nullptr;
   DBuf w, m, v, wq, grad, partial;
   float* hgrad = nullptr;  // pinned, GRAD_SLOTS floats
+  float* hgrad_dev = nullptr;  // its device address
   int step = 0;
 };
 
@@ -580,10 +650,12 @@ void upload_weights(dc_mlp* m, const float* w) {
   m->step = 0;
 }
 
-void run_grad(dc_mlp* m, const uint16_t* X, const uint8_t* y, int64_t n, float pw) {
+// host: the reduction also writes its sums to m->hgrad (no copy).
+void run_grad(dc_mlp* m, const uint16_t* X, const uint8_t* y, int64_t n, float pw, bool host) {
   m->partial.ensure(size_t(mlp_partial_floats(n)) * 4);
   m->grad.ensure(GRAD_SLOTS * 4);
-  mlp_grad(m->wq.as<uint16_t>(), X, y, n, pw, m->partial.as<float>(), m->grad.as<float>(), m->st);
+  mlp_grad(m->wq.as<uint16_t>(), X, y, n, pw, m->partial.as<float>(), m->grad.as<float>(), m->st,
+           host ? m->hgrad_dev : nullptr);
 }
 
 }  // namespace
@@ -598,6 +670,7 @@ dc_status dc_mlp_create(dc_mlp** out, const float* w, void* stream) {
   m->st = static_cast<hipStream_t>(stream);
   dc_status s = mlp_guarded(m, [&] {
     DC_HIP(hipHostMalloc(reinterpret_cast<void**>(&m->hgrad), GRAD_SLOTS * 4));
+    DC_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&m->hgrad_dev), m->hgrad, 0));
     (void)scratch_on_current_device();  // set-up of dc_mlp_grad_noalloc's scratch
     upload_weights(m, w);
     return DC_OK;
@@ -640,8 +713,7 @@ dc_status dc_mlp_grad(dc_mlp* m, const uint16_t* X, const uint8_t* y, int64_t n,
                       float pos_weight, float* grad, double* loss) {
   if (n < 1 || !X || !y || !(pos_weight > 0.f)) return DC_E_ARG;
   return mlp_guarded(m, [&] {
-    run_grad(m, X, y, n, pos_weight);
-    DC_HIP(hipMemcpyAsync(m->hgrad, m->grad.p, GRAD_SLOTS * 4, hipMemcpyDeviceToHost, m->st));
+    run_grad(m, X, y, n, pos_weight, true);
     DC_HIP(hipStreamSynchronize(m->st));
     if (grad) std::memcpy(grad, m->hgrad, MLP_P * 4);
     if (loss) *loss = double(m->hgrad[MLP_P]) / double(n);
@@ -662,8 +734,8 @@ dc_status dc_mlp_grad_noalloc(dc_mlp* m, const uint16_t* X, const uint8_t* y, in
     }
     float* base = scratch_on_current_device();
     float* g = base + NOALLOC_PARTIAL;
-    mlp_grad(m->wq.as<uint16_t>(), X, y, n, pos_weight, base, g, m->st);
-    DC_HIP(hipMemcpyAsync(m->hgrad, g, GRAD_SLOTS * 4, hipMemcpyDeviceToHost, m->st));
+    mlp_grad(m->wq.as<uint16_t>(), X, y, n, pos_weight, base, g, m->st,
+             m->hgrad_dev);
     DC_HIP(hipStreamSynchronize(m->st));
     if (grad) std::memcpy(grad, m->hgrad, MLP_P * 4);
     if (loss) *loss = double(m->hgrad[MLP_P]) / double(n);
@@ -675,13 +747,10 @@ dc_status dc_mlp_train_step(dc_mlp* m, const uint16_t* X, const uint8_t* y, int6
                             float pos_weight, float lr, double* loss) {
   if (n < 1 || !X || !y || !(pos_weight > 0.f) || !(lr > 0.f)) return DC_E_ARG;
   return mlp_guarded(m, [&] {
-    run_grad(m, X, y, n, pos_weight);
+    run_grad(m, X, y, n, pos_weight, loss != nullptr);
     m->step += 1;
     mlp_adam(m->w.as<float>(), m->m.as<float>(), m->v.as<float>(), m->grad.as<float>(), m->step,
              lr, m->wq.as<uint16_t>(), m->st);
-    if (loss)
-      DC_HIP(hipMemcpyAsync(m->hgrad + MLP_P, m->grad.as<float>() + MLP_P, 4,
-                            hipMemcpyDeviceToHost, m->st));
     DC_HIP(hipStreamSynchronize(m->st));
     if (loss) *loss = double(m->hgrad[MLP_P]) / double(n);
     return DC_OK;
