@@ -531,7 +531,7 @@ dc_status status_from_flags(int32_t f) {
   return DC_OK;
 }
 
-int sort_bits(int32_t n) { return ilog2_ceil(uint64_t(n) * uint64_t(n)); }
+int sort_bits(int32_t n) { return 2 * key_bits(n); }
 
 dc_status do_init(dc_ctx* c, const dc_edges* g1) {
   hipStream_t st = c->st;

@@ -101,7 +101,7 @@ __global__ void k_chunk_heads(const uint64_t* __restrict__ rkey,
 // independent entries, finding its member in LDS-staged row starts).
 // The diagonal sum and the occupied slots are appended as partials.
 __device__ __forceinline__ void emit_partials(const int* keys, const int* vals, uint32_t cap,
-                                              uint64_t row, int32_t nc, long long diag,
+                                              uint64_t row, int kb, long long diag,
                                               uint64_t* pkey, uint32_t* pval, int32_t* pcount,
                                               int* wc, int* bbase) {
   const int wid = threadIdx.x / WAVE, lane = lane_id();
@@ -117,7 +117,7 @@ __device__ __forceinline__ void emit_partials(const int* keys, const int* vals, 
     const int b = atomicAdd(pcount, tot);
     *bbase = b;
     if (diag != 0) {
-      pkey[b] = row * uint64_t(nc) + row;
+      pkey[b] = pair_key(row, row, kb);
       pval[b] = uint32_t(diag);
     }
   }
@@ -130,7 +130,7 @@ __device__ __forceinline__ void emit_partials(const int* keys, const int* vals, 
     const uint64_t m = __ballot(occ);
     if (occ) {
       const int at = pos + __popcll(m & lt);
-      pkey[at] = row * uint64_t(nc) + uint64_t(keys[s]);
+      pkey[at] = pair_key(row, uint32_t(keys[s]), kb);
       pval[at] = uint32_t(vals[s]);
     }
     pos += __popcll(m);
@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(TPB)
     k_coarse_partials(const int32_t* __restrict__ chunks, const uint64_t* __restrict__ rkey,
                       const uint32_t* __restrict__ members, const int32_t* __restrict__ mvol,
                       const int32_t* __restrict__ off, const int2* __restrict__ adj,
-                      const int32_t* __restrict__ rc, int32_t nc, uint64_t* pkey,
+                      const int32_t* __restrict__ rc, int kb, uint64_t* pkey,
                       uint32_t* pval, int32_t* pcount) {
   __shared__ int keys[CHUNK_SLOTS];
   __shared__ int vals[CHUNK_SLOTS];
@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(TPB)
           table_add(keys, vals, CHUNK_SLOTS - 1, Y, e.y);
       }
       diag = block_sum(diag, red);
-      emit_partials(keys, vals, CHUNK_SLOTS, uint64_t(r), nc, diag, pkey, pval, pcount, wc,
+      emit_partials(keys, vals, CHUNK_SLOTS, uint64_t(r), kb, diag, pkey, pval, pcount, wc,
                     &bbase);
     }
     return;
@@ -223,7 +223,7 @@ __global__ void __launch_bounds__(TPB)
       table_add(keys, vals, cap - 1, Y, e.y);
   }
   diag = block_sum(diag, red);
-  emit_partials(keys, vals, cap, uint64_t(r), nc, diag, pkey, pval, pcount, wc, &bbase);
+  emit_partials(keys, vals, cap, uint64_t(r), kb, diag, pkey, pval, pcount, wc, &bbase);
 }
 
 // Segment sums of sorted partials: the u-th distinct key spans positions
@@ -231,13 +231,13 @@ __global__ void __launch_bounds__(TPB)
 // exclusive prefix of the weights.
 __global__ void k_segment_sums(const uint64_t* __restrict__ pkey,
                                const int32_t* __restrict__ hidx, int64_t U,
-                               const int32_t* __restrict__ S, int32_t nc, int2* cadj,
+                               const int32_t* __restrict__ S, int kb, int2* cadj,
                                uint64_t* ukey) {
   for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < U;
        u += int64_t(gridDim.x) * blockDim.x) {
     const int32_t i = hidx[u], j = hidx[u + 1];
     const uint64_t k = pkey[i];
-    cadj[u] = make_int2(int32_t(k % uint64_t(nc)), S[j] - S[i]);
+    cadj[u] = make_int2(int32_t(key_col(k, kb)), S[j] - S[i]);
     ukey[u] = k;
   }
 }
@@ -329,10 +329,10 @@ __global__ void k_final_project(const int32_t* __restrict__ lab,
 __global__ void __launch_bounds__(TPB)
     k_emit_movers(const int32_t* __restrict__ Cl, const int32_t* __restrict__ Cold,
                   const int32_t* __restrict__ off, const int2* __restrict__ adj,
-                  const int32_t* __restrict__ mpos, int32_t n, uint64_t* keys, uint32_t* vals) {
+                  const int32_t* __restrict__ mpos, int32_t n, int kb,
+                  uint64_t* keys, uint32_t* vals) {
   const int64_t nbatch = ceil_div(n, WAVE);
   const int64_t nwaves = int64_t(gridDim.x) * (TPB / WAVE);
-  const uint64_t N = uint64_t(n);
   const int lane = lane_id();
   for (int64_t bt = int64_t(blockIdx.x) * (TPB / WAVE) + threadIdx.x / WAVE; bt < nbatch;
        bt += nwaves) {
@@ -352,13 +352,13 @@ __global__ void __launch_bounds__(TPB)
         const int vo = Cold[en.x], vn = Cl[en.x];
         const bool still = vo == vn;
         const int64_t at = base + 4 * int64_t(q - b);
-        keys[at] = uint64_t(cu_old) * N + uint64_t(vo);
+        keys[at] = pair_key(cu_old, vo, kb);
         vals[at] = uint32_t(-en.y);
-        keys[at + 1] = uint64_t(cu_new) * N + uint64_t(vn);
+        keys[at + 1] = pair_key(cu_new, vn, kb);
         vals[at + 1] = uint32_t(en.y);
-        keys[at + 2] = uint64_t(vo) * N + uint64_t(cu_old);
+        keys[at + 2] = pair_key(vo, cu_old, kb);
         vals[at + 2] = still ? uint32_t(-en.y) : 0u;
-        keys[at + 3] = uint64_t(vn) * N + uint64_t(cu_new);
+        keys[at + 3] = pair_key(vn, cu_new, kb);
         vals[at + 3] = still ? uint32_t(en.y) : 0u;
       }
     }
@@ -367,12 +367,11 @@ __global__ void __launch_bounds__(TPB)
 
 // The batch's directed changes between the old communities.
 __global__ void k_emit_changes(const uint64_t* __restrict__ ch_key,
-                               const int32_t* __restrict__ ch_dk, int64_t nch, int32_t n,
+                               const int32_t* __restrict__ ch_dk, int64_t nch, int kb,
                                const int32_t* __restrict__ Cold, uint64_t* keys, uint32_t* vals) {
   GRID_STRIDE(i, nch) {
     const uint64_t k = ch_key[i];
-    const int32_t u = int32_t(k / uint64_t(n)), v = int32_t(k % uint64_t(n));
-    keys[i] = uint64_t(Cold[u]) * uint64_t(n) + uint64_t(Cold[v]);
+    keys[i] = pair_key(Cold[key_row(k, kb)], Cold[key_col(k, kb)], kb);
     vals[i] = uint32_t(ch_dk[i]);
   }
 }
@@ -428,14 +427,14 @@ __global__ void k_inc_flags(const int32_t* __restrict__ sz, const int32_t* __res
 // an empty community or has a weight below 1 (cannot happen when H is the
 // graph of communities it claims to be).
 // The coarse CSR entries of the summed community pairs, and the level-1
-// graph kept for the next step (keys x*nc + y, weights).  An entry of an
+// graph kept for the next step (pair keys, weights).  An entry of an
 // empty community or of weight below 1 sets the flag in host memory.
 __global__ void k_inc_csr(const uint64_t* __restrict__ keys, const int32_t* __restrict__ w,
                           int64_t cnt, const int32_t* __restrict__ rank,
-                          const int32_t* __restrict__ sz, int32_t n, int32_t nc, int2* adj,
+                          const int32_t* __restrict__ sz, int kb, int kbc, int2* adj,
                           uint64_t* ukey, int32_t* uw, int32_t* bad_host) {
   GRID_STRIDE(i, cnt) {
-    const int32_t X = int32_t(keys[i] / uint64_t(n)), Y = int32_t(keys[i] % uint64_t(n));
+    const int32_t X = int32_t(key_row(keys[i], kb)), Y = int32_t(key_col(keys[i], kb));
     if (sz[X] <= 0 || sz[Y] <= 0 || w[i] < 1) {
       host_store(bad_host, 1);
       adj[i] = make_int2(0, 0);
@@ -445,7 +444,7 @@ __global__ void k_inc_csr(const uint64_t* __restrict__ keys, const int32_t* __re
     }
     const int32_t x = rank[X], y = rank[Y];
     adj[i] = make_int2(y, w[i]);
-    ukey[i] = uint64_t(x) * uint64_t(nc) + uint64_t(y);
+    ukey[i] = pair_key(x, y, kbc);
     uw[i] = w[i];
   }
 }
@@ -457,13 +456,12 @@ __global__ void k_adj_weights(const int2* __restrict__ adj, int64_t m, int32_t* 
 // Level-1 entries relabelled by the final labels of their vertices (the
 // final label of a level-0 community is that of any of its members).
 __global__ void k_relabel(const uint64_t* __restrict__ lkey, const int32_t* __restrict__ lw,
-                          int64_t m, int32_t nc, const int32_t* __restrict__ lminv,
-                          const int32_t* __restrict__ Ct, int32_t n, uint64_t* okey,
+                          int64_t m, int kbc, const int32_t* __restrict__ lminv,
+                          const int32_t* __restrict__ Ct, int kb, uint64_t* okey,
                           uint32_t* ow) {
   GRID_STRIDE(i, m) {
     const uint64_t k = lkey[i];
-    okey[i] = uint64_t(Ct[lminv[int32_t(k / uint64_t(nc))]]) * uint64_t(n) +
-              uint64_t(Ct[lminv[int32_t(k % uint64_t(nc))]]);
+    okey[i] = pair_key(Ct[lminv[key_row(k, kbc)]], Ct[lminv[key_col(k, kbc)]], kb);
     ow[i] = uint32_t(lw[i]);
   }
 }
@@ -570,7 +568,8 @@ void coarsen(const LevelView& g, const int32_t* C, const int32_t* sz, const int3
   int32_t* pcnt_dev = s.pcnt.as<int32_t>();
   fill_i32(pcnt_dev, 0, 1, st);
   if (nchunks > 0) {
-    k_coarse_partials<<<nchunks, TPB, 0, st>>>(chunks, rkey, members, mvol, g.off, g.adj, rc, nc,
+    k_coarse_partials<<<nchunks, TPB, 0, st>>>(chunks, rkey, members, mvol, g.off, g.adj, rc,
+                                               key_bits(nc),
                                                pkey, pval, pcnt_dev);
     DC_LAUNCH_CHECK();
   }
@@ -578,7 +577,7 @@ void coarsen(const LevelView& g, const int32_t* C, const int32_t* sz, const int3
   DC_HIP(hipStreamSynchronize(st));
   const int64_t P = host[0];
   radix_sort_pairs(pkey, pval, s.pk1.as<uint64_t>(), s.pv1.as<uint32_t>(), P,
-                   ilog2_ceil(uint64_t(nc) * uint64_t(nc)), st);
+                   2 * key_bits(nc), st);
   int32_t* ph = s.ph.as<int32_t>();
   int32_t* pp = s.pp.as<int32_t>();
   int32_t* pS = s.pS.as<int32_t>();
@@ -602,7 +601,7 @@ void coarsen(const LevelView& g, const int32_t* C, const int32_t* sz, const int3
   s.ukey.ensure(size_t(cnnz + 1) * 8);
   int32_t* coff = out.off.as<int32_t>();
   if (P > 0) {
-    k_segment_sums<<<grid_for(cnnz), TPB, 0, st>>>(pkey, hidx, cnnz, pS, nc,
+    k_segment_sums<<<grid_for(cnnz), TPB, 0, st>>>(pkey, hidx, cnnz, pS, key_bits(nc),
                                                    out.adj.as<int2>(), s.ukey.as<uint64_t>());
     DC_LAUNCH_CHECK();
   }
@@ -758,16 +757,17 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
   uint64_t* ek = H.ek0.as<uint64_t>();
   uint32_t* ev = H.ev0.as<uint32_t>();
   if (nch > 0) {
-    k_emit_changes<<<grid_for(nch), TPB, 0, st>>>(ch_key, ch_dk, nch, nl, Cold, ek + h, ev + h);
+    k_emit_changes<<<grid_for(nch), TPB, 0, st>>>(ch_key, ch_dk, nch, key_bits(nl), Cold,
+                                                    ek + h, ev + h);
     DC_LAUNCH_CHECK();
   }
   if (vol > 0) {
     k_emit_movers<<<grid_for(ceil_div(nl, WAVE) * WAVE), TPB, 0, st>>>(Cl, Cold, g.off, g.adj, mpos, nl,
-                                                              ek + h + nch, ev + h + nch);
+                                                              key_bits(nl), ek + h + nch, ev + h + nch);
     DC_LAUNCH_CHECK();
   }
   radix_sort_pairs(ek, ev, H.ek1.as<uint64_t>(), H.ev1.as<uint32_t>(), m,
-                   ilog2_ceil(uint64_t(nl) * uint64_t(nl)), st);
+                   2 * key_bits(nl), st);
   H.tkey.ensure(size_t(m + 1) * 8);
   H.tw.ensure(size_t(m + 1) * 4);
   const int64_t cnnz = reduce_sorted(ek, ev, m, H.tkey.as<uint64_t>(), H.tw.as<int32_t>(), H,
@@ -785,7 +785,7 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
   host[2] = 0;  // the self-check flag, set by the kernel in host memory
   if (cnnz > 0) {
     k_inc_csr<<<grid_for(cnnz), TPB, 0, st>>>(H.tkey.as<uint64_t>(), H.tw.as<int32_t>(), cnnz,
-                                              rank, sz, nl, nc, out.adj.as<int2>(),
+                                              rank, sz, key_bits(nl), key_bits(nc), out.adj.as<int2>(),
                                               H.lkey.as<uint64_t>(), H.lw.as<int32_t>(),
                                               hdev + 2);
     DC_LAUNCH_CHECK();
@@ -837,8 +837,9 @@ void inc_finish(IncCoarsen& H, const int32_t* Ct, int32_t n, CoarsenScratch& s,
   H.ek0.ensure(size_t(m + 1) * 8);
   H.ev0.ensure(size_t(m + 1) * 4);
   if (m > 0) {
-    k_relabel<<<grid_for(m), TPB, 0, st>>>(H.lkey.as<uint64_t>(), H.lw.as<int32_t>(), m, H.lnc,
-                                           H.lminv.as<int32_t>(), Ct, n, H.ek0.as<uint64_t>(),
+    k_relabel<<<grid_for(m), TPB, 0, st>>>(H.lkey.as<uint64_t>(), H.lw.as<int32_t>(), m,
+                                           key_bits(H.lnc), H.lminv.as<int32_t>(), Ct, key_bits(n),
+                                           H.ek0.as<uint64_t>(),
                                            H.ev0.as<uint32_t>());
     DC_LAUNCH_CHECK();
   }

@@ -102,6 +102,22 @@ inline int ilog2_ceil(uint64_t x) {
   return b;
 }
 
+// A directed pair (row, col) of ids below n as one sort key: row << b | col
+// with b = key_bits(n), 2 b bits in all, so it splits with a shift and a mask
+// (a 64-bit division by n, some hundred instructions, made the kernels that
+// walk the change list of a large batch issue-bound).
+inline int key_bits(int64_t n) {
+  const int b = ilog2_ceil(uint64_t(n));
+  return b < 1 ? 1 : b;
+}
+__host__ __device__ inline uint64_t pair_key(uint64_t row, uint64_t col, int b) {
+  return row << b | col;
+}
+__host__ __device__ inline uint64_t key_row(uint64_t key, int b) { return key >> b; }
+__host__ __device__ inline uint64_t key_col(uint64_t key, int b) {
+  return key & ((uint64_t(1) << b) - 1);
+}
+
 // ---------------------------------------------------------------------------
 // device helpers
 

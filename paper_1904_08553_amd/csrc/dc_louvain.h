@@ -90,11 +90,11 @@ struct EvalArgs {
   int32_t* ovf_list;     // bins W and B: vertices whose labels overflowed the
   int32_t* ovf_count;    // small LDS table (device count)
   long long* stat;
-  const uint64_t* ins_keys;  // Alg. 2: sorted directed insertions src*n0+dst
+  const uint64_t* ins_keys;  // Alg. 2: sorted directed insertions (pair keys)
   const int32_t* seg_beg;    // per source vertex: its sinks are ins_keys[beg, end)
   const int32_t* seg_end;
   int64_t n_ins;
-  int32_t n0;
+  int32_t kb;                // key_bits of the level-0 graph
   uint8_t* R;
   uint8_t* cflag;
   uint8_t* accflag;  // EV_DSADD: accepted sources flagged here (null: not kept)

@@ -294,7 +294,7 @@ __device__ __forceinline__ long long group_item(const EvalArgs& A, int i, bool h
     const int q0 = have ? A.seg_beg[i] : 0;
     const int nsk = have ? A.seg_end[i] - q0 : 0;  // sinks are neighbours: <= GS
     const bool has = gl < nsk;
-    const int sj = has ? int(A.ins_keys[q0 + gl] - uint64_t(i) * uint64_t(A.n0)) : 0;
+    const int sj = has ? int(key_col(A.ins_keys[q0 + gl], A.kb)) : 0;
     const int Xj = has ? A.C[sj] : EMPTY_KEY;
     long long ej = 0;
     const int ndw = wave_max(nd);
@@ -468,8 +468,8 @@ __device__ __forceinline__ long long screen_pair(const EvalArgs& A, int i0, bool
   const uint64_t kq1 = A.ins_keys[s1 ? sb1 + gl : 0];
   const int ao0 = A.a[c0], ao1 = A.a[c1];
   const int y0 = A.C[v0 ? e0.x : 0], y1 = A.C[v1 ? e1.x : 0];
-  const int j0 = s0 ? int(kq0 - uint64_t(i0) * uint64_t(A.n0)) : 0;
-  const int j1 = s1 ? int(kq1 - uint64_t(i1) * uint64_t(A.n0)) : 0;
+  const int j0 = s0 ? int(key_col(kq0, A.kb)) : 0;
+  const int j1 = s1 ? int(key_col(kq1, A.kb)) : 0;
   const int X0 = A.C[j0], X1 = A.C[j1];
   // the labels are grouped as in the sweep; a sink lane also learns the rank
   // of its sink's label among them (a sink is an entry of the row, so its
@@ -760,9 +760,8 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
   const int uf = MODE == EV_DSBOTH ? int(A.uflag[i]) : (MODE == EV_DSADD ? 1 : 2);
   const bool dsadd = (MODE == EV_DSADD || MODE == EV_DSBOTH) && (uf & 1);
   const int64_t q0 = dsadd ? A.seg_beg[i] : 0, q1 = dsadd ? A.seg_end[i] : 0;
-  const uint64_t base = uint64_t(i) * uint64_t(A.n0);
   const bool pf = q0 + t < q1;
-  const int pj = pf ? int(A.ins_keys[q0 + t] - base) : 0;
+  const int pj = pf ? int(key_col(A.ins_keys[q0 + t], A.kb)) : 0;
   const int pX = pf ? A.C[pj] : 0;
   const int paX = pf ? A.a[pX] : 0;
   for (uint32_t s = t; s <= mask; s += G) {
@@ -820,7 +819,7 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
     Cand best = {NO_SCORE, NO_LABEL, NO_LABEL};
     for (int64_t q = q0 + t; q < q1; q += G) {
       const bool first = q == q0 + t;  // the prefetched sink
-      const int j = first ? pj : int(A.ins_keys[q] - base);
+      const int j = first ? pj : int(key_col(A.ins_keys[q], A.kb));
       const int X = first ? pX : A.C[j];
       const int aX = first ? paX : A.a[X];
       long long g = 0;
@@ -1414,7 +1413,6 @@ __global__ void __launch_bounds__(TPB)
   __shared__ int wsum[NW];
   __shared__ long long bbase;
   const int lane = lane_id(), wid = threadIdx.x / WAVE;
-  const uint64_t n0 = uint64_t(A.n0);
   long long accepted = 0, accvol = 0;
   for (int64_t base = int64_t(blockIdx.x) * TPB; base < A.n_ins;
        base += int64_t(gridDim.x) * TPB) {  // block-uniform
@@ -1423,8 +1421,7 @@ __global__ void __launch_bounds__(TPB)
     int nit = 0;
     if (q < A.n_ins) {
       const uint64_t key = A.ins_keys[q];
-      const int j = int(key / n0);
-      const int i = int(key - uint64_t(j) * n0);
+      const int j = int(key_row(key, A.kb)), i = int(key_col(key, A.kb));
       if (A.best_j[i] == j && A.best_g[i] >= A.sink_g[q]) {
         A.R[i] = 1;
         A.R[j] = 1;
@@ -1687,7 +1684,7 @@ void sweep_eval(const LevelView& g, const int32_t* C, int32_t* Cn, const int32_t
   A.two_m = two_m;
   A.guard = guard;
   A.stat = stat;
-  A.n0 = g.n;
+  A.kb = key_bits(g.n);
   launch_eval<EV_SWEEP>(A, bins, st, ev0, ev1);
 }
 
@@ -1726,7 +1723,7 @@ void ds_additions(const LevelView& g, const int32_t* C, const int32_t* a, long l
   A.seg_beg = seg_beg;
   A.seg_end = seg_end;
   A.n_ins = n_ins;
-  A.n0 = g.n;
+  A.kb = key_bits(g.n);
   A.R = R;
   A.cflag = cflag;
   A.accflag = accflag;
@@ -1758,7 +1755,7 @@ void ds_both(const LevelView& g, const int32_t* C, const int32_t* a, const int32
   A.seg_beg = seg_beg;
   A.seg_end = seg_end;
   A.n_ins = n_ins;
-  A.n0 = g.n;
+  A.kb = key_bits(g.n);
   A.R = R;
   A.cflag = cflag;
   A.accflag = accflag;
@@ -1785,7 +1782,7 @@ void feat_eval(const LevelView& g, const int32_t* C, const int32_t* a, long long
   A.C = C;
   A.a = a;
   A.two_m = two_m;
-  A.n0 = g.n;
+  A.kb = key_bits(g.n);
   A.f_own = f_own;
   A.f_g1 = f_g1;
   A.f_g2 = f_g2;
@@ -1806,7 +1803,7 @@ EvalArgs sweep_args(const LevelView& g, const int32_t* C, int32_t* Cn, const int
   A.sz = sz;
   A.two_m = two_m;
   A.guard = guard;
-  A.n0 = g.n;
+  A.kb = key_bits(g.n);
   return A;
 }
 

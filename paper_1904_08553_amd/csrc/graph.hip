@@ -42,11 +42,11 @@ __global__ void k_validate(const int32_t* __restrict__ u,
 __global__ void k_make_directed(const int32_t* __restrict__ u,
                                 const int32_t* __restrict__ v,
                                 const int32_t* __restrict__ w, int64_t m,
-                                int32_t n, uint64_t* keys, uint32_t* vals) {
+                                int kb, uint64_t* keys, uint32_t* vals) {
   GRID_STRIDE(e, m) {
     uint64_t a = uint32_t(u[e]), b = uint32_t(v[e]);
-    keys[2 * e] = a * uint64_t(n) + b;
-    keys[2 * e + 1] = b * uint64_t(n) + a;
+    keys[2 * e] = pair_key(a, b, kb);
+    keys[2 * e + 1] = pair_key(b, a, kb);
     vals[2 * e] = uint32_t(w[e]);
     vals[2 * e + 1] = uint32_t(w[e]);
   }
@@ -73,20 +73,21 @@ __global__ void k_reduce_runs(const uint64_t* __restrict__ keys,
   }
 }
 
-// row_ptr[r] = index of the first key of row r or a later row (row = key /
-// n, keys sorted), row_ptr[n] = m.  Thread per key, plus one past the end:
+// row_ptr[r] = index of the first key of row r or a later row (pair keys,
+// sorted), row_ptr[n] = m.  Thread per key, plus one past the end:
 // the first key of a row writes the bounds of the rows from the previous
 // key's row (exclusive) to its own; a long run of empty rows is written by
 // the whole wave.
 __global__ void __launch_bounds__(TPB)
-    k_row_bounds(const uint64_t* __restrict__ keys, int64_t m, int32_t n, int32_t* row_ptr) {
+    k_row_bounds(const uint64_t* __restrict__ keys, int64_t m, int32_t n, int kb,
+                 int32_t* row_ptr) {
   const int lane = lane_id();
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
   // the loop runs while the wave's first thread is in range (whole waves)
   for (int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; q - lane <= m; q += stride) {
     const bool h = q <= m;
-    const long long r1 = !h ? 0 : (q < m ? (long long)(keys[q] / uint64_t(n)) : (long long)n);
-    const long long r0 = !h ? 0 : (q > 0 ? (long long)(keys[q - 1] / uint64_t(n)) : -1);
+    const long long r1 = !h ? 0 : (q < m ? (long long)key_row(keys[q], kb) : (long long)n);
+    const long long r0 = !h ? 0 : (q > 0 ? (long long)key_row(keys[q - 1], kb) : -1);
     const bool wide = h && r1 - r0 > WAVE;
     if (h && !wide)
       for (long long r = r0 + 1; r <= r1; ++r) row_ptr[r] = int32_t(q);
@@ -101,8 +102,8 @@ __global__ void __launch_bounds__(TPB)
 
 __global__ void k_keys_to_adj(const uint64_t* __restrict__ keys,
                               const int32_t* __restrict__ w, int64_t m,
-                              int32_t n, int2* adj) {
-  GRID_STRIDE(i, m) { adj[i] = make_int2(int32_t(keys[i] % uint64_t(n)), w[i]); }
+                              int kb, int2* adj) {
+  GRID_STRIDE(i, m) { adj[i] = make_int2(int32_t(key_col(keys[i], kb)), w[i]); }
 }
 
 // one wave per row
@@ -132,19 +133,19 @@ __device__ __forceinline__ int32_t find_in_row(const int2* adj, int32_t b,
   return b;
 }
 
-// Directed change records straight from the batch: deletion e gives keys
-// u*n+v and v*n+u with value 2e, insertion e the same keys with value 2e+1.
+// Directed change records straight from the batch: deletion e gives the
+// pair keys (u, v) and (v, u) with value 2e, insertion e the same keys with value 2e+1.
 __global__ void k_batch_records(const int32_t* __restrict__ du, const int32_t* __restrict__ dv,
                                 int64_t nd, const int32_t* __restrict__ au,
-                                const int32_t* __restrict__ av, int64_t na, int32_t n,
+                                const int32_t* __restrict__ av, int64_t na, int kb,
                                 uint64_t* keys, uint32_t* vals) {
   GRID_STRIDE(i, nd + na) {
     const bool del = i < nd;
     const int64_t j = del ? i : i - nd;
     const uint64_t a = uint32_t(del ? du[j] : au[j]), b = uint32_t(del ? dv[j] : av[j]);
     const uint32_t val = (uint32_t(j) << 1) | (del ? 0u : 1u);
-    keys[2 * i] = a * uint64_t(n) + b;
-    keys[2 * i + 1] = b * uint64_t(n) + a;
+    keys[2 * i] = pair_key(a, b, kb);
+    keys[2 * i + 1] = pair_key(b, a, kb);
     vals[2 * i] = val;
     vals[2 * i + 1] = val;
   }
@@ -179,7 +180,7 @@ __global__ void k_run_accumulate(const uint64_t* __restrict__ keys,
 __global__ void k_resolve_runs(const uint64_t* __restrict__ run_key,
                                const int32_t* __restrict__ run_w,
                                const int32_t* __restrict__ run_ndel,
-                               const int32_t* __restrict__ nruns, int32_t n,
+                               const int32_t* __restrict__ nruns, int32_t n, int kb,
                                const int32_t* __restrict__ off, const int2* __restrict__ adj,
                                uint64_t* ch_key, int32_t* ch_op, int32_t* ch_w, int32_t* ch_dk,
                                int32_t* dnet, int32_t* flags, long long* wsum) {
@@ -188,7 +189,7 @@ __global__ void k_resolve_runs(const uint64_t* __restrict__ run_key,
   long long s = 0;
   GRID_STRIDE(r, cnt) {
     const uint64_t key = run_key[r];
-    const uint64_t src = key / uint64_t(n), dst = key % uint64_t(n);
+    const uint64_t src = key_row(key, kb), dst = key_col(key, kb);
     const int32_t nd = run_ndel[r], wi = run_w[r];
     int32_t wo = 0;
     bool exists = false;
@@ -395,7 +396,7 @@ __device__ __forceinline__ int nbr_rank(const int32_t* nbr, int a, int b, int32_
 __global__ void __launch_bounds__(TPB)
     k_merge_tiles(const int32_t* __restrict__ off_old, const int2* __restrict__ adj_old,
                   int64_t nnz_old, const int32_t* __restrict__ off_new, int2* adj_new,
-                  int32_t n, const int32_t* __restrict__ cptr,
+                  int kb, const int32_t* __restrict__ cptr,
                   const int32_t* __restrict__ tile_row, const uint64_t* __restrict__ ch_key,
                   const int32_t* __restrict__ ch_op, const int32_t* __restrict__ ch_w,
                   const int32_t* __restrict__ cnet, int64_t nch, int nib) {
@@ -412,8 +413,7 @@ __global__ void __launch_bounds__(TPB)
     for (int64_t q = int64_t(blockIdx.x) * TPB + threadIdx.x; q < nch; q += int64_t(nib) * TPB) {
       if (ch_op[q] != OP_NEW) continue;
       const uint64_t key = ch_key[q];
-      const int32_t src = int32_t(key / uint64_t(n));
-      const int32_t dst = int32_t(key - uint64_t(src) * uint64_t(n));
+      const int32_t src = int32_t(key_row(key, kb)), dst = int32_t(key_col(key, kb));
       const int32_t ob = off_old[src], oe = off_old[src + 1];
       const int32_t less = find_in_row(adj_old, ob, oe, dst) - ob;
       adj_new[off_new[src] + less + cnet[q] - cnet[cptr[src]]] = make_int2(dst, ch_w[q]);
@@ -462,8 +462,7 @@ __global__ void __launch_bounds__(TPB)
     for (int u = 0; u < MT_ST; ++u) {
       const int k = u * TPB + int(threadIdx.x);
       if (k < nloc) {
-        const uint64_t row = sk[u] / uint64_t(n);
-        s_nbr[k] = int32_t(sk[u] - row * uint64_t(n));
+        s_nbr[k] = int32_t(key_col(sk[u], kb));
         s_w[k] = sw[u];
         s_nop[k] = (sn[u] - base) * 8 + so[u];
       } else if (k == nloc) {
@@ -511,7 +510,7 @@ __global__ void __launch_bounds__(TPB)
           w = s_w[k];
         }
       } else {
-        const uint64_t key = uint64_t(r) * uint64_t(n) + uint64_t(uint32_t(v.x));
+        const uint64_t key = pair_key(uint32_t(r), uint32_t(v.x), kb);
         const int k = change_rank(ch_key, cb, ce, key);
         shift += cnet[k] - cnet[cb];
         if (k < ce && ch_key[k] == key) {
@@ -627,7 +626,7 @@ void make_directed(const int32_t* u, const int32_t* v, const int32_t* w,
                    int64_t m, int32_t n, uint64_t* keys, uint32_t* vals,
                    hipStream_t st) {
   if (m <= 0) return;
-  k_make_directed<<<grid_for(m), TPB, 0, st>>>(u, v, w, m, n, keys, vals);
+  k_make_directed<<<grid_for(m), TPB, 0, st>>>(u, v, w, m, key_bits(n), keys, vals);
   DC_LAUNCH_CHECK();
 }
 
@@ -647,14 +646,14 @@ void reduce_runs(const uint64_t* keys, const uint32_t* vals,
 
 void row_bounds(const uint64_t* keys, int64_t m, int32_t n, int32_t* row_ptr,
                 hipStream_t st) {
-  k_row_bounds<<<grid_for(m + 1), TPB, 0, st>>>(keys, m, n, row_ptr);
+  k_row_bounds<<<grid_for(m + 1), TPB, 0, st>>>(keys, m, n, key_bits(n), row_ptr);
   DC_LAUNCH_CHECK();
 }
 
 void keys_to_adj(const uint64_t* keys, const int32_t* w, int64_t m, int32_t n,
                  int2* adj, hipStream_t st) {
   if (m <= 0) return;
-  k_keys_to_adj<<<grid_for(m), TPB, 0, st>>>(keys, w, m, n, adj);
+  k_keys_to_adj<<<grid_for(m), TPB, 0, st>>>(keys, w, m, key_bits(n), adj);
   DC_LAUNCH_CHECK();
 }
 
@@ -669,7 +668,8 @@ void batch_records(const int32_t* du, const int32_t* dv, int64_t nd, const int32
                    const int32_t* av, int64_t na, int32_t n, uint64_t* keys, uint32_t* vals,
                    hipStream_t st) {
   if (nd + na <= 0) return;
-  k_batch_records<<<grid_for(nd + na), TPB, 0, st>>>(du, dv, nd, au, av, na, n, keys, vals);
+  k_batch_records<<<grid_for(nd + na), TPB, 0, st>>>(du, dv, nd, au, av, na, key_bits(n), keys,
+                                                    vals);
   DC_LAUNCH_CHECK();
 }
 
@@ -685,8 +685,8 @@ void resolve_changes(const uint64_t* keys, const uint32_t* vals, const int32_t* 
   k_run_accumulate<<<grid_for(m), TPB, 0, st>>>(keys, vals, pos, m, ins_w, run_key, run_w,
                                                 run_ndel);
   DC_LAUNCH_CHECK();
-  k_resolve_runs<<<grid_for(m), TPB, 0, st>>>(run_key, run_w, run_ndel, nruns, n, off, adj,
-                                              ch_key, ch_op, ch_w, ch_dk, dnet, flags, wsum);
+  k_resolve_runs<<<grid_for(m), TPB, 0, st>>>(run_key, run_w, run_ndel, nruns, n,
+                                              key_bits(n), off, adj, ch_key, ch_op, ch_w, ch_dk, dnet, flags, wsum);
   DC_LAUNCH_CHECK();
 }
 
@@ -708,7 +708,7 @@ void merge_rows(const int32_t* off_old, const int2* adj_old, int64_t nnz_old,
   const int nib = nch > 0 ? grid_for(nch, TPB, 1024) : 0;
   if (ntiles + nib == 0) return;
   k_merge_tiles<<<int(ntiles + nib), TPB, 0, st>>>(off_old, adj_old, nnz_old, off_new, adj_new,
-                                                   n, cptr, tile_row, ch_key, ch_op, ch_w, cnet,
+                                                   key_bits(n), cptr, tile_row, ch_key, ch_op, ch_w, cnet,
                                                    nch, nib);
   DC_LAUNCH_CHECK();
 }
