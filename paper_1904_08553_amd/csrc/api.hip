@@ -283,7 +283,7 @@ void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
   finalize_labels(g.n, Cl, al, szl, cntL, minvL, c->n, c->map0.as<int32_t>(),
                   c->lab.as<int32_t>(), c->cntf.as<int32_t>(), c->C.as<int32_t>(),
                   c->a0.as<int32_t>(), c->sz0.as<int32_t>(), st, stat + ST_I);
-  inc_finish(c->inc, c->C.as<int32_t>(), c->n, c->cs, st);  // H(G_t, C_t) for the next step
+  c->inc.valid = true;  // with C_t the level-1 graph just kept is H(G_t, C_t)
   c->inc_ready = false;
   // exact numerator on the final level (coarsening preserves N); C_t goes
   // to the caller of dc_apply_batch before the same wait
@@ -1068,9 +1068,8 @@ void for_each_buf(dc_ctx* c, F&& f) {
                   &c->cs.pv1, &c->cs.ph, &c->cs.pp, &c->cs.pS, &c->cs.pcnt, &c->cs.hidx,
                   &c->cs.ukey, &c->cs.rc, &c->inc.lkey, &c->inc.lw,
                   &c->inc.lminv, &c->inc.ek0, &c->inc.ek1, &c->inc.ev0, &c->inc.ev1,
-                  &c->inc.heads, &c->inc.hpos, &c->inc.v64, &c->inc.S, &c->inc.starts,
-                  &c->inc.nz, &c->inc.npos, &c->inc.mflag, &c->inc.mvol, &c->inc.tkey,
-                  &c->inc.tw})
+                  &c->inc.orank, &c->inc.nrank, &c->inc.mpos, &c->inc.part64, &c->inc.part32,
+                  &c->inc.rkey, &c->inc.ssum, &c->inc.nruns})
     f(*b);
 }
 
@@ -1103,7 +1102,7 @@ void ctx_evict(dc_ctx* c, SavedState& s) {
   for_each_buf(c, [](DBuf& b) { b.release(); });
   pool_trim();  // the evicted bytes leave the GPU, not just the context
   c->inc.valid = false;  // the first step after restore compacts from all of G_t
-  c->inc.h = 0;
+  c->inc.lh = 0;
 }
 
 void ensure_vertex_state(dc_ctx* c);

@@ -15,6 +15,7 @@
 #include <utility>
 
 #include "dc_louvain.h"
+#include "dc_scan.h"
 
 namespace dc {
 
@@ -257,12 +258,10 @@ __global__ void k_first_level_meta(const int32_t* __restrict__ labof,
                                    const int32_t* __restrict__ sz,
                                    const int32_t* __restrict__ mstart,
                                    const uint32_t* __restrict__ members, int32_t nc,
-                                   int32_t* cnt_out, int32_t* minv_out, int32_t* minv_keep) {
+                                   int32_t* cnt_out, int32_t* minv_out) {
   GRID_STRIDE(r, nc) {
     cnt_out[r] = sz[labof[r]];
-    const int32_t v = int32_t(members[mstart[r]]);
-    minv_out[r] = v;
-    if (minv_keep) minv_keep[r] = v;
+    minv_out[r] = int32_t(members[mstart[r]]);
   }
 }
 
@@ -320,150 +319,344 @@ __global__ void k_final_project(const int32_t* __restrict__ lab,
 
 // ---- incremental first-level compaction ----------------------------------
 
-// Entry q of mover u's row (u -> v, weight w) owns four slots from
+// The compaction numbers things twice: rank is the coarse id of a label that
+// is non-empty now (Cl), orank the position of a label among those of the
+// old partition (Cold; a canonical label is one of its own members, so label
+// x exists when Cold[x] == x).  Level-0 moves only take labels that exist, so
+// every entry of the old and the new graph of communities is a pair of old
+// labels, and keys of (orank, orank) sort as the labels do in fewer digits:
+// for 576 communities of 1M vertices two radix passes instead of four.  What
+// follows takes two launches for the ranks, one for everything that needs
+// them, the sort, and four for the sums; in flags, scans, compactions and a
+// sort of the members as launches of their own (29 of them beside the sort's)
+// a step of the 1M/20M graph took 1548 us, now 1385, and one of a
+// 2,000-vertex graph 692, now 533.
+
+// Tile totals: non-empty labels (low half of p64), old labels (high half),
+// and the row volumes of the level-0 movers (p32).
+__global__ void __launch_bounds__(SCAN_THREADS)
+    k_inc_totals(const int32_t* __restrict__ sz, const int32_t* __restrict__ Cl,
+                 const int32_t* __restrict__ Cold, const int32_t* __restrict__ off, int32_t n,
+                 long long* p64, int32_t* p32) {
+  __shared__ long long l64[SCAN_THREADS / WAVE];
+  __shared__ int32_t l32[SCAN_THREADS / WAVE];
+  long long s = 0;
+  int32_t vol = 0;
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    const int64_t x = int64_t(blockIdx.x) * SCAN_TILE + int64_t(i) * SCAN_THREADS + threadIdx.x;
+    const int64_t xc = x < n ? x : n - 1;  // clamped (n >= 1): the loads in flight together
+    const int32_t z = sz[xc], cn = Cl[xc], co = Cold[xc], b = off[xc], e = off[xc + 1];
+    if (x >= n) continue;
+    s += (z > 0 ? 1ll : 0ll) + (co == int32_t(x) ? 1ll << 32 : 0ll);
+    vol += cn != co ? e - b : 0;
+  }
+  s = block_total<long long>(s, l64);
+  vol = block_total<int32_t>(vol, l32);
+  if (threadIdx.x == 0) {
+    p64[blockIdx.x] = s;
+    p32[blockIdx.x] = vol;
+  }
+}
+
+// The scans of the same flags and volumes, and what follows from the ranks:
+// per non-empty label its coarse vertex's size, degree, and starting value of
+// the smallest member (the label itself while it is a member); per old label
+// its coarse id now (nrank, -1 when empty); per mover the entries before its
+// row (mpos).  The three totals go to host memory.
+__global__ void __launch_bounds__(SCAN_THREADS)
+    k_inc_ranks(const int32_t* __restrict__ sz, const int32_t* __restrict__ a,
+                const int32_t* __restrict__ Cl, const int32_t* __restrict__ Cold,
+                const int32_t* __restrict__ off, int32_t n, const long long* __restrict__ p64,
+                const int32_t* __restrict__ p32, int raw, int64_t nt, int32_t* rank,
+                int32_t* orank, int32_t* nrank, int32_t* mpos, int32_t* cnt_out, int32_t* k_out,
+                int32_t* minv, int32_t* host) {
+  __shared__ long long l64[SCAN_THREADS / WAVE];
+  __shared__ int32_t l32[SCAN_THREADS / WAVE];
+  const int64_t base = int64_t(blockIdx.x) * SCAN_TILE + int64_t(threadIdx.x) * SCAN_ITEMS;
+  int32_t z[SCAN_ITEMS], cn[SCAN_ITEMS], co[SCAN_ITEMS], o[SCAN_ITEMS + 1];
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    const int64_t xc = base + i < n ? base + i : n - 1;
+    z[i] = sz[xc];
+    cn[i] = Cl[xc];
+    co[i] = Cold[xc];
+  }
+#pragma unroll
+  for (int i = 0; i <= SCAN_ITEMS; ++i) o[i] = off[base + i < n ? base + i : n];
+  const long long off64 = tile_offset<long long>(p64, raw, nt, l64);
+  const int32_t off32 = tile_offset<int32_t>(p32, raw, nt, l32);
+  long long s = 0;
+  int32_t vol = 0;
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    if (base + i >= n) {  // nothing of it below
+      z[i] = 0;
+      cn[i] = co[i] = -1;
+    }
+    s += (z[i] > 0 ? 1ll : 0ll) + (co[i] == int32_t(base + i) ? 1ll << 32 : 0ll);
+    vol += cn[i] != co[i] ? o[i + 1] - o[i] : 0;
+  }
+  long long tot64;
+  int32_t tot32;
+  long long run = off64 + block_excl_scan<long long>(s, l64, &tot64);
+  int32_t mv = off32 + block_excl_scan<int32_t>(vol, l32, &tot32);
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    const int32_t x = int32_t(base + i);
+    const int32_t r = int32_t(run & 0xffffffffll), q = int32_t(run >> 32);
+    const bool now = z[i] > 0, old = co[i] == x;
+    if (now) {
+      rank[x] = r;
+      cnt_out[r] = z[i];
+      k_out[r] = a[x];
+      minv[r] = cn[i] == x ? x : 0x7fffffff;
+    }
+    if (old) {
+      orank[x] = q;
+      nrank[q] = now ? r : -1;
+    }
+    if (cn[i] != co[i]) {
+      mpos[x] = mv;
+      mv += o[i + 1] - o[i];
+    }
+    run += (now ? 1ll : 0ll) + (old ? 1ll << 32 : 0ll);
+  }
+  if (blockIdx.x == nt - 1 && threadIdx.x == 0) {
+    host_store(host, int32_t((off64 + tot64) & 0xffffffffll));
+    host_store(host + 1, off32 + tot32);
+    host_store(host + 3, int32_t((off64 + tot64) >> 32));
+  }
+}
+
+struct IncEmit {
+  const int32_t *Cl, *Cold, *off;
+  const int2* adj;
+  const int32_t *rank, *orank, *mpos;
+  int32_t n;
+  int ob;  // key_bits of the old labels: the keys below are (orank, orank) pairs
+  int32_t *map0, *minv;
+  const uint64_t* lkey;  // the level-1 graph kept from the last step, lh entries
+  const int32_t *lw, *lminv;
+  int64_t lh;
+  int lb;
+  const uint64_t* ch_key;  // the batch's directed changes
+  const int32_t* ch_dk;
+  int64_t nch;
+  int kb;
+  uint64_t* ekey;  // out: kept entries, changes, then four slots per mover entry
+  uint32_t* ew;
+  int nbv, nbh;  // blocks over vertices and over kept entries; the rest: changes
+};
+
+// Everything that follows from the ranks, in one launch of three block ranges.
+//   Vertices: the coarse id of each, the smallest member of each coarse vertex
+// (only a vertex below the current value takes part, and a wave sends one
+// atomic per coarse vertex, from its lowest lane: the vertices of a label that
+// lost its own vertex would otherwise queue at one word), and the movers'
+// rows.  Entry q of mover u's row (u -> v, weight w) owns four slots from
 // 4 * (mpos[u] + q): w leaves (Cold u, Cold v) and joins (Cl u, Cl v); when v
 // did not move, the mirror entry (v -> u) moves the same way (a moving v's
-// own row carries it, so its mirror slots get weight 0).  A wave checks 64
-// consecutive vertices with one load and emits the movers' rows one after
-// the other, all lanes on each row.
-__global__ void __launch_bounds__(TPB)
-    k_emit_movers(const int32_t* __restrict__ Cl, const int32_t* __restrict__ Cold,
-                  const int32_t* __restrict__ off, const int2* __restrict__ adj,
-                  const int32_t* __restrict__ mpos, int32_t n, int kb,
-                  uint64_t* keys, uint32_t* vals) {
-  const int64_t nbatch = ceil_div(n, WAVE);
-  const int64_t nwaves = int64_t(gridDim.x) * (TPB / WAVE);
+// own row carries it, so its mirror slots get weight 0).
+//   Kept entries: the level-1 graph of the last step between the labels its
+// vertices ended in (that of any of their members).
+//   Changes: the batch's directed changes between the old communities.
+__global__ void __launch_bounds__(TPB) k_inc_emit(IncEmit A) {
+  if (int(blockIdx.x) >= A.nbv + A.nbh) {
+    const int64_t i = (int64_t(blockIdx.x) - A.nbv - A.nbh) * TPB + threadIdx.x;
+    if (i >= A.nch) return;
+    const uint64_t k = A.ch_key[i];
+    A.ekey[A.lh + i] = pair_key(A.orank[A.Cold[key_row(k, A.kb)]],
+                                A.orank[A.Cold[key_col(k, A.kb)]], A.ob);
+    A.ew[A.lh + i] = uint32_t(A.ch_dk[i]);
+    return;
+  }
+  if (int(blockIdx.x) >= A.nbv) {
+    const int64_t i = (int64_t(blockIdx.x) - A.nbv) * TPB + threadIdx.x;
+    if (i >= A.lh) return;
+    const uint64_t k = A.lkey[i];
+    A.ekey[i] = pair_key(A.orank[A.Cold[A.lminv[key_row(k, A.lb)]]],
+                         A.orank[A.Cold[A.lminv[key_col(k, A.lb)]]], A.ob);
+    A.ew[i] = uint32_t(A.lw[i]);
+    return;
+  }
   const int lane = lane_id();
-  for (int64_t bt = int64_t(blockIdx.x) * (TPB / WAVE) + threadIdx.x / WAVE; bt < nbatch;
-       bt += nwaves) {
-    const int64_t u = bt * WAVE + lane;
-    const int co = u < n ? Cold[u] : 0, cn = u < n ? Cl[u] : 0;
-    const bool mover = u < n && co != cn;
-    const int32_t rb = mover ? off[u] : 0, re = mover ? off[u + 1] : 0;
-    const int32_t mp = mover ? mpos[u] : 0;
-    for (uint64_t m = __ballot(mover); m; m &= m - 1) {
-      const int l = __ffsll((unsigned long long)m) - 1;
-      const int cu_old = __builtin_amdgcn_readlane(co, l);
-      const int cu_new = __builtin_amdgcn_readlane(cn, l);
-      const int32_t b = __builtin_amdgcn_readlane(rb, l), e = __builtin_amdgcn_readlane(re, l);
-      const int64_t base = 4 * int64_t(__builtin_amdgcn_readlane(mp, l));
-      for (int32_t q = b + lane; q < e; q += WAVE) {
-        const int2 en = adj[q];
-        const int vo = Cold[en.x], vn = Cl[en.x];
-        const bool still = vo == vn;
-        const int64_t at = base + 4 * int64_t(q - b);
-        keys[at] = pair_key(cu_old, vo, kb);
-        vals[at] = uint32_t(-en.y);
-        keys[at + 1] = pair_key(cu_new, vn, kb);
-        vals[at + 1] = uint32_t(en.y);
-        keys[at + 2] = pair_key(vo, cu_old, kb);
-        vals[at + 2] = still ? uint32_t(-en.y) : 0u;
-        keys[at + 3] = pair_key(vn, cu_new, kb);
-        vals[at + 3] = still ? uint32_t(en.y) : 0u;
-      }
+  const int64_t u = int64_t(blockIdx.x) * TPB + threadIdx.x;
+  const bool in = u < A.n;
+  const int64_t uc = in ? u : A.n - 1;
+  const int cn = A.Cl[uc], co = A.Cold[uc];
+  const int r = A.rank[cn];
+  if (in) A.map0[u] = r;
+  for (uint64_t todo = __ballot(in && int(u) < A.minv[r]); todo;) {
+    const int l = __ffsll((unsigned long long)todo) - 1;
+    const int rl = __builtin_amdgcn_readlane(r, l);
+    if (lane == l) atomicMin(&A.minv[r], int(u));
+    todo &= ~__ballot(r == rl);
+  }
+  const bool mover = in && co != cn;
+  uint64_t movers = __ballot(mover);
+  if (!movers) return;
+  const int32_t rb = mover ? A.off[u] : 0, re = mover ? A.off[u + 1] : 0;
+  const int32_t mp = mover ? A.mpos[u] : 0;
+  const int oo = mover ? A.orank[co] : 0, on = mover ? A.orank[cn] : 0;
+  uint64_t* const key = A.ekey + A.lh + A.nch;
+  uint32_t* const w = A.ew + A.lh + A.nch;
+  for (; movers; movers &= movers - 1) {
+    const int l = __ffsll((unsigned long long)movers) - 1;
+    const int u_old = __builtin_amdgcn_readlane(oo, l), u_new = __builtin_amdgcn_readlane(on, l);
+    const int32_t b = __builtin_amdgcn_readlane(rb, l), e = __builtin_amdgcn_readlane(re, l);
+    const int64_t base = 4 * int64_t(__builtin_amdgcn_readlane(mp, l));
+    for (int32_t q = b + lane; q < e; q += WAVE) {
+      const int2 en = A.adj[q];
+      const int lo = A.Cold[en.x], ln = A.Cl[en.x];
+      const bool still = lo == ln;
+      const int vo = A.orank[lo], vn = still ? vo : A.orank[ln];
+      const int64_t at = base + 4 * int64_t(q - b);
+      key[at] = pair_key(u_old, vo, A.ob);
+      w[at] = uint32_t(-en.y);
+      key[at + 1] = pair_key(u_new, vn, A.ob);
+      w[at + 1] = uint32_t(en.y);
+      key[at + 2] = pair_key(vo, u_old, A.ob);
+      w[at + 2] = still ? uint32_t(-en.y) : 0u;
+      key[at + 3] = pair_key(vn, u_new, A.ob);
+      w[at + 3] = still ? uint32_t(en.y) : 0u;
     }
   }
 }
 
-// The batch's directed changes between the old communities.
-__global__ void k_emit_changes(const uint64_t* __restrict__ ch_key,
-                               const int32_t* __restrict__ ch_dk, int64_t nch, int kb,
-                               const int32_t* __restrict__ Cold, uint64_t* keys, uint32_t* vals) {
-  GRID_STRIDE(i, nch) {
-    const uint64_t k = ch_key[i];
-    keys[i] = pair_key(Cold[key_row(k, kb)], Cold[key_col(k, kb)], kb);
-    vals[i] = uint32_t(ch_dk[i]);
+// Sums of the runs of equal keys of a sorted list.  The prefix sums of the
+// weights are taken modulo 2^32: a run's sum is a difference of two of them,
+// and lies in [0, 2^31).  First the tile totals: run heads (low half) and
+// weights (high half).
+__global__ void __launch_bounds__(SCAN_THREADS)
+    k_run_totals(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ w, int64_t m,
+                 unsigned long long* part) {
+  __shared__ unsigned long long lds[SCAN_THREADS / WAVE];
+  uint32_t heads = 0, sum = 0;
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    const int64_t x = int64_t(blockIdx.x) * SCAN_TILE + int64_t(i) * SCAN_THREADS + threadIdx.x;
+    const int64_t xc = x < m ? x : m - 1;
+    const uint64_t k = keys[xc], before = keys[xc > 0 ? xc - 1 : 0];
+    const uint32_t y = w[xc];
+    if (x >= m) continue;
+    heads += (x == 0 || k != before) ? 1u : 0u;
+    sum += y;
   }
+  const unsigned long long t =
+      block_total<unsigned long long>(heads | (unsigned long long)sum << 32, lds);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-__global__ void k_signed_to_i64(const uint32_t* __restrict__ in, int64_t m, long long* out) {
-  GRID_STRIDE(i, m) { out[i] = (long long)int32_t(in[i]); }
-}
-
-__global__ void k_set_at(int32_t* arr, const int32_t* __restrict__ idx, int32_t v) {
-  arr[*idx] = v;
-}
-
-// Run of equal keys starting at head i: sum = S[end] - S[i] (S the exclusive
-// prefix sums); flags the runs whose sum is not zero.
-__global__ void k_run_sums(const int32_t* __restrict__ heads, const int32_t* __restrict__ hpos,
-                           const int32_t* __restrict__ starts, const long long* __restrict__ S,
-                           int64_t m, int32_t* nz, long long* rsum) {
-  GRID_STRIDE(i, m) {
-    int32_t f = 0;
-    long long w = 0;
-    if (heads[i]) {
-      w = S[starts[hpos[i] + 1]] - S[i];
-      f = w != 0 ? 1 : 0;
+// Per run r: its key and the prefix sum at its head; ssum[U] the total of
+// all weights, *nruns = U.
+__global__ void __launch_bounds__(SCAN_THREADS)
+    k_run_starts(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ w, int64_t m,
+                 const unsigned long long* __restrict__ part, int raw, int64_t nt,
+                 uint64_t* rkey, uint32_t* ssum, int32_t* nruns) {
+  __shared__ unsigned long long lds[SCAN_THREADS / WAVE];
+  const int64_t base = int64_t(blockIdx.x) * SCAN_TILE + int64_t(threadIdx.x) * SCAN_ITEMS;
+  uint64_t k[SCAN_ITEMS + 1];
+  uint32_t y[SCAN_ITEMS];
+  k[0] = keys[base < m ? (base > 0 ? base - 1 : 0) : m - 1];
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    const int64_t x = base + i < m ? base + i : m - 1;
+    k[i + 1] = keys[x];
+    y[i] = w[x];
+  }
+  const unsigned long long offs = tile_offset<unsigned long long>(part, raw, nt, lds);
+  uint32_t heads = 0, sum = 0;
+  bool h[SCAN_ITEMS];
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    h[i] = base + i < m && (base + i == 0 || k[i + 1] != k[i]);
+    heads += h[i] ? 1u : 0u;
+    sum += base + i < m ? y[i] : 0u;
+  }
+  unsigned long long tot;
+  const unsigned long long at =
+      offs + block_excl_scan<unsigned long long>(heads | (unsigned long long)sum << 32, lds, &tot);
+  uint32_t r = uint32_t(at), s = uint32_t(at >> 32);
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    if (h[i]) {
+      rkey[r] = k[i + 1];
+      ssum[r] = s;
+      ++r;
     }
-    nz[i] = f;
-    rsum[i] = w;
+    s += y[i];
+  }
+  if (blockIdx.x == nt - 1 && threadIdx.x == 0) {
+    const uint32_t U = uint32_t(offs + tot);
+    ssum[U] = uint32_t((offs + tot) >> 32);
+    *nruns = int32_t(U);
   }
 }
 
-__global__ void k_compact_runs(const uint64_t* __restrict__ keys, const int32_t* __restrict__ nz,
-                               const int32_t* __restrict__ npos, const long long* __restrict__ rsum,
-                               int64_t m, uint64_t* okey, int32_t* ow) {
-  GRID_STRIDE(i, m) {
-    if (nz[i]) {
-      okey[npos[i]] = keys[i];
-      ow[npos[i]] = int32_t(rsum[i]);
-    }
+// Tile totals of the runs whose sum is not zero (tiles past *nruns: 0).
+__global__ void __launch_bounds__(SCAN_THREADS)
+    k_run_nonzero(const uint32_t* __restrict__ ssum, const int32_t* __restrict__ nruns,
+                  int32_t* part) {
+  __shared__ int32_t lds[SCAN_THREADS / WAVE];
+  const int64_t U = *nruns;
+  int32_t c = 0;
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    const int64_t r = int64_t(blockIdx.x) * SCAN_TILE + int64_t(i) * SCAN_THREADS + threadIdx.x;
+    const int64_t rc = r < U ? r : U - 1;  // U >= 1
+    c += r < U && ssum[rc + 1] != ssum[rc] ? 1 : 0;
   }
+  c = block_total<int32_t>(c, lds);
+  if (threadIdx.x == 0) part[blockIdx.x] = c;
 }
 
-// The two flag arrays of the incremental compaction: non-empty labels and
-// the row volumes of the level-0 movers.
-__global__ void k_inc_flags(const int32_t* __restrict__ sz, const int32_t* __restrict__ Cl,
-                            const int32_t* __restrict__ Cold, const int32_t* __restrict__ off,
-                            int32_t n, int32_t* flag, int32_t* mvol) {
-  GRID_STRIDE(v, n) {
-    flag[v] = sz[v] > 0 ? 1 : 0;
-    mvol[v] = Cl[v] != Cold[v] ? off[v + 1] - off[v] : 0;
+// The runs of non-zero sum, in order: the coarse CSR's entries, and the
+// level-1 graph kept for the next step (pair keys, weights; smallest members
+// copied from minv).  An entry of an empty community or of weight below 1
+// (cannot happen when the kept graph is the graph of communities it claims
+// to be) sets the flag in host memory; the entry count goes there too.
+__global__ void __launch_bounds__(SCAN_THREADS)
+    k_inc_csr(const uint64_t* __restrict__ rkey, const uint32_t* __restrict__ ssum,
+              const int32_t* __restrict__ nruns, const int32_t* __restrict__ part, int raw,
+              int64_t nt, const int32_t* __restrict__ nrank, int ob, int nb, int2* adj,
+              uint64_t* lkey, int32_t* lw, const int32_t* __restrict__ minv, int32_t* lminv,
+              int32_t nc, int32_t* host) {
+  __shared__ int32_t lds[SCAN_THREADS / WAVE];
+  for (int64_t r = int64_t(blockIdx.x) * SCAN_THREADS + threadIdx.x; r < nc;
+       r += int64_t(gridDim.x) * SCAN_THREADS)
+    lminv[r] = minv[r];
+  const int64_t U = *nruns;
+  const int64_t base = int64_t(blockIdx.x) * SCAN_TILE + int64_t(threadIdx.x) * SCAN_ITEMS;
+  uint32_t s[SCAN_ITEMS + 1];
+#pragma unroll
+  for (int i = 0; i <= SCAN_ITEMS; ++i) s[i] = ssum[base + i < U ? base + i : U];
+  const int32_t offs = tile_offset<int32_t>(part, raw, nt, lds);
+  int32_t c = 0;
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) c += base + i < U && s[i + 1] != s[i] ? 1 : 0;
+  int32_t tot;
+  int32_t p = offs + block_excl_scan<int32_t>(c, lds, &tot);
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < SCAN_ITEMS; ++i) {
+    if (base + i >= U || s[i + 1] == s[i]) continue;
+    const uint64_t k = rkey[base + i];
+    const int32_t x = nrank[key_row(k, ob)], y = nrank[key_col(k, ob)];
+    const int32_t w = int32_t(s[i + 1] - s[i]);
+    const bool ok = x >= 0 && y >= 0 && w >= 1;
+    bad |= !ok;
+    adj[p] = ok ? make_int2(y, w) : make_int2(0, 0);
+    lkey[p] = ok ? pair_key(x, y, nb) : 0;
+    lw[p] = ok ? w : 0;
+    ++p;
   }
-}
-
-// Community-label entries to coarse ids; bad |= 1 for an entry that touches
-// an empty community or has a weight below 1 (cannot happen when H is the
-// graph of communities it claims to be).
-// The coarse CSR entries of the summed community pairs, and the level-1
-// graph kept for the next step (pair keys, weights).  An entry of an
-// empty community or of weight below 1 sets the flag in host memory.
-__global__ void k_inc_csr(const uint64_t* __restrict__ keys, const int32_t* __restrict__ w,
-                          int64_t cnt, const int32_t* __restrict__ rank,
-                          const int32_t* __restrict__ sz, int kb, int kbc, int2* adj,
-                          uint64_t* ukey, int32_t* uw, int32_t* bad_host) {
-  GRID_STRIDE(i, cnt) {
-    const int32_t X = int32_t(key_row(keys[i], kb)), Y = int32_t(key_col(keys[i], kb));
-    if (sz[X] <= 0 || sz[Y] <= 0 || w[i] < 1) {
-      host_store(bad_host, 1);
-      adj[i] = make_int2(0, 0);
-      ukey[i] = 0;
-      uw[i] = 0;
-      continue;
-    }
-    const int32_t x = rank[X], y = rank[Y];
-    adj[i] = make_int2(y, w[i]);
-    ukey[i] = pair_key(x, y, kbc);
-    uw[i] = w[i];
-  }
+  if (bad) host_store(host + 2, 1);
+  if (blockIdx.x == nt - 1 && threadIdx.x == 0) host_store(host, offs + tot);
 }
 
 __global__ void k_adj_weights(const int2* __restrict__ adj, int64_t m, int32_t* w) {
   GRID_STRIDE(i, m) { w[i] = adj[i].y; }
-}
-
-// Level-1 entries relabelled by the final labels of their vertices (the
-// final label of a level-0 community is that of any of its members).
-__global__ void k_relabel(const uint64_t* __restrict__ lkey, const int32_t* __restrict__ lw,
-                          int64_t m, int kbc, const int32_t* __restrict__ lminv,
-                          const int32_t* __restrict__ Ct, int kb, uint64_t* okey,
-                          uint32_t* ow) {
-  GRID_STRIDE(i, m) {
-    const uint64_t k = lkey[i];
-    okey[i] = pair_key(Ct[lminv[key_row(k, kbc)]], Ct[lminv[key_col(k, kbc)]], kb);
-    ow[i] = uint32_t(lw[i]);
-  }
 }
 
 // Starting values of finalize_labels: the smallest-member labels at +inf,
@@ -614,7 +807,7 @@ void coarsen(const LevelView& g, const int32_t* C, const int32_t* sz, const int3
   // level-0 vertex counts and smallest level-0 ids of the coarse vertices
   if (first_level) {
     k_first_level_meta<<<grid_for(nc), TPB, 0, st>>>(labof, sz, mstart, members, nc, cnt_out,
-                                                     minv_out, nullptr);
+                                                     minv_out);
     DC_LAUNCH_CHECK();
   } else {
     s.mcnt.ensure(size_t(nl + 1) * 4);
@@ -634,62 +827,9 @@ void coarsen(const LevelView& g, const int32_t* C, const int32_t* sz, const int3
 
 namespace {
 
-void swap_buf(DBuf& x, DBuf& y) {
-  std::swap(x.p, y.p);
-  std::swap(x.bytes, y.bytes);
-}
-
-// ensure(bytes) that keeps the first `keep` bytes when the buffer grows
-void grow_keep(DBuf& b, size_t bytes, size_t keep, hipStream_t st) {
-  if (b.p && bytes <= b.bytes) return;
-  DBuf nb;
-  nb.ensure(bytes);
-  if (keep > 0 && b.p) DC_HIP(hipMemcpyAsync(nb.p, b.p, keep, hipMemcpyDeviceToDevice, st));
-  swap_buf(b, nb);  // the old buffer is freed (after the copy) with nb
-}
-
 int32_t* host_alias(CoarsenScratch& s) {
   if (!s.host_dev) DC_HIP(hipHostGetDevicePointer(&s.host_dev, s.host, 0));
   return static_cast<int32_t*>(s.host_dev);
-}
-
-// Sums runs of equal keys of a sorted list (values: int32 bit patterns) into
-// (okey, ow), dropping runs that sum to zero; returns the number kept.
-int64_t reduce_sorted(const uint64_t* keys, const uint32_t* vals, int64_t m, uint64_t* okey,
-                      int32_t* ow, IncCoarsen& H, int32_t* host, int32_t* host_dev,
-                      hipStream_t st) {
-  if (m <= 0) return 0;
-  const size_t mm = size_t(m) + 1;
-  H.heads.ensure(mm * 4);
-  H.hpos.ensure(mm * 4);
-  H.starts.ensure(mm * 4);
-  H.nz.ensure(mm * 4);
-  H.npos.ensure(mm * 4);
-  H.v64.ensure(mm * 8);
-  H.S.ensure(mm * 8);
-  int32_t* heads = H.heads.as<int32_t>();
-  int32_t* hpos = H.hpos.as<int32_t>();
-  int32_t* starts = H.starts.as<int32_t>();
-  int32_t* nz = H.nz.as<int32_t>();
-  int32_t* npos = H.npos.as<int32_t>();
-  long long* v64 = H.v64.as<long long>();
-  long long* S = H.S.as<long long>();
-  run_heads(keys, m, heads, st);
-  scan_excl_i32(heads, hpos, m, hpos + m, st);
-  compact_index(heads, hpos, m, starts, st);
-  k_set_at<<<1, 1, 0, st>>>(starts, hpos + m, int32_t(m));
-  DC_LAUNCH_CHECK();
-  k_signed_to_i64<<<grid_for(m), TPB, 0, st>>>(vals, m, v64);
-  DC_LAUNCH_CHECK();
-  scan_excl_i64(reinterpret_cast<int64_t*>(v64), reinterpret_cast<int64_t*>(S), m,
-                reinterpret_cast<int64_t*>(S + m), st);
-  k_run_sums<<<grid_for(m), TPB, 0, st>>>(heads, hpos, starts, S, m, nz, v64);
-  DC_LAUNCH_CHECK();
-  scan_excl_i32(nz, npos, m, npos + m, st, host_dev);
-  k_compact_runs<<<grid_for(m), TPB, 0, st>>>(keys, nz, npos, v64, m, okey, ow);
-  DC_LAUNCH_CHECK();
-  DC_HIP(hipStreamSynchronize(st));
-  return host[0];
 }
 
 }  // namespace
@@ -702,105 +842,123 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
   const int32_t nl = g.n;
   int32_t* host = static_cast<int32_t*>(s.host);
   int32_t* hdev = host_alias(s);  // the kernels write the sizes the host reads here
-  // ranks of the non-empty labels (as coarsen)
-  s.flag.ensure(size_t(nl + 1) * 4);
+  const int64_t nt = ceil_div(nl, SCAN_TILE);
   s.rank.ensure(size_t(nl + 1) * 4);
-  int32_t* flag = s.flag.as<int32_t>();
+  H.orank.ensure(size_t(nl + 1) * 4);
+  H.nrank.ensure(size_t(nl + 1) * 4);
+  H.mpos.ensure(size_t(nl + 1) * 4);
+  H.part64.ensure(size_t(nt) * 8);
+  H.part32.ensure(size_t(nt) * 4);
+  out.k.ensure(size_t(nl + 1) * 4);
   int32_t* rank = s.rank.as<int32_t>();
-  // and the movers' row volumes
-  H.mvol.ensure(size_t(nl + 1) * 4);
-  H.mflag.ensure(size_t(nl + 1) * 4);
-  int32_t* mvol = H.mvol.as<int32_t>();
-  int32_t* mpos = H.mflag.as<int32_t>();
-  k_inc_flags<<<grid_for(nl), TPB, 0, st>>>(sz, Cl, Cold, g.off, nl, flag, mvol);
+  int64_t* p64 = H.part64.as<int64_t>();
+  int32_t* p32 = H.part32.as<int32_t>();
+  if (nt > 1) {  // a single tile needs no offsets
+    k_inc_totals<<<int(nt), SCAN_THREADS, 0, st>>>(sz, Cl, Cold, g.off, nl,
+                                                   reinterpret_cast<long long*>(p64), p32);
+    DC_LAUNCH_CHECK();
+  }
+  const int raw = nt <= SCAN_RAW_MAX;
+  if (!raw) {
+    scan_excl_i64(p64, p64, nt, nullptr, st);
+    scan_excl_i32(p32, p32, nt, nullptr, st);
+  }
+  k_inc_ranks<<<int(nt), SCAN_THREADS, 0, st>>>(
+      sz, a, Cl, Cold, g.off, nl, nt > 1 ? reinterpret_cast<long long*>(p64) : nullptr,
+      nt > 1 ? p32 : nullptr, raw, nt, rank, H.orank.as<int32_t>(), H.nrank.as<int32_t>(),
+      H.mpos.as<int32_t>(), cnt_out, out.k.as<int32_t>(), minv_out, hdev);
   DC_LAUNCH_CHECK();
-  scan_excl_i32(flag, rank, nl, rank + nl, st, hdev);
-  scan_excl_i32(mvol, mpos, nl, mpos + nl, st, hdev + 1);
   DC_HIP(hipStreamSynchronize(st));
-  const int32_t nc = host[0];
+  const int32_t nc = host[0], nold = host[3];
   const int64_t vol = host[1];
 
-  // members grouped by coarse id: counts and smallest members (as coarsen)
-  s.keys0.ensure(size_t(nl) * 8);
-  s.keys1.ensure(size_t(nl) * 8);
-  s.vals0.ensure(size_t(nl) * 4);
-  s.vals1.ensure(size_t(nl) * 4);
-  uint64_t* rkey = s.keys0.as<uint64_t>();
-  uint32_t* members = s.vals0.as<uint32_t>();
-  s.rc.ensure(size_t(nl + 1) * 4);
-  k_member_pairs<<<grid_for(nl), TPB, 0, st>>>(Cl, rank, nl, rkey, members, s.rc.as<int32_t>());
-  DC_LAUNCH_CHECK();
-  if (radix_sort_pairs_swap(rkey, members, s.keys1.as<uint64_t>(), s.vals1.as<uint32_t>(), nl,
-                            ilog2_ceil(uint64_t(nc)), st)) {
-    swap_buf(s.keys0, s.keys1);  // the sorted pairs are in the second buffers
-    swap_buf(s.vals0, s.vals1);
-    rkey = s.keys0.as<uint64_t>();
-    members = s.vals0.as<uint32_t>();
-  }
-  s.cntr.ensure(size_t(nc + 1) * 4);
-  s.mstart.ensure(size_t(nc + 1) * 4);
-  s.labof.ensure(size_t(nc + 1) * 4);
-  int32_t* cntr = s.cntr.as<int32_t>();
-  int32_t* mstart = s.mstart.as<int32_t>();
-  int32_t* labof = s.labof.as<int32_t>();
-  k_comm_info<<<grid_for(nl), TPB, 0, st>>>(flag, rank, sz, nl, cntr, labof);
-  DC_LAUNCH_CHECK();
-  scan_excl_i32(cntr, mstart, nc, mstart + nc, st);
-
-  // H(G_{t-1}, C_{t-1}) + the batch's changes + the movers' rows, one sort;
-  // H's h entries already lead the sort's input buffers (inc_finish)
-  const int64_t h = H.h, m = h + nch + 4 * vol;
-  grow_keep(H.ek0, size_t(m + 1) * 8, size_t(h) * 8, st);
-  grow_keep(H.ev0, size_t(m + 1) * 4, size_t(h) * 4, st);
+  // H(G_{t-1}, C_{t-1}) + the batch's changes + the movers' rows, one sort
+  const int64_t m = H.lh + nch + 4 * vol;
+  H.ek0.ensure(size_t(m + 1) * 8);
+  H.ev0.ensure(size_t(m + 1) * 4);
   H.ek1.ensure(size_t(m + 1) * 8);
   H.ev1.ensure(size_t(m + 1) * 4);
-  uint64_t* ek = H.ek0.as<uint64_t>();
-  uint32_t* ev = H.ev0.as<uint32_t>();
-  if (nch > 0) {
-    k_emit_changes<<<grid_for(nch), TPB, 0, st>>>(ch_key, ch_dk, nch, key_bits(nl), Cold,
-                                                    ek + h, ev + h);
-    DC_LAUNCH_CHECK();
-  }
-  if (vol > 0) {
-    k_emit_movers<<<grid_for(ceil_div(nl, WAVE) * WAVE), TPB, 0, st>>>(Cl, Cold, g.off, g.adj, mpos, nl,
-                                                              key_bits(nl), ek + h + nch, ev + h + nch);
-    DC_LAUNCH_CHECK();
-  }
-  radix_sort_pairs(ek, ev, H.ek1.as<uint64_t>(), H.ev1.as<uint32_t>(), m,
-                   2 * key_bits(nl), st);
-  H.tkey.ensure(size_t(m + 1) * 8);
-  H.tw.ensure(size_t(m + 1) * 4);
-  const int64_t cnnz = reduce_sorted(ek, ev, m, H.tkey.as<uint64_t>(), H.tw.as<int32_t>(), H,
-                                     host, hdev, st);
-
-  // coarse CSR over coarse ids (rows come out sorted: ranks keep label order)
-  // its entries go to the coarse CSR and, as the level-1 graph kept for the
-  // next step, to H.lkey / H.lw
-  out.off.ensure(size_t(nc + 1) * 4);
-  out.adj.ensure(size_t(cnnz + 1) * 8);
-  out.k.ensure(size_t(nc + 1) * 4);
-  H.lkey.ensure(size_t(cnnz + 1) * 8);
-  H.lw.ensure(size_t(cnnz + 1) * 4);
-  H.lminv.ensure(size_t(nc + 1) * 4);
-  host[2] = 0;  // the self-check flag, set by the kernel in host memory
-  if (cnnz > 0) {
-    k_inc_csr<<<grid_for(cnnz), TPB, 0, st>>>(H.tkey.as<uint64_t>(), H.tw.as<int32_t>(), cnnz,
-                                              rank, sz, key_bits(nl), key_bits(nc), out.adj.as<int2>(),
-                                              H.lkey.as<uint64_t>(), H.lw.as<int32_t>(),
-                                              hdev + 2);
-    DC_LAUNCH_CHECK();
-  }
-  s.inc_check = true;  // read after the caller's next wait (inc_check)
-  row_bounds(H.lkey.as<uint64_t>(), cnnz, nc, out.off.as<int32_t>(), st);
-  k_coarse_k<<<grid_for(nc), TPB, 0, st>>>(labof, a, nc, out.k.as<int32_t>());
+  IncEmit A{};
+  A.Cl = Cl;
+  A.Cold = Cold;
+  A.off = g.off;
+  A.adj = g.adj;
+  A.rank = rank;
+  A.orank = H.orank.as<int32_t>();
+  A.mpos = H.mpos.as<int32_t>();
+  A.n = nl;
+  A.ob = key_bits(nold);
+  A.map0 = map0;
+  A.minv = minv_out;
+  A.lkey = H.lkey.as<uint64_t>();
+  A.lw = H.lw.as<int32_t>();
+  A.lminv = H.lminv.as<int32_t>();
+  A.lh = H.lh;
+  A.lb = key_bits(H.lnc);
+  A.ch_key = ch_key;
+  A.ch_dk = ch_dk;
+  A.nch = nch;
+  A.kb = key_bits(nl);
+  A.ekey = H.ek0.as<uint64_t>();
+  A.ew = H.ev0.as<uint32_t>();
+  A.nbv = int(ceil_div(nl, TPB));
+  A.nbh = int(ceil_div(H.lh, TPB));
+  k_inc_emit<<<A.nbv + A.nbh + int(ceil_div(nch, TPB)), TPB, 0, st>>>(A);
   DC_LAUNCH_CHECK();
+
+  // (the kept graph's buffers are read by the launch above and grow after it)
+  out.off.ensure(size_t(nc + 1) * 4);
+  out.adj.ensure(size_t(m + 1) * 8);
+  H.lkey.ensure(size_t(m + 1) * 8);
+  H.lw.ensure(size_t(m + 1) * 4);
+  H.lminv.ensure(size_t(nc + 1) * 4);
+  host[0] = 0;
+  host[2] = 0;  // the self-check flag, set by the kernel in host memory
+  int64_t cnnz = 0;
+  if (m > 0) {
+    const bool second =
+        radix_sort_pairs_swap(A.ekey, A.ew, H.ek1.as<uint64_t>(), H.ev1.as<uint32_t>(), m,
+                              2 * A.ob, st);
+    const uint64_t* ek = second ? H.ek1.as<uint64_t>() : A.ekey;
+    const uint32_t* ew = second ? H.ev1.as<uint32_t>() : A.ew;
+    H.rkey.ensure(size_t(m + 1) * 8);
+    H.ssum.ensure(size_t(m + 1) * 4);
+    H.nruns.ensure(4);
+    const int64_t mt = ceil_div(m, SCAN_TILE);
+    H.part64.ensure(size_t(mt) * 8);
+    H.part32.ensure(size_t(mt) * 4);
+    p64 = H.part64.as<int64_t>();
+    p32 = H.part32.as<int32_t>();
+    auto* pu = reinterpret_cast<unsigned long long*>(p64);
+    const int mraw = mt <= SCAN_RAW_MAX;
+    const bool one = mt == 1;
+    if (!one) {
+      k_run_totals<<<int(mt), SCAN_THREADS, 0, st>>>(ek, ew, m, pu);
+      DC_LAUNCH_CHECK();
+    }
+    if (!mraw) scan_excl_i64(p64, p64, mt, nullptr, st);
+    k_run_starts<<<int(mt), SCAN_THREADS, 0, st>>>(ek, ew, m, one ? nullptr : pu, mraw, mt,
+                                                   H.rkey.as<uint64_t>(), H.ssum.as<uint32_t>(),
+                                                   H.nruns.as<int32_t>());
+    DC_LAUNCH_CHECK();
+    if (!one) {
+      k_run_nonzero<<<int(mt), SCAN_THREADS, 0, st>>>(H.ssum.as<uint32_t>(),
+                                                      H.nruns.as<int32_t>(), p32);
+      DC_LAUNCH_CHECK();
+    }
+    if (!mraw) scan_excl_i32(p32, p32, mt, nullptr, st);
+    k_inc_csr<<<int(mt), SCAN_THREADS, 0, st>>>(
+        H.rkey.as<uint64_t>(), H.ssum.as<uint32_t>(), H.nruns.as<int32_t>(), one ? nullptr : p32,
+        mraw, mt, H.nrank.as<int32_t>(), A.ob, key_bits(nc), out.adj.as<int2>(),
+        H.lkey.as<uint64_t>(), H.lw.as<int32_t>(), minv_out, H.lminv.as<int32_t>(), nc, hdev);
+    DC_LAUNCH_CHECK();
+    DC_HIP(hipStreamSynchronize(st));
+    cnnz = host[0];
+  }
+  s.inc_check = true;  // read by inc_check
+  row_bounds(H.lkey.as<uint64_t>(), cnnz, nc, out.off.as<int32_t>(), st);
   out.n = nc;
   out.nnz = cnnz;
-  k_first_level_meta<<<grid_for(nc), TPB, 0, st>>>(labof, sz, mstart, members, nc, cnt_out,
-                                                   minv_out, H.lminv.as<int32_t>());
-  DC_LAUNCH_CHECK();
-  k_project<<<grid_for(nl), TPB, 0, st>>>(Cl, rank, nl, true, map0);
-  DC_LAUNCH_CHECK();
   H.lh = cnnz;
   H.lnc = nc;
 }
@@ -827,24 +985,6 @@ void save_level1(const CoarseGraph& out, const CoarsenScratch& s, const int32_t*
     DC_HIP(hipMemcpyAsync(H.lminv.p, minv, size_t(out.n) * 4, hipMemcpyDeviceToDevice, st));
   H.lh = out.nnz;
   H.lnc = out.n;
-}
-
-void inc_finish(IncCoarsen& H, const int32_t* Ct, int32_t n, CoarsenScratch& s,
-                hipStream_t st) {
-  (void)s;
-  const int64_t m = H.lh;
-  // written where the next step's sort reads its input (coarsen_first_inc)
-  H.ek0.ensure(size_t(m + 1) * 8);
-  H.ev0.ensure(size_t(m + 1) * 4);
-  if (m > 0) {
-    k_relabel<<<grid_for(m), TPB, 0, st>>>(H.lkey.as<uint64_t>(), H.lw.as<int32_t>(), m,
-                                           key_bits(H.lnc), H.lminv.as<int32_t>(), Ct, key_bits(n),
-                                           H.ek0.as<uint64_t>(),
-                                           H.ev0.as<uint32_t>());
-    DC_LAUNCH_CHECK();
-  }
-  H.h = m;
-  H.valid = true;
 }
 
 void finalize_labels(int32_t nL, const int32_t* CL, const int32_t* aL, const int32_t* szL,

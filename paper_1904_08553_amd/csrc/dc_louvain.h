@@ -410,17 +410,15 @@ void coarsen(const LevelView& g, const int32_t* C, const int32_t* sz, const int3
 
 // ---- incremental first-level compaction (coarsen.hip) ----
 // H(G, C): the graph of communities of the current graph and partition,
-// keys X*n + Y over community labels, weights > 0, sorted and unique; plus
-// the last level-1 graph (keys x*nc + y over coarse ids, weights) and the
-// smallest level-0 member of each of its vertices, from which the next H
-// is relabelled once the final labels are known.
+// kept as the last level-1 graph (lh entries: pair keys over its lnc coarse
+// ids, weights) and the smallest level-0 member of each of its vertices,
+// whose label is the entry's community.
 struct IncCoarsen {
-  int64_t h = 0;  // entries of H, at the front of ek0 / ev0
   bool valid = false;
   DBuf lkey, lw, lminv;
   int64_t lh = 0;
   int32_t lnc = 0;
-  DBuf ek0, ek1, ev0, ev1, heads, hpos, v64, S, starts, nz, npos, mflag, mvol, tkey, tw;
+  DBuf ek0, ek1, ev0, ev1, orank, nrank, mpos, part64, part32, rkey, ssum, nruns;
 };
 
 // Level 0 -> 1 from H(G_{t-1}, C_{t-1}) instead of all of G_t: H plus the
@@ -442,13 +440,6 @@ void inc_check(CoarsenScratch& s);
 // coarsen_first_inc keeps its own as it builds it.
 void save_level1(const CoarseGraph& out, const CoarsenScratch& s, const int32_t* minv,
                  IncCoarsen& H, hipStream_t st);
-// H(G_t, C_t) from the saved level-1 graph and the final labels C_t: its
-// entries relabelled, neither sorted nor merged (communities that merged
-// above level 0 leave repeated keys); the next step's sort orders them and
-// sums equal keys with the batch's and the movers' entries.
-void inc_finish(IncCoarsen& H, const int32_t* Ct, int32_t n, CoarsenScratch& s,
-                hipStream_t st);
-
 // Canonical labels of the final partition (smallest level-0 id per
 // community), the level-0 totals and sizes by label, and C_t.  zero2 (may
 // be null): two int64 counters cleared on the way (the caller's next sums).

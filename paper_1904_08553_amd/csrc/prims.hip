@@ -3,7 +3,7 @@
 // radix ranking by one 64-bit ballot per digit bit, running digit counts per wave.
 #include <cstdlib>
 
-#include "dc_common.h"
+#include "dc_scan.h"
 
 namespace dc {
 
@@ -21,35 +21,6 @@ PrimScratch& prim_scratch() {
 }
 
 namespace {
-
-constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_ITEMS = 8;
-constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;  // 2048
-constexpr int64_t SCAN_RAW_MAX = 1024;  // tiles whose offsets are summed in-kernel
-static_assert(SCAN_RAW_MAX % SCAN_THREADS == 0, "raw partials per thread");
-
-template <class T, int NT = SCAN_THREADS>
-__device__ T block_excl_scan(T v, T* lds, T* total) {
-  const int lane = lane_id(), wid = threadIdx.x / WAVE;
-  T x = v;
-#pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) {
-    T y = __shfl_up(x, o, WAVE);
-    if (lane >= o) x += y;
-  }
-  if (lane == WAVE - 1) lds[wid] = x;
-  __syncthreads();
-  T pre = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < NT / WAVE; ++w) {
-    T t = lds[w];
-    pre += (w < wid) ? t : T(0);
-    tot += t;
-  }
-  __syncthreads();
-  *total = tot;
-  return pre + x - v;
-}
 
 template <class T>
 __global__ void __launch_bounds__(SCAN_THREADS)
@@ -89,22 +60,7 @@ __global__ void __launch_bounds__(SCAN_THREADS)
     const T x = in[idx < n ? idx : n - 1];
     v[i] = idx < n ? x : T(0);
   }
-  T off = 0;
-  if (part && raw) {  // nblocks <= SCAN_RAW_MAX
-    T pv[SCAN_RAW_MAX / SCAN_THREADS];
-#pragma unroll
-    for (int j = 0; j < SCAN_RAW_MAX / SCAN_THREADS; ++j) {
-      const int64_t b = int64_t(threadIdx.x) + int64_t(j) * SCAN_THREADS;
-      const T x = part[b < nblocks ? b : nblocks - 1];
-      pv[j] = b < int64_t(blockIdx.x) ? x : T(0);
-    }
-    T acc = 0;
-#pragma unroll
-    for (int j = 0; j < SCAN_RAW_MAX / SCAN_THREADS; ++j) acc += pv[j];
-    (void)block_excl_scan<T>(acc, lds, &off);
-  } else if (part) {
-    off = part[blockIdx.x];
-  }
+  const T off = tile_offset<T>(part, raw, nblocks, lds);
   T s = 0;
 #pragma unroll
   for (int i = 0; i < SCAN_ITEMS; ++i) s += v[i];

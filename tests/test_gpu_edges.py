@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 import torch
 
+from gpu_common import compare, make_pair, step_pair
 from oracle import mlp as M
 from paper_1904_08553_amd import dc
+from paper_1904_08553_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +41,17 @@ def test_forward_tiles_and_nan_rows(n):
     assert np.all(np.isfinite(z))
     net.close()
     net0.close()
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 4097])
+def test_steps_at_scan_tile_edges(n):
+    """Vertex counts around the scan tile (2,048) with weighted changes: the
+    restricted compaction's ranks, movers and run sums over one tile, a full
+    one and a remainder of one element."""
+    print(f"case: steps n={n}", flush=True)
+    (u, v, w), batches = W.DCSBM(n=n, m=6 * n, blocks=20, dmax=200, seed=n).stream(3, frac=0.05)
+    o, g = make_pair(n, u, v, w)
+    compare(o, g, "init")
+    for t, b in enumerate(batches):
+        step_pair(o, g, b)
+        compare(o, g, f"n={n} step {t}")
