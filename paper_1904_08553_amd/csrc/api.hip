@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "dc_scan.h"
 
 using namespace dc;
 
@@ -615,38 +616,41 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
   const int64_t na = add ? add->count : 0;
   const int64_t nd = del ? del->count : 0;
   int32_t* flags = reinterpret_cast<int32_t*>(stat + ST_FLAGS);
-  validate_edges(du, dv, nullptr, nd, n, flags, nullptr, st);
-  validate_edges(au, av, aw, na, n, flags, stat + ST_WSUM_ADD, st);
-  const int bits = sort_bits(n);
   // every deletion and insertion as two directed records, sorted once; a
-  // run of equal keys is one directed pair of the batch
+  // run of equal keys is one directed pair of the batch, one change
   const int32_t* off_old = c->off[c->cur].as<int32_t>();
   const int2* adj_old = c->adj[c->cur].as<int2>();
   const int64_t nr = 2 * (nd + na);
-  for (DBuf* b : {&c->rkeys, &c->rk1, &c->ch_key, &c->ukeys}) b->ensure(size_t(nr + 1) * 8);
-  for (DBuf* b : {&c->rvals, &c->rv1, &c->rheads, &c->rpos, &c->ch_op, &c->ch_w, &c->ch_dk,
-                  &c->dnet, &c->cnet, &c->ins_flag, &c->ins_pos,
-                  &c->src_flag, &c->src_pos, &c->src_list, &c->uw, &c->dw_old})
+  for (DBuf* b : {&c->rkeys, &c->rk1, &c->ch_key, &c->ins_keys}) b->ensure(size_t(nr + 1) * 8);
+  for (DBuf* b : {&c->rvals, &c->rv1, &c->ch_op, &c->ch_w, &c->ch_dk, &c->cnet, &c->ins_pos})
     b->ensure(size_t(nr + 1) * 4);
-  c->ins_keys.ensure(size_t(nr + 1) * 8);
   uint64_t* rkeys = c->rkeys.as<uint64_t>();
   uint32_t* rvals = c->rvals.as<uint32_t>();
-  batch_records(du, dv, nd, au, av, na, n, rkeys, rvals, st);
-  radix_sort_pairs(rkeys, rvals, c->rk1.as<uint64_t>(), c->rv1.as<uint32_t>(), nr, bits, st);
-  int32_t* rheads = c->rheads.as<int32_t>();
-  int32_t* rpos = c->rpos.as<int32_t>();
-  run_heads(rkeys, nr, rheads, st);
-  int32_t* nruns = reinterpret_cast<int32_t*>(stat + ST_N1);
-  scan_excl_i32(rheads, rpos, nr, nruns, st);
   uint64_t* ch_key = c->ch_key.as<uint64_t>();
   int32_t* ch_op = c->ch_op.as<int32_t>();
   int32_t* ch_w = c->ch_w.as<int32_t>();
   int32_t* ch_dk = c->ch_dk.as<int32_t>();
-  resolve_changes(rkeys, rvals, rpos, nr, nruns, aw, n, off_old, adj_old,
-                  c->ukeys.as<uint64_t>(), c->uw.as<int32_t>(), c->dw_old.as<int32_t>(), ch_key,
-                  ch_op, ch_w, ch_dk, c->dnet.as<int32_t>(), flags,
-                  stat + ST_WSUM_DEL, st);
-  read_stat(c);
+  int32_t* cnet = c->cnet.as<int32_t>();
+  int32_t* ins_pos = c->ins_pos.as<int32_t>();
+  uint64_t* ins_keys = c->ins_keys.as<uint64_t>();
+  int32_t* hb = static_cast<int32_t*>(c->hbuf);
+  hb[0] = hb[1] = hb[2] = 0;
+  batch_records(du, dv, nd, au, av, aw, na, n, rkeys, rvals, flags, stat + ST_WSUM_ADD, st);
+  if (radix_sort_pairs_swap(rkeys, rvals, c->rk1.as<uint64_t>(), c->rv1.as<uint32_t>(), nr,
+                            sort_bits(n), st)) {
+    rkeys = c->rk1.as<uint64_t>();
+    rvals = c->rv1.as<uint32_t>();
+  }
+  resolve_changes(rkeys, rvals, nr, aw, n, off_old, adj_old, c->rpart, c->npart, ch_key, ch_op,
+                  ch_w, ch_dk, cnet, ins_pos, ins_keys, reinterpret_cast<int32_t*>(stat + ST_N1),
+                  flags, stat + ST_WSUM_DEL, stat, ST_COUNT, c->hstat_dev, c->hbuf_dev, st);
+  if (nr > 0) {
+    DC_HIP(hipStreamSynchronize(st));
+    check_stat_errors(hs);
+  } else {
+    std::fill(hs, hs + ST_COUNT, 0ll);
+    fill_i32(cnet, 0, 1, st);
+  }
   // checks in the documented order; nothing has been changed yet
   if (int32_t f = int32_t(hs[ST_FLAGS])) return status_from_flags(f);
   const long long two_m_new =
@@ -654,41 +658,56 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
   if (two_m_new >= TWO_M_LIMIT) return DC_E_OVERFLOW;
 
   // ---- from here on the state changes ----
-  const int64_t nch = nr > 0 ? int32_t(hs[ST_N1]) : 0;
+  const int64_t nch = hb[0], n_ins = hb[1], nnz_new = c->nnz + hb[2];
   c->nch_last = nch;
-  int32_t* cnet = c->cnet.as<int32_t>();
-  scan_excl_i32(c->dnet.as<int32_t>(), cnet, nch, cnet + nch, st);
+  c->n_ins_last = n_ins;
   c->cptr.ensure(size_t(n + 1) * 4);
   c->new_deg.ensure(size_t(n + 1) * 4);
+  c->deg_part.ensure(size_t(ceil_div(n, SCAN_TILE)) * 4);
   int32_t* cptr = c->cptr.as<int32_t>();
-  row_bounds(ch_key, nch, n, cptr, st);
   const int mode = c->opt.mode;
   const bool samples = mode == DC_MODE_LEARNED || c->opt.collect;
+  const bool screening = mode == DC_MODE_DELTA || samples;
+  const bool fused = c->opt.del_rule == DC_DEL_GAIN;
+  const bool cascade = c->opt.cascade_den > 0;
+  // without the cascade the fused screening pass needs no list of insertion
+  // sources: its vertex set comes straight from the rows of the change list
+  const bool direct = screening && fused && !cascade;
   c->T_count = 0;
   c->have_y = c->have_logits = false;
   if (samples) {
     ensure_sample_state(c);
     DC_HIP(hipMemcpyAsync(c->kprev.p, c->k0.p, size_t(n) * 4, hipMemcpyDeviceToDevice, st));
+    c->chsrc.ensure(size_t(std::min<int64_t>(n, nch) + 1) * 4);
+  }
+  if (screening && fused) {
+    c->uflag.ensure(size_t(n) + 1);
+    c->ulist.ensure(size_t(n + 1) * 4);
   }
   c->tile_row.ensure(size_t(ceil_div(c->nnz, MERGE_TILE) + 1) * 4);
-  row_changes(cptr, ch_op, ch_dk, off_old, n, c->new_deg.as<int32_t>(), c->k0.as<int32_t>(),
-              c->C.as<int32_t>(), c->a0.as<int32_t>(), c->tile_row.as<int32_t>(), st);
+  RowOut rows{};
+  rows.cptr = cptr;
+  rows.new_deg = c->new_deg.as<int32_t>();
+  rows.deg_part = c->deg_part.as<int32_t>();
+  rows.tile_row = c->tile_row.as<int32_t>();
+  rows.k = c->k0.as<int32_t>();
+  rows.a = c->a0.as<int32_t>();
+  rows.ucount = reinterpret_cast<int32_t*>(stat + ST_N0);
+  rows.ccount = reinterpret_cast<int32_t*>(stat + ST_N2);
+  if (direct) {
+    rows.uflag = c->uflag.as<uint8_t>();
+    rows.seg_beg = c->seg_beg.as<int32_t>();
+    rows.seg_end = c->seg_end.as<int32_t>();
+    rows.ulist = c->ulist.as<int32_t>();
+    rows.n_src = stat + ST_NSRC;
+    rows.n_dsrc = stat + ST_NDSRC;
+  }
+  if (samples) rows.crows = c->chsrc.as<int32_t>();
+  row_changes(ch_key, ch_op, ch_dk, ins_pos, nch, n_ins, off_old, c->C.as<int32_t>(), n, rows, st);
   const int nxt = c->cur ^ 1;
   c->off[nxt].ensure(size_t(n + 1) * 4);
   int32_t* off_new = c->off[nxt].as<int32_t>();
-  // (the scans write the new entry count and the insertion count to host
-  // memory as well: one wait, no copy)
-  int32_t* hb = static_cast<int32_t*>(c->hbuf);
-  scan_excl_i32(c->new_deg.as<int32_t>(), off_new, n, off_new + n, st, c->hbuf_dev);
-  // insertion keys (sorted directed pairs) and their sources
-  select_insertions(ch_op, nch, c->ins_flag.as<int32_t>(), st);
-  hb[1] = 0;
-  scan_excl_i32(c->ins_flag.as<int32_t>(), c->ins_pos.as<int32_t>(), nch,
-                reinterpret_cast<int32_t*>(stat + ST_N2), st, c->hbuf_dev + 1);
-  DC_HIP(hipStreamSynchronize(st));
-  const int64_t nnz_new = hb[0];
-  const int64_t n_ins = nch > 0 ? hb[1] : 0;
-  c->n_ins_last = n_ins;
+  scan_tiles_i32(rows.new_deg, off_new, n, rows.deg_part, off_new + n, st);
   c->adj[nxt].ensure(size_t(nnz_new + 1) * 8);
   merge_rows(off_old, adj_old, c->nnz, off_new, c->adj[nxt].as<int2>(), n, cptr,
              c->tile_row.as<int32_t>(), ch_key, ch_op, ch_w, cnet, nch, st);
@@ -703,42 +722,27 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
   LevelView g0{n, c->nnz, c->off[c->cur].as<int32_t>(), c->adj[c->cur].as<int2>(),
                c->k0.as<int32_t>()};
   if (samples) {
-    // endpoints of the changed pairs (the distinct sources of the change
-    // list) and their neighbours in G_t
-    int32_t* crow_flag = c->rheads.as<int32_t>();
-    int32_t* crow_pos = c->rpos.as<int32_t>();
-    c->chsrc.ensure(size_t(nr + 1) * 4);
-    int32_t* crows = c->chsrc.as<int32_t>();
-    source_heads(ch_key, nch, n, crow_flag, st);
-    scan_excl_i32(crow_flag, crow_pos, nch, crow_pos + nch, st);
-    gather_sources(ch_key, crow_flag, crow_pos, nch, n, crows, st);
+    // endpoints of the changed pairs (the rows with a change) and their
+    // neighbours in G_t
     fill_u8(c->tmark.as<uint8_t>(), 0, n, st);
-    mark_touched(crows, crow_pos + nch, nch, g0.off, g0.adj, c->tmark.as<uint8_t>(), st);
+    mark_touched(rows.crows, rows.ccount, nch, g0.off, g0.adj, c->tmark.as<uint8_t>(), st);
   }
-  if (mode == DC_MODE_DELTA || samples) {
-    const bool fused = c->opt.del_rule == DC_DEL_GAIN;
-    const bool cascade = c->opt.cascade_den > 0;
+  if (screening) {
     if (cascade) c->accflag.ensure(size_t(n) + 1);
-    if (fused) {
-      c->uflag.ensure(size_t(n) + 1);
-      c->ulist.ensure(size_t(n + 1) * 4);
-    }
     uint8_t* R = c->R.as<uint8_t>();
     uint8_t* cflag = c->cflag.as<uint8_t>();
     int32_t* dflag = c->dflag.as<int32_t>();
     uint8_t* accflag = cascade ? c->accflag.as<uint8_t>() : nullptr;
     {
-      // R, the community flags, the deletion-source flags, the accepted
-      // flags (cascade), the union flags (fused) and the count of R_t's
-      // list start at zero
+      // R, the community flags and the count of R_t's list start at zero, and
+      // unless row_changes has written them the deletion-source flags, the
+      // union flags (fused) and the accepted flags (cascade)
       void* zp[6] = {R, cflag, dflag, accflag, fused ? c->uflag.p : nullptr,
                      c->rpos2.as<int32_t>() + n};
-      const int64_t zb[6] = {n, n, 4 * int64_t(n), cascade ? int64_t(n) : 0,
-                             fused ? int64_t(n) : 0, 4};
+      const int64_t zb[6] = {n, n, direct ? 0 : 4 * int64_t(n), cascade ? int64_t(n) : 0,
+                             fused && !direct ? int64_t(n) : 0, 4};
       zero_buffers(zp, zb, 6, st);
     }
-    uint64_t* ins_keys = c->ins_keys.as<uint64_t>();
-    gather_u64(ch_key, c->ins_flag.as<int32_t>(), c->ins_pos.as<int32_t>(), nch, ins_keys, st);
     // Alg. 2 scratch: a gain per insertion record, the best sink per source
     const int64_t item_cap = ds_item_cap(std::min<int64_t>(n, n_ins), c->nnz);
     c->sink_g.ensure(size_t(n_ins + 1) * 8);
@@ -748,12 +752,10 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
     const DsScratch dsx{c->sink_g.as<long long>(), c->best_j.as<int32_t>(),
                         c->best_g.as<long long>(), c->ds_items.as<int2>(), stat + ST_MARK,
                         item_cap};
-    int32_t* src_flag = c->src_flag.as<int32_t>();
-    int32_t* src_pos = c->src_pos.as<int32_t>();
-    // without the cascade the fused pass needs no list of insertion sources:
-    // its vertex set comes straight from the change list
-    const bool direct = fused && !cascade;
     if (!direct) {
+      for (DBuf* b : {&c->src_flag, &c->src_pos, &c->src_list}) b->ensure(size_t(nr + 1) * 4);
+      int32_t* src_flag = c->src_flag.as<int32_t>();
+      int32_t* src_pos = c->src_pos.as<int32_t>();
       source_heads(ins_keys, n_ins, n, src_flag, st);
       scan_excl_i32(src_flag, src_pos, n_ins, reinterpret_cast<int32_t*>(stat + ST_N3), st);
       gather_sources(ins_keys, src_flag, src_pos, n_ins, n, c->src_list.as<int32_t>(), st);
@@ -771,17 +773,10 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
       Bins b;
       bool binned = false;
       if (direct) {
-        // uflag, sink segments and the heads of the flagged sources in one
-        // pass over the sorted changes; the union list is the heads' sources,
-        // binned by its device count (at most nch) with the counters copied
-        // back before the binning's wait
-        screen_union(ch_key, ch_op, c->ins_pos.as<int32_t>(), ins_keys, n_ins, nch, n,
-                     c->C.as<int32_t>(), dflag, uflag, c->seg_beg.as<int32_t>(),
-                     c->seg_end.as<int32_t>(), src_flag, stat + ST_NSRC, stat + ST_NDSRC, st);
-        scan_excl_i32(src_flag, src_pos, nch, reinterpret_cast<int32_t*>(stat + ST_N0), st);
-        gather_sources(ch_key, src_flag, src_pos, nch, n, c->ulist.as<int32_t>(), st);
-        make_bins(c->ulist.as<int32_t>(), nch, g0.off, b, c->bins, st, nullptr,
-                  reinterpret_cast<const int32_t*>(stat + ST_N0), stat, c->hstat_dev, ST_COUNT);
+        // the union list from row_changes, binned by its device count (at
+        // most nch) with the counters copied back before the binning's wait
+        make_bins(rows.ulist, std::min<int64_t>(n, nch), g0.off, b, c->bins, st, nullptr,
+                  rows.ucount, stat, c->hstat_dev, ST_COUNT);
         check_stat_errors(hs);
         binned = true;
         n_src = slot_total(hs, ST_NSRC);
@@ -1045,10 +1040,10 @@ void destroy_ctx(dc_ctx* c) {
 template <class F>
 void for_each_buf(dc_ctx* c, F&& f) {
   for (DBuf* b : {&c->off[0], &c->off[1], &c->adj[0], &c->adj[1], &c->k0, &c->C, &c->a0,
-                  &c->sz0, &c->in_au, &c->in_av, &c->in_aw, &c->in_du, &c->in_dv, &c->dw_old, &c->akeys, &c->avals, &c->ak1,
+                  &c->sz0, &c->in_au, &c->in_av, &c->in_aw, &c->in_du, &c->in_dv, &c->akeys, &c->avals, &c->ak1,
                   &c->av1, &c->aheads, &c->apos, &c->ukeys, &c->uw, &c->rkeys, &c->rvals,
-                  &c->rk1, &c->rv1, &c->rheads, &c->rpos, &c->ch_key, &c->ch_op, &c->ch_w,
-                  &c->ch_dk, &c->dnet, &c->cnet, &c->cptr, &c->new_deg, &c->tile_row, &c->ins_flag, &c->ins_pos, &c->ins_keys, &c->src_flag,
+                  &c->rk1, &c->rv1, &c->rpart, &c->npart, &c->ch_key, &c->ch_op, &c->ch_w,
+                  &c->ch_dk, &c->cnet, &c->cptr, &c->new_deg, &c->deg_part, &c->tile_row, &c->ins_pos, &c->ins_keys, &c->src_flag,
                   &c->src_pos, &c->src_list, &c->dflag, &c->dpos, &c->dlist, &c->R, &c->cflag,
                   &c->rflag, &c->rpos2, &c->Rlist, &c->seg_beg, &c->seg_end, &c->chsrc,
                   &c->accflag, &c->cascand, &c->clist, &c->uflag, &c->ulist, &c->pre, &c->sink_g, &c->best_j,

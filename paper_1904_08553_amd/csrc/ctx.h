@@ -22,11 +22,10 @@ struct dc_ctx {
   DBuf k0, C, a0, sz0;
   // batch
   DBuf in_au, in_av, in_aw, in_du, in_dv;
-  DBuf dw_old;
   DBuf akeys, avals, ak1, av1, aheads, apos, ukeys, uw;
-  DBuf rkeys, rvals, rk1, rv1, rheads, rpos;
-  DBuf ch_key, ch_op, ch_w, ch_dk, dnet, cnet, cptr, new_deg, tile_row;
-  DBuf ins_flag, ins_pos, ins_keys, src_flag, src_pos, src_list, dflag, dpos, dlist;
+  DBuf rkeys, rvals, rk1, rv1, rpart, npart;
+  DBuf ch_key, ch_op, ch_w, ch_dk, cnet, cptr, new_deg, deg_part, tile_row;
+  DBuf ins_pos, ins_keys, src_flag, src_pos, src_list, dflag, dpos, dlist;
   DBuf R, cflag, rflag, rpos2, Rlist, seg_beg, seg_end, chsrc;
   DBuf accflag, cascand, clist;  // cascade-aware screening
   DBuf uflag, ulist;             // union of insertion sources and deletion endpoints

@@ -383,6 +383,11 @@ void scan_excl_i32(const int32_t* in, int32_t* out, int64_t n,
 void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n,
                    int64_t* total, hipStream_t st, int64_t* host_total = nullptr);
 
+// scan_excl_i32 whose tile totals the caller's kernel has already written to
+// part (one per SCAN_TILE elements of dc_scan.h; overwritten).
+void scan_tiles_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* part, int32_t* total,
+                    hipStream_t st);
+
 // Stable LSD radix sort of (key, value) pairs on key bits [0, bits).
 // Sorted data ends in (k0, v0); (k1, v1) are scratch of the same size.
 void radix_sort_pairs(uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1,

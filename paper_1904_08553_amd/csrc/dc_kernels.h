@@ -68,8 +68,8 @@ void validate_edges(const int32_t* u, const int32_t* v, const int32_t* w,
                     int64_t m, int32_t n, int32_t* flags, long long* wsum,
                     hipStream_t st);
 
-// Directed entries of an edge list for the initial CSR: keys u*n+v and v*n+u
-// with the weight as value.
+// Directed entries of an edge list for the initial CSR: pair keys (u, v) and
+// (v, u) with the weight as value.
 void make_directed(const int32_t* u, const int32_t* v, const int32_t* w,
                    int64_t m, int32_t n, uint64_t* keys, uint32_t* vals,
                    hipStream_t st);
@@ -84,7 +84,7 @@ void reduce_runs(const uint64_t* keys, const uint32_t* vals,
                  const int32_t* wsrc, const int32_t* pos, int64_t m,
                  uint64_t* out_key, int32_t* out_w, hipStream_t st);
 
-// row_ptr[u] = first index i with keys[i] >= u*n (u in [0, n]).
+// row_ptr[u] = first index i whose key's row is at least u (u in [0, n]).
 void row_bounds(const uint64_t* keys, int64_t m, int32_t n, int32_t* row_ptr,
                 hipStream_t st);
 
@@ -96,42 +96,67 @@ void keys_to_adj(const uint64_t* keys, const int32_t* w, int64_t m, int32_t n,
 void row_weight_sums(const int32_t* off, const int2* adj, int32_t n,
                      int32_t* k, hipStream_t st);
 
-// Change records of a batch, sorted by directed key src*n+dst.
+// Change records of a batch, sorted by pair key (src, dst).
 enum ChangeOp : int32_t { OP_DELETE = 1, OP_ADD = 2, OP_NEW = 3, OP_REPLACE = 4 };
 
-// Directed records of a batch: deletion e gives keys u*n+v and v*n+u with
-// value (e<<1)|0, insertion e the same keys with value (e<<1)|1.
+// Directed records of a batch: deletion e gives the pair keys (u, v) and
+// (v, u) with value (e<<1)|0, insertion e the same keys with value (e<<1)|1.
+// flags |= F_RANGE / F_SELF / F_WEIGHT; wsum (SUM_SLOTS counters) += the
+// inserted weights.
 void batch_records(const int32_t* du, const int32_t* dv, int64_t nd, const int32_t* au,
-                   const int32_t* av, int64_t na, int32_t n, uint64_t* keys, uint32_t* vals,
-                   hipStream_t st);
+                   const int32_t* av, const int32_t* aw, int64_t na, int32_t n, uint64_t* keys,
+                   uint32_t* vals, int32_t* flags, long long* wsum, hipStream_t st);
 
-// One change per run of equal sorted record keys (pos: exclusive scan of the
-// run heads, *nruns on the device): ch_key, ch_op, ch_w (new weight for NEW
-// and REPLACE, added weight for ADD), ch_dk (change of the row's weighted
-// degree), dnet (+1 for NEW, -1 for DELETE, else 0); flags |= F_DUP (a pair
-// deleted twice) and F_NO_EDGE (a deletion of a pair absent from off/adj);
-// wsum (SUM_SLOTS counters) += the old weights of the deleted edges.
-// run_key/run_w/run_ndel: scratch of m.
-void resolve_changes(const uint64_t* keys, const uint32_t* vals, const int32_t* pos, int64_t m,
-                     const int32_t* nruns, const int32_t* ins_w, int32_t n, const int32_t* off,
-                     const int2* adj, uint64_t* run_key, int32_t* run_w, int32_t* run_ndel,
+// One change per run of equal sorted record keys (*nruns of them, on the
+// device): ch_key, ch_op, ch_w (new weight for NEW and REPLACE, added weight
+// for ADD), ch_dk (change of the row's weighted degree); cnet (exclusive
+// prefix sum of +1 per NEW and -1 per DELETE, *nruns + 1 ints), ins_pos
+// (insertion records, all but DELETE, before each change) and ins_keys (their
+// keys); flags |= F_DUP (a pair deleted twice) and F_NO_EDGE (a deletion of a
+// pair absent from off/adj); wsum (SUM_SLOTS counters) += the old weights of
+// the deleted edges.  Pinned host memory (device addresses) receives the
+// first nstat slots of stat, flags and sums included, and host[0..2] =
+// {changes, insertion records, NEW minus DELETE}.  part, npart: scratch.
+// Nothing is launched for m = 0.
+void resolve_changes(const uint64_t* keys, const uint32_t* vals, int64_t m, const int32_t* ins_w,
+                     int32_t n, const int32_t* off, const int2* adj, DBuf& part, DBuf& npart,
                      uint64_t* ch_key, int32_t* ch_op, int32_t* ch_w, int32_t* ch_dk,
-                     int32_t* dnet, int32_t* flags, long long* wsum, hipStream_t st);
+                     int32_t* cnet, int32_t* ins_pos, uint64_t* ins_keys, int32_t* nruns,
+                     int32_t* flags, long long* wsum, const long long* stat, int nstat,
+                     long long* host_stat, int32_t* host, hipStream_t st);
 
 // Old CSR entries per block of the merge.
 constexpr int MERGE_TILE = 1024;
 
-// Per row: new degree and degree-weight change; k += dk; a[C[u]] += dk.
-// tile_row (ceil(off[n] / MERGE_TILE) + 1 ints): the row holding entry
-// t * MERGE_TILE for each tile t, then the row holding the last entry.
-void row_changes(const int32_t* cptr, const int32_t* ch_op, const int32_t* ch_dk,
-                 const int32_t* off, int32_t n, int32_t* new_deg, int32_t* k,
-                 const int32_t* C, int32_t* a, int32_t* tile_row, hipStream_t st);
+// Outputs of row_changes, per row u unless said otherwise.
+struct RowOut {
+  int32_t* cptr;      // first change of the row (n + 1 ints)
+  int32_t* new_deg;   // its degree in G_t
+  int32_t* deg_part;  // sums of new_deg per SCAN_TILE rows (scan_tiles_i32)
+  int32_t* tile_row;  // ceil(off[n] / MERGE_TILE) + 1 ints: the row holding entry
+                      // t * MERGE_TILE for each tile t, then the row of the last entry
+  int32_t* k;         // += the row's weight change
+  int32_t* a;         // a[C[u]] += the same
+  // screening set (uflag null: not asked for)
+  uint8_t* uflag;     // bit 0: an insertion record; bit 1: a deletion or replacement
+                      // inside one community of C
+  int32_t* seg_beg;   // rows of bit 0: their insertion records [seg_beg, seg_end)
+  int32_t* seg_end;
+  int32_t* ulist;     // the rows with a bit set, in no fixed order; *ucount (zeroed) their
+  int32_t* ucount;    // number
+  long long* n_src;   // SUM_SLOTS counters each: rows of bit 0, rows of bit 1
+  long long* n_dsrc;
+  int32_t* crows;     // (null: not asked for) the rows with a change, in no fixed order;
+  int32_t* ccount;    // *ccount (zeroed) their number
+};
+void row_changes(const uint64_t* ch_key, const int32_t* ch_op, const int32_t* ch_dk,
+                 const int32_t* ins_pos, int64_t nch, int64_t n_ins, const int32_t* off,
+                 const int32_t* C, int32_t n, const RowOut& o, hipStream_t st);
 
 // Merge G_{t-1} with the sorted change list (ch_*, nch entries, row bounds
 // cptr) into G_t: one launch, tiles of MERGE_TILE old entries (tile_row from
 // row_changes) plus blocks that place the NEW pairs.  cnet: exclusive prefix
-// sum of dnet over the change list (nch + 1 ints).  off_new must already
+// sum of NEW minus DELETE over the change list (nch + 1 ints).  off_new must already
 // hold G_t's offsets.
 void merge_rows(const int32_t* off_old, const int2* adj_old, int64_t nnz_old,
                 const int32_t* off_new, int2* adj_new, int32_t n, const int32_t* cptr,

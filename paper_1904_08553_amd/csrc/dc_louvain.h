@@ -323,10 +323,6 @@ void feat_eval(const LevelView& g, const int32_t* C, const int32_t* a, long long
 // out[pos[i]] = i for flag[i] != 0 (pos = exclusive scan of flag).
 void compact_index(const int32_t* flag, const int32_t* pos, int64_t n, int32_t* out,
                    hipStream_t st);
-// Insertion changes (op != DELETE) of the sorted change list, compacted.
-void select_insertions(const int32_t* ch_op, int64_t nch, int32_t* flag, hipStream_t st);
-void gather_u64(const uint64_t* in, const int32_t* flag, const int32_t* pos, int64_t n,
-                uint64_t* out, hipStream_t st);
 // flag[q] = 1 where the source of sorted directed keys changes; out ids.
 void source_heads(const uint64_t* keys, int64_t m, int32_t n, int32_t* flag, hipStream_t st);
 void gather_sources(const uint64_t* keys, const int32_t* flag, const int32_t* pos, int64_t m,
@@ -337,18 +333,6 @@ void source_segments(const uint64_t* keys, int64_t m, int32_t n, int32_t* seg_be
 // dflag[src] = 1 for deleted pairs inside one community.
 void deletion_sources(const uint64_t* ch_key, const int32_t* ch_op, int64_t nch, int32_t n,
                       const int32_t* C, int32_t* dflag, hipStream_t st);
-// The fused screening set from the sorted change list (labels C = C_{t-1}):
-// per source, uflag bit 0 (an insertion record: an Alg. 2 source, its sinks
-// ins_keys[seg_beg, seg_end), ins_pos locating each record there) and bit
-// 1 (an intra-community deletion); hflag[q] = 1 at the first change of
-// each flagged source (nch entries); n_src / n_dsrc (SUM_SLOTS counters
-// each) += the sources of each kind.  sbits (n ints) and uflag must be zero
-// beforehand.
-void screen_union(const uint64_t* ch_key, const int32_t* ch_op, const int32_t* ins_pos,
-                  const uint64_t* ins_keys, int64_t n_ins, int64_t nch, int32_t n,
-                  const int32_t* C, int32_t* sbits, uint8_t* uflag, int32_t* seg_beg,
-                  int32_t* seg_end, int32_t* hflag, long long* n_src, long long* n_dsrc,
-                  hipStream_t st);
 // R[i] = 1 and R[Gamma(i)] = 1 for every listed vertex.
 void mark_neighbourhoods(const int32_t* list, int64_t cnt, const int32_t* off, const int2* adj,
                          uint8_t* R, hipStream_t st);

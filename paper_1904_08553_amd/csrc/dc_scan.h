@@ -11,7 +11,6 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;  // 2048
 constexpr int64_t SCAN_RAW_MAX = 1024;  // tiles whose offsets are summed in-kernel
-static_assert(SCAN_RAW_MAX % SCAN_THREADS == 0, "raw partials per thread");
 
 template <class T, int NT = SCAN_THREADS>
 __device__ T block_excl_scan(T v, T* lds, T* total) {
@@ -36,33 +35,34 @@ __device__ T block_excl_scan(T v, T* lds, T* total) {
   return pre + x - v;
 }
 
-// Sum of the block's SCAN_THREADS values, in every thread.
-template <class T>
+// Sum of the block's NT values, in every thread.
+template <class T, int NT = SCAN_THREADS>
 __device__ T block_total(T v, T* lds) {
   T tot;
-  (void)block_excl_scan<T>(v, lds, &tot);
+  (void)block_excl_scan<T, NT>(v, lds, &tot);
   return tot;
 }
 
 // Offset of tile blockIdx.x of nt: part[blockIdx.x] when part holds exclusive
 // prefixes (raw = 0), the sum of part[0, blockIdx.x) when it holds the raw
 // tile totals (raw = 1, nt <= SCAN_RAW_MAX; clamped loads, all in flight
-// together), 0 when part is null.
-template <class T>
+// together), 0 when part is null.  Blocks of NT threads.
+template <class T, int NT = SCAN_THREADS>
 __device__ T tile_offset(const T* __restrict__ part, int raw, int64_t nt, T* lds) {
+  static_assert(SCAN_RAW_MAX % NT == 0, "raw partials per thread");
   if (!part) return T(0);
   if (!raw) return part[blockIdx.x];
-  T pv[SCAN_RAW_MAX / SCAN_THREADS];
+  T pv[SCAN_RAW_MAX / NT];
 #pragma unroll
-  for (int j = 0; j < SCAN_RAW_MAX / SCAN_THREADS; ++j) {
-    const int64_t b = int64_t(threadIdx.x) + int64_t(j) * SCAN_THREADS;
+  for (int j = 0; j < SCAN_RAW_MAX / NT; ++j) {
+    const int64_t b = int64_t(threadIdx.x) + int64_t(j) * NT;
     const T x = part[b < nt ? b : nt - 1];
     pv[j] = b < int64_t(blockIdx.x) ? x : T(0);
   }
   T acc = 0;
 #pragma unroll
-  for (int j = 0; j < SCAN_RAW_MAX / SCAN_THREADS; ++j) acc += pv[j];
-  return block_total<T>(acc, lds);
+  for (int j = 0; j < SCAN_RAW_MAX / NT; ++j) acc += pv[j];
+  return block_total<T, NT>(acc, lds);
 }
 
 }  // namespace dc

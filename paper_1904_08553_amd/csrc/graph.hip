@@ -2,6 +2,7 @@
 // validation, and the sorted merge of a batch of additions and deletions into
 // the next CSR (a streaming pass over tiles of old entries).
 #include "dc_kernels.h"
+#include "dc_scan.h"
 
 namespace dc {
 
@@ -133,64 +134,136 @@ __device__ __forceinline__ int32_t find_in_row(const int2* adj, int32_t b,
   return b;
 }
 
-// Directed change records straight from the batch: deletion e gives the
-// pair keys (u, v) and (v, u) with value 2e, insertion e the same keys with value 2e+1.
-__global__ void k_batch_records(const int32_t* __restrict__ du, const int32_t* __restrict__ dv,
-                                int64_t nd, const int32_t* __restrict__ au,
-                                const int32_t* __restrict__ av, int64_t na, int kb,
-                                uint64_t* keys, uint32_t* vals) {
+// Directed change records straight from the batch, and its validation: a
+// deletion e gives the pair keys (u, v) and (v, u) with value 2e, an
+// insertion e the same keys with value 2e+1.  Ids out of range give keys
+// that nothing uses (their batch fails on F_RANGE).
+__global__ void __launch_bounds__(TPB)
+    k_batch_records(const int32_t* __restrict__ du, const int32_t* __restrict__ dv, int64_t nd,
+                    const int32_t* __restrict__ au, const int32_t* __restrict__ av,
+                    const int32_t* __restrict__ aw, int64_t na, int32_t n, int kb,
+                    uint64_t* keys, uint32_t* vals, int32_t* flags, long long* wsum) {
+  int32_t f = 0;
+  long long s = 0;
   GRID_STRIDE(i, nd + na) {
     const bool del = i < nd;
     const int64_t j = del ? i : i - nd;
-    const uint64_t a = uint32_t(del ? du[j] : au[j]), b = uint32_t(del ? dv[j] : av[j]);
+    const int32_t a = del ? du[j] : au[j], b = del ? dv[j] : av[j];
+    if (a < 0 || a >= n || b < 0 || b >= n) f |= F_RANGE;
+    if (a == b) f |= F_SELF;
+    if (!del) {
+      const int32_t x = aw[j];
+      if (x < 1) f |= F_WEIGHT;
+      s += x;
+    }
     const uint32_t val = (uint32_t(j) << 1) | (del ? 0u : 1u);
-    keys[2 * i] = pair_key(a, b, kb);
-    keys[2 * i + 1] = pair_key(b, a, kb);
+    keys[2 * i] = pair_key(uint32_t(a), uint32_t(b), kb);
+    keys[2 * i + 1] = pair_key(uint32_t(b), uint32_t(a), kb);
     vals[2 * i] = val;
     vals[2 * i + 1] = val;
   }
+  block_or(f, flags);
+  block_add(s, wsum + blockIdx.x % SUM_SLOTS);
 }
 
-// Per sorted record: its run (pos = exclusive scan of the run heads) gets
-// the record's insertion weight, or one more deletion.  run_w and run_ndel
-// must be zeroed.
-__global__ void k_run_accumulate(const uint64_t* __restrict__ keys,
-                                 const uint32_t* __restrict__ vals,
-                                 const int32_t* __restrict__ pos, int64_t m,
-                                 const int32_t* __restrict__ ins_w, uint64_t* run_key,
-                                 int32_t* run_w, int32_t* run_ndel) {
-  GRID_STRIDE(i, m) {
-    const bool head = i == 0 || keys[i] != keys[i - 1];
-    const int32_t r = head ? pos[i] : pos[i] - 1;
-    if (head) run_key[r] = keys[i];
-    const uint32_t v = vals[i];
-    if (v & 1u)
-      atomicAdd(&run_w[r], ins_w[v >> 1]);
-    else
-      atomicAdd(&run_ndel[r], 1);
+// Batch resolution: tiles of RES_TILE sorted records, one record a thread.  A
+// run of equal keys (one directed pair of the batch) becomes one change at
+// the number of runs before it.
+constexpr int RES_TILE = 512;
+constexpr int RES_OWN = 8;  // records of a run that its own thread sums; the
+                            // wave takes the rest of a longer run together
+static_assert(SCAN_RAW_MAX % RES_TILE == 0, "raw partials per thread");
+
+// What a change adds to the scans over the change list: an insertion record
+// (low half), NEW minus DELETE (high half).
+__device__ __forceinline__ long long change_counts(int32_t op) {
+  return (op != OP_DELETE ? 1ll : 0ll) + (op == OP_NEW ? 1ll << 32 : 0ll) -
+         (op == OP_DELETE ? 1ll << 32 : 0ll);
+}
+
+// Runs that begin in each tile (batches of more than one).
+__global__ void __launch_bounds__(RES_TILE)
+    k_count_runs(const uint64_t* __restrict__ keys, int64_t m, int32_t* part) {
+  __shared__ int32_t lds[RES_TILE / WAVE];
+  const int64_t i = int64_t(blockIdx.x) * RES_TILE + threadIdx.x;
+  const int64_t ic = i < m ? i : m - 1;
+  const uint64_t k = keys[ic], before = keys[ic > 0 ? ic - 1 : 0];
+  const int32_t c = i < m && (i == 0 || k != before) ? 1 : 0;
+  const int32_t t = block_total<int32_t, RES_TILE>(c, lds);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+
+// The change of each run: two deletions of one pair flag F_DUP, a deletion of
+// a pair absent from G_{t-1} flags F_NO_EDGE; *wsum += the old weights of the
+// deleted pairs (counted once, at src < dst).  A deletion with insertions is
+// a REPLACE (new weight = their sum), a deletion alone a DELETE, insertions
+// alone an ADD to an existing pair or a NEW one.  Per tile: its changes'
+// insertion records (low half of npart) and NEW minus DELETE (high half).
+// Bound by the row search's scattered reads (a 1% batch of the 1M/20M graph,
+// 400K records: 47 us, of which 6 were the run sums' own launch).
+__global__ void __launch_bounds__(RES_TILE)
+    k_resolve_runs(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals,
+                   int64_t m, const int32_t* __restrict__ part, int raw, int64_t nt,
+                   const int32_t* __restrict__ ins_w, int32_t n, int kb,
+                   const int32_t* __restrict__ off, const int2* __restrict__ adj,
+                   uint64_t* ch_key, int32_t* ch_op, int32_t* ch_w, int32_t* ch_dk,
+                   long long* npart, int32_t* nruns, int32_t* flags, long long* wsum) {
+  __shared__ int32_t l32[RES_TILE / WAVE];
+  __shared__ long long l64[RES_TILE / WAVE];
+  const int lane = lane_id();
+  const int64_t i = int64_t(blockIdx.x) * RES_TILE + threadIdx.x;
+  const int64_t ic = i < m ? i : m - 1;
+  const uint64_t key = keys[ic], before = keys[ic > 0 ? ic - 1 : 0];
+  const int32_t offs = tile_offset<int32_t, RES_TILE>(part, raw, nt, l32);
+  const bool head = i < m && (i == 0 || key != before);
+  int32_t tot;
+  const int32_t r = offs + block_excl_scan<int32_t, RES_TILE>(head ? 1 : 0, l32, &tot);
+  if (blockIdx.x == nt - 1 && threadIdx.x == 0) *nruns = offs + tot;
+  int32_t wi = 0, nd = 0;
+  int64_t j = i;
+  if (head) {
+    for (; j < m && j < i + RES_OWN && keys[j] == key; ++j) {
+      const uint32_t v = vals[j];
+      if (v & 1u)
+        wi += ins_w[v >> 1];
+      else
+        nd += 1;
+    }
   }
-}
-
-// One change per directed pair (run r < *nruns): two deletions of one pair
-// flag F_DUP, a deletion of a pair absent from G_{t-1} flags F_NO_EDGE;
-// *wsum += the old weights of the deleted pairs (counted once, at src < dst).
-// A deletion with insertions is a REPLACE (new weight = their sum), a
-// deletion alone a DELETE, insertions alone an ADD to an existing pair or a
-// NEW one.  Ids out of range are skipped (their batch fails on F_RANGE).
-__global__ void k_resolve_runs(const uint64_t* __restrict__ run_key,
-                               const int32_t* __restrict__ run_w,
-                               const int32_t* __restrict__ run_ndel,
-                               const int32_t* __restrict__ nruns, int32_t n, int kb,
-                               const int32_t* __restrict__ off, const int2* __restrict__ adj,
-                               uint64_t* ch_key, int32_t* ch_op, int32_t* ch_w, int32_t* ch_dk,
-                               int32_t* dnet, int32_t* flags, long long* wsum) {
-  const int64_t cnt = *nruns;
+  for (uint64_t more = __ballot(head && j == i + RES_OWN && j < m && keys[j] == key); more;
+       more &= more - 1) {
+    const int l = __ffsll((unsigned long long)more) - 1;
+    const uint64_t kl = uint64_t(readlane64((long long)key, l));
+    int32_t sw = 0, sd = 0;
+    for (int64_t p = int64_t(readlane64(j, l)) + lane;; p += 4 * WAVE) {
+      uint64_t kk[4];
+      uint32_t vv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {  // clamped: the loads in flight together
+        const int64_t pc = p + u * WAVE < m ? p + u * WAVE : m - 1;
+        kk[u] = keys[pc];
+        vv[u] = vals[pc];
+      }
+      bool in = true;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        in = p + u * WAVE < m && kk[u] == kl;
+        if (in && (vv[u] & 1u)) sw += ins_w[vv[u] >> 1];
+        if (in && !(vv[u] & 1u)) sd += 1;
+      }
+      if (__ballot(!in)) break;  // the run ends within these records
+    }
+    sw = wave_sum(sw);
+    sd = wave_sum(sd);
+    if (lane == l) {
+      wi += sw;
+      nd += sd;
+    }
+  }
   int32_t f = 0;
-  long long s = 0;
-  GRID_STRIDE(r, cnt) {
-    const uint64_t key = run_key[r];
+  long long s = 0, net = 0;
+  if (head) {
     const uint64_t src = key_row(key, kb), dst = key_col(key, kb);
-    const int32_t nd = run_ndel[r], wi = run_w[r];
     int32_t wo = 0;
     bool exists = false;
     if (src < uint64_t(n) && dst < uint64_t(n)) {
@@ -225,115 +298,244 @@ __global__ void k_resolve_runs(const uint64_t* __restrict__ run_key,
     ch_op[r] = op;
     ch_w[r] = w;
     ch_dk[r] = dk;
-    dnet[r] = op == OP_NEW ? 1 : (op == OP_DELETE ? -1 : 0);
+    net = change_counts(op);
   }
+  net = block_total<long long, RES_TILE>(net, l64);
+  if (threadIdx.x == 0) npart[blockIdx.x] = net;
   block_or(f, flags);
   block_add(s, wsum + blockIdx.x % SUM_SLOTS);
 }
 
-
-// Thread per row: new degree, k += the row's weight change, the label
-// totals a[C(u)] += the same change, and the rows that begin the merge's
-// tiles.  A block walks many rows and sums the
-// label changes in its LDS table first, so a large community receives one
-// update per block instead of one per row (same-address atomics serialise).
-constexpr int RC_U = 4;        // rows a thread takes per iteration
-constexpr int RC_MANY = 8;     // rows with more changes are summed by a wave
-constexpr int RC_TPB = 1024;   // one large block per CU: fewer flushes per label
-constexpr int RC_BLOCKS = 256;
-__global__ void __launch_bounds__(RC_TPB)
-    k_row_changes(const int32_t* __restrict__ cptr,
-                  const int32_t* __restrict__ ch_op,
-                  const int32_t* __restrict__ ch_dk,
-                  const int32_t* __restrict__ off, int32_t n, int32_t* new_deg,
-                  int32_t* k, const int32_t* __restrict__ C, int32_t* a,
-                  int32_t* tile_row) {
-  __shared__ AggLds agg;
-  agg_init(agg);
-  __syncthreads();
-  const int32_t nnz = off[n];
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  // RC_U rows per iteration, their loads issued before any is used; the
-  // loop runs while the wave's first row is in range, so whole waves take
-  // part in the wave sums below
-  for (int64_t u0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u0 - lane_id() < n;
-       u0 += RC_U * stride) {
-    int32_t b[RC_U], e[RC_U], ob[RC_U], oe[RC_U], cu[RC_U];
-#pragma unroll
-    for (int r = 0; r < RC_U; ++r) {
-      // clamped index (n >= 1): unconditional loads, all in flight together
-      const int64_t u = u0 + r * stride;
-      const bool h = u < n;
-      const int64_t uc = h ? u : n - 1;
-      const int32_t x0 = cptr[uc], x1 = cptr[uc + 1], y0 = off[uc], y1 = off[uc + 1], c = C[uc];
-      b[r] = h ? x0 : 0;
-      e[r] = h ? x1 : 0;
-      ob[r] = h ? y0 : 0;
-      oe[r] = h ? y1 : 0;
-      cu[r] = h ? c : 0;
-    }
-#pragma unroll
-    for (int r = 0; r < RC_U; ++r) {
-      const int64_t u = u0 + r * stride;
-      int32_t dd = 0, dk = 0;
-      // a row with many changes (a hub) is summed by the whole wave, one
-      // such row after the other; the others by their own thread
-      uint64_t many = __ballot(e[r] - b[r] > RC_MANY);
-      while (many) {
-        const int l = __ffsll((unsigned long long)many) - 1;
-        many &= many - 1;
-        const int32_t qb = __builtin_amdgcn_readlane(b[r], l);
-        const int32_t qe = __builtin_amdgcn_readlane(e[r], l);
-        int32_t sd = 0, sk = 0;
-        for (int32_t q = qb + lane_id(); q < qe; q += WAVE) {
-          const int32_t op = ch_op[q];
-          sd += op == OP_NEW ? 1 : (op == OP_DELETE ? -1 : 0);
-          sk += ch_dk[q];
-        }
-        sd = wave_sum(sd);
-        sk = wave_sum(sk);
-        if (lane_id() == l) {
-          dd = sd;
-          dk = sk;
-        }
-      }
-      if (e[r] > b[r] && e[r] - b[r] <= RC_MANY) {
-        // all RC_MANY slots loaded at once (indexes clamped to the row's
-        // last change), then the ones inside the row summed
-        int32_t ops[RC_MANY], dks[RC_MANY];
-#pragma unroll
-        for (int j = 0; j < RC_MANY; ++j) {
-          const int32_t q = b[r] + j < e[r] ? b[r] + j : e[r] - 1;
-          ops[j] = ch_op[q];
-          dks[j] = ch_dk[q];
-        }
-#pragma unroll
-        for (int j = 0; j < RC_MANY; ++j) {
-          if (b[r] + j < e[r]) {
-            dd += ops[j] == OP_NEW ? 1 : (ops[j] == OP_DELETE ? -1 : 0);
-            dk += dks[j];
-          }
-        }
-      }
-      if (u >= n) continue;
-      new_deg[u] = oe[r] - ob[r] + dd;
-      // merge tiles: the row holding each tile's first entry, and after
-      // the last tile the row holding the last entry
-      if (oe[r] > ob[r]) {
-        for (int64_t t = ceil_div(ob[r], MERGE_TILE); t * MERGE_TILE < oe[r]; ++t)
-          tile_row[t] = int32_t(u);
-        if (oe[r] == nnz) tile_row[ceil_div(nnz, MERGE_TILE)] = int32_t(u);
-      }
-      if (dk != 0) {
-        k[u] += dk;
-        if (!agg_try(agg, cu[r], dk)) atomicAdd(&a[cu[r]], dk);
-      }
-    }
+// Scans over the change list, a tile of records' changes per block: cnet (NEW
+// minus DELETE before each change, nch + 1 ints), ins_pos (insertion records
+// before it), and the insertion records' keys.  The status block and the
+// totals {changes, insertion records, NEW minus DELETE} go to host memory.
+__global__ void __launch_bounds__(RES_TILE)
+    k_scan_changes(const uint64_t* __restrict__ ch_key, const int32_t* __restrict__ ch_op,
+                   const int32_t* __restrict__ part, int raw, int64_t nt,
+                   const long long* __restrict__ npart, const int32_t* __restrict__ nruns,
+                   int32_t* cnet, int32_t* ins_pos, uint64_t* ins_keys,
+                   const long long* __restrict__ stat, int nstat, long long* host_stat,
+                   int32_t* host) {
+  __shared__ int32_t l32[RES_TILE / WAVE];
+  __shared__ long long l64[RES_TILE / WAVE];
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < nstat; k += RES_TILE) host_store(host_stat + k, stat[k]);
+  const int32_t nch = *nruns;
+  const int32_t c0 = tile_offset<int32_t, RES_TILE>(part, raw, nt, l32);
+  const bool last = int64_t(blockIdx.x) == nt - 1;
+  const int32_t c1 = last ? nch : (raw ? c0 + part[blockIdx.x] : part[blockIdx.x + 1]);
+  const long long offs = tile_offset<long long, RES_TILE>(npart, raw, nt, l64);
+  const int32_t q = c0 + int32_t(threadIdx.x);
+  long long v = 0;
+  uint64_t key = 0;
+  int32_t op = OP_DELETE;
+  if (q < c1) {
+    op = ch_op[q];
+    key = ch_key[q];
+    v = change_counts(op);
   }
-  __syncthreads();
-  for (int s = threadIdx.x; s < AGG_SLOTS; s += blockDim.x) {
+  long long tot;
+  const long long at = offs + block_excl_scan<long long, RES_TILE>(v, l64, &tot);
+  if (q < c1) {
+    const int32_t p = int32_t(at & 0xffffffffll);
+    cnet[q] = int32_t(at >> 32);
+    ins_pos[q] = p;
+    if (op != OP_DELETE) ins_keys[p] = key;
+  }
+  if (last && threadIdx.x == 0) {
+    const long long t = offs + tot;
+    cnet[nch] = int32_t(t >> 32);
+    host_store(host, nch);
+    host_store(host + 1, int32_t(t & 0xffffffffll));
+    host_store(host + 2, int32_t(t >> 32));
+  }
+}
+
+// First k in [0, m) with keys[k] >= key (m if none), by the whole wave: 64
+// probes a round, so four dependent loads for 400K keys instead of nineteen.
+__device__ __forceinline__ int32_t wave_lower_bound(const uint64_t* __restrict__ keys, int32_t m,
+                                                    uint64_t key) {
+  const int lane = lane_id();
+  int32_t a = 0, b = m;
+  while (b - a > WAVE) {
+    const int32_t step = (b - a + WAVE) / (WAVE + 1);
+    const int64_t p = a + int64_t(lane + 1) * step - 1;
+    const bool less = p < b && keys[p < b ? p : b - 1] < key;
+    const int c = __popcll(__ballot(less));
+    const int64_t e = a + int64_t(c + 1) * step - 1;  // the first probe at or past key
+    a += c * step;
+    if (c < WAVE && e < b) b = int32_t(e);
+  }
+  if (a >= b) return a;
+  const bool less = a + lane < b && keys[a + lane < b ? a + lane : b - 1] < key;
+  return a + __popcll(__ballot(less));
+}
+
+// The rows of a batch, in tiles of SCAN_TILE rows: a tile's changes are one
+// contiguous slice of the sorted list, so a block adds them up per row in LDS
+// (coalesced reads, hub rows included) and everything per row follows from
+// the sums: its change range (cptr), new degree (and the tile's total, for
+// the scan to the new offsets), k += the weight change, the label totals
+// a[C(u)] += the same, the rows that begin the merge's tiles, and for the
+// screening (uflag not null) the row's kind (bit 0: it has an insertion
+// record, an Alg. 2 source; bit 1: the deletion or replacement of a pair
+// inside one community C_{t-1}), its sink segment, and the list of rows with
+// a kind; crows (not null): the list of rows with a change.  The lists are
+// in no fixed order (one reservation per tile).
+//
+// A block walks many tiles and sums the label changes in its LDS table
+// first, so a large community receives one update per block instead of one
+// per row (same-address atomics serialise): hence 256 blocks of 1024 threads.
+// Bound by the tile's chain of dependent reads and barriers: 54 us for 400K
+// changes over 1M rows, where the change bounds, per-row sums, screening
+// kinds, heads, compactions and tile totals took ten launches and 85 us.
+constexpr int RC_TPB = 1024;
+constexpr int RC_BLOCKS = 256;
+constexpr int RC_ROWS = SCAN_TILE / RC_TPB;  // rows of a thread
+__global__ void __launch_bounds__(RC_TPB)
+    k_row_changes(const uint64_t* __restrict__ ch_key, const int32_t* __restrict__ ch_op,
+                  const int32_t* __restrict__ ch_dk, const int32_t* __restrict__ ins_pos,
+                  int32_t nch, int32_t n_ins, int kb, const int32_t* __restrict__ off,
+                  const int32_t* __restrict__ C, int32_t n, RowOut o) {
+  __shared__ AggLds agg;
+  __shared__ int32_t s_cnt[SCAN_TILE], s_ins[SCAN_TILE], s_net[SCAN_TILE], s_dk[SCAN_TILE];
+  __shared__ int32_t s_del[SCAN_TILE];
+  __shared__ unsigned long long l64[RC_TPB / WAVE];
+  __shared__ int32_t s_lo, s_hi, s_ub, s_cb;
+  const int t = threadIdx.x, wid = t / WAVE;
+  agg_init(agg);
+  const int32_t nnz = off[n];
+  const int64_t ntiles = ceil_div(n, SCAN_TILE);
+  long long ns = 0, nds = 0;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int64_t r0 = tile * SCAN_TILE;
+    const int64_t r1 = r0 + SCAN_TILE < n ? r0 + SCAN_TILE : n;
+    // the thread's rows are loaded first (clamped, n >= 1) and used last
+    int32_t ob[RC_ROWS + 1], cu[RC_ROWS];
+#pragma unroll
+    for (int i = 0; i <= RC_ROWS; ++i) {
+      const int64_t r = r0 + t * RC_ROWS + i;
+      ob[i] = off[r < n ? r : n];
+    }
+#pragma unroll
+    for (int i = 0; i < RC_ROWS; ++i) {
+      const int64_t r = r0 + t * RC_ROWS + i;
+      cu[i] = C[r < n ? r : n - 1];
+    }
+    if (wid < 2) {
+      const int32_t b = wave_lower_bound(ch_key, nch, pair_key(wid == 0 ? r0 : r1, 0, kb));
+      if (lane_id() == 0) (wid == 0 ? s_lo : s_hi) = b;
+    }
+#pragma unroll
+    for (int i = 0; i < RC_ROWS; ++i) {
+      const int x = t + i * RC_TPB;
+      s_cnt[x] = s_ins[x] = s_net[x] = s_dk[x] = s_del[x] = 0;
+    }
+    __syncthreads();
+    const int32_t lo = s_lo, hi = s_hi;
+    for (int32_t q0 = lo; q0 < hi; q0 += RC_TPB) {  // block-uniform
+      const int32_t q = q0 + t;
+      const bool in = q < hi;
+      const int32_t qc = in ? q : hi - 1;
+      const uint64_t key = ch_key[qc];
+      const int32_t op = ch_op[qc];
+      int32_t dk = in ? ch_dk[qc] : 0;
+      const int32_t row = int32_t(key_row(key, kb)), x = int32_t(row - r0);
+      int32_t cnt = in ? 1 : 0, ins = in && op != OP_DELETE ? 1 : 0;
+      int32_t net = in ? (op == OP_NEW ? 1 : (op == OP_DELETE ? -1 : 0)) : 0;
+      int32_t del = 0;
+      if (o.uflag && in && (op == OP_DELETE || op == OP_REPLACE))
+        del = C[int32_t(key_col(key, kb))] == C[row] ? 1 : 0;
+      // a hub's changes fill whole waves: one update for all of them
+      const bool same = __ballot(x != __builtin_amdgcn_readfirstlane(x)) == 0;
+      if (same) {
+        cnt = wave_sum(cnt);
+        ins = wave_sum(ins);
+        net = wave_sum(net);
+        dk = wave_sum(dk);
+        del = wave_or(del);
+      }
+      if (same ? lane_id() == 0 : in) {
+        if (cnt) atomicAdd(&s_cnt[x], cnt);
+        if (ins) atomicAdd(&s_ins[x], ins);
+        if (net) atomicAdd(&s_net[x], net);
+        if (dk) atomicAdd(&s_dk[x], dk);
+        if (del) s_del[x] = 1;
+      }
+    }
+    __syncthreads();
+    int32_t cnt[RC_ROWS], ins[RC_ROWS], deg[RC_ROWS], kind[RC_ROWS];
+    unsigned long long sa = 0, sb = 0;
+#pragma unroll
+    for (int i = 0; i < RC_ROWS; ++i) {
+      const int x = t * RC_ROWS + i;
+      const bool in = r0 + x < r1;
+      cnt[i] = s_cnt[x];
+      ins[i] = s_ins[x];
+      deg[i] = in ? ob[i + 1] - ob[i] + s_net[x] : 0;
+      kind[i] = o.uflag ? (ins[i] > 0 ? 1 : 0) | (s_del[x] ? 2 : 0) : 0;
+      sa += (unsigned long long)uint32_t(cnt[i]) | (unsigned long long)uint32_t(ins[i]) << 32;
+      // degrees (40 bits), rows with a kind (12), rows with a change (12)
+      sb += (unsigned long long)uint32_t(deg[i]) | (kind[i] ? 1ull << 40 : 0ull) |
+            (cnt[i] ? 1ull << 52 : 0ull);
+    }
+    unsigned long long ta, tb;
+    const unsigned long long pa = block_excl_scan<unsigned long long, RC_TPB>(sa, l64, &ta);
+    const unsigned long long pb = block_excl_scan<unsigned long long, RC_TPB>(sb, l64, &tb);
+    if (t == 0) {
+      o.deg_part[tile] = int32_t(tb & 0xffffffffffull);
+      const int nu = int(tb >> 40 & 0xfff), nc = int(tb >> 52);
+      s_ub = nu ? atomicAdd(o.ucount, nu) : 0;
+      s_cb = o.crows && nc ? atomicAdd(o.ccount, nc) : 0;
+    }
+    __syncthreads();
+    int32_t c = lo + int32_t(pa & 0xffffffffull);
+    int32_t p = (lo < nch ? ins_pos[lo] : n_ins) + int32_t(pa >> 32);
+    int32_t u = s_ub + int32_t(pb >> 40 & 0xfff), w = s_cb + int32_t(pb >> 52);
+#pragma unroll
+    for (int i = 0; i < RC_ROWS; ++i) {
+      const int x = t * RC_ROWS + i;
+      const int64_t r = r0 + x;
+      if (r >= r1) break;
+      o.cptr[r] = c;
+      o.new_deg[r] = deg[i];
+      // merge tiles: the row holding each tile's first entry, and after the
+      // last tile the row holding the last entry
+      if (ob[i + 1] > ob[i]) {
+        for (int64_t k = ceil_div(ob[i], MERGE_TILE); k * MERGE_TILE < ob[i + 1]; ++k)
+          o.tile_row[k] = int32_t(r);
+        if (ob[i + 1] == nnz) o.tile_row[ceil_div(nnz, MERGE_TILE)] = int32_t(r);
+      }
+      const int32_t dk = s_dk[x];
+      if (dk != 0) {
+        o.k[r] += dk;
+        if (!agg_try(agg, cu[i], dk)) atomicAdd(&o.a[cu[i]], dk);
+      }
+      if (o.uflag) {
+        o.uflag[r] = uint8_t(kind[i]);
+        if (kind[i]) o.ulist[u++] = int32_t(r);
+        if (ins[i]) {
+          o.seg_beg[r] = p;
+          o.seg_end[r] = p + ins[i];
+        }
+        ns += kind[i] & 1;
+        nds += kind[i] >> 1;
+      }
+      if (o.crows && cnt[i]) o.crows[w++] = int32_t(r);
+      c += cnt[i];
+      p += ins[i];
+    }
+    if (r1 == n && t == 0) o.cptr[n] = nch;
+    __syncthreads();  // the sums are cleared for the next tile
+  }
+  for (int s = t; s < AGG_SLOTS; s += RC_TPB) {
     const int key = agg.keys[s];
-    if (key != EMPTY_KEY && agg.vals[s] != 0) atomicAdd(&a[key], int32_t(agg.vals[s]));
+    if (key != EMPTY_KEY && agg.vals[s] != 0) atomicAdd(&o.a[key], int32_t(agg.vals[s]));
+  }
+  if (o.uflag) {
+    block_add(ns, o.n_src + blockIdx.x % SUM_SLOTS);
+    block_add(nds, o.n_dsrc + blockIdx.x % SUM_SLOTS);
   }
 }
 
@@ -665,37 +867,52 @@ void row_weight_sums(const int32_t* off, const int2* adj, int32_t n, int32_t* k,
 }
 
 void batch_records(const int32_t* du, const int32_t* dv, int64_t nd, const int32_t* au,
-                   const int32_t* av, int64_t na, int32_t n, uint64_t* keys, uint32_t* vals,
-                   hipStream_t st) {
+                   const int32_t* av, const int32_t* aw, int64_t na, int32_t n, uint64_t* keys,
+                   uint32_t* vals, int32_t* flags, long long* wsum, hipStream_t st) {
   if (nd + na <= 0) return;
-  k_batch_records<<<grid_for(nd + na), TPB, 0, st>>>(du, dv, nd, au, av, na, key_bits(n), keys,
-                                                    vals);
+  k_batch_records<<<grid_for(nd + na), TPB, 0, st>>>(du, dv, nd, au, av, aw, na, n, key_bits(n),
+                                                    keys, vals, flags, wsum);
   DC_LAUNCH_CHECK();
 }
 
-void resolve_changes(const uint64_t* keys, const uint32_t* vals, const int32_t* pos, int64_t m,
-                     const int32_t* nruns, const int32_t* ins_w, int32_t n, const int32_t* off,
-                     const int2* adj, uint64_t* run_key, int32_t* run_w, int32_t* run_ndel,
+void resolve_changes(const uint64_t* keys, const uint32_t* vals, int64_t m, const int32_t* ins_w,
+                     int32_t n, const int32_t* off, const int2* adj, DBuf& part, DBuf& npart,
                      uint64_t* ch_key, int32_t* ch_op, int32_t* ch_w, int32_t* ch_dk,
-                     int32_t* dnet, int32_t* flags, long long* wsum, hipStream_t st) {
+                     int32_t* cnet, int32_t* ins_pos, uint64_t* ins_keys, int32_t* nruns,
+                     int32_t* flags, long long* wsum, const long long* stat, int nstat,
+                     long long* host_stat, int32_t* host, hipStream_t st) {
   if (m <= 0) return;
-  void* zp[2] = {run_w, run_ndel};
-  const int64_t zb[2] = {4 * m, 4 * m};
-  zero_buffers(zp, zb, 2, st);
-  k_run_accumulate<<<grid_for(m), TPB, 0, st>>>(keys, vals, pos, m, ins_w, run_key, run_w,
-                                                run_ndel);
+  const int64_t nt = ceil_div(m, RES_TILE);
+  const int raw = nt <= SCAN_RAW_MAX;
+  part.ensure(size_t(nt) * 4);
+  npart.ensure(size_t(nt) * 8);
+  int32_t* p32 = part.as<int32_t>();
+  int64_t* p64 = npart.as<int64_t>();
+  const int32_t* heads = nt > 1 ? p32 : nullptr;  // a single tile needs no offsets
+  if (heads) {
+    k_count_runs<<<int(nt), RES_TILE, 0, st>>>(keys, m, p32);
+    DC_LAUNCH_CHECK();
+  }
+  if (!raw) scan_excl_i32(p32, p32, nt, nullptr, st);
+  k_resolve_runs<<<int(nt), RES_TILE, 0, st>>>(keys, vals, m, heads, raw, nt, ins_w, n, key_bits(n),
+                                               off, adj, ch_key, ch_op, ch_w, ch_dk,
+                                               reinterpret_cast<long long*>(p64), nruns, flags,
+                                               wsum);
   DC_LAUNCH_CHECK();
-  k_resolve_runs<<<grid_for(m), TPB, 0, st>>>(run_key, run_w, run_ndel, nruns, n,
-                                              key_bits(n), off, adj, ch_key, ch_op, ch_w, ch_dk, dnet, flags, wsum);
+  if (!raw) scan_excl_i64(p64, p64, nt, nullptr, st);
+  k_scan_changes<<<int(nt), RES_TILE, 0, st>>>(
+      ch_key, ch_op, heads, raw, nt, heads ? reinterpret_cast<long long*>(p64) : nullptr, nruns,
+      cnet, ins_pos, ins_keys, stat, nstat, host_stat, host);
   DC_LAUNCH_CHECK();
 }
 
-void row_changes(const int32_t* cptr, const int32_t* ch_op, const int32_t* ch_dk,
-                 const int32_t* off, int32_t n, int32_t* new_deg, int32_t* k,
-                 const int32_t* C, int32_t* a, int32_t* tile_row, hipStream_t st) {
+void row_changes(const uint64_t* ch_key, const int32_t* ch_op, const int32_t* ch_dk,
+                 const int32_t* ins_pos, int64_t nch, int64_t n_ins, const int32_t* off,
+                 const int32_t* C, int32_t n, const RowOut& o, hipStream_t st) {
   if (n <= 0) return;
-  k_row_changes<<<grid_for(n, RC_TPB, RC_BLOCKS), RC_TPB, 0, st>>>(cptr, ch_op, ch_dk, off, n, new_deg, k,
-                                                       C, a, tile_row);
+  const int64_t tiles = ceil_div(n, SCAN_TILE);
+  k_row_changes<<<int(tiles < RC_BLOCKS ? tiles : RC_BLOCKS), RC_TPB, 0, st>>>(
+      ch_key, ch_op, ch_dk, ins_pos, int32_t(nch), int32_t(n_ins), key_bits(n), off, C, n, o);
   DC_LAUNCH_CHECK();
 }
 

@@ -359,6 +359,16 @@ void scan_excl_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* total,
   scan_excl<int32_t>(in, out, n, total, st, host_total);
 }
 
+void scan_tiles_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* part, int32_t* total,
+                    hipStream_t st) {
+  if (n <= 0) return;
+  const int64_t nb = ceil_div(n, SCAN_TILE);
+  const int raw = nb <= SCAN_RAW_MAX;
+  if (!raw) scan_excl_i32(part, part, nb, nullptr, st);
+  k_tile_scan<int32_t><<<nb, SCAN_THREADS, 0, st>>>(in, out, n, part, raw, total, nb, nullptr);
+  DC_LAUNCH_CHECK();
+}
+
 void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* total,
                    hipStream_t st, int64_t* host_total) {
   scan_excl<int64_t>(in, out, n, total, st, host_total);

@@ -28,20 +28,6 @@ __global__ void k_compact_index(const int32_t* __restrict__ flag,
   }
 }
 
-__global__ void k_select_insertions(const int32_t* __restrict__ op, int64_t n,
-                                    int32_t* flag) {
-  GRID_STRIDE(i, n) { flag[i] = op[i] != OP_DELETE ? 1 : 0; }
-}
-
-__global__ void k_gather_u64(const uint64_t* __restrict__ in,
-                             const int32_t* __restrict__ flag,
-                             const int32_t* __restrict__ pos, int64_t n,
-                             uint64_t* out) {
-  GRID_STRIDE(i, n) {
-    if (flag[i]) out[pos[i]] = in[i];
-  }
-}
-
 __global__ void k_source_heads(const uint64_t* __restrict__ keys, int64_t m,
                                int kb, int32_t* flag) {
   GRID_STRIDE(i, m) {
@@ -77,78 +63,6 @@ __global__ void k_deletion_sources(const uint64_t* __restrict__ key,
     int32_t s = int32_t(key_row(key[i], kb)), d = int32_t(key_col(key[i], kb));
     if (C[s] == C[d]) dflag[s] = 1;
   }
-}
-
-// The screening set of the fused pass straight from the sorted change list,
-// one thread per change.  First pass: the changes' kinds go into their
-// source's word sbits (bit 0: an insertion record, op != OP_DELETE, so the
-// source is an Alg. 2 source; bit 1: the deletion or replacement of a pair
-// inside one community C_{t-1}), and an insertion record at either end of
-// its source's run of insertion keys sets that end of the sink segment
-// [seg_beg, seg_end).  Second pass: the head of each source's run of
-// changes copies the word into uflag, marks itself in hflag when it is
-// non-zero (the union list, ascending, is the heads' compaction) and
-// counts the two kinds of sources (block b adds to counter b % SUM_SLOTS:
-// with a single counter the blocks' atomics would serialise).
-__global__ void k_screen_kinds(const uint64_t* __restrict__ key, const int32_t* __restrict__ op,
-                               const int32_t* __restrict__ ins_pos,
-                               const uint64_t* __restrict__ ins_keys, int64_t n_ins,
-                               int64_t nch, int kb, const int32_t* __restrict__ C,
-                               int32_t* sbits, int32_t* seg_beg, int32_t* seg_end) {
-  const int lane = lane_id();
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  // whole waves: the loop runs while the wave's first change is in range
-  for (int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; q - lane < nch; q += stride) {
-    const bool valid = q < nch;
-    const uint64_t kq = key[valid ? q : nch - 1];
-    const int32_t s = int32_t(key_row(kq, kb));
-    const int32_t o = op[valid ? q : nch - 1];
-    const bool add = valid && o != OP_DELETE;
-    if (add) {
-      const int64_t p = ins_pos[q];
-      if (p == 0 || int32_t(key_row(ins_keys[p - 1], kb)) != s) seg_beg[s] = int32_t(p);
-      if (p == n_ins - 1 || int32_t(key_row(ins_keys[p + 1], kb)) != s)
-        seg_end[s] = int32_t(p + 1);
-    }
-    const bool del = valid && (o == OP_DELETE || o == OP_REPLACE) &&
-                     C[int32_t(key_col(kq, kb))] == C[s];
-    // one atomic per source and wave: the source's changes are consecutive
-    // lanes, from its first lane to the next source's (with one per change
-    // the pass was bound by same-address atomics: 575 us for the 10.5M
-    // changes of an 8M-vertex graph, now 136; 16 and 10 us for 400K)
-    const int32_t before = __shfl_up(s, 1, WAVE);
-    const bool head = valid && (lane == 0 || before != s);
-    const uint64_t heads = __ballot(head), adds = __ballot(add), dels = __ballot(del);
-    if (head) {
-      const uint64_t from = ~uint64_t(0) << lane, later = heads & (from << 1);
-      const uint64_t run = later ? from & ((later & -later) - 1) : from;
-      const int b = ((adds & run) ? 1 : 0) | ((dels & run) ? 2 : 0);
-      if (b) atomicOr(&sbits[s], b);
-    }
-  }
-}
-
-__global__ void __launch_bounds__(TPB)
-    k_screen_heads(const uint64_t* __restrict__ key, int64_t nch, int kb,
-                   const int32_t* __restrict__ sbits, uint8_t* uflag, int32_t* hflag,
-                   long long* n_src, long long* n_dsrc) {
-  long long ns = 0, nd = 0;
-  GRID_STRIDE(q, nch) {
-    const int32_t s = int32_t(key_row(key[q], kb));
-    int32_t head = 0;
-    if (q == 0 || int32_t(key_row(key[q - 1], kb)) != s) {
-      const int bits = sbits[s];
-      if (bits) {
-        uflag[s] = uint8_t(bits);
-        head = 1;
-        ns += bits & 1;
-        nd += bits >> 1;
-      }
-    }
-    hflag[q] = head;
-  }
-  block_add(ns, n_src + blockIdx.x % SUM_SLOTS);
-  block_add(nd, n_dsrc + blockIdx.x % SUM_SLOTS);
 }
 
 // one wave per listed vertex
@@ -318,19 +232,6 @@ void compact_index(const int32_t* flag, const int32_t* pos, int64_t n, int32_t* 
   DC_LAUNCH_CHECK();
 }
 
-void select_insertions(const int32_t* ch_op, int64_t nch, int32_t* flag, hipStream_t st) {
-  if (nch <= 0) return;
-  k_select_insertions<<<grid_for(nch), TPB, 0, st>>>(ch_op, nch, flag);
-  DC_LAUNCH_CHECK();
-}
-
-void gather_u64(const uint64_t* in, const int32_t* flag, const int32_t* pos, int64_t n,
-                uint64_t* out, hipStream_t st) {
-  if (n <= 0) return;
-  k_gather_u64<<<grid_for(n), TPB, 0, st>>>(in, flag, pos, n, out);
-  DC_LAUNCH_CHECK();
-}
-
 void source_heads(const uint64_t* keys, int64_t m, int32_t n, int32_t* flag, hipStream_t st) {
   if (m <= 0) return;
   k_source_heads<<<grid_for(m), TPB, 0, st>>>(keys, m, key_bits(n), flag);
@@ -355,20 +256,6 @@ void deletion_sources(const uint64_t* ch_key, const int32_t* ch_op, int64_t nch,
                       const int32_t* C, int32_t* dflag, hipStream_t st) {
   if (nch <= 0) return;
   k_deletion_sources<<<grid_for(nch), TPB, 0, st>>>(ch_key, ch_op, nch, key_bits(n), C, dflag);
-  DC_LAUNCH_CHECK();
-}
-
-void screen_union(const uint64_t* ch_key, const int32_t* ch_op, const int32_t* ins_pos,
-                  const uint64_t* ins_keys, int64_t n_ins, int64_t nch, int32_t n,
-                  const int32_t* C, int32_t* sbits, uint8_t* uflag, int32_t* seg_beg,
-                  int32_t* seg_end, int32_t* hflag, long long* n_src, long long* n_dsrc,
-                  hipStream_t st) {
-  if (nch <= 0) return;
-  k_screen_kinds<<<grid_for(nch), TPB, 0, st>>>(ch_key, ch_op, ins_pos, ins_keys, n_ins, nch,
-                                                key_bits(n), C, sbits, seg_beg, seg_end);
-  DC_LAUNCH_CHECK();
-  k_screen_heads<<<grid_for(nch), TPB, 0, st>>>(ch_key, nch, key_bits(n), sbits, uflag, hflag,
-                                                      n_src, n_dsrc);
   DC_LAUNCH_CHECK();
 }
 

@@ -55,3 +55,32 @@ def test_steps_at_scan_tile_edges(n):
     for t, b in enumerate(batches):
         step_pair(o, g, b)
         compare(o, g, f"n={n} step {t}")
+
+
+@pytest.mark.parametrize("copies", [1, 8, 9, 8 + 256, 8 + 257, 1500])
+def test_runs_of_one_pair(copies):
+    """A pair inserted `copies` times in one batch (around the records its own
+    thread sums, and the wave's rounds over the rest), beside a hub whose
+    changes fill several waves of a row tile, in both screening kinds."""
+    print(f"case: runs of {copies}", flush=True)
+    n = 3000
+    rng = np.random.default_rng(copies)
+    u, v, w = W.DCSBM(n=n, m=5 * n, blocks=12, dmax=100, seed=7).graph()
+    hub = 2049
+    present = np.concatenate([v[u == hub], u[v == hub]])
+    fresh = np.setdiff1d(np.arange(n), np.concatenate([present, [hub]]))
+    add_u = np.concatenate([np.full(copies, u[0]), np.full(len(fresh), hub)]).astype(np.int32)
+    add_v = np.concatenate([np.full(copies, v[0]), fresh]).astype(np.int32)
+    add_w = rng.integers(1, 4, len(add_u)).astype(np.int32)
+    order = rng.permutation(len(add_u))
+    gone = np.setdiff1d(np.arange(1, len(u)), np.flatnonzero((u == hub) | (v == hub)))[:700]
+    first = W.Batch(add_u[order], add_v[order], add_w[order], u[gone], v[gone])
+    # the hub's row leaves again, the repeated pair is replaced
+    second = W.Batch(u[:1], v[:1], np.array([2], np.int32),
+                     np.concatenate([u[:1], np.full(len(fresh), hub)]).astype(np.int32),
+                     np.concatenate([v[:1], fresh]).astype(np.int32))
+    for mode in ("delta", "all"):
+        o, g = make_pair(n, u, v, w, mode=mode)
+        for t, b in enumerate((first, second)):
+            step_pair(o, g, b)
+            compare(o, g, f"copies={copies} {mode} step {t}")
