@@ -146,7 +146,7 @@ inline Bins first_part(const Bins& b) {
 }
 
 struct BinScratch {
-  DBuf lists, lists_rb, bcnt, boff, bvol, counts, tab_off, gkeys, gvals, ovf;
+  DBuf lists, lists_rb, words, counts, tab_off, gkeys, gvals, ovf;
   void* host = nullptr;      // pinned, 256 bytes
   void* host_dev = nullptr;  // its address for the kernels that write it
   hipStream_t side = nullptr;  // second stream and fork / join events of the
@@ -154,8 +154,8 @@ struct BinScratch {
   hipEvent_t join = nullptr;
 };
 
-// Splits a vertex list (null = all of [0, count)) into the row-length bins,
-// keeping list order within a bin; synchronises to read the bin sizes.
+// Splits a vertex list (null = all of [0, count)) into the row-length bins (a
+// bin's list in no fixed order); synchronises to read the bin sizes.
 // skip (may be null): vertices v with skip[v] != 0 go to the end of their
 // bin, after the first part (first_part gives the bins without them).
 // dcount (may be null): the list's length in device memory, count then

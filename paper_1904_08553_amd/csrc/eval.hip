@@ -1103,10 +1103,14 @@ __global__ void k_build_multi(const MultiSeg* __restrict__ segs, int nsegs, Mult
 }
 
 // --------------------------------------------------------------------------
-// binning by row length: per-block counts, one scan, stable scatter.
+// binning by row length: the rows' totals, then the placement, two launches
+// (8.7 and 9.5 us for the lists of a 1M-vertex step; with the counts of every
+// block scanned by a one-block launch between them 25 us for the three).
 
+constexpr int BIN_TPB = 1024;
+constexpr int BIN_WAVES = BIN_TPB / WAVE;
 constexpr int BIN_ITEMS = 4;
-constexpr int BIN_TILE = TPB * BIN_ITEMS;
+constexpr int BIN_TILE = BIN_TPB * BIN_ITEMS;
 
 // wmax: the longest row of bin W (WTAB_MAX, or half of it on coarse levels,
 // whose rows hold mostly distinct labels and would overflow the wave table)
@@ -1119,259 +1123,161 @@ __device__ __forceinline__ int bin_of(int d, int wmax) {
 // sweep), so that each bin's list holds its first-sweep vertices first.
 constexpr int NROWS = 2 * NBINS;
 
-__global__ void __launch_bounds__(TPB)
-    k_bin_count(const int32_t* __restrict__ list, int64_t cnt, const int32_t* __restrict__ dcnt,
-                const int32_t* __restrict__ off, const uint8_t* __restrict__ skip, int32_t* bcnt,
-                long long* bvol, int64_t nblocks, int wmax) {
-  if (dcnt) cnt = *dcnt;  // the list's length on the device (cnt: its bound)
-  __shared__ int c[NROWS];
-  __shared__ long long v[NROWS];
-  if (threadIdx.x < NROWS) {
-    c[threadIdx.x] = 0;
-    v[threadIdx.x] = 0;
-  }
-  __syncthreads();
-  int lc[NROWS];
-  long long lv[NROWS];
-#pragma unroll
-  for (int q = 0; q < NROWS; ++q) {
-    lc[q] = 0;
-    lv[q] = 0;
-  }
-  if (cnt > 0) {  // block-uniform
-    // the BIN_ITEMS vertices, then their bounds and flags: clamped indexes,
-    // so each round of loads is in flight together
-    int u[BIN_ITEMS], d[BIN_ITEMS], sk[BIN_ITEMS];
-#pragma unroll
-    for (int r = 0; r < BIN_ITEMS; ++r) {
-      const int64_t p = int64_t(blockIdx.x) * BIN_TILE + int64_t(r) * TPB + threadIdx.x;
-      const int64_t pc = p < cnt ? p : cnt - 1;
-      u[r] = list ? list[pc] : int(pc);
-    }
-#pragma unroll
-    for (int r = 0; r < BIN_ITEMS; ++r) d[r] = off[u[r] + 1] - off[u[r]];
-    if (skip) {
-#pragma unroll
-      for (int r = 0; r < BIN_ITEMS; ++r) sk[r] = skip[u[r]];
-    } else {
-#pragma unroll
-      for (int r = 0; r < BIN_ITEMS; ++r) sk[r] = 0;
-    }
-#pragma unroll
-    for (int r = 0; r < BIN_ITEMS; ++r) {
-      const int64_t p = int64_t(blockIdx.x) * BIN_TILE + int64_t(r) * TPB + threadIdx.x;
-      const int row = p < cnt ? 2 * bin_of(d[r], wmax) + (sk[r] ? 1 : 0) : -1;
-#pragma unroll
-      for (int q = 0; q < NROWS; ++q) {
-        if (row == q) {
-          lc[q]++;
-          lv[q] += d[r];
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int b = 0; b < NROWS; ++b) {
-    int x = wave_sum(lc[b]);
-    long long y = wave_sum(lv[b]);
-    if (lane_id() == 0) {
-      if (x) atomicAdd(&c[b], x);
-      if (y) atomicAdd((unsigned long long*)&v[b], (unsigned long long)y);
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < NROWS) {
-    bcnt[int64_t(threadIdx.x) * nblocks + blockIdx.x] = c[threadIdx.x];
-    bvol[int64_t(threadIdx.x) * nblocks + blockIdx.x] = v[threadIdx.x];
-  }
-}
-
-// out[boff[row][block] + rank] = vertex: rows are contiguous segments of
-// out, in list order within each row
-__global__ void __launch_bounds__(TPB)
-    k_bin_scatter(const int32_t* __restrict__ list, int64_t cnt,
-                  const int32_t* __restrict__ dcnt, const int32_t* __restrict__ off,
-                  const uint8_t* __restrict__ skip, const int32_t* __restrict__ boff,
-                  int64_t nblocks, int32_t* out, int32_t* out_rb, int wmax) {
-  if (dcnt) cnt = *dcnt;
-  __shared__ int base[NROWS];
-  __shared__ int wc[NW][NROWS];
-  const int wid = threadIdx.x / WAVE, lane = lane_id();
-  if (threadIdx.x < NROWS) base[threadIdx.x] = boff[int64_t(threadIdx.x) * nblocks + blockIdx.x];
-  __syncthreads();
-  const uint64_t lt = (uint64_t(1) << lane) - 1;
-  // every item's vertex, row start and row first (clamped indexes: the
-  // loads of a round are in flight together), then the ranking rounds
-  int uu[BIN_ITEMS], rrow[BIN_ITEMS], rrb[BIN_ITEMS];
-  if (cnt > 0) {  // block-uniform
-#pragma unroll
-    for (int r = 0; r < BIN_ITEMS; ++r) {
-      const int64_t p = int64_t(blockIdx.x) * BIN_TILE + int64_t(r) * TPB + threadIdx.x;
-      const int64_t pc = p < cnt ? p : cnt - 1;
-      uu[r] = list ? list[pc] : int(pc);
-    }
-    int b1[BIN_ITEMS], sk[BIN_ITEMS];
-#pragma unroll
-    for (int r = 0; r < BIN_ITEMS; ++r) {
-      rrb[r] = off[uu[r]];
-      b1[r] = off[uu[r] + 1];
-    }
-    if (skip) {
-#pragma unroll
-      for (int r = 0; r < BIN_ITEMS; ++r) sk[r] = skip[uu[r]];
-    } else {
-#pragma unroll
-      for (int r = 0; r < BIN_ITEMS; ++r) sk[r] = 0;
-    }
-#pragma unroll
-    for (int r = 0; r < BIN_ITEMS; ++r) {
-      const int64_t p = int64_t(blockIdx.x) * BIN_TILE + int64_t(r) * TPB + threadIdx.x;
-      rrow[r] = p < cnt ? 2 * bin_of(b1[r] - rrb[r], wmax) + (sk[r] ? 1 : 0) : -1;
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < BIN_ITEMS; ++r) {
-      uu[r] = 0;
-      rrb[r] = 0;
-      rrow[r] = -1;
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < BIN_ITEMS; ++r) {
-    const bool valid = rrow[r] >= 0;
-    const int u = uu[r], row = rrow[r], rb = rrb[r];
-    int rank = 0;
-#pragma unroll
-    for (int q = 0; q < NROWS; ++q) {
-      uint64_t m = __ballot(row == q);
-      if (lane == 0) wc[wid][q] = __popcll(m);
-      if (row == q) rank = __popcll(m & lt);
-    }
-    __syncthreads();
-    if (valid) {
-      int pos = base[row] + rank;
-      for (int w = 0; w < wid; ++w) pos += wc[w][row];
-      out[pos] = u;
-      out_rb[pos] = rb;
-    }
-    __syncthreads();
-    if (threadIdx.x < NROWS) {
-      int add = 0;
-      for (int w = 0; w < NW; ++w) add += wc[w][threadIdx.x];
-      base[threadIdx.x] += add;
-    }
-    __syncthreads();
-  }
-}
-
 // Metadata of a binning (int32 slots): [0, NBINS) bin sizes, [NBINS,
 // 2 NBINS) first-part sizes (row 2q), [2 NBINS, 3 NBINS) bin starts, then
-// the total, the overflow count and the overflow pass's finished blocks
-// (both zero); from slot 32 on the NROWS row volumes (int64).
-constexpr int M_START = 2 * NBINS, M_TOTAL = 3 * NBINS, M_OVF = 3 * NBINS + 1;
+// the overflow count and the overflow pass's finished blocks (both zero);
+// from slot 32 on the NROWS row volumes (int64).
+constexpr int M_START = 2 * NBINS, M_OVF = 3 * NBINS;
 constexpr int META_WORDS = 32 + 2 * NROWS;
 static_assert(M_OVF + 2 <= 32, "bin metadata slots overlap the volumes");
 static_assert(META_WORDS * 4 <= 256, "bin metadata must fit the pinned host buffer");
 
-constexpr int META_TPB = 1024;
-constexpr int META_PER = 32;                    // counts per thread in the scan
-constexpr int META_SCAN_MAX = META_TPB * META_PER;
+// Device words of a binning: per row its total (vertices << 32 | entries,
+// zero between two binnings) and its cursor, each on a cache line of its own.
+constexpr int BIN_STRIDE = 16;  // int64 words
+constexpr int BIN_WORDS = 2 * NROWS * BIN_STRIDE;
 
-// Inclusive prefix sum over a wave (shuffles: 6 steps).
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  const int lane = lane_id();
+// The BIN_ITEMS vertices of a thread, their row starts and rows (-1 past the
+// list): every round of loads at clamped indexes, in flight together.
+__device__ __forceinline__ void bin_load(const int32_t* __restrict__ list, int64_t cnt,
+                                         const int32_t* __restrict__ off,
+                                         const uint8_t* __restrict__ skip, int wmax,
+                                         int (&u)[BIN_ITEMS], int (&rb)[BIN_ITEMS],
+                                         int (&deg)[BIN_ITEMS], int (&row)[BIN_ITEMS]) {
+  int re[BIN_ITEMS], sk[BIN_ITEMS];
+  const int64_t base = int64_t(blockIdx.x) * BIN_TILE + threadIdx.x;
 #pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const int y = __shfl_up(v, o, WAVE);
-    if (lane >= o) v += y;
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    const int64_t p = base + int64_t(r) * BIN_TPB;
+    const int64_t pc = p < cnt ? p : cnt - 1;
+    u[r] = list ? list[pc] : int(pc);
   }
-  return v;
+#pragma unroll
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    rb[r] = off[u[r]];
+    re[r] = off[u[r] + 1];
+    sk[r] = skip ? skip[u[r]] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    deg[r] = re[r] - rb[r];
+    row[r] = base + int64_t(r) * BIN_TPB < cnt ? 2 * bin_of(deg[r], wmax) + (sk[r] ? 1 : 0) : -1;
+  }
 }
 
-// One block after k_bin_count: with scan, the exclusive scan of the per-block
-// row counts bcnt (row-major, NROWS * nblocks of them, at most META_SCAN_MAX)
-// into boff; without, boff and its total (counts[M_TOTAL]) are given.  Then
-// the metadata, written to counts and to host (device-visible pinned host
-// memory), and copy_n slots of copy_src copied to copy_dst (host memory too)
-// so that the caller's one wait brings back both.
-__global__ void __launch_bounds__(META_TPB)
-    k_bin_meta(const int32_t* __restrict__ bcnt, int32_t* boff,
-               const long long* __restrict__ bvol, int64_t nblocks, int scan, int32_t* counts,
-               int32_t* host, const long long* __restrict__ copy_src, long long* copy_dst,
-               int copy_n) {
-  __shared__ int wtot[META_TPB / WAVE];
-  __shared__ long long vpart[META_TPB / WAVE][NROWS];
+// The rows' totals: one atomic per block and row; the last block to finish
+// turns them into starts (the placement's cursors) and the metadata, written
+// to counts and to host (device-visible pinned host memory), and copies copy_n
+// slots of copy_src to copy_dst (host memory too), so that the caller's one
+// wait brings back both.
+__global__ void __launch_bounds__(BIN_TPB)
+    k_bin_count(const int32_t* __restrict__ list, int64_t cnt, const int32_t* __restrict__ dcnt,
+                const int32_t* __restrict__ off, const uint8_t* __restrict__ skip, int wmax,
+                unsigned long long* words, unsigned* done, int32_t* counts, int32_t* host,
+                const long long* __restrict__ copy_src, long long* copy_dst, int copy_n) {
+  if (dcnt) cnt = *dcnt;  // the list's length on the device (cnt: its bound)
+  __shared__ unsigned long long part[BIN_WAVES][NROWS];
+  __shared__ unsigned long long tot[NROWS];
   __shared__ int meta[META_WORDS];
   const int t = threadIdx.x, lane = lane_id(), wid = t / WAVE;
-  const int64_t M = int64_t(NROWS) * nblocks;
-  if (t < META_WORDS) meta[t] = 0;
-  __syncthreads();
-  // row volumes: row by row, the threads stride over the blocks' partials
-  // (all loads independent), then one wave sum per row and wave
-#pragma unroll 1
-  for (int r = 0; r < NROWS; ++r) {
-    long long acc = 0;
-    for (int64_t b = t; b < nblocks; b += META_TPB) acc += bvol[int64_t(r) * nblocks + b];
-    acc = wave_sum(acc);
-    if (lane == 0) vpart[wid][r] = acc;
-  }
-  if (scan) {
-    // thread t scans the contiguous chunk [t * per, (t + 1) * per), its
-    // counts held in registers (per <= META_PER)
-    const int per = int(ceil_div(M, META_TPB));
-    const int64_t b0 = int64_t(t) * per;
-    int v[META_PER];
-    int sum = 0;
+  if (int64_t(blockIdx.x) * BIN_TILE < cnt) {  // block-uniform
+    int u[BIN_ITEMS], rb[BIN_ITEMS], deg[BIN_ITEMS], row[BIN_ITEMS];
+    bin_load(list, cnt, off, skip, wmax, u, rb, deg, row);
 #pragma unroll
-    for (int i = 0; i < META_PER; ++i) {
-      v[i] = (i < per && b0 + i < M) ? bcnt[b0 + i] : 0;
-      sum += v[i];
-    }
-    const int incl = wave_incl_scan(sum);
-    if (lane == WAVE - 1) wtot[wid] = incl;
-    __syncthreads();
-    if (t == 0) {
-      int run = 0;
-      for (int w = 0; w < META_TPB / WAVE; ++w) {
-        const int x = wtot[w];
-        wtot[w] = run;
-        run += x;
+    for (int q = 0; q < NROWS; ++q) {
+      int n = 0, v = 0;  // a wave's entries fit int32 (all entries do)
+#pragma unroll
+      for (int r = 0; r < BIN_ITEMS; ++r) {
+        n += __popcll(__ballot(row[r] == q));
+        v += row[r] == q ? deg[r] : 0;
       }
-      meta[M_TOTAL] = run;
+      v = n ? wave_sum(v) : 0;  // n: wave-uniform
+      if (lane == 0) part[wid][q] = (unsigned long long)n << 32 | uint32_t(v);
     }
     __syncthreads();
-    int run = wtot[wid] + incl - sum;
-#pragma unroll
-    for (int i = 0; i < META_PER; ++i) {
-      if (i < per && b0 + i < M) boff[b0 + i] = run;
-      run += v[i];
-    }
-  } else if (t == 0) {
-    meta[M_TOTAL] = counts[M_TOTAL];
+    if (t < NROWS) {
+      unsigned long long x = 0;
+      for (int w = 0; w < BIN_WAVES; ++w) x += part[w][t];
+      if (x) atomicAdd(&words[t * BIN_STRIDE], x);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // performed before the block counts
+    }                                                   // as finished
   }
-  __syncthreads();  // boff (global, this block's writes) and the total
-  if (t < NBINS && M > 0) {
-    // boff is row-major: row r starts at boff[r * nblocks]
-    const int q = t;
-    const int s0 = boff[int64_t(2 * q) * nblocks];
-    const int s1 = boff[int64_t(2 * q + 1) * nblocks];
-    const int e = (q + 1 < NBINS) ? boff[int64_t(2 * q + 2) * nblocks] : meta[M_TOTAL];
-    meta[M_START + q] = s0;
-    meta[q] = e - s0;
-    meta[NBINS + q] = s1 - s0;
-  }
+  if (!last_block(done)) return;
+  if (t < META_WORDS) meta[t] = 0;
   if (t < NROWS) {
-    long long v = 0;
-    for (int w = 0; w < META_TPB / WAVE; ++w) v += vpart[w][t];
-    meta[32 + 2 * t] = int(uint32_t(uint64_t(v)));
-    meta[32 + 2 * t + 1] = int(uint32_t(uint64_t(v) >> 32));
+    tot[t] = __hip_atomic_load(&words[t * BIN_STRIDE], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    words[t * BIN_STRIDE] = 0;
+  }
+  __syncthreads();
+  if (t < NROWS) {
+    int start = 0;
+    for (int q = 0; q < t; ++q) start += int(tot[q] >> 32);
+    words[(NROWS + t) * BIN_STRIDE] = (unsigned long long)start;
+    if (t % 2 == 0) {
+      meta[M_START + t / 2] = start;
+      meta[t / 2] = int(tot[t] >> 32) + int(tot[t + 1] >> 32);
+      meta[NBINS + t / 2] = int(tot[t] >> 32);
+    }
+    meta[32 + 2 * t] = int(uint32_t(tot[t]));
   }
   __syncthreads();
   if (t < META_WORDS) {
     counts[t] = meta[t];
     host_store(&host[t], meta[t]);
   }
-  for (int i = t; i < copy_n; i += META_TPB) host_store(&copy_dst[i], copy_src[i]);
+  for (int i = t; i < copy_n; i += BIN_TPB) host_store(&copy_dst[i], copy_src[i]);
+}
+
+// The vertices to their rows' lists, row starts beside them: a block takes
+// its places in a row with one atomic on the row's cursor, so the blocks'
+// parts of a list are in no fixed order (every evaluation reads one snapshot
+// and every sum is exact, so the order changes no result).
+__global__ void __launch_bounds__(BIN_TPB)
+    k_bin_scatter(const int32_t* __restrict__ list, int64_t cnt, const int32_t* __restrict__ dcnt,
+                  const int32_t* __restrict__ off, const uint8_t* __restrict__ skip, int wmax,
+                  unsigned long long* words, int32_t* out, int32_t* out_rb) {
+  if (dcnt) cnt = *dcnt;
+  if (int64_t(blockIdx.x) * BIN_TILE >= cnt) return;  // block-uniform
+  __shared__ int at[NROWS][BIN_ITEMS * BIN_WAVES];
+  static_assert(BIN_ITEMS * BIN_WAVES == WAVE && NROWS <= BIN_WAVES, "a wave per row");
+  const int lane = lane_id(), wid = threadIdx.x / WAVE;
+  int u[BIN_ITEMS], rb[BIN_ITEMS], deg[BIN_ITEMS], row[BIN_ITEMS], rank[BIN_ITEMS];
+  bin_load(list, cnt, off, skip, wmax, u, rb, deg, row);
+  const uint64_t lt = (uint64_t(1) << lane) - 1;
+#pragma unroll
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    rank[r] = 0;
+#pragma unroll
+    for (int q = 0; q < NROWS; ++q) {
+      const uint64_t m = __ballot(row[r] == q);
+      if (lane == 0) at[q][r * BIN_WAVES + wid] = __popcll(m);
+      if (row[r] == q) rank[r] = __popcll(m & lt);
+    }
+  }
+  __syncthreads();
+  if (wid < NROWS) {  // wave q: the (round, wave) parts of row q
+    const int v = at[wid][lane];
+    int x = v;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const int y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
+    }
+    const int n = __builtin_amdgcn_readlane(x, WAVE - 1);
+    int base = 0;
+    if (lane == 0 && n)
+      base = int(atomicAdd(&words[(NROWS + wid) * BIN_STRIDE], (unsigned long long)n));
+    at[wid][lane] = __builtin_amdgcn_readfirstlane(base) + x - v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    if (row[r] < 0) continue;
+    const int pos = at[row[r]][r * BIN_WAVES + wid] + rank[r];
+    out[pos] = u[r];
+    out_rb[pos] = rb[r];
+  }
 }
 
 __global__ void k_table_caps(const int32_t* __restrict__ list, const int32_t* __restrict__ off,
@@ -1591,27 +1497,18 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
   const int64_t cap = count > 0 ? count : 1;
   s.lists.ensure(size_t(cap) * sizeof(int32_t));
   s.lists_rb.ensure(size_t(cap) * sizeof(int32_t));
-  s.bcnt.ensure(size_t(NROWS * nb + 1) * sizeof(int32_t));
-  s.boff.ensure(size_t(NROWS * nb + 1) * sizeof(int32_t));
-  s.bvol.ensure(size_t(NROWS * nb) * sizeof(long long));
   s.counts.ensure(META_WORDS * sizeof(int32_t));
-  int32_t* counts = s.counts.as<int32_t>();
-  int32_t* bcnt = s.bcnt.as<int32_t>();
-  int32_t* boff = s.boff.as<int32_t>();
-  long long* bvol = s.bvol.as<long long>();
-  if (!s.host_dev) DC_HIP(hipHostGetDevicePointer(&s.host_dev, s.host, 0));
-  // count, then the scan and the metadata in one block (the scan of many
-  // blocks' counts takes the two-launch scan first), then one wait
-  const int64_t M = count > 0 ? int64_t(NROWS) * nb : 0;
-  if (count > 0) {
-    k_bin_count<<<nb, TPB, 0, st>>>(list, count, dcount, off, skip, bcnt, bvol, nb, wmax);
-    DC_LAUNCH_CHECK();
+  if (!s.words.p) {  // totals and finished blocks start at zero, and end there
+    s.words.ensure(size_t(BIN_WORDS) * 8 + DONE_WORDS * 4);
+    fill_i32(s.words.as<int32_t>(), 0, 2 * BIN_WORDS + DONE_WORDS, st);
   }
-  const bool one_block = M <= META_SCAN_MAX;
-  if (!one_block) scan_excl_i32(bcnt, boff, M, counts + M_TOTAL, st);
-  k_bin_meta<<<1, META_TPB, 0, st>>>(bcnt, boff, bvol, count > 0 ? nb : 0, one_block ? 1 : 0,
-                                      counts, static_cast<int32_t*>(s.host_dev), copy_src,
-                                      copy_dst, copy_src ? copy_n : 0);
+  auto* words = s.words.as<unsigned long long>();
+  auto* done = reinterpret_cast<unsigned*>(words + BIN_WORDS);
+  int32_t* counts = s.counts.as<int32_t>();
+  if (!s.host_dev) DC_HIP(hipHostGetDevicePointer(&s.host_dev, s.host, 0));
+  k_bin_count<<<nb, BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, words, done, counts,
+                                      static_cast<int32_t*>(s.host_dev), copy_src, copy_dst,
+                                      copy_src ? copy_n : 0);
   DC_LAUNCH_CHECK();
   DC_HIP(hipStreamSynchronize(st));
   const int32_t* hc = static_cast<const int32_t*>(s.host);
@@ -1644,8 +1541,8 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
   b.tab_off = nullptr;
   b.gslots = 0;
   if (count > 0) {
-    k_bin_scatter<<<nb, TPB, 0, st>>>(list, count, dcount, off, skip, boff, nb, lists,
-                                      lists_rb, wmax);
+    k_bin_scatter<<<nb, BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, words, lists,
+                                          lists_rb);
     DC_LAUNCH_CHECK();
   }
   constexpr int G = NBINS - 1;
