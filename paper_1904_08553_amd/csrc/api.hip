@@ -189,9 +189,12 @@ long long run_sweeps(dc_ctx* c, const LevelView& g, const int32_t* act, int64_t 
     sweep_apply(g, act, nact, c->Cl.as<int32_t>(), c->Cn.as<int32_t>(), c->al.as<int32_t>(),
                 c->szl.as<int32_t>(), c->two_m, c->movers.as<int32_t>(),
                 c->dpack.as<long long>(), c->lflag.as<int32_t>(), c->tlist.as<int32_t>(),
-                c->stat.as<long long>(), c->done.as<unsigned>(), c->hstat_dev, st);
+                c->stat.as<long long>(), c->done.as<unsigned>(), c->hstat_dev, c->tag, st);
     // the status block reaches c->hstat from the sweep's last kernel
-    DC_HIP(hipStreamSynchronize(st));
+    if (timed)
+      DC_HIP(hipStreamSynchronize(st));  // the events too
+    else
+      wait_tag(c->tag, st);
     check_stat_errors(c->hstat);
     float ms = -1.f;
     if (timed) DC_HIP(hipEventElapsedTime(&ms, c->ev0, c->ev1));
@@ -643,9 +646,9 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
   }
   resolve_changes(rkeys, rvals, nr, aw, n, off_old, adj_old, c->rpart, c->npart, ch_key, ch_op,
                   ch_w, ch_dk, cnet, ins_pos, ins_keys, reinterpret_cast<int32_t*>(stat + ST_N1),
-                  flags, stat + ST_WSUM_DEL, stat, ST_COUNT, c->hstat_dev, c->hbuf_dev, st);
+                  flags, stat + ST_WSUM_DEL, stat, ST_COUNT, c->hstat_dev, c->hbuf_dev, c->tag, st);
   if (nr > 0) {
-    DC_HIP(hipStreamSynchronize(st));
+    wait_tag(c->tag, st);
     check_stat_errors(hs);
   } else {
     std::fill(hs, hs + ST_COUNT, 0ll);
@@ -1234,6 +1237,18 @@ void level0_merged(dc_ctx* const* cs, LevelRun* Ls, long long* gains, int m, Mer
   }
 }
 
+// Zeroed pinned host memory that kernels write while the host reads it, and
+// its device address; tag: its last word becomes a publication word.
+void pinned(void** host, void** dev, size_t bytes, HostTag* tag) {
+  DC_HIP(hipHostMalloc(host, bytes, hipHostMallocCoherent | hipHostMallocMapped));
+  std::memset(*host, 0, bytes);
+  DC_HIP(hipHostGetDevicePointer(dev, *host, 0));
+  if (tag) {
+    tag->host = static_cast<uint32_t*>(*host) + bytes / 4 - 1;
+    tag->dev = static_cast<uint32_t*>(*dev) + bytes / 4 - 1;
+  }
+}
+
 // A new context with its pinned host buffers, events and second stream;
 // `build` fills its device state.  On failure everything is released.
 template <class F>
@@ -1246,13 +1261,11 @@ dc_status create_ctx(dc_ctx** out, int32_t n, const dc_options* opt, F&& build) 
   c->st = static_cast<hipStream_t>(opt->stream);
   dc_status s;
   try {
-    DC_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->hstat), ST_COUNT * 8));
-    DC_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->hstat_dev), c->hstat, 0));
-    DC_HIP(hipHostMalloc(&c->hbuf, 64));
-    DC_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->hbuf_dev), c->hbuf, 0));
-    DC_HIP(hipHostMalloc(&c->bins.host, 256));
-    std::memset(c->bins.host, 0, 256);
-    DC_HIP(hipHostMalloc(&c->cs.host, 64));
+    pinned(reinterpret_cast<void**>(&c->hstat), reinterpret_cast<void**>(&c->hstat_dev),
+           ST_COUNT * 8, nullptr);
+    pinned(&c->hbuf, reinterpret_cast<void**>(&c->hbuf_dev), 64, &c->tag);
+    pinned(&c->bins.host, &c->bins.host_dev, 256, &c->bins.tag);
+    pinned(&c->cs.host, &c->cs.host_dev, 64, &c->cs.tag);
     DC_HIP(hipEventCreate(&c->ev0));
     DC_HIP(hipEventCreate(&c->ev1));
     for (hipEvent_t& e : c->evp) DC_HIP(hipEventCreate(&e));

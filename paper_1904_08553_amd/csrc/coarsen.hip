@@ -370,7 +370,7 @@ __global__ void __launch_bounds__(SCAN_THREADS)
                 const int32_t* __restrict__ off, int32_t n, const long long* __restrict__ p64,
                 const int32_t* __restrict__ p32, int raw, int64_t nt, int32_t* rank,
                 int32_t* orank, int32_t* nrank, int32_t* mpos, int32_t* cnt_out, int32_t* k_out,
-                int32_t* minv, int32_t* host) {
+                int32_t* minv, int32_t* host, uint32_t* tag, uint32_t tag_value) {
   __shared__ long long l64[SCAN_THREADS / WAVE];
   __shared__ int32_t l32[SCAN_THREADS / WAVE];
   const int64_t base = int64_t(blockIdx.x) * SCAN_TILE + int64_t(threadIdx.x) * SCAN_ITEMS;
@@ -422,11 +422,13 @@ __global__ void __launch_bounds__(SCAN_THREADS)
     }
     run += (now ? 1ll : 0ll) + (old ? 1ll << 32 : 0ll);
   }
-  if (blockIdx.x == nt - 1 && threadIdx.x == 0) {
+  if (blockIdx.x != nt - 1) return;
+  if (threadIdx.x == 0) {
     host_store(host, int32_t((off64 + tot64) & 0xffffffffll));
     host_store(host + 1, off32 + tot32);
     host_store(host + 3, int32_t((off64 + tot64) >> 32));
   }
+  host_publish(tag, tag_value);
 }
 
 struct IncEmit {
@@ -621,7 +623,7 @@ __global__ void __launch_bounds__(SCAN_THREADS)
               const int32_t* __restrict__ nruns, const int32_t* __restrict__ part, int raw,
               int64_t nt, const int32_t* __restrict__ nrank, int ob, int nb, int2* adj,
               uint64_t* lkey, int32_t* lw, const int32_t* __restrict__ minv, int32_t* lminv,
-              int32_t nc, int32_t* host) {
+              int32_t nc, int32_t* host, uint32_t* tag, uint32_t tag_value) {
   __shared__ int32_t lds[SCAN_THREADS / WAVE];
   for (int64_t r = int64_t(blockIdx.x) * SCAN_THREADS + threadIdx.x; r < nc;
        r += int64_t(gridDim.x) * SCAN_THREADS)
@@ -652,7 +654,9 @@ __global__ void __launch_bounds__(SCAN_THREADS)
     ++p;
   }
   if (bad) host_store(host + 2, 1);
-  if (blockIdx.x == nt - 1 && threadIdx.x == 0) host_store(host, offs + tot);
+  if (blockIdx.x != nt - 1) return;
+  if (threadIdx.x == 0) host_store(host, offs + tot);
+  host_publish(tag, tag_value);
 }
 
 __global__ void k_adj_weights(const int2* __restrict__ adj, int64_t m, int32_t* w) {
@@ -825,15 +829,6 @@ void coarsen(const LevelView& g, const int32_t* C, const int32_t* sz, const int3
   DC_LAUNCH_CHECK();
 }
 
-namespace {
-
-int32_t* host_alias(CoarsenScratch& s) {
-  if (!s.host_dev) DC_HIP(hipHostGetDevicePointer(&s.host_dev, s.host, 0));
-  return static_cast<int32_t*>(s.host_dev);
-}
-
-}  // namespace
-
 void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Cold,
                        const int32_t* sz, const int32_t* a, const uint64_t* ch_key,
                        const int32_t* ch_dk, int64_t nch, int32_t* map0, CoarseGraph& out,
@@ -841,7 +836,7 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
                        hipStream_t st) {
   const int32_t nl = g.n;
   int32_t* host = static_cast<int32_t*>(s.host);
-  int32_t* hdev = host_alias(s);  // the kernels write the sizes the host reads here
+  int32_t* hdev = static_cast<int32_t*>(s.host_dev);  // the kernels write the sizes the host reads here
   const int64_t nt = ceil_div(nl, SCAN_TILE);
   s.rank.ensure(size_t(nl + 1) * 4);
   H.orank.ensure(size_t(nl + 1) * 4);
@@ -866,9 +861,9 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
   k_inc_ranks<<<int(nt), SCAN_THREADS, 0, st>>>(
       sz, a, Cl, Cold, g.off, nl, nt > 1 ? reinterpret_cast<long long*>(p64) : nullptr,
       nt > 1 ? p32 : nullptr, raw, nt, rank, H.orank.as<int32_t>(), H.nrank.as<int32_t>(),
-      H.mpos.as<int32_t>(), cnt_out, out.k.as<int32_t>(), minv_out, hdev);
+      H.mpos.as<int32_t>(), cnt_out, out.k.as<int32_t>(), minv_out, hdev, s.tag.dev, s.tag.next());
   DC_LAUNCH_CHECK();
-  DC_HIP(hipStreamSynchronize(st));
+  wait_tag(s.tag, st);
   const int32_t nc = host[0], nold = host[3];
   const int64_t vol = host[1];
 
@@ -912,7 +907,6 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
   H.lkey.ensure(size_t(m + 1) * 8);
   H.lw.ensure(size_t(m + 1) * 4);
   H.lminv.ensure(size_t(nc + 1) * 4);
-  host[0] = 0;
   host[2] = 0;  // the self-check flag, set by the kernel in host memory
   int64_t cnnz = 0;
   if (m > 0) {
@@ -950,9 +944,10 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
     k_inc_csr<<<int(mt), SCAN_THREADS, 0, st>>>(
         H.rkey.as<uint64_t>(), H.ssum.as<uint32_t>(), H.nruns.as<int32_t>(), one ? nullptr : p32,
         mraw, mt, H.nrank.as<int32_t>(), A.ob, key_bits(nc), out.adj.as<int2>(),
-        H.lkey.as<uint64_t>(), H.lw.as<int32_t>(), minv_out, H.lminv.as<int32_t>(), nc, hdev);
+        H.lkey.as<uint64_t>(), H.lw.as<int32_t>(), minv_out, H.lminv.as<int32_t>(), nc, hdev,
+        s.tag.dev, s.tag.next());
     DC_LAUNCH_CHECK();
-    DC_HIP(hipStreamSynchronize(st));
+    wait_tag(s.tag, st);
     cnnz = host[0];
   }
   s.inc_check = true;  // read by inc_check

@@ -50,6 +50,7 @@ struct dc_ctx {
   DBuf done;                   // finished-block counters (DONE_WORDS, zero between launches)
   void* hbuf = nullptr;        // pinned scratch for the kernels' host reads
   int32_t* hbuf_dev = nullptr; // its address for the kernels that write it
+  HostTag tag;                 // publications of the batch's sizes and of the sweeps
   BinScratch bins;
   CoarsenScratch cs;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;

@@ -240,6 +240,29 @@ __device__ __forceinline__ void host_store(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// A kernel's publication to the host: a word of pinned host memory that the
+// kernel sets to the launch's own value once the data before it is there.
+// The host spins on the word (wait_tag), which returns some microseconds
+// before a wait on the stream would, and launches queued behind the kernel
+// run meanwhile.
+struct HostTag {
+  uint32_t* host = nullptr;
+  uint32_t* dev = nullptr;
+  uint32_t value = 0;
+  // the value of the next publication
+  uint32_t next() { return ++value; }
+};
+void wait_tag(const HostTag& t, hipStream_t st);
+
+// Every thread of the one publishing block calls this after its host_stores:
+// each wave waits until its stores have been performed, the barrier joins
+// the waves, then the word is set.
+__device__ __forceinline__ void host_publish(uint32_t* tag, uint32_t value) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) host_store(tag, value);
+}
+
 // Finished blocks of a launch: true in exactly one block, the last to get
 // here, once every block has passed the call, so the others' reads before
 // it are done (the barrier waits for them).  Their stores are not made

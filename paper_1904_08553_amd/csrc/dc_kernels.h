@@ -116,14 +116,14 @@ void batch_records(const int32_t* du, const int32_t* dv, int64_t nd, const int32
 // pair absent from off/adj); wsum (SUM_SLOTS counters) += the old weights of
 // the deleted edges.  Pinned host memory (device addresses) receives the
 // first nstat slots of stat, flags and sums included, and host[0..2] =
-// {changes, insertion records, NEW minus DELETE}.  part, npart: scratch.
+// {changes, insertion records, NEW minus DELETE}, published by tag.  part, npart: scratch.
 // Nothing is launched for m = 0.
 void resolve_changes(const uint64_t* keys, const uint32_t* vals, int64_t m, const int32_t* ins_w,
                      int32_t n, const int32_t* off, const int2* adj, DBuf& part, DBuf& npart,
                      uint64_t* ch_key, int32_t* ch_op, int32_t* ch_w, int32_t* ch_dk,
                      int32_t* cnet, int32_t* ins_pos, uint64_t* ins_keys, int32_t* nruns,
                      int32_t* flags, long long* wsum, const long long* stat, int nstat,
-                     long long* host_stat, int32_t* host, hipStream_t st);
+                     long long* host_stat, int32_t* host, HostTag& tag, hipStream_t st);
 
 // Old CSR entries per block of the merge.
 constexpr int MERGE_TILE = 1024;

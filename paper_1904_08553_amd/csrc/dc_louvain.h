@@ -149,6 +149,7 @@ struct BinScratch {
   DBuf lists, lists_rb, words, counts, tab_off, gkeys, gvals, ovf;
   void* host = nullptr;      // pinned, 256 bytes
   void* host_dev = nullptr;  // its address for the kernels that write it
+  HostTag tag;
   hipStream_t side = nullptr;  // second stream and fork / join events of the
   hipEvent_t fork = nullptr;   // evaluation launches (owned by the context)
   hipEvent_t join = nullptr;
@@ -183,12 +184,12 @@ void sweep_eval(const LevelView& g, const int32_t* C, int32_t* Cn, const int32_t
 // applies them, computes the exact Delta N and keeps or reverts the sweep.
 // The sweep's status block (ST_COUNT slots, ST_DN and ST_KEEP filled in)
 // is written to host_stat, a device-visible address of pinned host memory,
-// by the last kernel: after a wait on the stream it is there, with no copy.
+// by the last kernel, which then publishes tag: no copy, no wait on the stream.
 // done: DONE_WORDS zeroed words (finished-block counters).
 void sweep_apply(const LevelView& g, const int32_t* active, int64_t n_active, int32_t* C,
                  int32_t* Cn, int32_t* a, int32_t* sz, long long two_m, int32_t* movers,
                  long long* dpack, int32_t* tflag, int32_t* tlist, long long* stat,
-                 unsigned* done, long long* host_stat, hipStream_t st);
+                 unsigned* done, long long* host_stat, HostTag& tag, hipStream_t st);
 
 // Scratch of one Alg. 2 pass: per directed insertion record its gain
 // (sink_g, n_ins entries), per vertex the best sink and gain1 (best_j,
@@ -370,6 +371,7 @@ struct CoarsenScratch {
       chunks, mcnt, pk0, pk1, pv0, pv1, ph, pp, pS, pcnt, hidx, ukey, rc;
   void* host = nullptr;      // pinned, 64 bytes
   void* host_dev = nullptr;  // its address for the kernels that write it
+  HostTag tag;
   bool inc_check = false;    // coarsen_first_inc's self-check flag awaits a wait
 };
 

@@ -1130,7 +1130,7 @@ constexpr int NROWS = 2 * NBINS;
 constexpr int M_START = 2 * NBINS, M_OVF = 3 * NBINS;
 constexpr int META_WORDS = 32 + 2 * NROWS;
 static_assert(M_OVF + 2 <= 32, "bin metadata slots overlap the volumes");
-static_assert(META_WORDS * 4 <= 256, "bin metadata must fit the pinned host buffer");
+static_assert(META_WORDS * 4 < 256, "bin metadata must fit the pinned host buffer");
 
 // Device words of a binning: per row its total (vertices << 32 | entries,
 // zero between two binnings) and its cursor, each on a cache line of its own.
@@ -1174,7 +1174,8 @@ __global__ void __launch_bounds__(BIN_TPB)
     k_bin_count(const int32_t* __restrict__ list, int64_t cnt, const int32_t* __restrict__ dcnt,
                 const int32_t* __restrict__ off, const uint8_t* __restrict__ skip, int wmax,
                 unsigned long long* words, unsigned* done, int32_t* counts, int32_t* host,
-                const long long* __restrict__ copy_src, long long* copy_dst, int copy_n) {
+                const long long* __restrict__ copy_src, long long* copy_dst, int copy_n, uint32_t* tag,
+                uint32_t tag_value) {
   if (dcnt) cnt = *dcnt;  // the list's length on the device (cnt: its bound)
   __shared__ unsigned long long part[BIN_WAVES][NROWS];
   __shared__ unsigned long long tot[NROWS];
@@ -1227,6 +1228,7 @@ __global__ void __launch_bounds__(BIN_TPB)
     host_store(&host[t], meta[t]);
   }
   for (int i = t; i < copy_n; i += BIN_TPB) host_store(&copy_dst[i], copy_src[i]);
+  host_publish(tag, tag_value);
 }
 
 // The vertices to their rows' lists, row starts beside them: a block takes
@@ -1505,16 +1507,20 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
   auto* words = s.words.as<unsigned long long>();
   auto* done = reinterpret_cast<unsigned*>(words + BIN_WORDS);
   int32_t* counts = s.counts.as<int32_t>();
-  if (!s.host_dev) DC_HIP(hipHostGetDevicePointer(&s.host_dev, s.host, 0));
   k_bin_count<<<nb, BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, words, done, counts,
                                       static_cast<int32_t*>(s.host_dev), copy_src, copy_dst,
-                                      copy_src ? copy_n : 0);
+                                      copy_src ? copy_n : 0, s.tag.dev, s.tag.next());
   DC_LAUNCH_CHECK();
-  DC_HIP(hipStreamSynchronize(st));
-  const int32_t* hc = static_cast<const int32_t*>(s.host);
-  const long long* hv = reinterpret_cast<const long long*>(hc + 32);
   int32_t* lists = s.lists.as<int32_t>();
   int32_t* lists_rb = s.lists_rb.as<int32_t>();
+  if (count > 0) {  // runs while the host reads the metadata
+    k_bin_scatter<<<nb, BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, words, lists,
+                                          lists_rb);
+    DC_LAUNCH_CHECK();
+  }
+  wait_tag(s.tag, st);
+  const int32_t* hc = static_cast<const int32_t*>(s.host);
+  const long long* hv = reinterpret_cast<const long long*>(hc + 32);
   b.total = 0;
   for (int q = 0; q < NBINS; ++q) {
     b.n[q] = hc[q];
@@ -1540,11 +1546,6 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
   b.gvals = nullptr;
   b.tab_off = nullptr;
   b.gslots = 0;
-  if (count > 0) {
-    k_bin_scatter<<<nb, BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, words, lists,
-                                          lists_rb);
-    DC_LAUNCH_CHECK();
-  }
   constexpr int G = NBINS - 1;
   if (b.n[G] > 0) {
     s.tab_off.ensure(size_t(b.n[G] + 1) * sizeof(long long));

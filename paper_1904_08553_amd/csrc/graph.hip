@@ -316,11 +316,9 @@ __global__ void __launch_bounds__(RES_TILE)
                    const long long* __restrict__ npart, const int32_t* __restrict__ nruns,
                    int32_t* cnet, int32_t* ins_pos, uint64_t* ins_keys,
                    const long long* __restrict__ stat, int nstat, long long* host_stat,
-                   int32_t* host) {
+                   int32_t* host, uint32_t* tag, uint32_t tag_value) {
   __shared__ int32_t l32[RES_TILE / WAVE];
   __shared__ long long l64[RES_TILE / WAVE];
-  if (blockIdx.x == 0)
-    for (int k = threadIdx.x; k < nstat; k += RES_TILE) host_store(host_stat + k, stat[k]);
   const int32_t nch = *nruns;
   const int32_t c0 = tile_offset<int32_t, RES_TILE>(part, raw, nt, l32);
   const bool last = int64_t(blockIdx.x) == nt - 1;
@@ -343,13 +341,16 @@ __global__ void __launch_bounds__(RES_TILE)
     ins_pos[q] = p;
     if (op != OP_DELETE) ins_keys[p] = key;
   }
-  if (last && threadIdx.x == 0) {
+  if (!last) return;
+  for (int k = threadIdx.x; k < nstat; k += RES_TILE) host_store(host_stat + k, stat[k]);
+  if (threadIdx.x == 0) {
     const long long t = offs + tot;
     cnet[nch] = int32_t(t >> 32);
     host_store(host, nch);
     host_store(host + 1, int32_t(t & 0xffffffffll));
     host_store(host + 2, int32_t(t >> 32));
   }
+  host_publish(tag, tag_value);
 }
 
 // First k in [0, m) with keys[k] >= key (m if none), by the whole wave: 64
@@ -880,7 +881,7 @@ void resolve_changes(const uint64_t* keys, const uint32_t* vals, int64_t m, cons
                      uint64_t* ch_key, int32_t* ch_op, int32_t* ch_w, int32_t* ch_dk,
                      int32_t* cnet, int32_t* ins_pos, uint64_t* ins_keys, int32_t* nruns,
                      int32_t* flags, long long* wsum, const long long* stat, int nstat,
-                     long long* host_stat, int32_t* host, hipStream_t st) {
+                     long long* host_stat, int32_t* host, HostTag& tag, hipStream_t st) {
   if (m <= 0) return;
   const int64_t nt = ceil_div(m, RES_TILE);
   const int raw = nt <= SCAN_RAW_MAX;
@@ -902,7 +903,7 @@ void resolve_changes(const uint64_t* keys, const uint32_t* vals, int64_t m, cons
   if (!raw) scan_excl_i64(p64, p64, nt, nullptr, st);
   k_scan_changes<<<int(nt), RES_TILE, 0, st>>>(
       ch_key, ch_op, heads, raw, nt, heads ? reinterpret_cast<long long*>(p64) : nullptr, nruns,
-      cnet, ins_pos, ins_keys, stat, nstat, host_stat, host);
+      cnet, ins_pos, ins_keys, stat, nstat, host_stat, host, tag.dev, tag.next());
   DC_LAUNCH_CHECK();
 }
 

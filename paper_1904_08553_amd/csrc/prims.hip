@@ -15,6 +15,22 @@ bool sync_check_enabled() {
   return on;
 }
 
+void wait_tag(const HostTag& t, hipStream_t st) {
+  for (uint32_t spin = 1;; ++spin) {
+    if (__atomic_load_n(t.host, __ATOMIC_ACQUIRE) == t.value) return;
+    if (spin % 4096 == 0) {
+      // about every 100 us: a stream that failed, or that ended without
+      // the publication, ends the wait
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipErrorNotReady) continue;
+      DC_HIP(e);
+      if (__atomic_load_n(t.host, __ATOMIC_ACQUIRE) == t.value) return;
+      throw std::runtime_error("a kernel ended without its publication");
+    }
+    __builtin_ia32_pause();
+  }
+}
+
 PrimScratch& prim_scratch() {
   static thread_local PrimScratch s;
   return s;
