@@ -84,3 +84,26 @@ def test_runs_of_one_pair(copies):
         for t, b in enumerate((first, second)):
             step_pair(o, g, b)
             compare(o, g, f"copies={copies} {mode} step {t}")
+
+
+@pytest.mark.parametrize("records", [2, (1 << 20) - 2, 1 << 20, (1 << 20) + 2, 8192 * 131 + 2])
+def test_initial_csr_at_sort_sizes(records):
+    """The initial CSR (both directed records of every edge, sorted, equal
+    pairs summed) against numpy at the sizes where the radix sort changes its
+    tile, with ragged last tiles and a repeated pair."""
+    print(f"case: initial csr of {records} records", flush=True)
+    rng = np.random.default_rng(records)
+    n, m = 50_021, records // 2
+    u = rng.integers(0, n, m)
+    v = (u + rng.integers(1, n, m)) % n
+    w = rng.integers(1, 9, m)
+    if m > 1:
+        u[-1], v[-1] = v[0], u[0]
+    g = dc.DynamicCommunities(n, u.astype(np.int32), v.astype(np.int32), w.astype(np.int32),
+                              max_levels=1, max_sweeps=1)
+    off, col, cw = g.csr()
+    key = np.concatenate([u, v]) * n + np.concatenate([v, u])
+    uk, inv = np.unique(key, return_inverse=True)
+    assert np.array_equal(np.repeat(np.arange(n), np.diff(off)) * n + col, uk)
+    assert np.array_equal(cw, np.bincount(inv, weights=np.concatenate([w, w])).astype(np.int64))
+    g.close()
