@@ -189,7 +189,8 @@ long long run_sweeps(dc_ctx* c, const LevelView& g, const int32_t* act, int64_t 
     sweep_apply(g, act, nact, c->Cl.as<int32_t>(), c->Cn.as<int32_t>(), c->al.as<int32_t>(),
                 c->szl.as<int32_t>(), c->two_m, c->movers.as<int32_t>(),
                 c->dpack.as<long long>(), c->lflag.as<int32_t>(), c->tlist.as<int32_t>(),
-                c->stat.as<long long>(), c->done.as<unsigned>(), c->hstat_dev, c->tag, st);
+                c->stat.as<long long>(), c->done.as<unsigned>(), c->hstat_dev, c->tag, bins.ovf_count,
+                st);
     // the status block reaches c->hstat from the sweep's last kernel
     if (timed)
       DC_HIP(hipStreamSynchronize(st));  // the events too

@@ -127,8 +127,7 @@ struct Bins {
   const long long* tab_off;
   int64_t gslots;      // slots of gkeys / gvals
   int32_t* ovf_list;   // rows of bins W and B re-evaluated with the full table
-  int32_t* ovf_count;  // their device count (cleared by the re-evaluation)
-  int32_t* ovf_done;   // blocks of the re-evaluation that have finished
+  int32_t* ovf_count;  // their device count (cleared by a sweep's commit)
   hipStream_t side;    // the hub-row bin runs here, overlapping the other
   hipEvent_t fork;     // bins (null: on the caller's stream)
   hipEvent_t join;
@@ -185,11 +184,13 @@ void sweep_eval(const LevelView& g, const int32_t* C, int32_t* Cn, const int32_t
 // The sweep's status block (ST_COUNT slots, ST_DN and ST_KEEP filled in)
 // is written to host_stat, a device-visible address of pinned host memory,
 // by the last kernel, which then publishes tag: no copy, no wait on the stream.
-// done: DONE_WORDS zeroed words (finished-block counters).
+// done: DONE_WORDS zeroed words (finished-block counters).  ovf_count: the
+// evaluation's overflow count (Bins), cleared.
 void sweep_apply(const LevelView& g, const int32_t* active, int64_t n_active, int32_t* C,
                  int32_t* Cn, int32_t* a, int32_t* sz, long long two_m, int32_t* movers,
                  long long* dpack, int32_t* tflag, int32_t* tlist, long long* stat,
-                 unsigned* done, long long* host_stat, HostTag& tag, hipStream_t st);
+                 unsigned* done, long long* host_stat, HostTag& tag, int32_t* ovf_count,
+                 hipStream_t st);
 
 // Scratch of one Alg. 2 pass: per directed insertion record its gain
 // (sink_g, n_ins entries), per vertex the best sink and gain1 (best_j,

@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(TPB)
     k_commit(const int32_t* __restrict__ movers, const int32_t* __restrict__ tlist,
              long long* stat, long long two_m, int32_t* C, int32_t* Cn, long long* dpack,
              int32_t* tflag, int32_t* a, int32_t* sz, unsigned* done, long long* host_stat,
-             uint32_t* tag, uint32_t tag_value) {
+             int32_t* ovf_count, uint32_t* tag, uint32_t tag_value) {
   const int64_t nm = stat[ST_MOVES], nt = stat[ST_TOUCHED];
   const long long dN = two_m * stat[ST_DI] - stat[ST_DS];
   const bool keep = nm > 0 && dN >= 0;
@@ -254,6 +254,7 @@ __global__ void __launch_bounds__(TPB)
     stat[ST_DS] = 0;
     stat[ST_DN] = dN;
     stat[ST_KEEP] = keep ? 1 : 0;
+    *ovf_count = 0;
   }
   host_publish(tag, tag_value);
 }
@@ -281,7 +282,8 @@ void sweep_reset(long long* stat, hipStream_t st) {
 void sweep_apply(const LevelView& g, const int32_t* active, int64_t n_active, int32_t* C,
                  int32_t* Cn, int32_t* a, int32_t* sz, long long two_m, int32_t* movers,
                  long long* dpack, int32_t* tflag, int32_t* tlist, long long* stat,
-                 unsigned* done, long long* host_stat, HostTag& tag, hipStream_t st) {
+                 unsigned* done, long long* host_stat, HostTag& tag, int32_t* ovf_count,
+                 hipStream_t st) {
   const int64_t cnt = n_active > 0 ? n_active : 1;
   k_apply_moves<<<int(ceil_div(cnt, AM_ROUNDS * TPB)), TPB, 0, st>>>(
       active, n_active, C, Cn, g.k, dpack, tflag, tlist, movers, stat);
@@ -300,7 +302,8 @@ void sweep_apply(const LevelView& g, const int32_t* active, int64_t n_active, in
   }
   DC_LAUNCH_CHECK();
   k_commit<<<grid_for(2 * cnt, 512), TPB, 0, st>>>(movers, tlist, stat, two_m, C, Cn, dpack,
-                                                   tflag, a, sz, done, host_stat, tag.dev, tag.next());
+                                                   tflag, a, sz, done, host_stat, ovf_count, tag.dev,
+                                                   tag.next());
   DC_LAUNCH_CHECK();
 }
 
