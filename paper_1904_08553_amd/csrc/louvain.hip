@@ -2,6 +2,8 @@
 // collect the movers, apply their moves to the community totals a and sizes,
 // compute the exact change of N = 2m*I - sum a^2, and keep or revert the
 // sweep.  The evaluation kernels live in eval.hip.
+#include <type_traits>
+
 #include "dc_louvain.h"
 
 namespace dc {
@@ -30,38 +32,43 @@ __device__ __forceinline__ void touch_label(int X, long long v, long long* dpack
   }
 }
 
-// Block b takes AM_ROUNDS tiles of the active list; all its entries and
-// their labels are loaded first, the block reserves its movers' places in
-// the mover list with one atomic (a counter that every tile added to
-// serialised thousands of same-address atomics when the movers were few and
-// spread out), then lists them and applies their label changes.
-constexpr int AM_ROUNDS = 8;
-__global__ void __launch_bounds__(TPB)
+// Block b takes ROUNDS tiles of the active list; all its entries and their
+// labels are loaded first, the block reserves its movers' places in the mover
+// list with one atomic, then lists them and applies their label changes.
+// The reservations of all blocks queue at one counter (about 30 ns each), and
+// a block is one chain of dependent loads and barriers: 1024 threads and as
+// many rounds as keep the grid near 500 blocks.  Blocks of 2,048 entries
+// took 162 us for 8M active vertices (4,000 reservations) and 35 for 300K
+// (147 blocks on 256 CUs), these 108 and 25.
+constexpr int AM_TPB = 1024;
+constexpr int AM_NW = AM_TPB / WAVE;
+template <int ROUNDS>
+__global__ void __launch_bounds__(AM_TPB)
     k_apply_moves(const int32_t* __restrict__ list, int64_t cnt,
                   const int32_t* __restrict__ C, const int32_t* __restrict__ Cn,
                   const int32_t* __restrict__ k, long long* dpack, int32_t* tflag,
                   int32_t* tlist, int32_t* movers, long long* stat) {
   __shared__ AggLds agg;
-  __shared__ int wc[AM_ROUNDS][NW];
+  __shared__ int wc[ROUNDS][AM_NW];
   __shared__ long long bbase;
   __shared__ int btotal;
   const int wid = threadIdx.x / WAVE, lane = lane_id();
   const uint64_t lt = (uint64_t(1) << lane) - 1;
-  const int64_t v0 = int64_t(blockIdx.x) * (AM_ROUNDS * TPB) + threadIdx.x;
-  int u[AM_ROUNDS], from[AM_ROUNDS], to[AM_ROUNDS];
-  uint64_t fm[AM_ROUNDS];
+  const int64_t v0 = int64_t(blockIdx.x) * (ROUNDS * AM_TPB) + threadIdx.x;
+  int u[ROUNDS], from[ROUNDS], to[ROUNDS];
+  uint64_t fm[ROUNDS];
 #pragma unroll
-  for (int r = 0; r < AM_ROUNDS; ++r) {
-    const int64_t p = v0 + int64_t(r) * TPB;
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int64_t p = v0 + int64_t(r) * AM_TPB;
     u[r] = p < cnt ? (list ? list[p] : int(p)) : -1;
   }
 #pragma unroll
-  for (int r = 0; r < AM_ROUNDS; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     from[r] = u[r] >= 0 ? C[u[r]] : 0;
     to[r] = u[r] >= 0 ? Cn[u[r]] : 0;
   }
 #pragma unroll
-  for (int r = 0; r < AM_ROUNDS; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     fm[r] = __ballot(from[r] != to[r]);
     if (lane == 0) wc[r][wid] = __popcll(fm[r]);
   }
@@ -71,8 +78,8 @@ __global__ void __launch_bounds__(TPB)
   __syncthreads();
   if (threadIdx.x == 0) {
     int tot = 0;
-    for (int r = 0; r < AM_ROUNDS; ++r)
-      for (int w = 0; w < NW; ++w) tot += wc[r][w];
+    for (int r = 0; r < ROUNDS; ++r)
+      for (int w = 0; w < AM_NW; ++w) tot += wc[r][w];
     btotal = tot;
     bbase = tot ? (long long)atomicAdd((unsigned long long*)&stat[ST_MOVES],
                                        (unsigned long long)tot)
@@ -82,7 +89,7 @@ __global__ void __launch_bounds__(TPB)
   if (btotal == 0) return;  // uniform: nothing moved in this block's tiles
   long long run = bbase;
 #pragma unroll
-  for (int r = 0; r < AM_ROUNDS; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     if (from[r] != to[r]) {
       long long pos = run + __popcll(fm[r] & lt);
       for (int w = 0; w < wid; ++w) pos += wc[r][w];
@@ -93,23 +100,23 @@ __global__ void __launch_bounds__(TPB)
       if (!agg_try(agg, to[r], pack2(ku, 1)))
         touch_label(to[r], pack2(ku, 1), dpack, tflag, tlist, stat);
     }
-    for (int w = 0; w < NW; ++w) run += wc[r][w];
+    for (int w = 0; w < AM_NW; ++w) run += wc[r][w];
   }
   // every label left in the table gets one global update; the labels that
   // this sweep touches first are appended to tlist with one counter update
   // for the block
-  constexpr int FR = AGG_SLOTS / TPB;
-  __shared__ int fcount[FR][NW];
+  constexpr int FR = AGG_SLOTS / AM_TPB;
+  __shared__ int fcount[FR][AM_NW];
   __shared__ long long fbase;
   __syncthreads();
   int fx[FR];
   uint64_t gm[FR];
 #pragma unroll
   for (int r = 0; r < FR; ++r) {
-    const int X = agg.keys[r * TPB + threadIdx.x];
+    const int X = agg.keys[r * AM_TPB + threadIdx.x];
     bool first = false;
     if (X != EMPTY_KEY) {
-      const long long v = agg.vals[r * TPB + threadIdx.x];
+      const long long v = agg.vals[r * AM_TPB + threadIdx.x];
       if (v != 0) {
         atomicAdd((unsigned long long*)&dpack[X], (unsigned long long)v);
         first = atomicExch(&tflag[X], 1) == 0;
@@ -123,7 +130,7 @@ __global__ void __launch_bounds__(TPB)
   if (threadIdx.x == 0) {
     int tot = 0;
     for (int r = 0; r < FR; ++r)
-      for (int w = 0; w < NW; ++w) tot += fcount[r][w];
+      for (int w = 0; w < AM_NW; ++w) tot += fcount[r][w];
     fbase = tot ? (long long)atomicAdd((unsigned long long*)&stat[ST_TOUCHED],
                                        (unsigned long long)tot)
                 : 0;
@@ -137,7 +144,7 @@ __global__ void __launch_bounds__(TPB)
       for (int w = 0; w < wid; ++w) q += fcount[r][w];
       tlist[q] = fx[r];
     }
-    for (int w = 0; w < NW; ++w) pos += fcount[r][w];
+    for (int w = 0; w < AM_NW; ++w) pos += fcount[r][w];
   }
 }
 
@@ -147,10 +154,44 @@ __device__ __forceinline__ int unpack_hi(long long d) {
   return int((d - (long long)unpack_lo(d)) >> 32);
 }
 
+// Change of the intra-community weight over entries j, j + STEP, ... of
+// mover u's row (old label cu, new label nu): DT_U entries' loads in flight
+// together, at clamped indexes.
+constexpr int DT_U = 4;
+template <int STEP>
+__device__ __forceinline__ long long row_delta(int32_t j, int32_t re, int u, int cu, int nu,
+                                               const int2* __restrict__ adj,
+                                               const int32_t* __restrict__ C,
+                                               const int32_t* __restrict__ Cn) {
+  long long s = 0;
+  for (; j < re; j += STEP * DT_U) {
+    int2 e[DT_U];
+    int cy[DT_U], ny[DT_U];
+#pragma unroll
+    for (int x = 0; x < DT_U; ++x) e[x] = adj[j + x * STEP < re ? j + x * STEP : re - 1];
+#pragma unroll
+    for (int x = 0; x < DT_U; ++x) {
+      cy[x] = C[e[x].x];
+      ny[x] = Cn[e[x].x];
+    }
+#pragma unroll
+    for (int x = 0; x < DT_U; ++x) {
+      const int d = int(nu == ny[x]) - int(cu == cy[x]);
+      if (j + x * STEP < re && e[x].x != u && d) s += (long long)e[x].y * d * (cy[x] != ny[x] ? 1 : 2);
+    }
+  }
+  return s;
+}
+
 // The two terms of the exact Delta N in one launch: blocks [0, nb_intra)
-// sum the change of the intra-community weight over the movers' rows (GS
-// lanes per mover: 16 on graphs of short rows, a wave otherwise), the other
-// blocks the change of sum a^2 over the touched labels.
+// sum the change of the intra-community weight over the movers' rows, the
+// other blocks the change of sum a^2 over the touched labels.  Bound by the
+// chain mover -> row -> neighbours -> labels: GS lanes take a mover, so a
+// wave has WAVE / GS chains under way, with DT_U entries a lane each.  16 lanes
+// where rows average at most 64 entries (a wave per mover and one entry a
+// lane took 63 us a sweep of a 300K/6M graph's static run, this 38); the whole
+// wave on the dense graphs of higher levels (452 vertices of 389 entries:
+// 4.5 us, by 16 lanes 11).
 template <int GS>
 __global__ void __launch_bounds__(TPB)
     k_delta_terms(const int32_t* __restrict__ movers, const int32_t* __restrict__ tlist,
@@ -162,38 +203,24 @@ __global__ void __launch_bounds__(TPB)
   if (int(blockIdx.x) < nb_intra) {
     const int64_t cnt = stat[ST_MOVES];
     const int lane = lane_id(), gl = lane % GS;
+    constexpr int MPW = WAVE / GS;  // movers of a wave
     const int64_t nwaves = int64_t(nb_intra) * NW;
-    // a wave takes WAVE / GS movers per round; a row longer than a wave is
-    // left to the whole wave afterwards, so hubs keep wave speed
-    for (int64_t wb = (int64_t(blockIdx.x) * NW + threadIdx.x / WAVE) * (WAVE / GS);
-         wb < cnt; wb += nwaves * (WAVE / GS)) {
+    for (int64_t wb = (int64_t(blockIdx.x) * NW + threadIdx.x / WAVE) * MPW; wb < cnt;
+         wb += nwaves * MPW) {
       const int64_t p = wb + lane / GS;
       const bool have = p < cnt;
       const int u = have ? movers[p] : 0;
       const int32_t rb = have ? off[u] : 0, re = have ? off[u + 1] : 0;
       const int cu = have ? C[u] : 0, nu = have ? Cn[u] : 0;
-      const bool wide = GS < WAVE && re - rb > WAVE;
-      if (!wide) {
-        for (int32_t j = rb + gl; j < re; j += GS) {
-          const int2 e = adj[j];
-          if (e.x == u) continue;
-          const int cy = C[e.x], ny = Cn[e.x];
-          const int d = int(nu == ny) - int(cu == cy);
-          if (d) s += (long long)e.y * d * (cy != ny ? 1 : 2);
-        }
-      }
+      // a row past four rounds is left to the whole wave afterwards
+      const bool wide = GS < WAVE && re - rb > 4 * GS * DT_U;
+      if (!wide) s += row_delta<GS>(rb + gl, re, u, cu, nu, adj, C, Cn);
       for (uint64_t wm = __ballot(wide && gl == 0); wm; wm &= wm - 1) {
         const int l = __ffsll((unsigned long long)wm) - 1;
-        const int wu = __builtin_amdgcn_readlane(u, l);
-        const int wcu = __builtin_amdgcn_readlane(cu, l), wnu = __builtin_amdgcn_readlane(nu, l);
-        const int32_t wre = __builtin_amdgcn_readlane(re, l);
-        for (int32_t j = __builtin_amdgcn_readlane(rb, l) + lane; j < wre; j += WAVE) {
-          const int2 e = adj[j];
-          if (e.x == wu) continue;
-          const int cy = C[e.x], ny = Cn[e.x];
-          const int d = int(wnu == ny) - int(wcu == cy);
-          if (d) s += (long long)e.y * d * (cy != ny ? 1 : 2);
-        }
+        s += row_delta<WAVE>(__builtin_amdgcn_readlane(rb, l) + lane,
+                             __builtin_amdgcn_readlane(re, l), __builtin_amdgcn_readlane(u, l),
+                             __builtin_amdgcn_readlane(cu, l), __builtin_amdgcn_readlane(nu, l),
+                             adj, C, Cn);
       }
     }
     block_add(s, &stat[ST_DI]);
@@ -285,18 +312,27 @@ void sweep_apply(const LevelView& g, const int32_t* active, int64_t n_active, in
                  unsigned* done, long long* host_stat, HostTag& tag, int32_t* ovf_count,
                  hipStream_t st) {
   const int64_t cnt = n_active > 0 ? n_active : 1;
-  k_apply_moves<<<int(ceil_div(cnt, AM_ROUNDS * TPB)), TPB, 0, st>>>(
-      active, n_active, C, Cn, g.k, dpack, tflag, tlist, movers, stat);
+  auto apply = [&](auto rounds) {
+    constexpr int R = decltype(rounds)::value;
+    k_apply_moves<R><<<int(ceil_div(cnt, R * AM_TPB)), AM_TPB, 0, st>>>(
+        active, n_active, C, Cn, g.k, dpack, tflag, tlist, movers, stat);
+  };
+  if (cnt <= 512 * AM_TPB)
+    apply(std::integral_constant<int, 1>());
+  else if (cnt <= 2 * 512 * AM_TPB)
+    apply(std::integral_constant<int, 2>());
+  else
+    apply(std::integral_constant<int, 8>());
   DC_LAUNCH_CHECK();
   // grids sized for the active list (the movers are known on the device
   // only); the loops stride, so most sweeps' few movers leave blocks idle
   const int nb_sq = grid_for(2 * cnt, 256);
-  if (g.nnz <= 16 * int64_t(g.n)) {  // short rows: four movers per wave
-    const int nb_intra = grid_for(ceil_div(cnt, 4) * WAVE, 4096);
+  if (g.nnz <= 64 * int64_t(g.n)) {
+    const int nb_intra = grid_for(ceil_div(cnt, WAVE / 16) * WAVE, 2048);
     k_delta_terms<16><<<nb_intra + nb_sq, TPB, 0, st>>>(movers, tlist, g.off, g.adj, C, Cn,
                                                         dpack, a, nb_intra, stat);
   } else {
-    const int nb_intra = grid_for(cnt * WAVE, 4096);
+    const int nb_intra = grid_for(cnt * WAVE, 2048);
     k_delta_terms<WAVE><<<nb_intra + nb_sq, TPB, 0, st>>>(movers, tlist, g.off, g.adj, C, Cn,
                                                           dpack, a, nb_intra, stat);
   }
