@@ -199,8 +199,11 @@ __global__ void __launch_bounds__(RES_TILE)
 // a REPLACE (new weight = their sum), a deletion alone a DELETE, insertions
 // alone an ADD to an existing pair or a NEW one.  Per tile: its changes'
 // insertion records (low half of npart) and NEW minus DELETE (high half).
-// Bound by the row search's scattered reads (a 1% batch of the 1M/20M graph,
-// 400K records: 47 us, of which 6 were the run sums' own launch).
+// Bound by the row search's scattered reads.  The records are sorted by source,
+// so the search stays in the source's row, next to its neighbours' searches:
+// taking the shorter of the pair's two rows instead saves steps but reads the
+// other end's offsets and row at random (10.5M records of an 8M-vertex graph
+// 625 us against 330, 400K of the 1M/20M graph 48 against 44).
 __global__ void __launch_bounds__(RES_TILE)
     k_resolve_runs(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals,
                    int64_t m, const int32_t* __restrict__ part, int raw, int64_t nt,
@@ -267,12 +270,7 @@ __global__ void __launch_bounds__(RES_TILE)
     int32_t wo = 0;
     bool exists = false;
     if (src < uint64_t(n) && dst < uint64_t(n)) {
-      // G is symmetric: search the shorter of the two rows (a hub's
-      // neighbours find their pair in their own short row)
-      const int32_t bs = off[src], es = off[src + 1], bd = off[dst], ed = off[dst + 1];
-      const bool own = es - bs <= ed - bd;
-      const int32_t b = own ? bs : bd, e = own ? es : ed;
-      const int32_t x = own ? int32_t(dst) : int32_t(src);
+      const int32_t b = off[src], e = off[src + 1], x = int32_t(dst);
       const int32_t p = find_in_row(adj, b, e, x);
       exists = p < e && adj[p].x == x;
       wo = exists ? adj[p].y : 0;
