@@ -753,7 +753,7 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
     c->best_j.ensure(size_t(n + 1) * 4);
     c->best_g.ensure(size_t(n + 1) * 8);
     c->ds_items.ensure(size_t(item_cap) * 8);
-    const DsScratch dsx{c->sink_g.as<long long>(), c->best_j.as<int32_t>(),
+    DsScratch dsx{c->sink_g.as<long long>(), c->best_j.as<int32_t>(),
                         c->best_g.as<long long>(), c->ds_items.as<int2>(), stat + ST_MARK,
                         item_cap};
     if (!direct) {
@@ -807,6 +807,8 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
           c->pre.ensure(size_t(n) * 4);
           pre = c->pre.as<int32_t>();
         }
+        dsx.list = c->ulist.as<int32_t>();
+        dsx.count = n_u;
         ds_both(g0, c->C.as<int32_t>(), c->a0.as<int32_t>(), c->sz0.as<int32_t>(),
                 c->opt.singleton_guard, c->two_m, ins_keys, n_ins, c->seg_beg.as<int32_t>(),
                 c->seg_end.as<int32_t>(), uflag, b, R, cflag, accflag, pre, dsx, stat, st);
@@ -827,6 +829,8 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
         make_bins(c->src_list.as<int32_t>(), n_src, g0.off, b, c->bins, st);
         for (int q = 0; q < NBINS; ++q) S.screen_volume += b.vol[q];
         S.screen_vertices = n_src;
+        dsx.list = c->src_list.as<int32_t>();
+        dsx.count = n_src;
         ds_additions(g0, c->C.as<int32_t>(), c->a0.as<int32_t>(), c->two_m, ins_keys, n_ins,
                      c->seg_beg.as<int32_t>(), c->seg_end.as<int32_t>(), b, R, cflag, accflag,
                      dsx, stat, st);

@@ -195,7 +195,8 @@ void sweep_apply(const LevelView& g, const int32_t* active, int64_t n_active, in
 // Scratch of one Alg. 2 pass: per directed insertion record its gain
 // (sink_g, n_ins entries), per vertex the best sink and gain1 (best_j,
 // best_g, n entries), the accepted rows' chunks (items, item_cap entries from
-// ds_item_cap) and their count (a zeroed device counter).
+// ds_item_cap) and their count (a zeroed device counter).  list, count: the
+// evaluated vertices, every insertion source among them.
 struct DsScratch {
   long long* sink_g;
   int32_t* best_j;
@@ -203,6 +204,8 @@ struct DsScratch {
   int2* items;
   long long* item_count;
   int64_t item_cap;
+  const int32_t* list = nullptr;
+  int64_t count = 0;
 };
 int64_t ds_item_cap(int64_t n_sources, int64_t nnz);
 

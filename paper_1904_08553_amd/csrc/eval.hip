@@ -1305,65 +1305,88 @@ inline int wave_grid(int64_t items) {
   return int(g < 1 ? 1 : g);
 }
 
-// Alg. 2 acceptance, one thread per directed insertion record j -> i: the
-// record decides source i when j is i's best sink j*; then gain1 (stored
-// with i) is compared with gain2 = the gain stored at this record.  An
-// accepted source sets R[i], R[j*], the flag of C(j*) and (cascade) its
-// accepted flag, and lists its row in chunks of MARK_CHUNK entries for
-// k_mark_rows (R gets Gamma_t(i)); chunk positions come from a block scan
-// and one atomic per block.
+// Alg. 2 acceptance, one thread per source i whose best sink j* has a
+// positive gain: gain1 (stored with i) is compared with gain2, the gain
+// stored at the record j* -> i, found by bisection among j*'s sinks (a thread
+// per record instead reads a best sink for each).  An accepted source sets
+// R[i], R[j*], the flag of C(j*) and (cascade) its accepted flag, and lists
+// its row in chunks of MARK_CHUNK entries for k_mark_rows (R gets
+// Gamma_t(i)); chunk positions come from a block scan and one atomic per
+// block.  Those reservations queue at one counter (about 30 ns each), so a
+// block takes ITEMS * 1024 sources: 3.1M sources with 8.9M records 273 us by
+// records and blocks of 256, 180 by sources, 71 in blocks of 4,096; 125K
+// sources 13.6, 16.1 and 7.3 in blocks of 1,024 (below DR_LARGE sources,
+// where larger blocks leave CUs idle).
 constexpr int MARK_CHUNK = 256;
+constexpr int DR_TPB = 1024;
+constexpr int64_t DR_LARGE = int64_t(1) << 19;
 
-__global__ void __launch_bounds__(TPB)
-    k_ds_resolve(EvalArgs A, int2* __restrict__ items, long long* __restrict__ item_count) {
-  __shared__ int wsum[NW];
+template <int ITEMS>
+__global__ void __launch_bounds__(DR_TPB)
+    k_ds_resolve(EvalArgs A, const int32_t* __restrict__ list, int64_t cnt,
+                 int2* __restrict__ items, long long* __restrict__ item_count) {
+  __shared__ int wsum[DR_TPB / WAVE];
   __shared__ long long bbase;
   const int lane = lane_id(), wid = threadIdx.x / WAVE;
   long long accepted = 0, accvol = 0;
-  for (int64_t base = int64_t(blockIdx.x) * TPB; base < A.n_ins;
-       base += int64_t(gridDim.x) * TPB) {  // block-uniform
-    const int64_t q = base + threadIdx.x;
-    int32_t rb = 0, re = 0;
-    int nit = 0;
-    if (q < A.n_ins) {
-      const uint64_t key = A.ins_keys[q];
-      const int j = int(key_row(key, A.kb)), i = int(key_col(key, A.kb));
-      if (A.best_j[i] == j && A.best_g[i] >= A.sink_g[q]) {
-        A.R[i] = 1;
-        A.R[j] = 1;
-        A.cflag[A.C[j]] = 1;
-        if (A.accflag) A.accflag[i] = 1;
-        accepted += 1;
-        rb = A.off[i];
-        re = A.off[i + 1];
-        accvol += re - rb;
-        nit = int(ceil_div(re - rb, MARK_CHUNK));
-      }
-    }
-    // exclusive block scan of the chunk counts
-    int incl = nit;
+  int32_t rb[ITEMS], re[ITEMS];
+  int src[ITEMS], best[ITEMS];
+  int nit = 0;
 #pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-      const int y = __shfl_up(incl, o, WAVE);
-      if (lane >= o) incl += y;
-    }
-    if (lane == WAVE - 1) wsum[wid] = incl;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int tot = 0;
-      for (int w = 0; w < NW; ++w) tot += wsum[w];
-      bbase = tot ? (long long)atomicAdd((unsigned long long*)item_count, (unsigned long long)tot)
-                  : 0;
-    }
-    __syncthreads();
-    long long pos = bbase + incl - nit;
-    for (int w = 0; w < wid; ++w) pos += wsum[w];
-    for (int r = 0; r < nit; ++r) {
-      const int32_t cb = rb + r * MARK_CHUNK;
-      items[pos + r] = make_int2(cb, re - cb < MARK_CHUNK ? re : cb + MARK_CHUNK);
-    }
-    __syncthreads();  // wsum and bbase are rewritten by the next tile
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t p = int64_t(blockIdx.x) * (ITEMS * DR_TPB) + int64_t(r) * DR_TPB + threadIdx.x;
+    src[r] = list[p < cnt ? p : cnt - 1];
+    const bool on = p < cnt && (!A.uflag || (A.uflag[src[r]] & 1));
+    best[r] = on ? A.best_j[src[r]] : -1;
   }
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int i = src[r], j = best[r];
+    rb[r] = re[r] = 0;
+    if (j < 0) continue;
+    // j is a source with i among its sinks, so the record is there
+    const uint64_t key = pair_key(uint32_t(j), uint32_t(i), A.kb);
+    int32_t q = A.seg_beg[j], e = A.seg_end[j] - 1;
+    while (q < e) {
+      const int32_t mid = (q + e) >> 1;
+      if (A.ins_keys[mid] < key)
+        q = mid + 1;
+      else
+        e = mid;
+    }
+    if (A.best_g[i] < A.sink_g[q]) continue;
+    A.R[i] = 1;
+    A.R[j] = 1;
+    A.cflag[A.C[j]] = 1;
+    if (A.accflag) A.accflag[i] = 1;
+    accepted += 1;
+    rb[r] = A.off[i];
+    re[r] = A.off[i + 1];
+    accvol += re[r] - rb[r];
+    nit += int(ceil_div(re[r] - rb[r], MARK_CHUNK));
+  }
+  // exclusive block scan of the chunk counts
+  int incl = nit;
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const int y = __shfl_up(incl, o, WAVE);
+    if (lane >= o) incl += y;
+  }
+  if (lane == WAVE - 1) wsum[wid] = incl;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int tot = 0;
+    for (int w = 0; w < DR_TPB / WAVE; ++w) tot += wsum[w];
+    bbase = tot ? (long long)atomicAdd((unsigned long long*)item_count, (unsigned long long)tot)
+                : 0;
+  }
+  __syncthreads();
+  long long pos = bbase + incl - nit;
+  for (int w = 0; w < wid; ++w) pos += wsum[w];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r)
+    for (int32_t cb = rb[r]; cb < re[r]; cb += MARK_CHUNK)
+      items[pos++] = make_int2(cb, re[r] - cb < MARK_CHUNK ? re[r] : cb + MARK_CHUNK);
   block_add(accepted, &A.stat[ST_DS_ACC]);
   block_add(accvol, &A.stat[ST_ACCVOL]);
 }
@@ -1586,13 +1609,17 @@ void sweep_eval(const LevelView& g, const int32_t* C, int32_t* Cn, const int32_t
 // Alg. 2 acceptance after an evaluation pass (every source's best sink and
 // every record's gain stored): resolve, then mark the accepted rows.
 void ds_resolve(const EvalArgs& A, const DsScratch& X, hipStream_t st) {
-  if (A.n_ins <= 0) return;
-  // (each block adds its counts with one atomic per counter: few blocks)
-  k_ds_resolve<<<grid_for(A.n_ins, 512), TPB, 0, st>>>(A, X.items, X.item_count);
+  if (A.n_ins <= 0 || X.count <= 0) return;
+  if (X.count < DR_LARGE)
+    k_ds_resolve<1><<<int(ceil_div(X.count, DR_TPB)), DR_TPB, 0, st>>>(A, X.list, X.count, X.items,
+                                                                       X.item_count);
+  else
+    k_ds_resolve<4><<<int(ceil_div(X.count, 4 * DR_TPB)), DR_TPB, 0, st>>>(A, X.list, X.count,
+                                                                           X.items, X.item_count);
   DC_LAUNCH_CHECK();
   // chunks: at most one per source plus one per MARK_CHUNK entries of G_t
   const int64_t cap = X.item_cap;
-  k_mark_rows<<<wave_grid(cap < 65536 ? cap : 65536), TPB, 0, st>>>(X.items, X.item_count,
+  k_mark_rows<<<wave_grid(cap < 16384 ? cap : 16384), TPB, 0, st>>>(X.items, X.item_count,
                                                                     A.adj, A.R);
   DC_LAUNCH_CHECK();
 }
