@@ -65,4 +65,44 @@ __device__ T tile_offset(const T* __restrict__ part, int raw, int64_t nt, T* lds
   return block_total<T, NT>(acc, lds);
 }
 
+// Places in a list for the M parts of a block (cnt, in LDS, written by any
+// thread before the call): each count becomes its part's first place, the
+// block's places taken with one atomic on *counter by its first wave.  Returns
+// the block's total, in every thread.
+template <int M, class T>
+__device__ int reserve_places(int* cnt, T* counter) {
+  __shared__ int total;
+  __syncthreads();
+  if (threadIdx.x < WAVE) {
+    constexpr int P = (M + WAVE - 1) / WAVE;
+    const int lane = lane_id();
+    int v[P], s = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      v[i] = lane * P + i < M ? cnt[lane * P + i] : 0;
+      s += v[i];
+    }
+    int x = s;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const int y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
+    }
+    const int t = __builtin_amdgcn_readlane(x, WAVE - 1);
+    int base = 0;
+    if (lane == 0) {
+      total = t;
+      if (t) base = int(atomicAdd(counter, T(t)));
+    }
+    int run = __builtin_amdgcn_readfirstlane(base) + x - s;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      if (lane * P + i < M) cnt[lane * P + i] = run;
+      run += v[i];
+    }
+  }
+  __syncthreads();
+  return total;
+}
+
 }  // namespace dc

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "dc_louvain.h"
+#include "dc_scan.h"
 
 namespace dc {
 
@@ -50,8 +51,6 @@ __global__ void __launch_bounds__(AM_TPB)
                   int32_t* tlist, int32_t* movers, long long* stat) {
   __shared__ AggLds agg;
   __shared__ int wc[ROUNDS][AM_NW];
-  __shared__ long long bbase;
-  __shared__ int btotal;
   const int wid = threadIdx.x / WAVE, lane = lane_id();
   const uint64_t lt = (uint64_t(1) << lane) - 1;
   const int64_t v0 = int64_t(blockIdx.x) * (ROUNDS * AM_TPB) + threadIdx.x;
@@ -75,39 +74,25 @@ __global__ void __launch_bounds__(AM_TPB)
   // the block's label changes are summed in LDS, so a large community gets
   // one update per block (see agg_try)
   agg_init(agg);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int tot = 0;
-    for (int r = 0; r < ROUNDS; ++r)
-      for (int w = 0; w < AM_NW; ++w) tot += wc[r][w];
-    btotal = tot;
-    bbase = tot ? (long long)atomicAdd((unsigned long long*)&stat[ST_MOVES],
-                                       (unsigned long long)tot)
-                : 0;
-  }
-  __syncthreads();
-  if (btotal == 0) return;  // uniform: nothing moved in this block's tiles
-  long long run = bbase;
+  auto* const counters = reinterpret_cast<unsigned long long*>(stat);
+  if (reserve_places<ROUNDS * AM_NW>(&wc[0][0], counters + ST_MOVES) == 0)
+    return;  // uniform: nothing moved in this block's tiles
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     if (from[r] != to[r]) {
-      long long pos = run + __popcll(fm[r] & lt);
-      for (int w = 0; w < wid; ++w) pos += wc[r][w];
-      movers[pos] = u[r];
+      movers[wc[r][wid] + __popcll(fm[r] & lt)] = u[r];
       const int ku = k[u[r]];
       if (!agg_try(agg, from[r], pack2(-ku, -1)))
         touch_label(from[r], pack2(-ku, -1), dpack, tflag, tlist, stat);
       if (!agg_try(agg, to[r], pack2(ku, 1)))
         touch_label(to[r], pack2(ku, 1), dpack, tflag, tlist, stat);
     }
-    for (int w = 0; w < AM_NW; ++w) run += wc[r][w];
   }
   // every label left in the table gets one global update; the labels that
   // this sweep touches first are appended to tlist with one counter update
   // for the block
   constexpr int FR = AGG_SLOTS / AM_TPB;
   __shared__ int fcount[FR][AM_NW];
-  __shared__ long long fbase;
   __syncthreads();
   int fx[FR];
   uint64_t gm[FR];
@@ -126,26 +111,10 @@ __global__ void __launch_bounds__(AM_TPB)
     gm[r] = __ballot(first);
     if (lane == 0) fcount[r][wid] = __popcll(gm[r]);
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int tot = 0;
-    for (int r = 0; r < FR; ++r)
-      for (int w = 0; w < AM_NW; ++w) tot += fcount[r][w];
-    fbase = tot ? (long long)atomicAdd((unsigned long long*)&stat[ST_TOUCHED],
-                                       (unsigned long long)tot)
-                : 0;
-  }
-  __syncthreads();
-  long long pos = fbase;
+  (void)reserve_places<FR * AM_NW>(&fcount[0][0], counters + ST_TOUCHED);
 #pragma unroll
-  for (int r = 0; r < FR; ++r) {
-    if (fx[r] >= 0) {
-      long long q = pos + __popcll(gm[r] & lt);
-      for (int w = 0; w < wid; ++w) q += fcount[r][w];
-      tlist[q] = fx[r];
-    }
-    for (int w = 0; w < AM_NW; ++w) pos += fcount[r][w];
-  }
+  for (int r = 0; r < FR; ++r)
+    if (fx[r] >= 0) tlist[fcount[r][wid] + __popcll(gm[r] & lt)] = fx[r];
 }
 
 

@@ -3,6 +3,7 @@
 // intra-community deletions, and R_t = (marked vertices) union (members of
 // flagged communities C_{t-1}(j*)), compacted in ascending vertex order.
 #include "dc_louvain.h"
+#include "dc_scan.h"
 
 namespace dc {
 
@@ -79,18 +80,20 @@ __global__ void k_mark_neighbourhoods(const int32_t* __restrict__ list,
 }
 
 // R[v] |= cflag[C[v]] (cflag may be null), and the vertices of R appended
-// to list: a block
-// takes RL_ROUNDS tiles of TPB vertices and reserves its places with one
-// atomic on *count (ascending within the block, blocks in any order).
-constexpr int RL_ROUNDS = 8;
-__global__ void __launch_bounds__(TPB)
+// to list: a block takes ROUNDS tiles of RL_TPB vertices and reserves its
+// places with one atomic on *count (ascending within the block, blocks in any
+// order).  The reservations queue at the counter (about 25 ns each): blocks
+// of 2,048 vertices took 11.7 us for 1M and 55 for 8M, these 6.9 and 25.
+constexpr int RL_TPB = 1024;
+constexpr int RL_NW = RL_TPB / WAVE;
+template <int RL_ROUNDS>
+__global__ void __launch_bounds__(RL_TPB)
     k_materialize_R(uint8_t* R, const uint8_t* __restrict__ cflag,
                     const int32_t* __restrict__ C, int32_t n, int32_t* list, int32_t* count) {
-  __shared__ int wc[RL_ROUNDS][TPB / WAVE];
-  __shared__ int base;
+  __shared__ int wc[RL_ROUNDS][RL_NW];
   const int lane = lane_id(), wid = threadIdx.x / WAVE;
   const uint64_t lt = (uint64_t(1) << lane) - 1;
-  const int64_t v0 = int64_t(blockIdx.x) * (RL_ROUNDS * TPB) + threadIdx.x;
+  const int64_t v0 = int64_t(blockIdx.x) * (RL_ROUNDS * RL_TPB) + threadIdx.x;
   uint64_t fm[RL_ROUNDS];
   bool f[RL_ROUNDS];
   // the rounds' flags (and labels, then community flags) are loaded round
@@ -99,49 +102,35 @@ __global__ void __launch_bounds__(TPB)
   uint8_t x[RL_ROUNDS];
 #pragma unroll
   for (int r = 0; r < RL_ROUNDS; ++r) {
-    const int64_t v = v0 + int64_t(r) * TPB;
+    const int64_t v = v0 + int64_t(r) * RL_TPB;
     x[r] = R[v < n ? v : n - 1];
   }
   if (cflag) {
     int32_t c[RL_ROUNDS];
 #pragma unroll
     for (int r = 0; r < RL_ROUNDS; ++r) {
-      const int64_t v = v0 + int64_t(r) * TPB;
+      const int64_t v = v0 + int64_t(r) * RL_TPB;
       c[r] = C[v < n ? v : n - 1];
     }
 #pragma unroll
     for (int r = 0; r < RL_ROUNDS; ++r) x[r] |= cflag[c[r]];
 #pragma unroll
     for (int r = 0; r < RL_ROUNDS; ++r) {
-      const int64_t v = v0 + int64_t(r) * TPB;
+      const int64_t v = v0 + int64_t(r) * RL_TPB;
       if (v < n) R[v] = x[r];
     }
   }
 #pragma unroll
   for (int r = 0; r < RL_ROUNDS; ++r) {
-    const int64_t v = v0 + int64_t(r) * TPB;
+    const int64_t v = v0 + int64_t(r) * RL_TPB;
     f[r] = v < n && x[r] != 0;
     fm[r] = __ballot(f[r]);
     if (lane == 0) wc[r][wid] = __popcll(fm[r]);
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int tot = 0;
-    for (int r = 0; r < RL_ROUNDS; ++r)
-      for (int w = 0; w < TPB / WAVE; ++w) tot += wc[r][w];
-    base = tot ? atomicAdd(count, tot) : 0;
-  }
-  __syncthreads();
-  int pos = base;
+  (void)reserve_places<RL_ROUNDS * RL_NW>(&wc[0][0], count);
 #pragma unroll
-  for (int r = 0; r < RL_ROUNDS; ++r) {
-    if (f[r]) {
-      int q = pos + __popcll(fm[r] & lt);
-      for (int w = 0; w < wid; ++w) q += wc[r][w];
-      list[q] = int32_t(v0 + int64_t(r) * TPB);
-    }
-    for (int w = 0; w < TPB / WAVE; ++w) pos += wc[r][w];
-  }
+  for (int r = 0; r < RL_ROUNDS; ++r)
+    if (f[r]) list[wc[r][wid] + __popcll(fm[r] & lt)] = int32_t(v0 + int64_t(r) * RL_TPB);
 }
 
 __global__ void k_apply_pre(const int32_t* __restrict__ list, int64_t cnt,
@@ -269,8 +258,12 @@ void mark_neighbourhoods(const int32_t* list, int64_t cnt, const int32_t* off, c
 void materialize_R(uint8_t* R, const uint8_t* cflag, const int32_t* C, int32_t n,
                    int32_t* list, int32_t* count, hipStream_t st) {
   if (n <= 0) return;
-  k_materialize_R<<<int(ceil_div(n, RL_ROUNDS * TPB)), TPB, 0, st>>>(R, cflag, C, n, list,
-                                                                      count);
+  if (n <= 256 * RL_TPB)
+    k_materialize_R<1><<<int(ceil_div(n, RL_TPB)), RL_TPB, 0, st>>>(R, cflag, C, n, list, count);
+  else if (n <= 512 * RL_TPB)
+    k_materialize_R<2><<<int(ceil_div(n, 2 * RL_TPB)), RL_TPB, 0, st>>>(R, cflag, C, n, list, count);
+  else
+    k_materialize_R<8><<<int(ceil_div(n, 8 * RL_TPB)), RL_TPB, 0, st>>>(R, cflag, C, n, list, count);
   DC_LAUNCH_CHECK();
 }
 
