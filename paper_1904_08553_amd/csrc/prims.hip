@@ -458,6 +458,108 @@ __global__ void __launch_bounds__(RS_THREADS)
   }
 }
 
+// A list of at most RS_SMALL keys sorted by one block in one launch: the keys
+// and values stay in registers, ranked as in the scatter (16-bit counts), and
+// change places through LDS after every digit.  Such a list is bound by
+// launches: three a digit took 51 us of kernels for 2,000 keys of 40 bits
+// without the gaps between twelve launches, this 19 in one.  One block's
+// ranking is bound by its vector instructions: 8,002 keys of 30 bits took
+// 39.5 us either way, so the line is at 4,096.
+constexpr int RS_SMALL_BITS = 8;
+constexpr int64_t RS_SMALL = 4 * RS_THREADS;
+template <int ROUNDS>
+__global__ void __launch_bounds__(RS_THREADS)
+    k_radix_small(uint64_t* keys, uint32_t* vals, int n, int passes, int dbits) {
+  constexpr int TILE = RS_THREADS * ROUNDS, BINS = 1 << RS_SMALL_BITS;
+  __shared__ uint64_t kbuf[TILE];
+  __shared__ uint32_t vbuf[TILE];
+  __shared__ uint16_t wcnt[RS_WAVES][BINS];
+  __shared__ int32_t lds[RS_WAVES];
+  const int t = threadIdx.x, lane = lane_id(), wid = t / WAVE;
+  const int first_key = wid * (ROUNDS * WAVE) + lane;  // of the thread, then every WAVE-th
+  const uint64_t lt = (uint64_t(1) << lane) - 1;
+  const uint64_t mask = (uint64_t(1) << dbits) - 1;
+  uint64_t kr[ROUNDS];
+  uint32_t vr[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {  // clamped (n >= 2): all in flight together
+    const int i = first_key + r * WAVE;
+    kr[r] = keys[i < n ? i : n - 1];
+    vr[r] = vals[i < n ? i : n - 1];
+  }
+  for (int p = 0; p < passes; ++p) {
+    const int shift = p * dbits;
+    for (int i = t; i < RS_WAVES * BINS; i += RS_THREADS) (&wcnt[0][0])[i] = 0;
+    __syncthreads();
+    uint16_t* own = wcnt[wid];
+    int rk[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const bool valid = first_key + r * WAVE < n;
+      const int d = int((kr[r] >> shift) & mask);
+      uint64_t m = __ballot(valid);
+      for (int b = 0; b < dbits; ++b) {
+        const bool bit = (d >> b) & 1;
+        const uint64_t bb = __ballot(valid && bit);
+        m &= bit ? bb : ~bb;
+      }
+      const int first = valid ? __ffsll((unsigned long long)m) - 1 : lane;
+      int old = 0;
+      if (valid && first == lane) {  // the wave's own row: one lane per digit
+        old = own[d];
+        own[d] = uint16_t(old + __popcll(m));
+      }
+      wave_sync();
+      old = __shfl(old, first);
+      rk[r] = old + __popcll(m & lt);
+    }
+    __syncthreads();
+    {
+      // digit t: its keys per wave, then before it (threads past the digits
+      // take part in the scan with nothing)
+      int c[RS_WAVES], s = 0;
+#pragma unroll
+      for (int w = 0; w < RS_WAVES; ++w) {
+        c[w] = t < BINS ? wcnt[w][t] : 0;
+        s += c[w];
+      }
+      int32_t total;
+      int run = block_excl_scan<int32_t, RS_THREADS>(s, lds, &total);
+#pragma unroll
+      for (int w = 0; w < RS_WAVES; ++w) {
+        if (t < BINS) wcnt[w][t] = uint16_t(run);
+        run += c[w];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      if (first_key + r * WAVE < n) {
+        const int pos = own[int((kr[r] >> shift) & mask)] + rk[r];
+        kbuf[pos] = kr[r];
+        vbuf[pos] = vr[r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int i = first_key + r * WAVE;
+      if (i < n) {
+        kr[r] = kbuf[i];
+        vr[r] = vbuf[i];
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int i = first_key + r * WAVE;
+    if (i < n) {
+      keys[i] = kr[r];
+      vals[i] = vr[r];
+    }
+  }
+}
+
 template <class T>
 __global__ void k_fill(T* p, T v, int64_t n) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -532,6 +634,16 @@ void radix_sort_pairs(uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1,
 bool radix_sort_pairs_swap(uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1,
                            int64_t n, int bits, hipStream_t st) {
   if (n <= 1 || bits <= 0) return false;
+  if (n <= RS_SMALL) {
+    const int passes = (bits + RS_SMALL_BITS - 1) / RS_SMALL_BITS;
+    const int dbits = (bits + passes - 1) / passes;
+    if (n <= 2 * RS_THREADS)
+      k_radix_small<2><<<1, RS_THREADS, 0, st>>>(k0, v0, int(n), passes, dbits);
+    else
+      k_radix_small<4><<<1, RS_THREADS, 0, st>>>(k0, v0, int(n), passes, dbits);
+    DC_LAUNCH_CHECK();
+    return false;
+  }
   // fewest passes with digits of at most RS_MAX_DIGIT bits, equal widths
   const int passes = (bits + RS_MAX_DIGIT - 1) / RS_MAX_DIGIT;
   const int dbits = (bits + passes - 1) / passes;

@@ -86,7 +86,7 @@ def test_runs_of_one_pair(copies):
             compare(o, g, f"copies={copies} {mode} step {t}")
 
 
-@pytest.mark.parametrize("records", [2, (1 << 20) - 2, 1 << 20, (1 << 20) + 2, 8192 * 131 + 2])
+@pytest.mark.parametrize("records", [2, 2046, 2048, 2050, 4096, 4098, (1 << 20) - 2, 1 << 20, (1 << 20) + 2, 8192 * 131 + 2])
 def test_initial_csr_at_sort_sizes(records):
     """The initial CSR (both directed records of every edge, sorted, equal
     pairs summed) against numpy at the sizes where the radix sort changes its
