@@ -180,7 +180,6 @@ long long run_sweeps(dc_ctx* c, const LevelView& g, const int32_t* act, int64_t 
   Bins bins = pre_done ? first_part(all_bins) : all_bins;
   for (int s = 0; s < c->opt.max_sweeps; ++s) {
     if (s == 1) bins = all_bins;
-    if (s == 0) sweep_reset(c->stat.as<long long>(), st);  // later: cleared by sweep_apply
     const bool timed = record && c->opt.timing && bins.n[0] + bins.n[1] + bins.n[2] > 0;
     sweep_eval(g, c->Cl.as<int32_t>(), c->Cn.as<int32_t>(), c->al.as<int32_t>(),
                c->szl.as<int32_t>(), c->two_m, c->opt.singleton_guard, bins,
@@ -205,14 +204,24 @@ long long run_sweeps(dc_ctx* c, const LevelView& g, const int32_t* act, int64_t 
 }
 
 // Alg. 1 in two parts around the level-0 sweeps, so that several graphs can
-// run their level-0 sweeps together: levels_begin bins R_t for level 0
-// (null = every vertex) over the level-0 partition (Cl, al, szl) the caller
-// prepared; levels_finish coarsens, runs the upper levels and writes the
-// canonical labels, the totals and N.
+// run their level-0 sweeps together: levels_begin loads the level-0 partition
+// from (C, a0, sz0) and bins the active vertices (R_t as the screening left
+// it, the list `active`, or every vertex); levels_finish coarsens, runs the
+// upper levels and writes the canonical labels, the totals and N.
+//
+// Screening evaluated its vertices on the state the first level-0 sweep
+// reads (labels C_{t-1}, totals and sizes on G_t): their decisions go into Cn
+// and the first sweep evaluates only the rest of R_t (L.pre_done).
 
-void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& L,
-                  const uint8_t* skip) {
-  c->pre_count = 0;  // the screening's first-sweep labels serve run_levels only
+void load_level0_partition(dc_ctx* c);
+
+void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& L) {
+  const bool open = c->R_open;
+  const int64_t npre = open || active ? c->pre_count : 0;
+  const uint8_t* skip = npre > 0 ? c->pre_skip : nullptr;
+  c->R_open = false;
+  c->pre_count = 0;
+  L.pre_done = npre > 0;
   const long long two_m = c->two_m;
   L.T = c->opt.tau_den > 0 ? (two_m * two_m) / c->opt.tau_den : 0;
   L.g = LevelView{c->n, c->nnz, c->off[c->cur].as<int32_t>(), c->adj[c->cur].as<int2>(),
@@ -220,19 +229,37 @@ void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& 
   L.act = active;
   L.nact = n_active;
   c->trace.clear();
-  if (active && c->R_dcount) {
-    // R_t from the screening pass: binned by its device length, which comes
-    // back with the binning's wait together with the screening counters
-    make_bins(active, n_active, L.g.off, L.bins, c->bins, c->st, skip, c->R_dcount,
-              c->stat.as<long long>(), c->hstat_dev, ST_COUNT);
-    check_stat_errors(c->hstat);
-    c->R_dcount = nullptr;
-    c->R_count = L.bins.total;
-    L.nact = L.bins.total;
-    screening_counts(c);
+  if (active) {
+    load_level0_partition(c);
+    if (skip)
+      apply_pre(c->pre_list, npre, c->R.as<uint8_t>(), c->pre.as<int32_t>(), c->Cn.as<int32_t>(),
+                c->st);
+    make_bins(active, n_active, L.g.off, L.bins, c->bins, c->st, skip);
     return;
   }
-  make_bins(active, n_active, L.g.off, L.bins, c->bins, c->st, skip);
+  const Level0Start A{c->C.as<int32_t>(),
+                      c->a0.as<int32_t>(),
+                      c->sz0.as<int32_t>(),
+                      c->Cl.as<int32_t>(),
+                      c->Cn.as<int32_t>(),
+                      c->al.as<int32_t>(),
+                      c->szl.as<int32_t>(),
+                      open ? c->R.as<uint8_t>() : nullptr,
+                      open ? c->R_cflag : nullptr,
+                      skip,
+                      c->pre.as<int32_t>()};
+  if (!open) {
+    level0_start(A, c->n, L.g.off, L.bins, c->bins, c->st);
+    return;
+  }
+  // |R_t| and the screening counters come back with the binning's sizes
+  level0_start(A, c->n, L.g.off, L.bins, c->bins, c->st, c->stat.as<long long>(), c->hstat_dev,
+               ST_COUNT);
+  check_stat_errors(c->hstat);
+  c->R_count = L.bins.total;
+  L.act = L.bins.all;
+  L.nact = L.bins.total;
+  screening_counts(c);
 }
 
 void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
@@ -336,15 +363,8 @@ void finish_stats(dc_ctx* c, const LevelView& g) {
 //      communities) and runs local moving over every vertex.
 void run_levels_slm(dc_ctx* c, const int32_t* active, int64_t n_active) {
   hipStream_t st = c->st;
-  const int64_t npre = active ? c->pre_count : 0;
-  const uint8_t* skip = nullptr;
-  if (npre > 0) {
-    apply_pre(c->pre_list, npre, c->R.as<uint8_t>(), c->pre.as<int32_t>(), c->Cn.as<int32_t>(),
-              st);
-    skip = c->pre_skip;
-  }
   LevelRun L;
-  levels_begin(c, active, n_active, L, skip);
+  levels_begin(c, active, n_active, L);
   const long long T = L.T;
   LevelView g = L.g;
   int32_t* Cl = c->Cl.as<int32_t>();
@@ -356,7 +376,7 @@ void run_levels_slm(dc_ctx* c, const int32_t* active, int64_t n_active) {
   for (DBuf* b : {&c->sub_cnt, &c->sub_off, &c->par, &c->first}) b->ensure(n4);
   int32_t* par = c->par.as<int32_t>();
   int level = 0;
-  (void)run_sweeps(c, g, L.act, L.nact, L.bins, 0, T, true, npre > 0);
+  (void)run_sweeps(c, g, L.act, L.nact, L.bins, 0, T, true, L.pre_done);
   mark_phase(c, 3);
   while (true) {
     // 2. communities after the local moving
@@ -430,23 +450,11 @@ void run_levels(dc_ctx* c, const int32_t* active, int64_t n_active) {
     return;
   }
   LevelRun L;
-  // Screening evaluated its vertices on the state the first level-0 sweep
-  // reads (labels C_{t-1}, totals and sizes on G_t): their decisions go
-  // into Cn and the first sweep evaluates only the rest of R_t.
-  const int64_t npre = active ? c->pre_count : 0;
-  const uint8_t* skip = nullptr;
-  if (npre > 0) {
-    apply_pre(c->pre_list, npre, c->R.as<uint8_t>(), c->pre.as<int32_t>(), c->Cn.as<int32_t>(),
-              c->st);
-    skip = c->pre_skip;
-  }
-  levels_begin(c, active, n_active, L, skip);
-  const long long gain0 = run_sweeps(c, L.g, L.act, L.nact, L.bins, 0, L.T, true, npre > 0);
+  levels_begin(c, active, n_active, L);
+  const long long gain0 = run_sweeps(c, L.g, L.act, L.nact, L.bins, 0, L.T, true, L.pre_done);
   mark_phase(c, 3);
   levels_finish(c, L, gain0);
 }
-
-void load_level0_partition(dc_ctx* c);
 
 // Move labels of the touched vertices: level 0 rerun from C_{t-1} with every
 // vertex active (full re-evaluation), nothing recorded, state untouched.
@@ -588,7 +596,6 @@ dc_status do_init(dc_ctx* c, const dc_edges* g1) {
   c->nnz = U;
   c->two_m = 2 * wsum;
   start_from_singletons(c);
-  load_level0_partition(c);
   c->stats = dc_step_stats{};
   c->stats.R_size = c->n;
   c->inc_ready = false;
@@ -601,13 +608,13 @@ dc_status do_init(dc_ctx* c, const dc_edges* g1) {
   return DC_OK;
 }
 
-// First part of a time step: validate, merge, choose R_t; on success the
-// level-0 partition is loaded and *act / *nact give the level-0 active set
-// (null = every vertex).
+// First part of a time step: validate, merge, choose R_t; on success *act /
+// *nact give the level-0 active set (null: R_t as c->R holds it when
+// c->R_open, else every vertex).
 dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const int32_t** act,
                       int64_t* nact) {
   hipStream_t st = c->st;
-  c->R_dcount = nullptr;
+  c->R_open = false;
   const int32_t n = c->n;
   long long* stat = c->stat.as<long long>();
   long long* hs = c->hstat;
@@ -700,6 +707,8 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
   rows.ccount = reinterpret_cast<int32_t*>(stat + ST_N2);
   if (direct) {
     rows.uflag = c->uflag.as<uint8_t>();
+    rows.R = c->R.as<uint8_t>();
+    rows.cflag = c->cflag.as<uint8_t>();
     rows.seg_beg = c->seg_beg.as<int32_t>();
     rows.seg_end = c->seg_end.as<int32_t>();
     rows.ulist = c->ulist.as<int32_t>();
@@ -738,13 +747,13 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
     int32_t* dflag = c->dflag.as<int32_t>();
     uint8_t* accflag = cascade ? c->accflag.as<uint8_t>() : nullptr;
     {
-      // R, the community flags and the count of R_t's list start at zero, and
-      // unless row_changes has written them the deletion-source flags, the
-      // union flags (fused) and the accepted flags (cascade)
+      // R and the community flags start at zero, the deletion-source flags,
+      // the union flags (fused) and the accepted flags (cascade) too (row_changes
+      // has seen to those of the direct pass), and the count of R_t's list
+      const int64_t N = direct ? 0 : n;
       void* zp[6] = {R, cflag, dflag, accflag, fused ? c->uflag.p : nullptr,
                      c->rpos2.as<int32_t>() + n};
-      const int64_t zb[6] = {n, n, direct ? 0 : 4 * int64_t(n), cascade ? int64_t(n) : 0,
-                             fused && !direct ? int64_t(n) : 0, 4};
+      const int64_t zb[6] = {N, N, 4 * N, cascade ? N : 0, fused ? N : 0, samples || !direct ? 4 : 0};
       zero_buffers(zp, zb, 6, st);
     }
     // Alg. 2 scratch: a gain per insertion record, the best sink per source
@@ -867,23 +876,23 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
     }
     if (n_dsrc > 0 && !fused)
       mark_neighbourhoods(c->dlist.as<int32_t>(), n_dsrc, g0.off, g0.adj, R, st);
-    int32_t* rpos2 = c->rpos2.as<int32_t>();
-    materialize_R(R, cflag, c->C.as<int32_t>(), n, c->Rlist.as<int32_t>(), rpos2 + n, st);
     S.ds_sources = n_src;
     S.del_sources = n_dsrc;
     S.vertex_evals += S.ds_sources + S.del_sources + S.cascade_candidates;
     if (mode == DC_MODE_DELTA && !samples) {
-      // R_t goes to level 0 as is: its length and the screening counters
-      // are read with the level-0 binning's wait (levels_begin)
-      c->R_dcount = rpos2 + n;
-      c->R_count = n;
-    } else if (mode == DC_MODE_LEARNED && c->have_scr) {
-      // the scores choose R_t below; the counters come back with its binning
+      // level 0 completes R_t and reads its length and the screening
+      // counters with its binning (levels_begin)
+      c->R_open = true;
+      c->R_cflag = cflag;
     } else {
-      DC_HIP(hipMemcpyAsync(c->hbuf, rpos2 + n, 4, hipMemcpyDeviceToHost, st));
-      read_stat(c);
-      c->R_count = *static_cast<int32_t*>(c->hbuf);
-      screening_counts(c);
+      int32_t* rpos2 = c->rpos2.as<int32_t>();
+      materialize_R(R, cflag, c->C.as<int32_t>(), n, c->Rlist.as<int32_t>(), rpos2 + n, st);
+      if (mode != DC_MODE_LEARNED || !c->have_scr) {
+        DC_HIP(hipMemcpyAsync(c->hbuf, rpos2 + n, 4, hipMemcpyDeviceToHost, st));
+        read_stat(c);
+        c->R_count = *static_cast<int32_t*>(c->hbuf);
+        screening_counts(c);
+      }  // else the scores choose R_t below; the counters come back with its binning
     }
   }
   if (samples) {
@@ -893,16 +902,12 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
     if (score) {
       // R_t = touched vertices scoring at least theta
       uint8_t* R = c->R.as<uint8_t>();
-      int32_t* rpos2 = c->rpos2.as<int32_t>();
-      void* zp[2] = {R, rpos2 + n};
-      const int64_t zb[2] = {n, 4};
-      zero_buffers(zp, zb, 2, st);
+      fill_u8(R, 0, n, st);
       select_by_score(c->Tlist.as<int32_t>(), c->T_count, c->logits.as<float>(), c->theta, R,
                       st);
-      materialize_R(R, nullptr, nullptr, n, c->Rlist.as<int32_t>(), rpos2 + n, st);
-      // its length is read with the level-0 binning's wait (levels_begin)
-      c->R_dcount = rpos2 + n;
-      c->R_count = n;
+      // its length is read with the level-0 binning (levels_begin)
+      c->R_open = true;
+      c->R_cflag = nullptr;
       S.screened = 1;
     }
   }
@@ -910,12 +915,10 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
   mark_phase(c, 2);
   if (mode == DC_MODE_DELTA || mode == DC_MODE_LEARNED) {
     c->have_R_all = false;
-    load_level0_partition(c);
-    *act = c->Rlist.as<int32_t>();
-    *nact = c->R_count;
+    *act = c->R_open ? nullptr : c->Rlist.as<int32_t>();
+    *nact = c->R_open ? n : c->R_count;
   } else {
     if (mode == DC_MODE_STATIC) start_from_singletons(c);
-    load_level0_partition(c);
     S.R_size = n;
     c->have_R_all = true;
     *act = nullptr;
@@ -1228,6 +1231,7 @@ void level0_merged(dc_ctx* const* cs, LevelRun* Ls, long long* gains, int m, Mer
   for (int j = 0; j < m; ++j)
     DC_HIP(hipMemcpyAsync(cs[j]->hstat, cs[j]->stat.p, ST_COUNT * 8, hipMemcpyDeviceToHost, st));
   DC_HIP(hipStreamSynchronize(st));
+  for (int j = 0; j < m; ++j) sweep_reset(cs[j]->stat.as<long long>(), st);
   for (int j = 0; j < m; ++j) {
     dc_ctx* c = cs[j];
     check_stat_errors(c->hstat);

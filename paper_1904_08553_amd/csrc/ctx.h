@@ -61,7 +61,8 @@ struct dc_ctx {
   int32_t* out_C = nullptr;   // C_t's destination of the running dc_apply_batch (copied
   int32_t out_on_device = 0;  // with the last wait of the step)
   int64_t R_count = 0;
-  const int32_t* R_dcount = nullptr;  // |R_t| in device memory, not yet read back
+  bool R_open = false;           // R holds R_t but for the members of the communities that
+  const uint8_t* R_cflag = nullptr;  // R_cflag flags (null: none); level 0 completes it
   bool have_R_all = true;
   // graph of communities kept across steps (incremental level-0 compaction)
   IncCoarsen inc;
@@ -105,8 +106,7 @@ struct MergeScratch {
 
 dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const int32_t** act,
                       int64_t* nact);
-void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& L,
-                  const uint8_t* skip = nullptr);
+void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& L);
 void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain);
 void apply_output(dc_ctx* c, int32_t* C_out, int32_t out_on_device);
 // All levels of one step (Louvain or SLM per the options), level 0 over

@@ -140,6 +140,8 @@ struct RowOut {
   // screening set (uflag null: not asked for)
   uint8_t* uflag;     // bit 0: an insertion record; bit 1: a deletion or replacement
                       // inside one community of C
+  uint8_t* R;         // 0: what the screening starts from
+  uint8_t* cflag;
   int32_t* seg_beg;   // rows of bit 0: their insertion records [seg_beg, seg_end)
   int32_t* seg_end;
   int32_t* ulist;     // the rows with a bit set, in no fixed order; *ucount (zeroed) their

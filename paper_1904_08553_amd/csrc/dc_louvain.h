@@ -116,6 +116,7 @@ struct Bins {
   const int32_t* list_rb[NBINS];  // row start (off[v]) of each listed vertex
   long long vol[NBINS];       // adjacency entries of each bin
   int64_t total = 0;          // vertices binned (the sum of n)
+  const int32_t* all;         // and all of them, bin after bin
   const int32_t* count_dev;   // NBINS device counts
   // each bin's list starts with the vertices that make_bins' skip flags
   // leave unset: their number, volume and device counts
@@ -170,8 +171,22 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
                const long long* copy_src = nullptr, long long* copy_dst = nullptr,
                int copy_n = 0, bool coarse = false);
 
-// Clears the per-sweep counters of the status block (before the first
-// sweep of a level; each sweep_apply clears them again for the next one).
+// The start of a level 0 (k_level0_start), binned as make_bins would bin R_t.
+struct Level0Start {
+  const int32_t *C, *a0, *sz0;        // the inherited partition
+  int32_t *Cl, *Cn, *al, *szl;        // the level's
+  uint8_t* R;                         // the active vertices (null: all)
+  const uint8_t* cflag;               // (may be null) communities that join R
+  const uint8_t* skip;                // (may be null) the vertices whose first-sweep label
+  const int32_t* pre;                 // is pre[v]: binned after the others, applied to Cn
+};
+void level0_start(const Level0Start& A, int32_t n, const int32_t* off, Bins& b, BinScratch& s,
+                  hipStream_t st, const long long* copy_src = nullptr,
+                  long long* copy_dst = nullptr, int copy_n = 0);
+
+// Clears the per-sweep counters of the status block.  A step starts with
+// them cleared and each sweep_apply clears them again, so only merged sweeps
+// call this, when they are done.
 void sweep_reset(long long* stat, hipStream_t st);
 // Writes the next label of every active vertex that moves.  ev0/ev1 (may be
 // null) bracket the one launch of bins [0, TIMED_BINS) (rows of at most 64

@@ -1136,13 +1136,15 @@ constexpr int BIN_STRIDE = 16;  // int64 words
 constexpr int BIN_WORDS = 2 * NROWS * BIN_STRIDE;
 
 // The BIN_ITEMS vertices of a thread, their row starts and rows (-1 past the
-// list): every round of loads at clamped indexes, in flight together.
+// list, and where only, when given, is not set): every round of loads at
+// clamped indexes, in flight together.
 __device__ __forceinline__ void bin_load(const int32_t* __restrict__ list, int64_t cnt,
                                          const int32_t* __restrict__ off,
-                                         const uint8_t* __restrict__ skip, int wmax,
+                                         const uint8_t* __restrict__ skip,
+                                         const uint8_t* __restrict__ only, int wmax,
                                          int (&u)[BIN_ITEMS], int (&rb)[BIN_ITEMS],
                                          int (&deg)[BIN_ITEMS], int (&row)[BIN_ITEMS]) {
-  int re[BIN_ITEMS], sk[BIN_ITEMS];
+  int re[BIN_ITEMS], sk[BIN_ITEMS], on[BIN_ITEMS];
   const int64_t base = int64_t(blockIdx.x) * BIN_TILE + threadIdx.x;
 #pragma unroll
   for (int r = 0; r < BIN_ITEMS; ++r) {
@@ -1155,64 +1157,75 @@ __device__ __forceinline__ void bin_load(const int32_t* __restrict__ list, int64
     rb[r] = off[u[r]];
     re[r] = off[u[r] + 1];
     sk[r] = skip ? skip[u[r]] : 0;
+    on[r] = only ? only[u[r]] : 1;
   }
 #pragma unroll
   for (int r = 0; r < BIN_ITEMS; ++r) {
     deg[r] = re[r] - rb[r];
-    row[r] = base + int64_t(r) * BIN_TPB < cnt ? 2 * bin_of(deg[r], wmax) + (sk[r] ? 1 : 0) : -1;
+    row[r] = base + int64_t(r) * BIN_TPB < cnt && on[r] ? 2 * bin_of(deg[r], wmax) + (sk[r] ? 1 : 0) : -1;
   }
 }
 
-// The rows' totals: one atomic per block and row; the last block to finish
-// turns them into starts (the placement's cursors) and the metadata, written
-// to counts and to host (device-visible pinned host memory), and copies copy_n
-// slots of copy_src to copy_dst (host memory too), so that the caller's one
-// wait brings back both.
-__global__ void __launch_bounds__(BIN_TPB)
-    k_bin_count(const int32_t* __restrict__ list, int64_t cnt, const int32_t* __restrict__ dcnt,
-                const int32_t* __restrict__ off, const uint8_t* __restrict__ skip, int wmax,
-                unsigned long long* words, unsigned* done, int32_t* counts, int32_t* host,
-                const long long* __restrict__ copy_src, long long* copy_dst, int copy_n, uint32_t* tag,
-                uint32_t tag_value) {
-  if (dcnt) cnt = *dcnt;  // the list's length on the device (cnt: its bound)
+// Where a binning leaves its sizes: device words and metadata, host memory
+// (device-visible, pinned), and copy_n slots of copy_src copied to copy_dst
+// (host memory too), so that the caller's one wait brings back both.
+struct BinOut {
+  unsigned long long* words;
+  unsigned* done;
+  int32_t* counts;
+  int32_t* host;
+  const long long* copy_src;
+  long long* copy_dst;
+  int copy_n;
+  uint32_t* tag;
+  uint32_t tag_value;
+};
+
+// The rows' totals of a block's vertices: one atomic per block and row.
+__device__ __forceinline__ void bin_totals(const int (&deg)[BIN_ITEMS],
+                                           const int (&row)[BIN_ITEMS],
+                                           unsigned long long* words) {
   __shared__ unsigned long long part[BIN_WAVES][NROWS];
+  const int t = threadIdx.x, lane = lane_id(), wid = t / WAVE;
+#pragma unroll
+  for (int q = 0; q < NROWS; ++q) {
+    int n = 0, v = 0;  // a wave's entries fit int32 (all entries do)
+#pragma unroll
+    for (int r = 0; r < BIN_ITEMS; ++r) {
+      n += __popcll(__ballot(row[r] == q));
+      v += row[r] == q ? deg[r] : 0;
+    }
+    v = n ? wave_sum(v) : 0;  // n: wave-uniform
+    if (lane == 0) part[wid][q] = (unsigned long long)n << 32 | uint32_t(v);
+  }
+  __syncthreads();
+  if (t < NROWS) {
+    unsigned long long x = 0;
+    for (int w = 0; w < BIN_WAVES; ++w) x += part[w][t];
+    if (x) atomicAdd(&words[t * BIN_STRIDE], x);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // performed before the block counts
+  }                                                   // as finished
+}
+
+// Every block of the counting launch ends here: the last one to finish turns
+// the totals into starts (the placement's cursors) and metadata and
+// publishes them.
+__device__ __forceinline__ void bin_publish(const BinOut& o) {
   __shared__ unsigned long long tot[NROWS];
   __shared__ int meta[META_WORDS];
-  const int t = threadIdx.x, lane = lane_id(), wid = t / WAVE;
-  if (int64_t(blockIdx.x) * BIN_TILE < cnt) {  // block-uniform
-    int u[BIN_ITEMS], rb[BIN_ITEMS], deg[BIN_ITEMS], row[BIN_ITEMS];
-    bin_load(list, cnt, off, skip, wmax, u, rb, deg, row);
-#pragma unroll
-    for (int q = 0; q < NROWS; ++q) {
-      int n = 0, v = 0;  // a wave's entries fit int32 (all entries do)
-#pragma unroll
-      for (int r = 0; r < BIN_ITEMS; ++r) {
-        n += __popcll(__ballot(row[r] == q));
-        v += row[r] == q ? deg[r] : 0;
-      }
-      v = n ? wave_sum(v) : 0;  // n: wave-uniform
-      if (lane == 0) part[wid][q] = (unsigned long long)n << 32 | uint32_t(v);
-    }
-    __syncthreads();
-    if (t < NROWS) {
-      unsigned long long x = 0;
-      for (int w = 0; w < BIN_WAVES; ++w) x += part[w][t];
-      if (x) atomicAdd(&words[t * BIN_STRIDE], x);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // performed before the block counts
-    }                                                   // as finished
-  }
-  if (!last_block(done)) return;
+  const int t = threadIdx.x;
+  if (!last_block(o.done)) return;
   if (t < META_WORDS) meta[t] = 0;
   if (t < NROWS) {
-    tot[t] = __hip_atomic_load(&words[t * BIN_STRIDE], __ATOMIC_RELAXED,
+    tot[t] = __hip_atomic_load(&o.words[t * BIN_STRIDE], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-    words[t * BIN_STRIDE] = 0;
+    o.words[t * BIN_STRIDE] = 0;
   }
   __syncthreads();
   if (t < NROWS) {
     int start = 0;
     for (int q = 0; q < t; ++q) start += int(tot[q] >> 32);
-    words[(NROWS + t) * BIN_STRIDE] = (unsigned long long)start;
+    o.words[(NROWS + t) * BIN_STRIDE] = (unsigned long long)start;
     if (t % 2 == 0) {
       meta[M_START + t / 2] = start;
       meta[t / 2] = int(tot[t] >> 32) + int(tot[t + 1] >> 32);
@@ -1222,11 +1235,69 @@ __global__ void __launch_bounds__(BIN_TPB)
   }
   __syncthreads();
   if (t < META_WORDS) {
-    counts[t] = meta[t];
-    host_store(&host[t], meta[t]);
+    o.counts[t] = meta[t];
+    host_store(&o.host[t], meta[t]);
   }
-  for (int i = t; i < copy_n; i += BIN_TPB) host_store(&copy_dst[i], copy_src[i]);
-  host_publish(tag, tag_value);
+  for (int i = t; i < o.copy_n; i += BIN_TPB) host_store(&o.copy_dst[i], o.copy_src[i]);
+  host_publish(o.tag, o.tag_value);
+}
+
+__global__ void __launch_bounds__(BIN_TPB)
+    k_bin_count(const int32_t* __restrict__ list, int64_t cnt, const int32_t* __restrict__ dcnt,
+                const int32_t* __restrict__ off, const uint8_t* __restrict__ skip, int wmax,
+                BinOut o) {
+  if (dcnt) cnt = *dcnt;  // the list's length on the device (cnt: its bound)
+  if (int64_t(blockIdx.x) * BIN_TILE < cnt) {  // block-uniform
+    int u[BIN_ITEMS], rb[BIN_ITEMS], deg[BIN_ITEMS], row[BIN_ITEMS];
+    bin_load(list, cnt, off, skip, nullptr, wmax, u, rb, deg, row);
+    bin_totals(deg, row, o.words);
+  }
+  bin_publish(o);
+}
+
+// The start of a level 0 in one pass over the vertices: R_t completed (R[v]
+// |= cflag[C[v]]; R null: every vertex), the level's partition (Cl, al, szl)
+// and next labels (the first sweep's decision where the screening pass has
+// taken it, else the own label), and the counts of the level's binning.
+// Completing R_t, listing it, copying the partition, the decisions and the
+// count were five launches (31 us of a 1M-vertex step's 1% batch, now 17).
+__global__ void __launch_bounds__(BIN_TPB)
+    k_level0_start(Level0Start A, int32_t n, const int32_t* __restrict__ off, int wmax, BinOut o) {
+  const int64_t base = int64_t(blockIdx.x) * BIN_TILE + threadIdx.x;
+  int deg[BIN_ITEMS], row[BIN_ITEMS], c[BIN_ITEMS], f[BIN_ITEMS], sk[BIN_ITEMS], pre[BIN_ITEMS];
+  int av[BIN_ITEMS], zv[BIN_ITEMS];
+  // clamped (n >= 1): every kind of load in flight together
+#pragma unroll
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    const int64_t p = base + int64_t(r) * BIN_TPB;
+    const int64_t v = p < n ? p : n - 1;
+    c[r] = A.C[v];
+    f[r] = A.R ? A.R[v] : 1;
+    sk[r] = A.skip ? A.skip[v] : 0;
+    deg[r] = off[v + 1] - off[v];
+    av[r] = A.a0[v];
+    zv[r] = A.sz0[v];
+  }
+#pragma unroll
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    const int64_t p = base + int64_t(r) * BIN_TPB;
+    if (A.cflag) f[r] |= A.cflag[c[r]];
+    pre[r] = c[r];
+    if (A.skip && sk[r] && f[r]) pre[r] = A.pre[p < n ? p : n - 1];
+  }
+#pragma unroll
+  for (int r = 0; r < BIN_ITEMS; ++r) {
+    const int64_t p = base + int64_t(r) * BIN_TPB;
+    row[r] = p < n && f[r] ? 2 * bin_of(deg[r], wmax) + (sk[r] ? 1 : 0) : -1;
+    if (p >= n) continue;
+    if (A.cflag) A.R[p] = uint8_t(f[r] ? 1 : 0);
+    A.Cl[p] = c[r];
+    A.Cn[p] = pre[r];
+    A.al[p] = av[r];
+    A.szl[p] = zv[r];
+  }
+  bin_totals(deg, row, o.words);
+  bin_publish(o);
 }
 
 // The vertices to their rows' lists, row starts beside them: a block takes
@@ -1235,15 +1306,16 @@ __global__ void __launch_bounds__(BIN_TPB)
 // and every sum is exact, so the order changes no result).
 __global__ void __launch_bounds__(BIN_TPB)
     k_bin_scatter(const int32_t* __restrict__ list, int64_t cnt, const int32_t* __restrict__ dcnt,
-                  const int32_t* __restrict__ off, const uint8_t* __restrict__ skip, int wmax,
-                  unsigned long long* words, int32_t* out, int32_t* out_rb) {
+                  const int32_t* __restrict__ off, const uint8_t* __restrict__ skip,
+                  const uint8_t* __restrict__ only, int wmax, unsigned long long* words,
+                  int32_t* out, int32_t* out_rb) {
   if (dcnt) cnt = *dcnt;
   if (int64_t(blockIdx.x) * BIN_TILE >= cnt) return;  // block-uniform
   __shared__ int at[NROWS][BIN_ITEMS * BIN_WAVES];
   static_assert(BIN_ITEMS * BIN_WAVES == WAVE && NROWS <= BIN_WAVES, "a wave per row");
   const int lane = lane_id(), wid = threadIdx.x / WAVE;
   int u[BIN_ITEMS], rb[BIN_ITEMS], deg[BIN_ITEMS], row[BIN_ITEMS], rank[BIN_ITEMS];
-  bin_load(list, cnt, off, skip, wmax, u, rb, deg, row);
+  bin_load(list, cnt, off, skip, only, wmax, u, rb, deg, row);
   const uint64_t lt = (uint64_t(1) << lane) - 1;
 #pragma unroll
   for (int r = 0; r < BIN_ITEMS; ++r) {
@@ -1512,31 +1584,46 @@ void launch_eval(const EvalArgs& base, const Bins& bins, hipStream_t st, hipEven
 
 }  // namespace
 
-void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, BinScratch& s,
-               hipStream_t st, const uint8_t* skip, const int32_t* dcount,
-               const long long* copy_src, long long* copy_dst, int copy_n, bool coarse) {
-  const int wmax = coarse ? WTAB_MAX / 2 : WTAB_MAX;
-  const int64_t nb = count > 0 ? ceil_div(count, BIN_TILE) : 1;
-  const int64_t cap = count > 0 ? count : 1;
-  s.lists.ensure(size_t(cap) * sizeof(int32_t));
-  s.lists_rb.ensure(size_t(cap) * sizeof(int32_t));
+namespace {
+
+// Scratch of a binning of at most count vertices, and where its sizes go.
+BinOut bin_out(int64_t count, BinScratch& s, hipStream_t st, const long long* copy_src,
+               long long* copy_dst, int copy_n) {
+  const size_t cap = size_t(count > 0 ? count : 1);
+  s.lists.ensure(cap * sizeof(int32_t));
+  s.lists_rb.ensure(cap * sizeof(int32_t));
   s.counts.ensure(META_WORDS * sizeof(int32_t));
+  // overflow list of bins W and B; its count sits in the zeroed metadata and
+  // is cleared again by each sweep's commit
+  s.ovf.ensure(cap * sizeof(int32_t));
   if (!s.words.p) {  // totals and finished blocks start at zero, and end there
     s.words.ensure(size_t(BIN_WORDS) * 8 + DONE_WORDS * 4);
     fill_i32(s.words.as<int32_t>(), 0, 2 * BIN_WORDS + DONE_WORDS, st);
   }
   auto* words = s.words.as<unsigned long long>();
-  auto* done = reinterpret_cast<unsigned*>(words + BIN_WORDS);
-  int32_t* counts = s.counts.as<int32_t>();
-  k_bin_count<<<nb, BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, words, done, counts,
-                                      static_cast<int32_t*>(s.host_dev), copy_src, copy_dst,
-                                      copy_src ? copy_n : 0, s.tag.dev, s.tag.next());
-  DC_LAUNCH_CHECK();
+  return BinOut{words,
+                reinterpret_cast<unsigned*>(words + BIN_WORDS),
+                s.counts.as<int32_t>(),
+                static_cast<int32_t*>(s.host_dev),
+                copy_src,
+                copy_dst,
+                copy_src ? copy_n : 0,
+                s.tag.dev,
+                s.tag.next()};
+}
+
+// After the counting launch: the placement, the sizes from host memory, and
+// the hub rows' tables.
+void bin_place(const int32_t* list, int64_t count, const int32_t* dcount, const int32_t* off,
+               const uint8_t* skip, const uint8_t* only, int wmax, Bins& b, BinScratch& s,
+               hipStream_t st) {
   int32_t* lists = s.lists.as<int32_t>();
   int32_t* lists_rb = s.lists_rb.as<int32_t>();
+  int32_t* counts = s.counts.as<int32_t>();
   if (count > 0) {  // runs while the host reads the metadata
-    k_bin_scatter<<<nb, BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, words, lists,
-                                          lists_rb);
+    k_bin_scatter<<<int(ceil_div(count, BIN_TILE)), BIN_TPB, 0, st>>>(
+        list, count, dcount, off, skip, only, wmax, s.words.as<unsigned long long>(), lists,
+        lists_rb);
     DC_LAUNCH_CHECK();
   }
   wait_tag(s.tag, st);
@@ -1552,11 +1639,9 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
     b.vol[q] = hv[2 * q] + hv[2 * q + 1];
     b.vol_first[q] = hv[2 * q];
   }
+  b.all = lists;
   b.count_dev = counts;
   b.count_first_dev = counts + NBINS;
-  // overflow list of bins W and B; its count sits in the zeroed metadata and
-  // is cleared again by each sweep's commit
-  s.ovf.ensure(size_t(cap) * sizeof(int32_t));
   b.ovf_list = s.ovf.as<int32_t>();
   b.ovf_count = counts + M_OVF;
   b.side = s.side;
@@ -1585,6 +1670,27 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
     b.tab_off = caps;
     b.gslots = int64_t(slots);
   }
+}
+
+}  // namespace
+
+void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, BinScratch& s,
+               hipStream_t st, const uint8_t* skip, const int32_t* dcount,
+               const long long* copy_src, long long* copy_dst, int copy_n, bool coarse) {
+  const int wmax = coarse ? WTAB_MAX / 2 : WTAB_MAX;
+  const int64_t nb = count > 0 ? ceil_div(count, BIN_TILE) : 1;
+  const BinOut o = bin_out(count, s, st, copy_src, copy_dst, copy_n);
+  k_bin_count<<<int(nb), BIN_TPB, 0, st>>>(list, count, dcount, off, skip, wmax, o);
+  DC_LAUNCH_CHECK();
+  bin_place(list, count, dcount, off, skip, nullptr, wmax, b, s, st);
+}
+
+void level0_start(const Level0Start& A, int32_t n, const int32_t* off, Bins& b, BinScratch& s,
+                  hipStream_t st, const long long* copy_src, long long* copy_dst, int copy_n) {
+  const BinOut o = bin_out(n, s, st, copy_src, copy_dst, copy_n);
+  k_level0_start<<<int(ceil_div(n, BIN_TILE)), BIN_TPB, 0, st>>>(A, n, off, WTAB_MAX, o);
+  DC_LAUNCH_CHECK();
+  bin_place(nullptr, n, nullptr, off, A.skip, A.R, WTAB_MAX, b, s, st);
 }
 
 void sweep_eval(const LevelView& g, const int32_t* C, int32_t* Cn, const int32_t* a,

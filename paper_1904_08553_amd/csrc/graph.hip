@@ -513,6 +513,8 @@ __global__ void __launch_bounds__(RC_TPB)
       }
       if (o.uflag) {
         o.uflag[r] = uint8_t(kind[i]);
+        o.R[r] = 0;
+        o.cflag[r] = 0;
         if (kind[i]) o.ulist[u++] = int32_t(r);
         if (ins[i]) {
           o.seg_beg[r] = p;

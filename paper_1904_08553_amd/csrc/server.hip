@@ -267,17 +267,8 @@ void dc_server::run() {
           finish(r, DC_OK);
           continue;
         }
-        // the screening pass's first-sweep decisions, as in run_levels
-        const int64_t npre = act ? c->pre_count : 0;
-        const uint8_t* skip = nullptr;
-        if (npre > 0) {
-          apply_pre(c->pre_list, npre, c->R.as<uint8_t>(), c->pre.as<int32_t>(),
-                    c->Cn.as<int32_t>(), c->st);
-          skip = c->pre_skip;
-        }
         LevelRun L;
-        levels_begin(c, act, nact, L, skip);
-        L.pre_done = skip != nullptr;
+        levels_begin(c, act, nact, L);
         cs.push_back(c);
         Ls.push_back(L);
         swept.push_back(r);
