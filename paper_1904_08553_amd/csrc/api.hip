@@ -262,16 +262,30 @@ void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& 
   screening_counts(c);
 }
 
+// The step's level and sweep counts, and its numerator and modularity from
+// the status block in c->hstat.
+void final_stats(dc_ctx* c) {
+  dc_step_stats& S = c->stats;
+  S.levels = c->trace.empty() ? 1 : c->trace.back().level + 1;
+  S.sweeps = int32_t(c->trace.size());
+  S.N = c->two_m * c->hstat[ST_I] - c->hstat[ST_S];
+  S.two_m = c->two_m;
+  S.q = c->two_m == 0 ? 0.0 : double(S.N) / (double(c->two_m) * double(c->two_m));
+}
+
 void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
   hipStream_t st = c->st;
-  const long long two_m = c->two_m;
   const long long T = L.T;
   LevelView g = L.g;
   int32_t* Cl = c->Cl.as<int32_t>();
   int32_t* Cn = c->Cn.as<int32_t>();
   int32_t* al = c->al.as<int32_t>();
   int32_t* szl = c->szl.as<int32_t>();
-  dc_step_stats& S = c->stats;
+  long long* stat = c->stat.as<long long>();
+  static_assert(ST_S == ST_I + 1, "the numerator's counters are adjacent");
+  const FinalLabels F{c->lab.as<int32_t>(), c->cntf.as<int32_t>(), c->a0.as<int32_t>(),
+                      c->sz0.as<int32_t>(), c->C.as<int32_t>(), stat + ST_I};
+  bool final_ready = false;
   int level = 0;
   long long level_gain = level0_gain;
   while (true) {
@@ -290,11 +304,12 @@ void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
     const int32_t* minv_in = level == 0 ? nullptr : c->minv[(level - 1) % 2].as<int32_t>();
     const bool inc = level == 0 && c->inc.valid && c->inc_ready &&
                      c->opt.mode != DC_MODE_STATIC && !c->opt.full_coarsen;
+    if (inc) final_ready = true;
     if (inc)
       coarsen_first_inc(g, Cl, c->C.as<int32_t>(), szl, al, c->ch_key.as<uint64_t>(),
                         c->ch_dk.as<int32_t>(), c->nch_last, c->map0.as<int32_t>(), c->cg[next],
                         c->cnt[next].as<int32_t>(), c->minv[next].as<int32_t>(), c->cs, c->inc,
-                        st);
+                        F, st);
     else
       coarsen(g, Cl, szl, al, cnt_in, minv_in, level == 0, c->n, c->map0.as<int32_t>(),
               c->cg[next], c->cnt[next].as<int32_t>(), c->minv[next].as<int32_t>(), c->cs, st);
@@ -305,48 +320,25 @@ void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
     level++;
     if (stop) break;  // max_levels == 1: final = the identity partition of level 1
   }
-  S.levels = c->trace.empty() ? 1 : c->trace.back().level + 1;
-  S.sweeps = int32_t(c->trace.size());
   const int32_t* cntL = c->cnt[(level - 1) % 2].as<int32_t>();
   const int32_t* minvL = c->minv[(level - 1) % 2].as<int32_t>();
-  // (the labels' first launch also clears the numerator's two counters)
-  long long* stat = c->stat.as<long long>();
-  static_assert(ST_S == ST_I + 1, "the numerator's counters are adjacent");
-  finalize_labels(g.n, Cl, al, szl, cntL, minvL, c->n, c->map0.as<int32_t>(),
-                  c->lab.as<int32_t>(), c->cntf.as<int32_t>(), c->C.as<int32_t>(),
-                  c->a0.as<int32_t>(), c->sz0.as<int32_t>(), st, stat + ST_I);
+  if (!final_ready) final_init(g.n, c->n, F, st);
+  finalize_labels(g, Cl, al, szl, cntL, minvL, c->n, c->map0.as<int32_t>(), F, stat, ST_COUNT,
+                  c->hstat_dev, st);
   c->inc.valid = true;  // with C_t the level-1 graph just kept is H(G_t, C_t)
   c->inc_ready = false;
-  // exact numerator on the final level (coarsening preserves N); C_t goes
-  // to the caller of dc_apply_batch before the same wait
-  modularity_terms(g.off, g.adj, Cl, al, g.n, stat + ST_I, stat + ST_S, st);
+  // C_t goes to the caller of dc_apply_batch before the same wait as the
+  // numerator's sums
   if (c->out_C) {
     DC_HIP(hipMemcpyAsync(c->out_C, c->C.p, size_t(c->n) * 4,
                           c->out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
                           st));
     c->out_C = nullptr;
   }
-  read_stat(c);
+  DC_HIP(hipStreamSynchronize(st));
+  check_stat_errors(c->hstat);
   inc_check(c->cs);
-  S.N = two_m * c->hstat[ST_I] - c->hstat[ST_S];
-  S.two_m = two_m;
-  S.q = two_m == 0 ? 0.0 : double(S.N) / (double(two_m) * double(two_m));
-}
-
-// Exact numerator of the final partition (Cl, al over the last level g;
-// compaction preserves N) and the step's level and sweep counts.
-void finish_stats(dc_ctx* c, const LevelView& g) {
-  dc_step_stats& S = c->stats;
-  S.levels = c->trace.empty() ? 1 : c->trace.back().level + 1;
-  S.sweeps = int32_t(c->trace.size());
-  long long* stat = c->stat.as<long long>();
-  DC_HIP(hipMemsetAsync(stat + ST_I, 0, 16, c->st));
-  modularity_terms(g.off, g.adj, c->Cl.as<int32_t>(), c->al.as<int32_t>(), g.n, stat + ST_I,
-                   stat + ST_S, c->st);
-  read_stat(c);
-  S.N = c->two_m * c->hstat[ST_I] - c->hstat[ST_S];
-  S.two_m = c->two_m;
-  S.q = c->two_m == 0 ? 0.0 : double(S.N) / (double(c->two_m) * double(c->two_m));
+  final_stats(c);
 }
 
 // Levels of smart local moving (the SLM host method of Sec. 3.4, level
@@ -434,12 +426,16 @@ void run_levels_slm(dc_ctx* c, const int32_t* active, int64_t n_active) {
     cntL = c->cnt[(level - 1) % 2].as<int32_t>();
     minvL = c->minv[(level - 1) % 2].as<int32_t>();
   }
-  finalize_labels(g.n, Cl, al, szl, cntL, minvL, c->n, c->map0.as<int32_t>(),
-                  c->lab.as<int32_t>(), c->cntf.as<int32_t>(), c->C.as<int32_t>(),
-                  c->a0.as<int32_t>(), c->sz0.as<int32_t>(), st);
+  const FinalLabels F{c->lab.as<int32_t>(), c->cntf.as<int32_t>(), c->a0.as<int32_t>(),
+                      c->sz0.as<int32_t>(), c->C.as<int32_t>(), stat + ST_I};
+  final_init(g.n, c->n, F, st);
+  finalize_labels(g, Cl, al, szl, cntL, minvL, c->n, c->map0.as<int32_t>(), F, stat, ST_COUNT,
+                  c->hstat_dev, st);
   c->inc.valid = false;  // the first compaction follows the refinement, not H(G, C)
   c->inc_ready = false;
-  finish_stats(c, g);
+  DC_HIP(hipStreamSynchronize(st));
+  check_stat_errors(c->hstat);
+  final_stats(c);
 }
 
 // Alg. 1 with level 0 visiting `active` (null = every vertex).  The level-0

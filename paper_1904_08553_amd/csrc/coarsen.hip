@@ -288,33 +288,62 @@ __global__ void k_project(const int32_t* __restrict__ C, const int32_t* __restri
   }
 }
 
-__global__ void k_final_min(const int32_t* __restrict__ CL, const int32_t* __restrict__ cntL,
-                            const int32_t* __restrict__ minvL, int32_t nL, int32_t* lab,
-                            int32_t* cntf) {
-  GRID_STRIDE(x, nL) {
-    int32_t Y = CL[x];
-    atomicMin(&lab[Y], minvL[x]);
-    atomicAdd(&cntf[Y], cntL[x]);
+// The final labels, first launch.  Blocks [0, nbm): the smallest level-0 id
+// and the level-0 size of each community of the last level; the others: the
+// numerator's two sums over the last level's graph, nb_intra blocks of them
+// the intra-community weight (a wave per row), the rest the squares of the
+// totals.  Second launch: the totals and sizes by final label and the label of
+// every vertex; its first block writes the status block to host memory.
+__global__ void __launch_bounds__(TPB)
+    k_final_min(LevelView g, const int32_t* __restrict__ CL, const int32_t* __restrict__ aL,
+                const int32_t* __restrict__ cntL, const int32_t* __restrict__ minvL, int32_t* lab,
+                int32_t* cntf, int nbm, int nb_intra, long long* I, long long* S) {
+  const int64_t b = int64_t(blockIdx.x) - nbm;
+  if (b < 0) {
+    for (int64_t x = int64_t(blockIdx.x) * TPB + threadIdx.x; x < g.n; x += int64_t(nbm) * TPB) {
+      const int32_t Y = CL[x];
+      atomicMin(&lab[Y], minvL[x]);
+      atomicAdd(&cntf[Y], cntL[x]);
+    }
+    return;
+  }
+  long long s = 0;
+  if (b < nb_intra) {
+    for (int64_t row = b * (TPB / WAVE) + threadIdx.x / WAVE; row < g.n;
+         row += int64_t(nb_intra) * (TPB / WAVE)) {
+      const int32_t c = CL[row];
+      for (int32_t j = g.off[row] + lane_id(); j < g.off[row + 1]; j += WAVE) {
+        const int2 e = g.adj[j];
+        if (CL[e.x] == c) s += e.y;
+      }
+    }
+    block_add(s, I);
+  } else {
+    const int64_t nbs = int64_t(gridDim.x) - nbm - nb_intra;
+    for (int64_t x = (b - nb_intra) * TPB + threadIdx.x; x < g.n; x += nbs * TPB) {
+      const long long y = aL[x];
+      s += y * y;
+    }
+    block_add(s, S);
   }
 }
 
-__global__ void k_final_scatter(const int32_t* __restrict__ lab,
-                                const int32_t* __restrict__ cntf,
-                                const int32_t* __restrict__ aL,
-                                const int32_t* __restrict__ szL, int32_t nL, int32_t* a0,
-                                int32_t* sz0) {
-  GRID_STRIDE(Y, nL) {
-    if (szL[Y] <= 0) continue;
-    int32_t l = lab[Y];
-    a0[l] = aL[Y];
-    sz0[l] = cntf[Y];
+__global__ void __launch_bounds__(TPB)
+    k_final_project(const int32_t* __restrict__ lab, const int32_t* __restrict__ cntf,
+                    const int32_t* __restrict__ CL, const int32_t* __restrict__ aL,
+                    const int32_t* __restrict__ szL, int32_t nL, int32_t* a0, int32_t* sz0,
+                    const int32_t* __restrict__ map0, int32_t n0, int32_t* C0,
+                    const long long* __restrict__ stat, int nstat, long long* host_stat) {
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < nstat; i += TPB) host_store(host_stat + i, stat[i]);
+  GRID_STRIDE(v, n0) {
+    C0[v] = lab[CL[map0[v]]];
+    if (v < nL && szL[v] > 0) {  // nL <= n0
+      const int32_t l = lab[v];
+      a0[l] = aL[v];
+      sz0[l] = cntf[v];
+    }
   }
-}
-
-__global__ void k_final_project(const int32_t* __restrict__ lab,
-                                const int32_t* __restrict__ CL,
-                                const int32_t* __restrict__ map0, int32_t n0, int32_t* C0) {
-  GRID_STRIDE(v, n0) { C0[v] = lab[CL[map0[v]]]; }
 }
 
 // ---- incremental first-level compaction ----------------------------------
@@ -446,13 +475,17 @@ struct IncEmit {
   const int32_t* ch_dk;
   int64_t nch;
   int kb;
+  int32_t *a0, *sz0, *lab, *cntf;  // cleared for the final labels (n, n, nc, nc entries)
+  int32_t nc;
+  long long* zero2;  // the numerator's two counters, cleared
   uint64_t* ekey;  // out: kept entries, changes, then four slots per mover entry
   uint32_t* ew;
   int nbv, nbh;  // blocks over vertices and over kept entries; the rest: changes
 };
 
 // Everything that follows from the ranks, in one launch of three block ranges.
-//   Vertices: the coarse id of each, the smallest member of each coarse vertex
+//   Vertices: the coarse id of each, what the final labels and the numerator
+// start from (the level-0 totals and sizes are not read again), the smallest member of each coarse vertex
 // (only a vertex below the current value takes part, and a wave sends one
 // atomic per coarse vertex, from its lowest lane: the vertices of a label that
 // lost its own vertex would otherwise queue at one word), and the movers'
@@ -488,7 +521,16 @@ __global__ void __launch_bounds__(TPB) k_inc_emit(IncEmit A) {
   const int64_t uc = in ? u : A.n - 1;
   const int cn = A.Cl[uc], co = A.Cold[uc];
   const int r = A.rank[cn];
-  if (in) A.map0[u] = r;
+  if (in) {
+    A.map0[u] = r;
+    A.a0[u] = 0;
+    A.sz0[u] = 0;
+    if (u < A.nc) {
+      A.lab[u] = 0x7fffffff;
+      A.cntf[u] = 0;
+    }
+  }
+  if (u < 2) A.zero2[u] = 0;
   for (uint64_t todo = __ballot(in && int(u) < A.minv[r]); todo;) {
     const int l = __ffsll((unsigned long long)todo) - 1;
     const int rl = __builtin_amdgcn_readlane(r, l);
@@ -664,8 +706,8 @@ __global__ void k_adj_weights(const int2* __restrict__ adj, int64_t m, int32_t* 
 }
 
 // Starting values of finalize_labels: the smallest-member labels at +inf,
-// the member counts and the level-0 totals and sizes at zero, and the two
-// counters zero2 (may be null) at zero.
+// the member counts and the level-0 totals and sizes at zero, and the
+// numerator's two counters at zero.
 __global__ void k_final_init(int32_t* lab, int32_t* cntf, int32_t nL, int32_t* a0, int32_t* sz0,
                              int32_t n0, long long* zero2) {
   const int64_t n = nL > n0 ? nL : n0;
@@ -679,7 +721,7 @@ __global__ void k_final_init(int32_t* lab, int32_t* cntf, int32_t nL, int32_t* a
       sz0[i] = 0;
     }
   }
-  if (zero2 && blockIdx.x == 0 && threadIdx.x < 2) zero2[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 2) zero2[threadIdx.x] = 0;
 }
 
 }  // namespace
@@ -833,7 +875,7 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
                        const int32_t* sz, const int32_t* a, const uint64_t* ch_key,
                        const int32_t* ch_dk, int64_t nch, int32_t* map0, CoarseGraph& out,
                        int32_t* cnt_out, int32_t* minv_out, CoarsenScratch& s, IncCoarsen& H,
-                       hipStream_t st) {
+                       const FinalLabels& F, hipStream_t st) {
   const int32_t nl = g.n;
   int32_t* host = static_cast<int32_t*>(s.host);
   int32_t* hdev = static_cast<int32_t*>(s.host_dev);  // the kernels write the sizes the host reads here
@@ -885,6 +927,12 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
   A.ob = key_bits(nold);
   A.map0 = map0;
   A.minv = minv_out;
+  A.a0 = F.a0;
+  A.sz0 = F.sz0;
+  A.lab = F.lab;
+  A.cntf = F.cntf;
+  A.nc = nc;
+  A.zero2 = F.numerator;
   A.lkey = H.lkey.as<uint64_t>();
   A.lw = H.lw.as<int32_t>();
   A.lminv = H.lminv.as<int32_t>();
@@ -982,17 +1030,24 @@ void save_level1(const CoarseGraph& out, const CoarsenScratch& s, const int32_t*
   H.lnc = out.n;
 }
 
-void finalize_labels(int32_t nL, const int32_t* CL, const int32_t* aL, const int32_t* szL,
+void final_init(int32_t nL, int32_t n0, const FinalLabels& F, hipStream_t st) {
+  k_final_init<<<grid_for(nL > n0 ? nL : n0), TPB, 0, st>>>(F.lab, F.cntf, nL, F.a0, F.sz0, n0,
+                                                            F.numerator);
+  DC_LAUNCH_CHECK();
+}
+
+void finalize_labels(const LevelView& g, const int32_t* CL, const int32_t* aL, const int32_t* szL,
                      const int32_t* cntL, const int32_t* minvL, int32_t n0, const int32_t* map0,
-                     int32_t* lab, int32_t* cntf, int32_t* C0, int32_t* a0, int32_t* sz0,
-                     hipStream_t st, long long* zero2) {
-  k_final_init<<<grid_for(nL > n0 ? nL : n0), TPB, 0, st>>>(lab, cntf, nL, a0, sz0, n0, zero2);
+                     const FinalLabels& F, const long long* stat, int nstat, long long* host_stat,
+                     hipStream_t st) {
+  const int nbm = grid_for(g.n, 4096);
+  const int nb_intra = grid_for(int64_t(g.n) * WAVE, 4096);
+  const int nb_sq = grid_for(g.n, 2048);
+  k_final_min<<<nbm + nb_intra + nb_sq, TPB, 0, st>>>(g, CL, aL, cntL, minvL, F.lab, F.cntf, nbm,
+                                                      nb_intra, F.numerator, F.numerator + 1);
   DC_LAUNCH_CHECK();
-  k_final_min<<<grid_for(nL), TPB, 0, st>>>(CL, cntL, minvL, nL, lab, cntf);
-  DC_LAUNCH_CHECK();
-  k_final_scatter<<<grid_for(nL), TPB, 0, st>>>(lab, cntf, aL, szL, nL, a0, sz0);
-  DC_LAUNCH_CHECK();
-  k_final_project<<<grid_for(n0), TPB, 0, st>>>(lab, CL, map0, n0, C0);
+  k_final_project<<<grid_for(n0), TPB, 0, st>>>(F.lab, F.cntf, CL, aL, szL, g.n, F.a0, F.sz0,
+                                                map0, n0, F.C0, stat, nstat, host_stat);
   DC_LAUNCH_CHECK();
 }
 

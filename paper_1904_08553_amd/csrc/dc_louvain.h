@@ -426,6 +426,14 @@ struct IncCoarsen {
   DBuf ek0, ek1, ev0, ev1, orank, nrank, mpos, part64, part32, rkey, ssum, nruns;
 };
 
+// What finalize_labels writes: per community of the last level its smallest
+// level-0 id and level-0 size (scratch), the level-0 totals and sizes by
+// label, C_t, and the numerator's two sums {intra weight, sum of a^2}.
+struct FinalLabels {
+  int32_t *lab, *cntf, *a0, *sz0, *C0;
+  long long* numerator;
+};
+
 // Level 0 -> 1 from H(G_{t-1}, C_{t-1}) instead of all of G_t: H plus the
 // batch's directed changes mapped by Cold = C_{t-1} (ch_key / ch_dk, nch
 // records) plus the rows of the level-0 movers (Cl != Cold) moved from their
@@ -436,7 +444,7 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
                        const int32_t* sz, const int32_t* a, const uint64_t* ch_key,
                        const int32_t* ch_dk, int64_t nch, int32_t* map0, CoarseGraph& out,
                        int32_t* cnt_out, int32_t* minv_out, CoarsenScratch& s, IncCoarsen& H,
-                       hipStream_t st);
+                       const FinalLabels& F, hipStream_t st);
 // After the caller's next wait on the stream following coarsen_first_inc:
 // raises its self-check (an entry of an empty community or of weight below
 // 1 in the graph of communities), which the kernel reports in host memory.
@@ -445,12 +453,17 @@ void inc_check(CoarsenScratch& s);
 // coarsen_first_inc keeps its own as it builds it.
 void save_level1(const CoarseGraph& out, const CoarsenScratch& s, const int32_t* minv,
                  IncCoarsen& H, hipStream_t st);
-// Canonical labels of the final partition (smallest level-0 id per
-// community), the level-0 totals and sizes by label, and C_t.  zero2 (may
-// be null): two int64 counters cleared on the way (the caller's next sums).
-void finalize_labels(int32_t nL, const int32_t* CL, const int32_t* aL, const int32_t* szL,
+// Starting values of finalize_labels (lab, cntf: the last level's nL entries or
+// more); coarsen_first_inc sets them on its way.
+void final_init(int32_t nL, int32_t n0, const FinalLabels& F, hipStream_t st);
+// Canonical labels of the final partition CL (smallest level-0 id per
+// community) of the last level g, the level-0 totals and sizes by label, C_t,
+// and the exact numerator's sums (compaction preserves them).  The first
+// nstat slots of stat go to host_stat (device-visible pinned host memory), to
+// be read after a wait on the stream.
+void finalize_labels(const LevelView& g, const int32_t* CL, const int32_t* aL, const int32_t* szL,
                      const int32_t* cntL, const int32_t* minvL, int32_t n0, const int32_t* map0,
-                     int32_t* lab, int32_t* cntf, int32_t* C0, int32_t* a0, int32_t* sz0,
-                     hipStream_t st, long long* zero2 = nullptr);
+                     const FinalLabels& F, const long long* stat, int nstat, long long* host_stat,
+                     hipStream_t st);
 
 }  // namespace dc

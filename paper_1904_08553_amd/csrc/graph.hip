@@ -777,45 +777,7 @@ __global__ void k_sum_squares(const int32_t* __restrict__ a, int32_t n,
   block_add(s, S);
 }
 
-// Blocks [0, nb_intra) add the intra-community weight (one wave per row),
-// the others the squares of the label totals.
-__global__ void __launch_bounds__(TPB)
-    k_modularity_terms(const int32_t* __restrict__ off, const int2* __restrict__ adj,
-                       const int32_t* __restrict__ C, const int32_t* __restrict__ a, int32_t n,
-                       int nb_intra, long long* I, long long* S) {
-  long long s = 0;
-  if (int(blockIdx.x) < nb_intra) {
-    const int64_t nwaves = int64_t(nb_intra) * (TPB / WAVE);
-    const int lane = lane_id();
-    for (int64_t row = int64_t(blockIdx.x) * (TPB / WAVE) + threadIdx.x / WAVE; row < n;
-         row += nwaves) {
-      const int32_t c = C[row];
-      for (int32_t j = off[row] + lane; j < off[row + 1]; j += WAVE) {
-        const int2 e = adj[j];
-        if (C[e.x] == c) s += e.y;
-      }
-    }
-    block_add(s, I);
-  } else {
-    const int64_t nbs = int64_t(gridDim.x) - nb_intra;
-    for (int64_t i = (int64_t(blockIdx.x) - nb_intra) * TPB + threadIdx.x; i < n; i += nbs * TPB) {
-      const long long x = a[i];
-      s += x * x;
-    }
-    block_add(s, S);
-  }
-}
-
 }  // namespace
-
-void modularity_terms(const int32_t* off, const int2* adj, const int32_t* C, const int32_t* a,
-                      int32_t n, long long* I, long long* S, hipStream_t st) {
-  if (n <= 0) return;
-  const int nb_intra = grid_for(int64_t(n) * WAVE, TPB, 4096);
-  const int nb_sq = grid_for(n, TPB, 2048);
-  k_modularity_terms<<<nb_intra + nb_sq, TPB, 0, st>>>(off, adj, C, a, n, nb_intra, I, S);
-  DC_LAUNCH_CHECK();
-}
 
 void validate_edges(const int32_t* u, const int32_t* v, const int32_t* w,
                     int64_t m, int32_t n, int32_t* flags, long long* wsum,
