@@ -262,6 +262,14 @@ void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& 
   screening_counts(c);
 }
 
+// The bins of a level above 0, every vertex active.
+void coarse_bins(dc_ctx* c, const LevelView& g, Bins& b) {
+  if (g.n <= SMALL_LEVEL)
+    small_level(g, b, c->bins);
+  else
+    make_bins(nullptr, g.n, g.off, b, c->bins, c->st, nullptr, nullptr, nullptr, nullptr, 0, true);
+}
+
 // The step's level and sweep counts, and its numerator and modularity from
 // the status block in c->hstat.
 void final_stats(dc_ctx* c) {
@@ -291,9 +299,7 @@ void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
   while (true) {
     if (level > 0) {
       Bins bins;
-      make_bins(nullptr, g.n, g.off, bins, c->bins, st, nullptr, nullptr, nullptr, nullptr, 0,
-                true);
-      inc_check(c->cs);
+      coarse_bins(c, g, bins);
       level_gain = run_sweeps(c, g, nullptr, g.n, bins, level, T, true);
     }
     const bool stop = (level + 1 >= c->opt.max_levels) || (level >= 1 && level_gain <= T);
@@ -337,7 +343,6 @@ void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
   }
   DC_HIP(hipStreamSynchronize(st));
   check_stat_errors(c->hstat);
-  inc_check(c->cs);
   final_stats(c);
 }
 
@@ -387,8 +392,10 @@ void run_levels_slm(dc_ctx* c, const int32_t* active, int64_t n_active) {
     start_level(Cl, Cn, al, szl, g.k, g.n, st);
     const LevelView gs{g.n, nnz_s, c->sub_off.as<int32_t>(), c->sub_adj.as<int2>(), g.k};
     Bins rb;
-    make_bins(nullptr, g.n, gs.off, rb, c->bins, st, nullptr, nullptr, nullptr, nullptr, 0,
-              level > 0);
+    if (level > 0)
+      coarse_bins(c, gs, rb);
+    else
+      make_bins(nullptr, g.n, gs.off, rb, c->bins, st);
     (void)run_sweeps(c, gs, nullptr, g.n, rb, level, T, true, false, 1);
     // 4. compaction by the refined communities
     const int next = level % 2;
@@ -412,7 +419,7 @@ void run_levels_slm(dc_ctx* c, const int32_t* active, int64_t n_active) {
     totals_sizes(g.k, Cl, g.n, al, szl, st);
     if (!reduced) break;
     Bins b;
-    make_bins(nullptr, g.n, g.off, b, c->bins, st, nullptr, nullptr, nullptr, nullptr, 0, true);
+    coarse_bins(c, g, b);
     (void)run_sweeps(c, g, nullptr, g.n, b, level, T, true);
   }
   const int32_t *cntL, *minvL;

@@ -659,13 +659,15 @@ __global__ void __launch_bounds__(SCAN_THREADS)
 // level-1 graph kept for the next step (pair keys, weights; smallest members
 // copied from minv).  An entry of an empty community or of weight below 1
 // (cannot happen when the kept graph is the graph of communities it claims
-// to be) sets the flag in host memory; the entry count goes there too.
+// to be) sets the flag in host memory; the entry count goes there too, and the
+// last block to finish publishes both, so that nothing walks a graph that the
+// check has refused.
 __global__ void __launch_bounds__(SCAN_THREADS)
     k_inc_csr(const uint64_t* __restrict__ rkey, const uint32_t* __restrict__ ssum,
               const int32_t* __restrict__ nruns, const int32_t* __restrict__ part, int raw,
               int64_t nt, const int32_t* __restrict__ nrank, int ob, int nb, int2* adj,
               uint64_t* lkey, int32_t* lw, const int32_t* __restrict__ minv, int32_t* lminv,
-              int32_t nc, int32_t* host, uint32_t* tag, uint32_t tag_value) {
+              int32_t nc, int32_t* host, unsigned* done, uint32_t* tag, uint32_t tag_value) {
   __shared__ int32_t lds[SCAN_THREADS / WAVE];
   for (int64_t r = int64_t(blockIdx.x) * SCAN_THREADS + threadIdx.x; r < nc;
        r += int64_t(gridDim.x) * SCAN_THREADS)
@@ -696,9 +698,9 @@ __global__ void __launch_bounds__(SCAN_THREADS)
     ++p;
   }
   if (bad) host_store(host + 2, 1);
-  if (blockIdx.x != nt - 1) return;
-  if (threadIdx.x == 0) host_store(host, offs + tot);
-  host_publish(tag, tag_value);
+  if (blockIdx.x == nt - 1 && threadIdx.x == 0) host_store(host, offs + tot);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // performed before the block counts
+  if (last_block(done)) host_publish(tag, tag_value);  // as finished
 }
 
 __global__ void k_adj_weights(const int2* __restrict__ adj, int64_t m, int32_t* w) {
@@ -965,7 +967,10 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
     const uint32_t* ew = second ? H.ev1.as<uint32_t>() : A.ew;
     H.rkey.ensure(size_t(m + 1) * 8);
     H.ssum.ensure(size_t(m + 1) * 4);
-    H.nruns.ensure(4);
+    if (!H.nruns.p) {  // the run count, then the finished blocks (zero between launches)
+      H.nruns.ensure((DONE_STRIDE + DONE_WORDS) * 4);
+      fill_i32(H.nruns.as<int32_t>(), 0, DONE_STRIDE + DONE_WORDS, st);
+    }
     const int64_t mt = ceil_div(m, SCAN_TILE);
     H.part64.ensure(size_t(mt) * 8);
     H.part32.ensure(size_t(mt) * 4);
@@ -993,24 +998,18 @@ void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Col
         H.rkey.as<uint64_t>(), H.ssum.as<uint32_t>(), H.nruns.as<int32_t>(), one ? nullptr : p32,
         mraw, mt, H.nrank.as<int32_t>(), A.ob, key_bits(nc), out.adj.as<int2>(),
         H.lkey.as<uint64_t>(), H.lw.as<int32_t>(), minv_out, H.lminv.as<int32_t>(), nc, hdev,
-        s.tag.dev, s.tag.next());
+        H.nruns.as<unsigned>() + DONE_STRIDE, s.tag.dev, s.tag.next());
     DC_LAUNCH_CHECK();
     wait_tag(s.tag, st);
     cnnz = host[0];
+    if (host[2])
+      throw std::runtime_error("incremental coarsening: inconsistent community graph");
   }
-  s.inc_check = true;  // read by inc_check
   row_bounds(H.lkey.as<uint64_t>(), cnnz, nc, out.off.as<int32_t>(), st);
   out.n = nc;
   out.nnz = cnnz;
   H.lh = cnnz;
   H.lnc = nc;
-}
-
-void inc_check(CoarsenScratch& s) {
-  if (!s.inc_check) return;
-  s.inc_check = false;
-  if (static_cast<const int32_t*>(s.host)[2])
-    throw std::runtime_error("incremental coarsening: inconsistent community graph");
 }
 
 void save_level1(const CoarseGraph& out, const CoarsenScratch& s, const int32_t* minv,

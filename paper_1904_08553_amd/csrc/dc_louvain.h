@@ -117,6 +117,7 @@ struct Bins {
   long long vol[NBINS];       // adjacency entries of each bin
   int64_t total = 0;          // vertices binned (the sum of n)
   const int32_t* all;         // and all of them, bin after bin
+  bool small = false;         // small_level: nothing is listed, every vertex is evaluated
   const int32_t* count_dev;   // NBINS device counts
   // each bin's list starts with the vertices that make_bins' skip flags
   // leave unset: their number, volume and device counts
@@ -170,6 +171,12 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
                hipStream_t st, const uint8_t* skip = nullptr, const int32_t* dcount = nullptr,
                const long long* copy_src = nullptr, long long* copy_dst = nullptr,
                int copy_n = 0, bool coarse = false);
+
+// Levels above 0 of at most SMALL_LEVEL vertices are swept without bins: a wave
+// takes a row of any length, its label weights in a table with a slot per
+// label (b counts every vertex; s.counts must be there, from a make_bins).
+constexpr int SMALL_LEVEL = 2048;
+void small_level(const LevelView& g, Bins& b, BinScratch& s);
 
 // The start of a level 0 (k_level0_start), binned as make_bins would bin R_t.
 struct Level0Start {
@@ -391,7 +398,6 @@ struct CoarsenScratch {
   void* host = nullptr;      // pinned, 64 bytes
   void* host_dev = nullptr;  // its address for the kernels that write it
   HostTag tag;
-  bool inc_check = false;    // coarsen_first_inc's self-check flag awaits a wait
 };
 
 struct CoarseGraph {
@@ -438,17 +444,14 @@ struct FinalLabels {
 // batch's directed changes mapped by Cold = C_{t-1} (ch_key / ch_dk, nch
 // records) plus the rows of the level-0 movers (Cl != Cold) moved from their
 // old labels to their new ones, summed by one sort; the result (entries of
-// zero weight dropped) is the coarse graph of (G_t, Cl), numbered as
+// zero weight dropped; one of an empty community or of weight below 1 raises)
+// is the coarse graph of (G_t, Cl), numbered as
 // coarsen() numbers it.  Outputs as coarsen(first_level = true).
 void coarsen_first_inc(const LevelView& g, const int32_t* Cl, const int32_t* Cold,
                        const int32_t* sz, const int32_t* a, const uint64_t* ch_key,
                        const int32_t* ch_dk, int64_t nch, int32_t* map0, CoarseGraph& out,
                        int32_t* cnt_out, int32_t* minv_out, CoarsenScratch& s, IncCoarsen& H,
                        const FinalLabels& F, hipStream_t st);
-// After the caller's next wait on the stream following coarsen_first_inc:
-// raises its self-check (an entry of an empty community or of weight below
-// 1 in the graph of communities), which the kernel reports in host memory.
-void inc_check(CoarsenScratch& s);
 // Keeps the level-1 graph just built (and its vertices' smallest members);
 // coarsen_first_inc keeps its own as it builds it.
 void save_level1(const CoarseGraph& out, const CoarsenScratch& s, const int32_t* minv,

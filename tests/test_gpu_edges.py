@@ -107,3 +107,29 @@ def test_initial_csr_at_sort_sizes(records):
     assert np.array_equal(np.repeat(np.arange(n), np.diff(off)) * n + col, uk)
     assert np.array_equal(cw, np.bincount(inv, weights=np.concatenate([w, w])).astype(np.int64))
     g.close()
+
+
+@pytest.mark.parametrize("slm", [False, True])
+@pytest.mark.parametrize("cliques", [1, 65, 2047, 2048, 2049])
+def test_level_one_sizes(cliques, slm):
+    """A chain of heavy triangles: level 0 ends with one community each, so
+    level 1 has as many vertices, on both sides of the size up to which a
+    level is swept without bins; then changes that merge and split some."""
+    print(f"case: level 1 of {cliques} vertices slm={slm}", flush=True)
+    t = np.arange(cliques) * 3
+    u = np.concatenate([t, t, t + 1, t[:-1] + 2]).astype(np.int32)
+    v = np.concatenate([t + 1, t + 2, t + 2, t[1:]]).astype(np.int32)
+    w = np.concatenate([np.full(3 * cliques, 9), np.full(cliques - 1, 1)]).astype(np.int32)
+    n = 3 * cliques
+    o, g = make_pair(n, u, v, w, slm=slm)
+    compare(o, g, "init")
+    k = t[: cliques // 2]
+    near = np.column_stack([k, k + 4]) if len(k) else np.empty((0, 2), int)
+    first = W.Batch(near[:, 0].astype(np.int32), near[:, 1].astype(np.int32),
+                    np.full(len(near), 7, np.int32), t[: 1 + cliques // 5].astype(np.int32),
+                    (t[: 1 + cliques // 5] + 1).astype(np.int32))
+    second = W.Batch(first.del_u, first.del_v, np.full(len(first.del_u), 3, np.int32),
+                     first.add_u, first.add_v)
+    for i, b in enumerate((first, second)):
+        step_pair(o, g, b)
+        compare(o, g, f"cliques={cliques} step {i}")
