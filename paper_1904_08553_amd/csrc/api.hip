@@ -180,7 +180,7 @@ long long run_sweeps(dc_ctx* c, const LevelView& g, const int32_t* act, int64_t 
   Bins bins = pre_done ? first_part(all_bins) : all_bins;
   for (int s = 0; s < c->opt.max_sweeps; ++s) {
     if (s == 1) bins = all_bins;
-    const bool timed = record && c->opt.timing && bins.n[0] + bins.n[1] + bins.n[2] > 0;
+    const bool timed = record && c->opt.timing && short_rows(bins) > 0;
     sweep_eval(g, c->Cl.as<int32_t>(), c->Cn.as<int32_t>(), c->al.as<int32_t>(),
                c->szl.as<int32_t>(), c->two_m, c->opt.singleton_guard, bins,
                c->stat.as<long long>(), st, timed ? c->ev0 : nullptr,

@@ -138,10 +138,10 @@ __device__ __forceinline__ void wave_sync() {
 // joined with two readlanes.  No step goes through ds_bpermute.
 template <int S>
 __device__ __forceinline__ int xchg(int v) {
-  if constexpr (S == 0) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);
-  else if constexpr (S == 1) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);
-  else if constexpr (S == 2) return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);
-  else if constexpr (S == 3) return __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);
+  if constexpr (S == 0) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);
+  else if constexpr (S == 1) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);
+  else if constexpr (S == 2) return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);
+  else if constexpr (S == 3) return __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true);
   else return __builtin_amdgcn_ds_swizzle(v, 0x401F);
 }
 
@@ -158,7 +158,7 @@ __device__ __forceinline__ long long readlane64(long long v, int l) {
   return (long long)((uint64_t(hi) << 32) | lo);
 }
 
-// Integer wave sums and maxima (exact, so the combining order is free).
+// Integer wave sums (exact, so the combining order is free).
 __device__ __forceinline__ int wave_sum(int v) {
   v += xchg<0>(v);
   v += xchg<1>(v);
@@ -179,17 +179,6 @@ __device__ __forceinline__ long long wave_sum(long long v) {
 
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
   return (unsigned long long)wave_sum((long long)v);
-}
-
-__device__ __forceinline__ int wave_max(int v) {
-  int y;
-  y = xchg<0>(v); v = y > v ? y : v;
-  y = xchg<1>(v); v = y > v ? y : v;
-  y = xchg<2>(v); v = y > v ? y : v;
-  y = xchg<3>(v); v = y > v ? y : v;
-  y = xchg<4>(v); v = y > v ? y : v;
-  const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 32);
-  return a > b ? a : b;
 }
 
 __device__ __forceinline__ int wave_or(int v) {

@@ -50,15 +50,15 @@ inline long long slot_total(const long long* h, int base) {
 enum EvalMode : int { EV_SWEEP = 0, EV_DSADD = 1, EV_DSDEL = 2, EV_FEAT = 3, EV_DSBOTH = 4 };
 constexpr long long NO_GAIN = (long long)0x8000000000000000ull;
 
-// Row-length bins of the evaluation kernels (eval.hip): rows of at most 16,
-// 32 and 64 entries (4, 2 and 1 vertices per wave, no table), then
-constexpr int NBINS = 6;
+// Row-length bins of the evaluation kernels (eval.hip): rows of at most 8, 16,
+// 32 and 64 entries (8, 4, 2 and 1 vertices per wave, no table), then
+enum RowBin : int { BIN_8 = 0, BIN_16, BIN_32, BIN_64, BIN_W, BIN_B, BIN_G, NBINS };
 constexpr int WTAB_MAX = 512;     // one wave, wave-private LDS table
 constexpr int WTAB_SLOTS = 1024;  // (merged sweeps; single graphs use 512 slots
                                   // and a full-table retry on overflow)
 constexpr int BTAB_MAX = 4096;    // one block, block LDS table
 constexpr int BTAB_SLOTS = 8192;  // beyond: one block, global table
-constexpr int TIMED_BINS = 3;     // the timing option brackets the launch of bins [0, 3)
+constexpr int TIMED_BINS = BIN_W;  // the timing option brackets the launch of the bins before W
 
 struct LevelView {
   int32_t n;
@@ -134,6 +134,11 @@ struct Bins {
   hipEvent_t fork;     // bins (null: on the caller's stream)
   hipEvent_t join;
 };
+
+// The vertices of the bins that one launch takes (rows of at most 64 entries).
+inline int64_t short_rows(const Bins& b) {
+  return b.n[BIN_8] + b.n[BIN_16] + b.n[BIN_32] + b.n[BIN_64];
+}
 
 // The bins restricted to their first parts (the vertices not skipped).
 inline Bins first_part(const Bins& b) {

@@ -56,13 +56,12 @@ __device__ __forceinline__ bool cand_better(const Cand& p, const Cand& q) {
 // two, and no row is walked a second time.
 
 // --------------------------------------------------------------------------
-// bins S16/S32/S64: rows of at most GS entries, no table.  A wave is split
+// bins 8/16/32/64: rows of at most GS entries, no table.  A wave is split
 // into 64/GS groups of GS lanes, each group evaluating its own vertex: wave
-// instructions cost the same for 16 or 64 busy lanes, so packing four
-// 16-entry rows into one wave divides the instruction count per vertex by
-// four.  Ballots stay wave-wide, each group's leader label is read with a
-// scalar readlane, and reductions run within the group on DPP row
-// exchanges.
+// instructions cost the same for 8 or 64 busy lanes, so packing eight
+// 8-entry rows into one wave divides the instruction count per vertex by
+// eight.  Ballots stay wave-wide, and the exchanges and reductions run within
+// the group on DPP.
 
 template <int GS, int S = 0>
 __device__ __forceinline__ long long group_sum_ll(long long v) {
@@ -105,17 +104,55 @@ __device__ __forceinline__ Cand group_cand_w(Cand c) {
   }
 }
 
-// Value of lane r (uniform) of each lane's own group.
+// Value of the first lane of each lane's own group.
 template <int GS>
-__device__ __forceinline__ int group_bcast(int v, int r) {
-  constexpr int GPW = WAVE / GS;
-  int out = 0;
-#pragma unroll
-  for (int g = 0; g < GPW; ++g) {
-    const int x = __builtin_amdgcn_readlane(v, g * GS + r);
-    if (int(lane_id()) / GS == g) out = x;
+__device__ __forceinline__ int group_bcast(int v) {
+  if constexpr (GS == WAVE) return __builtin_amdgcn_readfirstlane(v);
+  return __shfl(v, lane_id() & ~(GS - 1), WAVE);
+}
+
+// Value of another lane of the own half row (GS = 8) or row (GS = 16): K = 1
+// .. GS - 1 name all the others, each once (the quads' permutations, straight
+// and after a half-row mirror; the row's rotations).
+template <int GS, int K>
+__device__ __forceinline__ int group_peer(int v) {
+  static_assert((GS == 8 || GS == 16) && K > 0 && K < GS, "a DPP exchange per peer");
+  if constexpr (GS == 16)
+    return __builtin_amdgcn_update_dpp(0, v, 0x120 + K, 0xF, 0xF, true);
+  else if constexpr (K == 1 || K == 2)
+    return xchg<K - 1>(v);
+  else if constexpr (K == 3)
+    return __builtin_amdgcn_update_dpp(0, v, 0x1B, 0xF, 0xF, true);
+  else if constexpr (K == 4)
+    return xchg<2>(v);
+  else
+    return group_peer<GS, K - 4>(xchg<2>(v));
+}
+
+// s plus the weights of the group's other lanes whose label is x.  Every two
+// peers end in a fence for the scheduler, which would take all exchanges first
+// (101 registers in the sweep for 50, 129 in the screening pass for 69).
+template <int GS, int K = 1>
+__device__ __forceinline__ int group_peers_of(int x, int key, int w, int s) {
+  if constexpr (GS == 32) {  // the own row, then the other
+    s = group_peers_of<16>(x, key, w, s);
+    const int yk = xchg<4>(key), yw = xchg<4>(w);
+    return group_peers_of<16>(x, yk, yw, s + (yk == x ? yw : 0));
+  } else if constexpr (K == GS) {
+    return s;
+  } else {
+    if constexpr (K % 2 == 0) asm("" : "+v"(key), "+v"(w), "+v"(s));
+    const int y = group_peer<GS, K>(key), z = group_peer<GS, K>(w);
+    return group_peers_of<GS, K + 1>(x, key, w, s + (y == x ? z : 0));
   }
-  return out;
+}
+
+template <int GS, int S = 0>
+__device__ __forceinline__ int group_sum(int v) {
+  if constexpr ((1 << S) >= GS)
+    return v;
+  else
+    return group_sum<GS, S + 1>(v + xchg<S>(v));
 }
 
 // The value of the lane of each lane's own group whose flag is set (at most
@@ -191,6 +228,69 @@ __device__ __forceinline__ int group_collect(bool valid, int key, int w, int* ls
   wave_sync();
   if (iters) *iters = it;  // wave-uniform: the largest count of any group
   return r;
+}
+
+// The labels of a group's valid lanes with their weight sums, and the sum of
+// label c (own).  A lane for which it returns true holds a label (ck) and that
+// label's sum (cs).  In groups of at most 32 lanes every lane compares its own
+// label with all the others', so several lanes may hold one label: straight-line
+// DPP code of two exchanges and three operations per peer, where the loop of
+// group_collect takes one label of each group per turn (a readlane and selects
+// per group) and ends in LDS atomics.  Its turns are as many as the distinct
+// labels of the wave's worst group: sweeps of the 316K planted graph took
+// 14.5 us with it and take 7.8, those of an 8M-vertex temporal graph 414 and
+// 362 (there L2 misses of the label gathers bound both), the first ones of a
+// 300K graph, from singletons, 78.6 and 65.6.  For 64 lanes the 63 compares are
+// more than the few turns most rows need.
+// it: a bound, one for the wave, of the lanes of a group that hold labels.
+template <int GS>
+__device__ __forceinline__ bool group_labels(bool valid, int y, int w, int c, int* lsum, int& ck,
+                                             int& cs, int& own, int& it) {
+  const int key = valid ? y : EMPTY_KEY;
+  if constexpr (GS <= 32) {
+    const int wv = valid ? w : 0;
+    ck = key;
+    cs = group_peers_of<GS>(key, key, wv, wv);
+    own = group_sum<GS>(key == c ? wv : 0);
+    it = GS;
+    return valid;
+  } else {
+    const int nd = group_collect<GS>(valid, key, w, lsum, ck, cs, &it);
+    const bool has = (lane_id() & (GS - 1)) < nd;
+    own = group_pick<GS>(has && ck == c, cs);
+    return has;
+  }
+}
+
+// The same, and the sum of label X in the lanes with sink set (the label is
+// one of the group's): sx, of no meaning in the others.
+template <int GS>
+__device__ __forceinline__ bool group_labels(bool valid, int y, int w, int c, int* lsum, int& ck,
+                                             int& cs, int& own, int& it, bool sink, int X,
+                                             int& sx) {
+  sx = 0;
+  if constexpr (GS <= 32) {
+    const bool has = group_labels<GS>(valid, y, w, c, lsum, ck, cs, own, it);
+    const int wv = valid ? w : 0;
+    const int lane = lane_id(), gl = lane & (GS - 1);
+    // the sinks sit in a group's first lanes; few sources have more than one
+    for (int r = 0; __ballot(sink && gl == r); ++r) {  // wave-uniform
+      const int Xr = __shfl(X, lane - gl + r, WAVE);
+      const int sum = group_sum<GS>(ck == Xr ? wv : 0);
+      if (gl == r) sx = sum;
+    }
+    return has;
+  } else {
+    const int lane = lane_id(), gl = lane & (GS - 1);
+    int xr = -1;
+    const int nd = group_collect<GS>(valid, valid ? y : EMPTY_KEY, w, lsum, ck, cs, &it,
+                                     sink ? X : EMPTY_KEY, &xr);
+    const int sv = __shfl(cs, lane - gl + (xr < 0 ? 0 : xr), WAVE);
+    if (xr >= 0) sx = sv;
+    const bool has = gl < nd;
+    own = group_pick<GS>(has && ck == c, cs);
+    return has;
+  }
 }
 
 // Best (score, label) of lanes [0, 2^steps) of each group, in the group's
@@ -283,29 +383,21 @@ __device__ __forceinline__ long long group_item(const EvalArgs& A, int i, bool h
   const long long ki = have ? A.k[i] : 0;
   const int2 e = rb + gl < re ? A.adj[rb + gl] : make_int2(-1, 0);
   const bool valid = e.x >= 0 && e.x != i;
-  const int key = valid ? A.C[e.x] : EMPTY_KEY;
-  int ck = EMPTY_KEY, cs = 0;
-  const int nd = group_collect<GS>(valid, key, e.y, lsum, ck, cs);
-  const bool pair = gl < nd;
-  const long long e_own = group_pick<GS>(pair && ck == c, cs);
+  const int y = valid ? A.C[e.x] : EMPTY_KEY;
   const int tm = int(A.two_m);  // 2m < 2^31: 32x32->64 products
-  const long long s_own = (long long)tm * e_own - ki * ((have ? A.a[c] : 0) - ki);
-  if (MODE == EV_DSADD) {
+  int ck = EMPTY_KEY, cs = 0, own = 0, it = 0;
+  if constexpr (MODE == EV_DSADD) {
     const int q0 = have ? A.seg_beg[i] : 0;
     const int nsk = have ? A.seg_end[i] - q0 : 0;  // sinks are neighbours: <= GS
     const bool has = gl < nsk;
     const int sj = has ? int(key_col(A.ins_keys[q0 + gl], A.kb)) : 0;
     const int Xj = has ? A.C[sj] : EMPTY_KEY;
-    long long ej = 0;
-    const int ndw = wave_max(nd);
-    for (int r = 0; r < ndw; ++r) {
-      const int kr = group_bcast<GS>(ck, r);
-      const int sr = group_bcast<GS>(cs, r);
-      if (r < nd && Xj == kr) ej = sr;
-    }
+    int ej = 0;
+    group_labels<GS>(valid, y, e.y, c, lsum, ck, cs, own, it, has, Xj, ej);
+    const long long s_own = (long long)tm * own - ki * ((have ? A.a[c] : 0) - ki);
     Cand cd = {NO_SCORE, NO_LABEL, NO_LABEL};
     if (has) {
-      long long g = Xj == c ? 0 : (long long)tm * int(ej) - (long long)int(ki) * A.a[Xj] - s_own;
+      long long g = Xj == c ? 0 : (long long)tm * ej - (long long)int(ki) * A.a[Xj] - s_own;
       cd = {g, Xj, sj};
       A.sink_g[q0 + gl] = g;
     }
@@ -317,6 +409,8 @@ __device__ __forceinline__ long long group_item(const EvalArgs& A, int i, bool h
     }
     return accepted;
   }
+  const bool pair = group_labels<GS>(valid, y, e.y, c, lsum, ck, cs, own, it);
+  const long long s_own = (long long)tm * own - ki * ((have ? A.a[c] : 0) - ki);
   Best b = {NO_SCORE, NO_LABEL};
   if (pair && ck != c) b = {(long long)tm * cs - (long long)int(ki) * A.a[ck], ck};
   b = group_best_w<GS>(b);
@@ -357,17 +451,13 @@ __device__ __forceinline__ void sweep_pair(const EvalArgs& A, int i0, bool h0, i
   const int ao0 = A.a[c0], ao1 = A.a[c1];
   const bool v0 = rb0 + gl < re0 && e0.x != i0, v1 = rb1 + gl < re1 && e1.x != i1;
   const int y0 = A.C[v0 ? e0.x : 0], y1 = A.C[v1 ? e1.x : 0];  // e.x is only valid in-row
-  const int key0 = v0 ? y0 : EMPTY_KEY;
-  const int key1 = v1 ? y1 : EMPTY_KEY;
   int ck0 = EMPTY_KEY, cs0 = 0, ck1 = EMPTY_KEY, cs1 = 0, it0 = 0, it1 = 0;
-  const int nd0 = group_collect<GS>(v0, key0, e0.y, lsum, ck0, cs0, &it0);
-  const int nd1 = group_collect<GS>(v1, key1, e1.y, lsum, ck1, cs1, &it1);
-  const bool p0 = gl < nd0 && ck0 != c0, p1 = gl < nd1 && ck1 != c1;
+  int own0, own1;  // e_{i->C(i)}
+  const bool l0 = group_labels<GS>(v0, y0, e0.y, c0, lsum, ck0, cs0, own0, it0);
+  const bool l1 = group_labels<GS>(v1, y1, e1.y, c1, lsum, ck1, cs1, own1, it1);
+  const bool p0 = l0 && ck0 != c0, p1 = l1 && ck1 != c1;
   const int ak0 = A.a[p0 ? ck0 : 0];
   const int ak1 = A.a[p1 ? ck1 : 0];
-  // e_{i->C(i)}: the weight sum parked in the one lane holding label C(i)
-  const int own0 = group_pick<GS>(gl < nd0 && ck0 == c0, cs0);
-  const int own1 = group_pick<GS>(gl < nd1 && ck1 == c1, cs1);
   // 2m < 2^31, so every factor fits in 32 bits: one 32x32->64 product each
   const int tm = int(A.two_m);
   const long long s0 = (long long)tm * own0 - (long long)k0 * (ao0 - k0);
@@ -401,12 +491,11 @@ __device__ __forceinline__ void feat_pair(const EvalArgs& A, int i0, bool h0, in
   const bool v0 = rb0 + gl < re0 && e0.x != i0, v1 = rb1 + gl < re1 && e1.x != i1;
   const int y0 = A.C[v0 ? e0.x : 0], y1 = A.C[v1 ? e1.x : 0];
   int ck0 = EMPTY_KEY, cs0 = 0, ck1 = EMPTY_KEY, cs1 = 0, it0 = 0, it1 = 0;
-  const int nd0 = group_collect<GS>(v0, v0 ? y0 : EMPTY_KEY, e0.y, lsum, ck0, cs0, &it0);
-  const int nd1 = group_collect<GS>(v1, v1 ? y1 : EMPTY_KEY, e1.y, lsum, ck1, cs1, &it1);
-  const bool p0 = gl < nd0 && ck0 != c0, p1 = gl < nd1 && ck1 != c1;
+  int own0, own1;
+  const bool l0 = group_labels<GS>(v0, y0, e0.y, c0, lsum, ck0, cs0, own0, it0);
+  const bool l1 = group_labels<GS>(v1, y1, e1.y, c1, lsum, ck1, cs1, own1, it1);
+  const bool p0 = l0 && ck0 != c0, p1 = l1 && ck1 != c1;
   const int ak0 = A.a[p0 ? ck0 : 0], ak1 = A.a[p1 ? ck1 : 0];
-  const int own0 = group_pick<GS>(gl < nd0 && ck0 == c0, cs0);
-  const int own1 = group_pick<GS>(gl < nd1 && ck1 == c1, cs1);
   const int tm = int(A.two_m);  // 2m < 2^31: 32x32->64 products
   const long long s0 = (long long)tm * own0 - (long long)k0 * (ao0 - k0);
   const long long s1 = (long long)tm * own1 - (long long)k1 * (ao1 - k1);
@@ -415,7 +504,7 @@ __device__ __forceinline__ void feat_pair(const EvalArgs& A, int i0, bool h0, in
   if (p1) b1 = {(long long)tm * cs1 - (long long)k1 * ak1, ck1};
   const Best f0 = group_best_first<GS>(b0, it0), f1 = group_best_first<GS>(b1, it1);
   // second best: the same candidates without the best label
-  const int x0b = group_bcast<GS>(f0.x, 0), x1b = group_bcast<GS>(f1.x, 0);
+  const int x0b = group_bcast<GS>(f0.x), x1b = group_bcast<GS>(f1.x);
   const Best g0 = group_best_first<GS>(b0.x != x0b ? b0 : Best{NO_SCORE, NO_LABEL}, it0);
   const Best g1 = group_best_first<GS>(b1.x != x1b ? b1 : Best{NO_SCORE, NO_LABEL}, it1);
   if (gl == 0) {
@@ -471,23 +560,16 @@ __device__ __forceinline__ long long screen_pair(const EvalArgs& A, int i0, bool
   const int j0 = s0 ? int(key_col(kq0, A.kb)) : 0;
   const int j1 = s1 ? int(key_col(kq1, A.kb)) : 0;
   const int X0 = A.C[j0], X1 = A.C[j1];
-  // the labels are grouped as in the sweep; a sink lane also learns the rank
-  // of its sink's label among them (a sink is an entry of the row, so its
-  // label is there), and reads that label's weight from the lane holding it
-  int ck0 = EMPTY_KEY, cs0 = 0, ck1 = EMPTY_KEY, cs1 = 0, it0 = 0, it1 = 0, xr0 = -1, xr1 = -1;
-  const int nd0 = group_collect<GS>(v0, v0 ? y0 : EMPTY_KEY, e0.y, lsum, ck0, cs0, &it0,
-                                    s0 ? X0 : EMPTY_KEY, &xr0);
-  const int nd1 = group_collect<GS>(v1, v1 ? y1 : EMPTY_KEY, e1.y, lsum, ck1, cs1, &it1,
-                                    s1 ? X1 : EMPTY_KEY, &xr1);
-  const int gbase = lane_id() - gl;
-  const int sx0 = __shfl(cs0, gbase + (xr0 < 0 ? 0 : xr0), WAVE);
-  const int sx1 = __shfl(cs1, gbase + (xr1 < 0 ? 0 : xr1), WAVE);
-  const int ej0 = xr0 < 0 ? 0 : sx0, ej1 = xr1 < 0 ? 0 : sx1;
-  const bool p0 = gl < nd0 && ck0 != c0, p1 = gl < nd1 && ck1 != c1;
+  // the labels are grouped as in the sweep; a sink lane also learns the weight
+  // to its sink's label (a sink is an entry of the row, so its label is there)
+  int ck0 = EMPTY_KEY, cs0 = 0, ck1 = EMPTY_KEY, cs1 = 0, it0 = 0, it1 = 0;
+  int own0, own1, ej0, ej1, e1w = e1.y;
+  const bool l0 = group_labels<GS>(v0, y0, e0.y, c0, lsum, ck0, cs0, own0, it0, s0, X0, ej0);
+  asm("" : "+v"(ej0), "+v"(cs0), "+v"(own0), "+v"(e1w));  // one item's sums, then the other's
+  const bool l1 = group_labels<GS>(v1, y1, e1w, c1, lsum, ck1, cs1, own1, it1, s1, X1, ej1);
+  const bool p0 = l0 && ck0 != c0, p1 = l1 && ck1 != c1;
   const int ak0 = A.a[p0 ? ck0 : 0], ak1 = A.a[p1 ? ck1 : 0];
   const int ax0 = A.a[X0], ax1 = A.a[X1];
-  const int own0 = group_pick<GS>(gl < nd0 && ck0 == c0, cs0);
-  const int own1 = group_pick<GS>(gl < nd1 && ck1 == c1, cs1);
   const int tm = int(A.two_m);  // 2m < 2^31: 32x32->64 products
   const long long so0 = (long long)tm * own0 - (long long)k0 * (ao0 - k0);
   const long long so1 = (long long)tm * own1 - (long long)k1 * (ao1 - k1);
@@ -532,8 +614,9 @@ __device__ __forceinline__ long long screen_pair(const EvalArgs& A, int i0, bool
   const bool d0 = gl == 0 && m0 && (uf0 & 2), d1 = gl == 0 && m1 && (uf1 & 2);
   if (__ballot(d0 || d1)) {  // wave-uniform; a deletion endpoint that would move
     // its group's lanes mark the row (the leader's decision, broadcast)
-    if (group_pick<GS>(d0, 1) && in0) A.R[e0.x] = 1;
-    if (group_pick<GS>(d1, 1) && in1) A.R[e1.x] = 1;
+    const int lead = lane_id() - gl;
+    if ((__ballot(d0) >> lead & 1) && in0) A.R[e0.x] = 1;
+    if ((__ballot(d1) >> lead & 1) && in1) A.R[e1.x] = 1;
     if (d0) {
       A.R[i0] = 1;
       A.cflag[b0.x] = 1;
@@ -548,16 +631,23 @@ __device__ __forceinline__ long long screen_pair(const EvalArgs& A, int i0, bool
   return accepted;
 }
 
+// A bin's vertices, their row starts and number (on the device).
+struct BinList {
+  const int32_t* list;
+  const int32_t* list_rb;
+  const int32_t* count;
+};
+
 // The items of one row-length bin of at most 64 entries, groups of GS
 // lanes, as block bid of nblocks (ls: the wave's zeroed LDS row).
 template <int MODE, int GS>
-__device__ __forceinline__ void eval_group_body(const EvalArgs& A, int64_t bid, int64_t nblocks,
-                                                int* ls) {
+__device__ __forceinline__ void eval_group_body(const EvalArgs& A, const BinList& L, int64_t bid,
+                                                int64_t nblocks, int* ls) {
   constexpr int GPW = WAVE / GS;  // groups per wave
   const int lane = lane_id();
   const int gl = lane & (GS - 1);
   const int gbase = lane - gl;
-  const int64_t cnt = *A.count;
+  const int64_t cnt = *L.count;
   const int64_t ngroups = nblocks * NW * GPW;
   long long accepted = 0;
   const int64_t g0 = (bid * NW + threadIdx.x / WAVE) * GPW + lane / GS;
@@ -569,9 +659,9 @@ __device__ __forceinline__ void eval_group_body(const EvalArgs& A, int64_t bid, 
       const int64_t idx0 = wb + lane / GS, idx1 = wb + ngroups + lane / GS;
       const bool h0 = idx0 < cnt, h1 = idx1 < cnt;
       const int64_t j0 = h0 ? idx0 : 0, j1 = h1 ? idx1 : 0;  // valid indices
-      const int i0 = h0 ? A.list[j0] : 0;
-      const int i1 = h1 ? A.list[j1] : 0;
-      const int32_t rb0 = A.list_rb[j0], rb1 = A.list_rb[j1];
+      const int i0 = h0 ? L.list[j0] : 0;
+      const int i1 = h1 ? L.list[j1] : 0;
+      const int32_t rb0 = L.list_rb[j0], rb1 = L.list_rb[j1];
       if constexpr (MODE == EV_SWEEP)
         sweep_pair<GS>(A, i0, h0, rb0, i1, h1, rb1, gl, ls);
       else if constexpr (MODE == EV_FEAT)
@@ -583,7 +673,7 @@ __device__ __forceinline__ void eval_group_body(const EvalArgs& A, int64_t bid, 
     for (int64_t wb = w0; wb < cnt; wb += ngroups) {
       const int64_t idx = wb + lane / GS;
       const bool have = idx < cnt;
-      const int i = have ? A.list[idx] : 0;
+      const int i = have ? L.list[idx] : 0;
       accepted += group_item<MODE, GS>(A, i, have, lane, gl, gbase, ls);
     }
   }
@@ -599,27 +689,36 @@ __global__ void __launch_bounds__(TPB) k_eval_group(EvalArgs A) {
   int* ls = lsum_all[threadIdx.x / WAVE];
   ls[lane_id()] = 0;
   wave_sync();
-  eval_group_body<MODE, GS>(A, blockIdx.x, gridDim.x, ls);
+  eval_group_body<MODE, GS>(A, BinList{A.list, A.list_rb, A.count}, blockIdx.x, gridDim.x, ls);
 }
 
-// The three short-row bins in one launch, block ranges [0, nb16), [nb16,
-// nb16 + nb32) and the rest: three launches in a row each waited out the
-// latency of one evaluation, which a bin too short to fill the chip (the
-// screening set's, the sweeps' over part of the vertices) cannot hide.
+// The four short-row bins in one launch, bin q in blocks [beg[q], beg[q + 1]):
+// launches in a row each waited out the latency of one evaluation, which a bin
+// too short to fill the chip (the screening set's, the sweeps' over part of the
+// vertices) cannot hide.
+struct ShortBins {
+  BinList bin[BIN_W];
+  int beg[BIN_W + 1];
+};
+
 template <int MODE>
-__global__ void __launch_bounds__(TPB)
-    k_eval_groups(EvalArgs A16, EvalArgs A32, EvalArgs A64, int nb16, int nb32) {
+__global__ void __launch_bounds__(TPB) k_eval_groups(EvalArgs A, ShortBins S) {
   __shared__ int lsum_all[NW][WAVE];
   int* ls = lsum_all[threadIdx.x / WAVE];
   ls[lane_id()] = 0;
   wave_sync();
   const int b = int(blockIdx.x);
-  if (b < nb16)
-    eval_group_body<MODE, 16>(A16, b, nb16, ls);
-  else if (b < nb16 + nb32)
-    eval_group_body<MODE, 32>(A32, b - nb16, nb32, ls);
+  if (b < S.beg[BIN_16])
+    eval_group_body<MODE, 8>(A, S.bin[BIN_8], b, S.beg[BIN_16], ls);
+  else if (b < S.beg[BIN_32])
+    eval_group_body<MODE, 16>(A, S.bin[BIN_16], b - S.beg[BIN_16], S.beg[BIN_32] - S.beg[BIN_16],
+                              ls);
+  else if (b < S.beg[BIN_64])
+    eval_group_body<MODE, 32>(A, S.bin[BIN_32], b - S.beg[BIN_32], S.beg[BIN_64] - S.beg[BIN_32],
+                              ls);
   else
-    eval_group_body<MODE, 64>(A64, b - nb16 - nb32, int64_t(gridDim.x) - nb16 - nb32, ls);
+    eval_group_body<MODE, 64>(A, S.bin[BIN_64], b - S.beg[BIN_64], S.beg[BIN_W] - S.beg[BIN_64],
+                              ls);
 }
 
 // --------------------------------------------------------------------------
@@ -1096,7 +1195,7 @@ __global__ void k_build_multi(const MultiSeg* __restrict__ segs, int nsegs, Mult
     for (int64_t i = threadIdx.x; i < sg.padded; i += blockDim.x) {
       lst[i] = i < sg.n ? sg.src[i] : -1;
       gd[i] = sg.gid;
-      if (sg.bin == NBINS - 1) D.lidx[sg.dst + i] = int32_t(i);
+      if (sg.bin == BIN_G) D.lidx[sg.dst + i] = int32_t(i);
     }
   }
 }
@@ -1114,7 +1213,13 @@ constexpr int BIN_TILE = BIN_TPB * BIN_ITEMS;
 // wmax: the longest row of bin W (WTAB_MAX, or half of it on coarse levels,
 // whose rows hold mostly distinct labels and would overflow the wave table)
 __device__ __forceinline__ int bin_of(int d, int wmax) {
-  return d <= 16 ? 0 : d <= 32 ? 1 : d <= 64 ? 2 : d <= wmax ? 3 : d <= BTAB_MAX ? 4 : 5;
+  return d <= 8    ? BIN_8
+         : d <= 16   ? BIN_16
+         : d <= 32   ? BIN_32
+         : d <= 64   ? BIN_64
+         : d <= wmax ? BIN_W
+         : d <= BTAB_MAX ? BIN_B
+                         : BIN_G;
 }
 
 // Rows of the binning: bin q of a vertex v is split into row 2q (evaluated
@@ -1554,84 +1659,88 @@ void launch_eval(const EvalArgs& base, const Bins& bins, hipStream_t st, hipEven
   // and the feature pass (their loads interleaved); a wave holds 64 / GS
   // groups
   constexpr int PAIR = (MODE == EV_SWEEP || MODE == EV_DSBOTH || MODE == EV_FEAT) ? 2 : 1;
-  // the sweeps and the screening and feature passes take their three
+  // the sweeps and the screening and feature passes take their four
   // short-row bins in one launch (k_eval_groups), which ev0 / ev1 bracket
   constexpr bool JOINT = MODE == EV_SWEEP || MODE == EV_DSBOTH || MODE == EV_FEAT;
   if constexpr (JOINT) {
-    if (bins.n[0] + bins.n[1] + bins.n[2] > 0) {
-      const int nb[3] = {bins.n[0] > 0 ? wave_grid(ceil_div(bins.n[0], 4 * PAIR)) : 0,
-                         bins.n[1] > 0 ? wave_grid(ceil_div(bins.n[1], 2 * PAIR)) : 0,
-                         bins.n[2] > 0 ? wave_grid(ceil_div(bins.n[2], PAIR)) : 0};
-      EvalArgs Aq[3];
-      for (int q = 0; q < 3; ++q) {
-        setbin(q);
-        Aq[q] = A;
+    if (short_rows(bins) > 0) {
+      ShortBins S;
+      S.beg[0] = 0;
+      for (int q = 0; q < BIN_W; ++q) {
+        S.bin[q] = BinList{bins.list[q], bins.list_rb[q], bins.count_dev + q};
+        S.beg[q + 1] = S.beg[q] + (bins.n[q] > 0
+                                       ? wave_grid(ceil_div(bins.n[q], (8 >> q) * PAIR))
+                                       : 0);
       }
       if (ev0) DC_HIP(hipEventRecord(ev0, st));
-      k_eval_groups<MODE><<<nb[0] + nb[1] + nb[2], TPB, 0, st>>>(Aq[0], Aq[1], Aq[2], nb[0],
-                                                                  nb[1]);
+      k_eval_groups<MODE><<<S.beg[BIN_W], TPB, 0, st>>>(A, S);
       DC_LAUNCH_CHECK();
       if (ev1) DC_HIP(hipEventRecord(ev1, st));
     }
   }
-  if (!JOINT && bins.n[0] > 0) {
-    setbin(0);
-    k_eval_group<MODE, 16><<<wave_grid(ceil_div(bins.n[0], 4 * PAIR)), TPB, 0, st>>>(A);
+  if (!JOINT && bins.n[BIN_8] > 0) {
+    setbin(BIN_8);
+    k_eval_group<MODE, 8><<<wave_grid(ceil_div(bins.n[BIN_8], 8 * PAIR)), TPB, 0, st>>>(A);
     DC_LAUNCH_CHECK();
   }
-  if (!JOINT && bins.n[1] > 0) {
-    setbin(1);
-    k_eval_group<MODE, 32><<<wave_grid(ceil_div(bins.n[1], 2 * PAIR)), TPB, 0, st>>>(A);
+  if (!JOINT && bins.n[BIN_16] > 0) {
+    setbin(BIN_16);
+    k_eval_group<MODE, 16><<<wave_grid(ceil_div(bins.n[BIN_16], 4 * PAIR)), TPB, 0, st>>>(A);
+    DC_LAUNCH_CHECK();
+  }
+  if (!JOINT && bins.n[BIN_32] > 0) {
+    setbin(BIN_32);
+    k_eval_group<MODE, 32><<<wave_grid(ceil_div(bins.n[BIN_32], 2 * PAIR)), TPB, 0, st>>>(A);
     DC_LAUNCH_CHECK();
   }
   // hub rows: few long blocks, so they run on the second stream beside the
   // other bins (all read one snapshot and write disjoint labels; shared
   // flags and counters are written as idempotent stores or atomics)
-  const bool fork = bins.n[5] > 0 && bins.side;
+  const bool fork = bins.n[BIN_G] > 0 && bins.side;
   if (fork) {
     EvalArgs G = A;
-    G.list = bins.list[5];
-    G.list_rb = bins.list_rb[5];
-    G.count = bins.count_dev + 5;
+    G.list = bins.list[BIN_G];
+    G.list_rb = bins.list_rb[BIN_G];
+    G.count = bins.count_dev + BIN_G;
     G.gkeys = bins.gkeys;
     G.gvals = bins.gvals;
     G.tab_off = bins.tab_off;
     G.gslots = bins.gslots;
     DC_HIP(hipEventRecord(bins.fork, st));
     DC_HIP(hipStreamWaitEvent(bins.side, bins.fork, 0));
-    k_eval_gtab<MODE><<<bins.n[5], GTPB, 0, bins.side>>>(G);
+    k_eval_gtab<MODE><<<bins.n[BIN_G], GTPB, 0, bins.side>>>(G);
     DC_LAUNCH_CHECK();
     DC_HIP(hipEventRecord(bins.join, bins.side));
   }
-  if (!JOINT && bins.n[2] > 0) {
-    setbin(2);
-    k_eval_group<MODE, 64><<<wave_grid(ceil_div(bins.n[2], PAIR)), TPB, 0, st>>>(A);
+  if (!JOINT && bins.n[BIN_64] > 0) {
+    setbin(BIN_64);
+    k_eval_group<MODE, 64><<<wave_grid(ceil_div(bins.n[BIN_64], PAIR)), TPB, 0, st>>>(A);
     DC_LAUNCH_CHECK();
   }
-  if (bins.n[3] > 0) {
-    setbin(3);
-    k_eval_wtab<MODE><<<wave_grid(bins.n[3]), TPB, 0, st>>>(A);
+  if (bins.n[BIN_W] > 0) {
+    setbin(BIN_W);
+    k_eval_wtab<MODE><<<wave_grid(bins.n[BIN_W]), TPB, 0, st>>>(A);
     DC_LAUNCH_CHECK();
   }
-  if (bins.n[4] > 0) {
-    setbin(4);
-    k_eval_btab<MODE><<<bins.n[4], TPB, 0, st>>>(A);
+  if (bins.n[BIN_B] > 0) {
+    setbin(BIN_B);
+    k_eval_btab<MODE><<<bins.n[BIN_B], TPB, 0, st>>>(A);
     DC_LAUNCH_CHECK();
   }
-  if (bins.n[3] + bins.n[4] > 0) {
-    const int64_t g = bins.n[3] + bins.n[4] < OVF_GRID ? bins.n[3] + bins.n[4] : OVF_GRID;
+  if (bins.n[BIN_W] + bins.n[BIN_B] > 0) {
+    const int64_t g = bins.n[BIN_W] + bins.n[BIN_B] < OVF_GRID ? bins.n[BIN_W] + bins.n[BIN_B] : OVF_GRID;
     k_eval_ovf<MODE><<<int(g), TPB, 0, st>>>(A);
     DC_LAUNCH_CHECK();
   }
   if (fork) {
     DC_HIP(hipStreamWaitEvent(st, bins.join, 0));
-  } else if (bins.n[5] > 0) {
-    setbin(5);
+  } else if (bins.n[BIN_G] > 0) {
+    setbin(BIN_G);
     A.gkeys = bins.gkeys;
     A.gvals = bins.gvals;
     A.tab_off = bins.tab_off;
     A.gslots = bins.gslots;
-    k_eval_gtab<MODE><<<bins.n[5], GTPB, 0, st>>>(A);
+    k_eval_gtab<MODE><<<bins.n[BIN_G], GTPB, 0, st>>>(A);
     DC_LAUNCH_CHECK();
   }
 }
@@ -1705,7 +1814,7 @@ void bin_place(const int32_t* list, int64_t count, const int32_t* dcount, const 
   b.gvals = nullptr;
   b.tab_off = nullptr;
   b.gslots = 0;
-  constexpr int G = NBINS - 1;
+  constexpr int G = BIN_G;
   if (b.n[G] > 0) {
     s.tab_off.ensure(size_t(b.n[G] + 1) * sizeof(long long));
     long long* caps = s.tab_off.as<long long>();
@@ -1742,8 +1851,8 @@ void make_bins(const int32_t* list, int64_t count, const int32_t* off, Bins& b, 
 void small_level(const LevelView& g, Bins& b, BinScratch& s) {
   b = Bins{};
   b.small = true;
-  b.n[3] = g.n;
-  b.vol[3] = g.nnz;
+  b.n[BIN_W] = g.n;
+  b.vol[BIN_W] = g.nnz;
   b.total = g.n;
   b.ovf_count = s.counts.as<int32_t>() + M_OVF;
 }
@@ -1905,7 +2014,7 @@ EvalArgs sweep_args(const LevelView& g, const int32_t* C, int32_t* Cn, const int
 
 void build_multi_bins(const Bins* const* bins, int ngraphs, MultiBins& mb, MultiSeg* segs_host,
                       DBuf& segs_dev, hipStream_t st) {
-  constexpr int PAD[NBINS] = {WAVE / 16, WAVE / 32, 1, 1, 1, 1};
+  constexpr int PAD[NBINS] = {WAVE / 8, WAVE / 16, WAVE / 32, 1, 1, 1, 1};
   int nsegs = 0;
   for (int q = 0; q < NBINS; ++q) {
     int64_t off = 0;
@@ -1920,7 +2029,7 @@ void build_multi_bins(const Bins* const* bins, int ngraphs, MultiBins& mb, Multi
     mb.list[q].ensure(size_t(off + 1) * 4);
     mb.gid[q].ensure(size_t(off + 1) * 4);
   }
-  mb.lidx.ensure(size_t(mb.count[NBINS - 1] + 1) * 4);
+  mb.lidx.ensure(size_t(mb.count[BIN_G] + 1) * 4);
   if (nsegs == 0) return;
   segs_dev.ensure(size_t(nsegs) * sizeof(MultiSeg));
   DC_HIP(hipMemcpyAsync(segs_dev.p, segs_host, size_t(nsegs) * sizeof(MultiSeg),
@@ -1941,29 +2050,33 @@ void sweep_eval_multi(const EvalArgs* descs, const int32_t* done, const MultiBin
     return MultiArgs{descs, mb.list[q].as<int32_t>(), mb.gid[q].as<int32_t>(), done,
                      mb.count[q]};
   };
-  if (mb.count[0] > 0) {
-    k_sweep_group_multi<16><<<wave_grid(ceil_div(mb.count[0], 4)), TPB, 0, st>>>(args(0));
+  if (mb.count[BIN_8] > 0) {
+    k_sweep_group_multi<8><<<wave_grid(ceil_div(mb.count[BIN_8], 8)), TPB, 0, st>>>(args(BIN_8));
     DC_LAUNCH_CHECK();
   }
-  if (mb.count[1] > 0) {
-    k_sweep_group_multi<32><<<wave_grid(ceil_div(mb.count[1], 2)), TPB, 0, st>>>(args(1));
+  if (mb.count[BIN_16] > 0) {
+    k_sweep_group_multi<16><<<wave_grid(ceil_div(mb.count[BIN_16], 4)), TPB, 0, st>>>(args(BIN_16));
     DC_LAUNCH_CHECK();
   }
-  if (mb.count[2] > 0) {
-    k_sweep_group_multi<64><<<wave_grid(mb.count[2]), TPB, 0, st>>>(args(2));
+  if (mb.count[BIN_32] > 0) {
+    k_sweep_group_multi<32><<<wave_grid(ceil_div(mb.count[BIN_32], 2)), TPB, 0, st>>>(args(BIN_32));
     DC_LAUNCH_CHECK();
   }
-  if (mb.count[3] > 0) {
-    k_sweep_wtab_multi<<<wave_grid(mb.count[3]), TPB, 0, st>>>(args(3));
+  if (mb.count[BIN_64] > 0) {
+    k_sweep_group_multi<64><<<wave_grid(mb.count[BIN_64]), TPB, 0, st>>>(args(BIN_64));
     DC_LAUNCH_CHECK();
   }
-  if (mb.count[4] > 0) {
-    const int64_t nb = mb.count[4] < 16384 ? mb.count[4] : 16384;
-    k_sweep_btab_multi<<<int(nb), TPB, 0, st>>>(args(4));
+  if (mb.count[BIN_W] > 0) {
+    k_sweep_wtab_multi<<<wave_grid(mb.count[BIN_W]), TPB, 0, st>>>(args(BIN_W));
     DC_LAUNCH_CHECK();
   }
-  if (mb.count[5] > 0) {
-    k_sweep_gtab_multi<<<int(mb.count[5]), GTPB, 0, st>>>(args(5), mb.lidx.as<int32_t>());
+  if (mb.count[BIN_B] > 0) {
+    const int64_t nb = mb.count[BIN_B] < 16384 ? mb.count[BIN_B] : 16384;
+    k_sweep_btab_multi<<<int(nb), TPB, 0, st>>>(args(BIN_B));
+    DC_LAUNCH_CHECK();
+  }
+  if (mb.count[BIN_G] > 0) {
+    k_sweep_gtab_multi<<<int(mb.count[BIN_G]), GTPB, 0, st>>>(args(BIN_G), mb.lidx.as<int32_t>());
     DC_LAUNCH_CHECK();
   }
 }

@@ -133,3 +133,36 @@ def test_level_one_sizes(cliques, slm):
     for i, b in enumerate((first, second)):
         step_pair(o, g, b)
         compare(o, g, f"cliques={cliques} step {i}")
+
+
+@pytest.mark.parametrize("del_rule", [0, 1])
+@pytest.mark.parametrize("entries", [7, 8, 9, 16, 17, 32, 33, 64, 65])
+def test_rows_at_bin_edges(entries, del_rule):
+    """Circulant graphs whose rows all have `entries` entries of random weight,
+    beside rows of one and two entries: full and nearly full groups of lanes,
+    all labels distinct in the first sweep; then batches in which new sources
+    have as many sinks, in both deletion rules' screening passes."""
+    print(f"case: rows of {entries} entries del_rule={del_rule}", flush=True)
+    rng = np.random.default_rng(entries)
+    n, half = 300, 150
+    i = np.arange(n)
+    u = [i for k in range(entries // 2)] + ([i[:half]] if entries % 2 else [])
+    v = [(i + 1 + k) % n for k in range(entries // 2)] + ([i[:half] + half] if entries % 2 else [])
+    u += [np.arange(n, n + 40), np.arange(n, n + 20)]  # a pendant path beside it
+    v += [np.arange(n + 1, n + 41), rng.integers(0, n, 20)]
+    u, v = np.concatenate(u).astype(np.int32), np.concatenate(v).astype(np.int32)
+    w = rng.integers(1, 6, len(u)).astype(np.int32)
+    total = n + 41 + 8
+    o, g = make_pair(total, u, v, w, del_rule=del_rule)
+    compare(o, g, "init")
+    for t in range(3):
+        src = total - 1 - t  # an isolated vertex so far
+        add_v = rng.choice(n, entries, replace=False).astype(np.int32)
+        cut = rng.choice(len(u), 30, replace=False)
+        b = W.Batch(np.full(entries, src, np.int32), add_v,
+                    rng.integers(1, 6, entries).astype(np.int32), u[cut], v[cut])
+        keep = np.setdiff1d(np.arange(len(u)), cut)
+        u = np.concatenate([u[keep], b.add_u])
+        v = np.concatenate([v[keep], b.add_v])
+        step_pair(o, g, b)
+        compare(o, g, f"entries={entries} step {t}")
