@@ -372,6 +372,31 @@ __device__ __forceinline__ void table_add_bounded(int* keys, int* vals, uint32_t
   }
 }
 
+// table_add into a clean table whose taken slots are listed: the first `limit`
+// of them in used, their number in *claimed (which may pass the limit).  The
+// caller stops adding once it has, before the table is full.
+__device__ __forceinline__ void table_add_listed(int* keys, int* vals, uint16_t* used,
+                                                 uint32_t mask, int key, int w, int* claimed,
+                                                 int limit) {
+  uint32_t h = hash_slot(key, mask);
+  while (true) {
+    int k = __hip_atomic_load(&keys[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (k == EMPTY_KEY) {
+      k = atomicCAS(&keys[h], EMPTY_KEY, key);
+      if (k == EMPTY_KEY) {
+        const int c = atomicAdd(claimed, 1);
+        if (c < limit) used[c] = uint16_t(h);
+        k = key;
+      }
+    }
+    if (k == key) {
+      atomicAdd(&vals[h], w);
+      return;
+    }
+    h = (h + 1) & mask;
+  }
+}
+
 __device__ __forceinline__ int table_get(const int* keys, const int* vals,
                                          uint32_t mask, int key) {
   uint32_t h = hash_slot(key, mask);

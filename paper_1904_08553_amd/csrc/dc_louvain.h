@@ -54,8 +54,6 @@ constexpr long long NO_GAIN = (long long)0x8000000000000000ull;
 // 32 and 64 entries (8, 4, 2 and 1 vertices per wave, no table), then
 enum RowBin : int { BIN_8 = 0, BIN_16, BIN_32, BIN_64, BIN_W, BIN_B, BIN_G, NBINS };
 constexpr int WTAB_MAX = 512;     // one wave, wave-private LDS table
-constexpr int WTAB_SLOTS = 1024;  // (merged sweeps; single graphs use 512 slots
-                                  // and a full-table retry on overflow)
 constexpr int BTAB_MAX = 4096;    // one block, block LDS table
 constexpr int BTAB_SLOTS = 8192;  // beyond: one block, global table
 constexpr int TIMED_BINS = BIN_W;  // the timing option brackets the launch of the bins before W

@@ -836,16 +836,39 @@ __device__ __forceinline__ Best table_best(const EvalArgs& A, const int* keys, c
   return b;
 }
 
+// The same over the n listed slots of a table.
+template <int G>
+__device__ __forceinline__ Best table_best_listed(const EvalArgs& A, const int* keys,
+                                                  const int* vals, const uint16_t* used, int n,
+                                                  long long ki, int skip, int t) {
+  Best b = {NO_SCORE, NO_LABEL};
+  for (int s = t; s < n; s += G) {
+    const int h = used[s], X = keys[h];
+    const long long sc = (long long)int(A.two_m) * vals[h] - (long long)int(ki) * A.a[X];
+    if (X != skip && better(sc, X, b.s, b.x)) b = {sc, X};
+  }
+  return b;
+}
+
 // One group (a wave, or the whole block) evaluates vertex i with table
 // (keys, vals, mask).  Returns the number of accepted screening tests (0/1)
 // in thread 0 of the group.  BOUNDED: the table may be too small (at most
 // (mask + 1) / 2 distinct labels fit); tstate holds two ints of group
 // scratch, and if the row brings more labels the call returns TABLE_FULL
 // to every thread before it has written anything outside the group.
+// A wave's table (LISTED) is clean before and after the call; its taken slots
+// are listed in used (used_cap entries, the limit then), and these alone are
+// scanned and cleared.  Most rows bring few labels: clearing and scanning all
+// 256 or 512 slots, and the code of eight chunks for rows of two, made bin W
+// 44 us a sweep of a 300K/6M graph's static run and 111 of a 1M/20M graph, now
+// 38 and 104 (L1 misses queueing for the label gathers bound it: its requests
+// come at the short-row kernel's rate).
 constexpr long long TABLE_FULL = -1;
 template <int MODE, int G, int UI, int US, bool BOUNDED = false>
 __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, uint32_t mask,
-                                GroupLds<G>& L, int* own, int* tstate = nullptr) {
+                                GroupLds<G>& L, int* tstate = nullptr,
+                                uint16_t* used = nullptr, int used_cap = 0) {
+  constexpr bool LISTED = BOUNDED && G == WAVE;
   const int t = (G == WAVE) ? lane_id() : int(threadIdx.x);
   const int lane = lane_id();
   const int32_t rb = A.off[i], re = A.off[i + 1];
@@ -863,10 +886,14 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
   const int pj = pf ? int(key_col(A.ins_keys[q0 + t], A.kb)) : 0;
   const int pX = pf ? A.C[pj] : 0;
   const int paX = pf ? A.a[pX] : 0;
-  for (uint32_t s = t; s <= mask; s += G) {
-    keys[s] = EMPTY_KEY;
-    vals[s] = 0;
-  }
+  auto clear = [&]() {
+    for (uint32_t s = t; s <= mask; s += G) {
+      keys[s] = EMPTY_KEY;
+      vals[s] = 0;
+    }
+  };
+  if (!LISTED) clear();
+  const int limit = LISTED ? used_cap : int((mask + 1) / 2);
   if (BOUNDED && t == 0) tstate[0] = tstate[1] = 0;
   group_sync<G>();
   // the own community (usually most of the row) is summed in registers;
@@ -875,33 +902,51 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
   // issued before any is waited on)
   long long own_part = 0;
   const int w0 = (G == WAVE) ? 0 : int(threadIdx.x) / WAVE;
-  for (int32_t c0 = rb + w0 * WAVE; c0 < re; c0 += UI * G) {
-    int2 e[UI];
-    bool valid[UI];
-    int key[UI];
+  auto add_row = [&](auto chunks) {
+    constexpr int U = decltype(chunks)::value;
+    for (int32_t c0 = rb + w0 * WAVE; c0 < re; c0 += U * G) {
+      int2 e[U];
+      bool valid[U];
+      int key[U];
 #pragma unroll
-    for (int u = 0; u < UI; ++u) {
-      const int32_t q = c0 + u * G + lane;
-      valid[u] = q < re;
-      e[u] = valid[u] ? A.adj[q] : make_int2(0, 0);
-    }
+      for (int u = 0; u < U; ++u) {
+        const int32_t q = c0 + u * G + lane;
+        valid[u] = q < re;
+        e[u] = valid[u] ? A.adj[q] : make_int2(0, 0);
+      }
 #pragma unroll
-    for (int u = 0; u < UI; ++u) {
-      if (e[u].x == i) valid[u] = false;
-      key[u] = valid[u] ? A.C[e[u].x] : EMPTY_KEY;
-    }
+      for (int u = 0; u < U; ++u) {
+        if (e[u].x == i) valid[u] = false;
+        key[u] = valid[u] ? A.C[e[u].x] : EMPTY_KEY;
+      }
 #pragma unroll
-    for (int u = 0; u < UI; ++u) {
-      if (key[u] == c)
-        own_part += e[u].y;
-      else if (valid[u]) {
-        if (BOUNDED)
-          table_add_bounded(keys, vals, mask, key[u], e[u].y, &tstate[0], &tstate[1],
-                            int((mask + 1) / 2));
-        else
-          table_add(keys, vals, mask, key[u], e[u].y);
+      for (int u = 0; u < U; ++u) {
+        // a wave's adds are done chunk by chunk, so at most WAVE slots past
+        // the limit are taken
+        if (LISTED && U == UI && *(volatile int*)&tstate[0] > limit) return;
+        if (key[u] == c)
+          own_part += e[u].y;
+        else if (valid[u]) {
+          if constexpr (LISTED)
+            table_add_listed(keys, vals, used, mask, key[u], e[u].y, &tstate[0], limit);
+          else if constexpr (BOUNDED)
+            table_add_bounded(keys, vals, mask, key[u], e[u].y, &tstate[0], &tstate[1], limit);
+          else
+            table_add(keys, vals, mask, key[u], e[u].y);
+        }
       }
     }
+  };
+  if constexpr (G == WAVE) {
+    static_assert(UI == 8, "rows of at most 2, 4 and 8 chunks");
+    if (re - rb <= 2 * WAVE)
+      add_row(std::integral_constant<int, 2>());
+    else if (re - rb <= 4 * WAVE)
+      add_row(std::integral_constant<int, 4>());
+    else
+      add_row(std::integral_constant<int, UI>());
+  } else {
+    add_row(std::integral_constant<int, UI>());
   }
   long long e_own = own_part, unused = 0;
   if constexpr (G == WAVE)
@@ -909,7 +954,23 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
   else
     group_sum2<G>(e_own, unused, L);
   group_sync<G>();
-  if (BOUNDED && tstate[1]) return TABLE_FULL;  // group-uniform after the sync
+  const int taken = LISTED ? tstate[0] : 0;
+  if (LISTED && taken > limit) {  // wave-uniform
+    clear();
+    group_sync<G>();
+    return TABLE_FULL;
+  }
+  if (BOUNDED && !LISTED && tstate[1]) return TABLE_FULL;  // group-uniform after the sync
+  auto clean = [&]() {  // the table for the group's next item
+    if (LISTED) {
+      for (int s = t; s < taken; s += G) {
+        const int h = used[s];
+        keys[h] = EMPTY_KEY;
+        vals[h] = 0;
+      }
+    }
+    group_sync<G>();
+  };
   long long accepted = 0;
   // EV_DSBOTH: Alg. 2 for an insertion source (flag bit 0), then the
   // deletion rule for a deletion endpoint (bit 1), on the same table
@@ -938,14 +999,23 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
     }
     group_sync<G>();  // the table is reused (by the deletion rule or the next item)
   }
-  if (MODE == EV_DSADD || (MODE == EV_DSBOTH && !(uf & 2) && !A.pre)) return accepted;
-  Best b = table_best<G, US>(A, keys, vals, mask, ki, EMPTY_KEY, t);
+  if (MODE == EV_DSADD || (MODE == EV_DSBOTH && !(uf & 2) && !A.pre)) {
+    if (LISTED) clean();
+    return accepted;
+  }
+  auto best_label = [&](int skip) {
+    if constexpr (LISTED)
+      return table_best_listed<G>(A, keys, vals, used, taken, ki, skip, t);
+    else
+      return table_best<G, US>(A, keys, vals, mask, ki, skip, t);
+  };
+  Best b = best_label(EMPTY_KEY);
   b = group_best<G>(b, L);
   group_sync<G>();
   const long long s_own = A.two_m * e_own - ki * (ac - ki);
   if (MODE == EV_FEAT) {
     // the table holds only foreign labels; a second scan skips the best
-    Best b2 = table_best<G, US>(A, keys, vals, mask, ki, b.x, t);
+    Best b2 = best_label(b.x);
     b2 = group_best<G>(b2, L);
     if (t == 0) {
       A.f_own[i] = int32_t(e_own);
@@ -953,7 +1023,7 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
       A.f_g2[i] = b2.x != NO_LABEL ? b2.s - s_own : NO_GAIN;
       if (A.pre) pre_commit(A, i, b.x != NO_LABEL && b.s > s_own, c, b.x);
     }
-    group_sync<G>();  // the table is reused by the next item of this group
+    clean();
     return 0;
   }
   bool move = b.x != NO_LABEL && b.s > s_own;
@@ -969,8 +1039,7 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
       accepted += ACC_DEL;
     }
   }
-  // the table is reused by the next item of this group
-  group_sync<G>();
+  clean();
   return accepted;
 }
 
@@ -982,23 +1051,32 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
 constexpr int WT_SLOTS = 512;   // bin W: per-wave table
 constexpr int BT_SLOTS = 2048;  // bin B: per-block table
 
+// A wave's table of WT_SLOTS slots, clean.
+__device__ __forceinline__ void table_empty(int* keys, int* vals) {
+  for (int s = lane_id(); s < WT_SLOTS; s += WAVE) {
+    keys[s] = EMPTY_KEY;
+    vals[s] = 0;
+  }
+  wave_sync();
+}
+
 // bin W: one wave per vertex, wave-private LDS table
 template <int MODE>
 __global__ void __launch_bounds__(TPB, MODE == EV_SWEEP ? 8 : 7) k_eval_wtab(EvalArgs A) {
   __shared__ int keys[NW][WT_SLOTS];
   __shared__ int vals[NW][WT_SLOTS];
+  __shared__ uint16_t used[NW][WT_SLOTS / 2];
   __shared__ GroupLds<WAVE> L[NW];
-  __shared__ int own[NW];
   __shared__ int tst[NW][2];
   const int wid = threadIdx.x / WAVE;
+  table_empty(keys[wid], vals[wid]);
   const int64_t cnt = *A.count;
   const int64_t nwaves = int64_t(gridDim.x) * NW;
   long long accepted = 0;
   for (int64_t idx = int64_t(blockIdx.x) * NW + wid; idx < cnt; idx += nwaves) {
     const int i = uniform(A.list[idx]);
-    const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], WT_SLOTS);
     const long long acc = eval_table<MODE, WAVE, WTAB_UI, WTAB_US, true>(
-        A, i, keys[wid], vals[wid], cap - 1, L[wid], &own[wid], tst[wid]);
+        A, i, keys[wid], vals[wid], WT_SLOTS - 1, L[wid], tst[wid], used[wid], WT_SLOTS / 2);
     if (acc == TABLE_FULL) {
       if (lane_id() == 0) A.ovf_list[atomicAdd(A.ovf_count, 1)] = i;
     } else {
@@ -1014,14 +1092,13 @@ __global__ void __launch_bounds__(TPB) k_eval_btab(EvalArgs A) {
   __shared__ int keys[BT_SLOTS];
   __shared__ int vals[BT_SLOTS];
   __shared__ GroupLds<TPB> L;
-  __shared__ int own;
   __shared__ int tst[2];
   const int64_t idx = blockIdx.x;
   if (idx >= *A.count) return;  // uniform over the block
   const int i = A.list[idx];
   const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], BT_SLOTS);
   const long long acc =
-      eval_table<MODE, TPB, 4, 8, true>(A, i, keys, vals, cap - 1, L, &own, tst);
+      eval_table<MODE, TPB, 4, 8, true>(A, i, keys, vals, cap - 1, L, tst);
   if (threadIdx.x != 0) return;
   if (acc == TABLE_FULL)
     A.ovf_list[atomicAdd(A.ovf_count, 1)] = i;
@@ -1042,13 +1119,12 @@ __global__ void __launch_bounds__(TPB) k_eval_ovf(EvalArgs A) {
   __shared__ int keys[BTAB_SLOTS];
   __shared__ int vals[BTAB_SLOTS];
   __shared__ GroupLds<TPB> L;
-  __shared__ int own;
   const int64_t cnt = *A.ovf_count;
   long long accepted = 0;
   for (int64_t idx = blockIdx.x; idx < cnt; idx += gridDim.x) {
     const int i = A.ovf_list[idx];
     const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], BTAB_SLOTS);
-    accepted += eval_table<MODE, TPB, 4, 8>(A, i, keys, vals, cap - 1, L, &own);
+    accepted += eval_table<MODE, TPB, 4, 8>(A, i, keys, vals, cap - 1, L);
   }
   if (MODE != EV_SWEEP && threadIdx.x == 0 && accepted) add_accepted(A.stat, accepted);
 }
@@ -1063,13 +1139,12 @@ __global__ void __launch_bounds__(GTPB) k_eval_gtab(EvalArgs A) {
   __shared__ int keys[BTAB_SLOTS];
   __shared__ int vals[BTAB_SLOTS];
   __shared__ GroupLds<GTPB> L;
-  __shared__ int own;
   __shared__ int tstate[2];
   const int64_t idx = blockIdx.x;
   if (idx >= *A.count) return;
   const int i = A.list[idx];
   long long acc = eval_table<MODE, GTPB, GT_UI, 8, true>(A, i, keys, vals, BTAB_SLOTS - 1, L,
-                                                         &own, tstate);
+                                                         tstate);
   if (acc == TABLE_FULL) {
     const long long o0 = A.tab_off[idx], o1 = A.tab_off[idx + 1];
     if (o1 > A.gslots) {
@@ -1078,7 +1153,7 @@ __global__ void __launch_bounds__(GTPB) k_eval_gtab(EvalArgs A) {
       return;
     }
     acc = eval_table<MODE, GTPB, 4, 8>(A, i, A.gkeys + o0, A.gvals + o0, uint32_t(o1 - o0) - 1,
-                                       L, &own);
+                                       L);
   }
   if (MODE != EV_SWEEP && threadIdx.x == 0 && acc) add_accepted(A.stat, acc);
 }
@@ -1118,20 +1193,23 @@ __global__ void __launch_bounds__(TPB) k_sweep_group_multi(MultiArgs M) {
 }
 
 __global__ void __launch_bounds__(TPB) k_sweep_wtab_multi(MultiArgs M) {
-  __shared__ int keys[NW][WTAB_SLOTS];
-  __shared__ int vals[NW][WTAB_SLOTS];
+  // no second try here: the table takes every label that a row can bring
+  static_assert(WT_SLOTS >= WTAB_MAX, "a slot per entry");
+  __shared__ int keys[NW][WT_SLOTS];
+  __shared__ int vals[NW][WT_SLOTS];
+  __shared__ uint16_t used[NW][WT_SLOTS];
   __shared__ GroupLds<WAVE> L[NW];
-  __shared__ int own[NW];
+  __shared__ int tst[NW][2];
   const int wid = threadIdx.x / WAVE;
+  table_empty(keys[wid], vals[wid]);
   const int64_t nwaves = int64_t(gridDim.x) * NW;
   for (int64_t idx = int64_t(blockIdx.x) * NW + wid; idx < M.count; idx += nwaves) {
     const int g = uniform(M.gid[idx]);
     if (M.done[g]) continue;
     const EvalArgs A = M.descs[g];
     const int i = uniform(M.list[idx]);
-    const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], WTAB_SLOTS);
-    (void)eval_table<EV_SWEEP, WAVE, WTAB_UI, WTAB_US>(A, i, keys[wid], vals[wid], cap - 1,
-                                                       L[wid], &own[wid]);
+    (void)eval_table<EV_SWEEP, WAVE, WTAB_UI, WTAB_US, true>(
+        A, i, keys[wid], vals[wid], WT_SLOTS - 1, L[wid], tst[wid], used[wid], WT_SLOTS);
   }
 }
 
@@ -1139,14 +1217,13 @@ __global__ void __launch_bounds__(TPB) k_sweep_btab_multi(MultiArgs M) {
   __shared__ int keys[BTAB_SLOTS];
   __shared__ int vals[BTAB_SLOTS];
   __shared__ GroupLds<TPB> L;
-  __shared__ int own;
   for (int64_t idx = blockIdx.x; idx < M.count; idx += gridDim.x) {
     const int g = M.gid[idx];  // uniform over the block
     if (M.done[g]) continue;
     const EvalArgs A = M.descs[g];
     const int i = M.list[idx];
     const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], BTAB_SLOTS);
-    (void)eval_table<EV_SWEEP, TPB, 4, 8>(A, i, keys, vals, cap - 1, L, &own);
+    (void)eval_table<EV_SWEEP, TPB, 4, 8>(A, i, keys, vals, cap - 1, L);
   }
 }
 
@@ -1157,7 +1234,6 @@ __global__ void __launch_bounds__(GTPB)
   __shared__ int keys[BTAB_SLOTS];
   __shared__ int vals[BTAB_SLOTS];
   __shared__ GroupLds<GTPB> L;
-  __shared__ int own;
   __shared__ int tstate[2];
   const int64_t idx = blockIdx.x;
   if (idx >= M.count) return;
@@ -1167,7 +1243,7 @@ __global__ void __launch_bounds__(GTPB)
   const int i = M.list[idx];
   const int64_t q = lidx[idx];
   const long long acc = eval_table<EV_SWEEP, GTPB, GT_UI, 8, true>(A, i, keys, vals,
-                                                                    BTAB_SLOTS - 1, L, &own, tstate);
+                                                                    BTAB_SLOTS - 1, L, tstate);
   if (acc == TABLE_FULL) {
     const long long o0 = A.tab_off[q], o1 = A.tab_off[q + 1];
     if (o1 > A.gslots) {
@@ -1175,7 +1251,7 @@ __global__ void __launch_bounds__(GTPB)
       return;
     }
     (void)eval_table<EV_SWEEP, GTPB, 4, 8>(A, i, A.gkeys + o0, A.gvals + o0,
-                                           uint32_t(o1 - o0) - 1, L, &own);
+                                           uint32_t(o1 - o0) - 1, L);
   }
 }
 

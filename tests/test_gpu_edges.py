@@ -166,3 +166,34 @@ def test_rows_at_bin_edges(entries, del_rule):
         v = np.concatenate([v[keep], b.add_v])
         step_pair(o, g, b)
         compare(o, g, f"entries={entries} step {t}")
+
+
+@pytest.mark.parametrize("labels", [128, 256, 257, 320, 321, 512, 513])
+def test_rows_of_distinct_labels(labels):
+    """A vertex joined to one end of each of `labels` heavy pairs, which stay
+    communities: a row that brings as many labels, around what the wave's table
+    lists and holds, alone and in the server's merged sweeps."""
+    print(f"case: a row of {labels} labels", flush=True)
+    i = np.arange(labels)
+    u, v, w = (2 * i).astype(np.int32), (2 * i + 1).astype(np.int32), np.full(labels, 9, np.int32)
+    n, hub = 2 * labels + 1, 2 * labels
+    none = np.empty(0, np.int32)
+    to = lambda k: W.Batch(np.full(len(k), hub, np.int32), (2 * k).astype(np.int32),
+                           (1 + k % 3).astype(np.int32), none, none)
+    cut = W.Batch(none, none, none, np.full(labels // 2, hub, np.int32), u[::2][: labels // 2])
+    batches = [to(i), cut, to(i[::2][: labels // 2])]
+    o, g = make_pair(n, u, v, w)
+    compare(o, g, "init")
+    want = []
+    for t, b in enumerate(batches):
+        step_pair(o, g, b)
+        compare(o, g, f"labels={labels} step {t}")
+        want.append(o.C.copy())
+    srv = dc.Server(max_inflight=2)
+    gids = [srv.add_graph(n, u, v, w) for _ in range(2)]
+    tickets = [(t, gid, srv.submit(gid, b.add_u, b.add_v, b.add_w, b.del_u, b.del_v))
+               for t, b in enumerate(batches) for gid in gids]
+    for t, gid, tk in tickets:
+        assert np.array_equal(srv.poll(tk, gid)[0], want[t]), f"graph {gid} batch {t}"
+    assert srv.stats()["merged_rounds"] > 0
+    srv.close()
