@@ -22,6 +22,7 @@
 // global memory beyond (bin G).  A sweep writes only the next label;
 // movers are collected afterwards.
 #include "dc_louvain.h"
+#include "dc_scan.h"
 
 namespace dc {
 
@@ -1533,16 +1534,26 @@ __global__ void __launch_bounds__(BIN_TPB)
   }
 }
 
-__global__ void k_table_caps(const int32_t* __restrict__ list, const int32_t* __restrict__ off,
-                             int64_t cnt, long long* caps) {
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < cnt;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const int v = list[i];
+// Where each hub row's global table starts (tab_off[cnt]: their end), the
+// tables back to back: one block (there are few such rows, and a launch for
+// the sizes with two for their scan cost more than the rows' own work).
+constexpr int TO_TPB = 1024;
+__global__ void __launch_bounds__(TO_TPB)
+    k_table_offsets(const int32_t* __restrict__ list, const int32_t* __restrict__ off, int64_t cnt,
+                    long long* tab_off) {
+  __shared__ long long lds[TO_TPB / WAVE];
+  long long at = 0;
+  for (int64_t i0 = 0; i0 < cnt; i0 += TO_TPB) {
+    const int64_t i = i0 + threadIdx.x;
+    const int v = list[i < cnt ? i : cnt - 1];
     const long long d = off[v + 1] - off[v];
-    long long c = 2;
+    long long c = 2, tot;
     while (c < 2 * d) c <<= 1;
-    caps[i] = c;
+    const long long p = at + block_excl_scan<long long, TO_TPB>(i < cnt ? c : 0, lds, &tot);
+    if (i < cnt) tab_off[i] = p;
+    at += tot;
   }
+  if (threadIdx.x == 0) tab_off[cnt] = at;
 }
 
 inline int grid_for(int64_t n, int cap = 4096) {
@@ -1894,10 +1905,8 @@ void bin_place(const int32_t* list, int64_t count, const int32_t* dcount, const 
   if (b.n[G] > 0) {
     s.tab_off.ensure(size_t(b.n[G] + 1) * sizeof(long long));
     long long* caps = s.tab_off.as<long long>();
-    k_table_caps<<<grid_for(b.n[G]), TPB, 0, st>>>(b.list[G], off, b.n[G], caps);
+    k_table_offsets<<<1, TO_TPB, 0, st>>>(b.list[G], off, b.n[G], caps);
     DC_LAUNCH_CHECK();
-    scan_excl_i64(reinterpret_cast<int64_t*>(caps), reinterpret_cast<int64_t*>(caps), b.n[G],
-                  reinterpret_cast<int64_t*>(caps + b.n[G]), st);
     // row v takes the power of two >= 2 deg(v) (< 4 deg(v) for deg(v) >= 1),
     // so the bin's volume bounds the sum; the kernel checks tab_off against
     // gslots before it writes

@@ -86,7 +86,7 @@ def test_runs_of_one_pair(copies):
             compare(o, g, f"copies={copies} {mode} step {t}")
 
 
-@pytest.mark.parametrize("records", [2, 2046, 2048, 2050, 4096, 4098, (1 << 20) - 2, 1 << 20, (1 << 20) + 2, 8192 * 131 + 2])
+@pytest.mark.parametrize("records", [2, 2046, 2048, 2050, 4096, 4098, 16 * 2048, 16 * 2048 + 2, 64 * 2048, 64 * 2048 + 2, (1 << 20) - 2, 1 << 20, (1 << 20) + 2, 8192 * 131 + 2])
 def test_initial_csr_at_sort_sizes(records):
     """The initial CSR (both directed records of every edge, sorted, equal
     pairs summed) against numpy at the sizes where the radix sort changes its
@@ -197,3 +197,17 @@ def test_rows_of_distinct_labels(labels):
         assert np.array_equal(srv.poll(tk, gid)[0], want[t]), f"graph {gid} batch {t}"
     assert srv.stats()["merged_rounds"] > 0
     srv.close()
+
+
+@pytest.mark.parametrize("hubs", [1, 1024, 1025])
+def test_hub_tables_past_one_round(hubs):
+    """Rows of 4,100 distinct labels (more than the LDS table takes, so each is
+    evaluated in its own part of the global tables), as many as one round of the
+    offsets' scan covers and one more."""
+    print(f"case: {hubs} hub rows", flush=True)
+    leaves = 4100
+    u = np.repeat(np.arange(hubs, dtype=np.int32), leaves)
+    v = np.tile(np.arange(hubs, hubs + leaves, dtype=np.int32), hubs)
+    w = ((u.astype(np.int64) * 7 + v * 13) % 5 + 1).astype(np.int32)
+    o, g = make_pair(hubs + leaves, u, v, w, max_levels=1, max_sweeps=1)
+    compare(o, g, f"hubs={hubs}")
