@@ -562,7 +562,7 @@ def main():
         ach = d["k_bytes"] / (d["k_ms"] * 1e-3) / 1e9
         out["roofline"] = {
             "kernel": "k_eval_groups<0> (level-0/1+ sweeps, rows of at most 64 entries: "
-                      "the bins of 16, 32 and 64 lanes per vertex in one launch)",
+                      "the bins of 8, 16, 32 and 64 lanes per vertex in one launch)",
             "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": ach / HBM_PEAK_GBS, "traffic": measured_traffic(),
             "launches": d["k_launch"], "avg_launch_us": d["k_ms"] * 1e3 / d["k_launch"],
