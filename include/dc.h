@@ -15,8 +15,10 @@
  * Conventions
  *   - Every call returns a dc_status: 0 on success, a negative code on error.
  *     No call throws.  A failing dc_apply_batch leaves the context exactly as
- *     it was (checks run before anything is changed) except DC_E_DEVICE, after
- *     which the context refuses further work with DC_E_STATE.
+ *     it was (checks run before anything is changed, and a step that runs out of
+ *     device memory is taken back; only the samples of dc_last_samples are
+ *     gone then) except DC_E_DEVICE, after which the context refuses further
+ *     work with DC_E_STATE.
  *   - Vertices are int32 ids in [0, n); n is fixed by dc_init.  Edges are
  *     undirected, without self-loops, with int32 weights >= 1.  The total
  *     weight 2m must stay below 2^31, so every gain fits int64 exactly.

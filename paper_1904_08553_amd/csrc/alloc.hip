@@ -96,9 +96,11 @@ void* pool_alloc(size_t bytes, size_t* got) {
       c.free.clear();
       e = hipMalloc(&p, cls);
     }
-    if (e != hipSuccess)
+    if (e != hipSuccess) {
+      (void)hipGetLastError();  // reported here: the next launch check must not see it
       throw DeviceError(e, std::string("hipMalloc(") + std::to_string(cls) + ") -> " +
                                hipGetErrorString(e));
+    }
   }
   c.live[p] = dev;
   *got = cls;

@@ -81,6 +81,7 @@ void ensure_vertex_state(dc_ctx* c) {
     b->ensure((n + 1) * 4);
   c->dpack.ensure((n + 1) * 8);
   c->R.ensure(n + 1);
+  c->R_before.ensure(n + 1);
   c->cflag.ensure(n + 1);
   c->stat.ensure(ST_COUNT * 8);
   DC_HIP(hipMemsetAsync(c->stat.p, 0, ST_COUNT * 8, c->st));  // counters and self-check flags
@@ -205,9 +206,10 @@ long long run_sweeps(dc_ctx* c, const LevelView& g, const int32_t* act, int64_t 
 
 // Alg. 1 in two parts around the level-0 sweeps, so that several graphs can
 // run their level-0 sweeps together: levels_begin loads the level-0 partition
-// from (C, a0, sz0) and bins the active vertices (R_t as the screening left
-// it, the list `active`, or every vertex); levels_finish coarsens, runs the
-// upper levels and writes the canonical labels, the totals and N.
+// (singletons, or that of (C, a0, sz0)) and bins the active vertices (R_t as
+// the screening left it, the list `active`, or every vertex); levels_finish
+// coarsens, runs the upper levels and writes the canonical labels, the totals
+// and N.
 //
 // Screening evaluated its vertices on the state the first level-0 sweep
 // reads (labels C_{t-1}, totals and sizes on G_t): their decisions go into Cn
@@ -229,6 +231,13 @@ void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& 
   L.act = active;
   L.nact = n_active;
   c->trace.clear();
+  if (c->singletons) {  // C, a0 and sz0 stay until the labels are final
+    c->singletons = false;
+    start_level(c->Cl.as<int32_t>(), c->Cn.as<int32_t>(), c->al.as<int32_t>(),
+                c->szl.as<int32_t>(), L.g.k, c->n, c->st);
+    make_bins(nullptr, c->n, L.g.off, L.bins, c->bins, c->st);
+    return;
+  }
   if (active) {
     load_level0_partition(c);
     if (skip)
@@ -328,6 +337,7 @@ void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain) {
   }
   const int32_t* cntL = c->cnt[(level - 1) % 2].as<int32_t>();
   const int32_t* minvL = c->minv[(level - 1) % 2].as<int32_t>();
+  if (c->step == STEP_OPEN) c->step = STEP_FINAL;
   if (!final_ready) final_init(g.n, c->n, F, st);
   finalize_labels(g, Cl, al, szl, cntL, minvL, c->n, c->map0.as<int32_t>(), F, stat, ST_COUNT,
                   c->hstat_dev, st);
@@ -435,6 +445,7 @@ void run_levels_slm(dc_ctx* c, const int32_t* active, int64_t n_active) {
   }
   const FinalLabels F{c->lab.as<int32_t>(), c->cntf.as<int32_t>(), c->a0.as<int32_t>(),
                       c->sz0.as<int32_t>(), c->C.as<int32_t>(), stat + ST_I};
+  if (c->step == STEP_OPEN) c->step = STEP_FINAL;
   final_init(g.n, c->n, F, st);
   finalize_labels(g, Cl, al, szl, cntL, minvL, c->n, c->map0.as<int32_t>(), F, stat, ST_COUNT,
                   c->hstat_dev, st);
@@ -523,12 +534,6 @@ void touched_samples(dc_ctx* c, const LevelView& g0, bool labels, bool score) {
   }
 }
 
-void start_from_singletons(dc_ctx* c) {
-  iota_i32(c->C.as<int32_t>(), c->n, c->st);
-  DC_HIP(hipMemcpyAsync(c->a0.p, c->k0.p, size_t(c->n) * 4, hipMemcpyDeviceToDevice, c->st));
-  fill_i32(c->sz0.as<int32_t>(), 1, c->n, c->st);
-}
-
 // (Cl, Cn, al, szl) = (C, C, a0, sz0): the level-0 start partition.
 void load_level0_partition(dc_ctx* c) {
   int32_t* dst[4] = {c->Cl.as<int32_t>(), c->Cn.as<int32_t>(), c->al.as<int32_t>(),
@@ -598,7 +603,7 @@ dc_status do_init(dc_ctx* c, const dc_edges* g1) {
   row_weight_sums(c->off[0].as<int32_t>(), c->adj[0].as<int2>(), c->n, c->k0.as<int32_t>(), st);
   c->nnz = U;
   c->two_m = 2 * wsum;
-  start_from_singletons(c);
+  c->singletons = true;
   c->stats = dc_step_stats{};
   c->stats.R_size = c->n;
   c->inc_ready = false;
@@ -609,6 +614,54 @@ dc_status do_init(dc_ctx* c, const dc_edges* g1) {
   for (DBuf* b : {&c->akeys, &c->ak1, &c->avals, &c->av1, &c->aheads, &c->apos, &c->ukeys, &c->uw})
     b->release();
   return DC_OK;
+}
+
+// A step's first change is about to be made.  What it replaces is kept, or
+// follows from what it leaves alone until its labels are final: the CSR of
+// G_{t-1} (the merge writes the other one) gives k, and with C_{t-1} the label
+// totals and sizes.
+void step_open(dc_ctx* c, bool screening) {
+  StepStart& b = c->before;
+  b.cur = c->cur;
+  b.nnz = c->nnz;
+  b.two_m = c->two_m;
+  b.R_count = c->R_count;
+  b.have_R_all = c->have_R_all;
+  b.R_kept = screening;
+  b.stats = c->stats;
+  b.trace.clear();
+  b.trace.swap(c->trace);
+  if (screening) swap_buf(c->R, c->R_before);
+  c->step = STEP_OPEN;
+}
+
+// Takes an OPEN step back (an allocation failed in it).  Nothing here allocates.
+// The graph of communities kept for the next step went into the step's own:
+// the next one compacts from all of G_t.  The samples of the last step are
+// gone.
+void step_undo(dc_ctx* c) {
+  StepStart& b = c->before;
+  c->step = STEP_NONE;
+  c->cur = b.cur;
+  c->nnz = b.nnz;
+  c->two_m = b.two_m;
+  c->R_count = b.R_count;
+  c->have_R_all = b.have_R_all;
+  c->stats = b.stats;
+  c->trace.swap(b.trace);
+  if (b.R_kept) swap_buf(c->R, c->R_before);
+  c->T_count = 0;
+  c->have_y = c->have_logits = false;
+  c->R_open = c->singletons = c->inc_ready = false;
+  c->pre_count = 0;
+  c->inc.valid = false;
+  c->inc.lh = 0;
+  c->phase_timing = false;
+  ensure_vertex_state(c);  // the status block and the sweeps' counters at zero
+  int32_t* k = c->k0.as<int32_t>();
+  row_weight_sums(c->off[c->cur].as<int32_t>(), c->adj[c->cur].as<int2>(), c->n, k, c->st);
+  totals_sizes(k, c->C.as<int32_t>(), c->n, c->a0.as<int32_t>(), c->sz0.as<int32_t>(), c->st);
+  DC_HIP(hipStreamSynchronize(c->st));
 }
 
 // First part of a time step: validate, merge, choose R_t; on success *act /
@@ -687,6 +740,7 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
   // without the cascade the fused screening pass needs no list of insertion
   // sources: its vertex set comes straight from the rows of the change list
   const bool direct = screening && fused && !cascade;
+  step_open(c, screening);
   c->T_count = 0;
   c->have_y = c->have_logits = false;
   if (samples) {
@@ -921,7 +975,7 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
     *act = c->R_open ? nullptr : c->Rlist.as<int32_t>();
     *nact = c->R_open ? n : c->R_count;
   } else {
-    if (mode == DC_MODE_STATIC) start_from_singletons(c);
+    c->singletons = mode == DC_MODE_STATIC;
     S.R_size = n;
     c->have_R_all = true;
     *act = nullptr;
@@ -945,12 +999,14 @@ void screening_counts(dc_ctx* c) {
 // Last part of a time step: C_t to the caller (device or host memory),
 // unless levels_finish has already copied it with its last wait.
 void apply_output(dc_ctx* c) {
-  if (!c->out_C) return;
-  DC_HIP(hipMemcpyAsync(c->out_C, c->C.p, size_t(c->n) * 4,
-                        c->out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                        c->st));
-  DC_HIP(hipStreamSynchronize(c->st));
-  c->out_C = nullptr;
+  if (c->out_C) {
+    DC_HIP(hipMemcpyAsync(c->out_C, c->C.p, size_t(c->n) * 4,
+                          c->out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                          c->st));
+    DC_HIP(hipStreamSynchronize(c->st));
+    c->out_C = nullptr;
+  }
+  c->step = STEP_NONE;
 }
 
 void apply_output(dc_ctx* c, int32_t* C_out, int32_t out_on_device) {
@@ -1005,26 +1061,42 @@ dc_status do_apply(dc_ctx* c, const dc_edges* add, const dc_edges* del, int32_t*
   return DC_OK;
 }
 
+dc_status call_failed(dc_ctx* c) {
+  dc_status s = DC_E_DEVICE;
+  try {
+    throw;
+  } catch (const DeviceError& e) {
+    s = map_device_error(e);
+  } catch (const std::bad_alloc&) {
+    g_last_error = "host allocation failed";
+    s = DC_E_OOM;
+  } catch (const std::exception& e) {
+    g_last_error = e.what();
+  } catch (...) {
+  }
+  // out of memory leaves the context as it was, or with labels half written
+  // nothing does
+  if (s == DC_E_OOM && c->step == STEP_OPEN) {
+    try {
+      step_undo(c);
+    } catch (...) {
+      s = DC_E_DEVICE;
+    }
+  } else if (c->step == STEP_FINAL) {
+    s = DC_E_DEVICE;
+  }
+  if (s == DC_E_DEVICE) c->poisoned = true;
+  return s;
+}
+
 template <class F>
 dc_status guarded(dc_ctx* c, F&& f) {
   if (!c) return DC_E_ARG;
   if (c->poisoned) return DC_E_STATE;
   try {
     return f();
-  } catch (const DeviceError& e) {
-    dc_status s = map_device_error(e);
-    if (s == DC_E_DEVICE) c->poisoned = true;
-    return s;
-  } catch (const std::bad_alloc&) {
-    g_last_error = "host allocation failed";
-    return DC_E_OOM;
-  } catch (const std::exception& e) {
-    g_last_error = e.what();
-    c->poisoned = true;
-    return DC_E_DEVICE;
   } catch (...) {
-    c->poisoned = true;
-    return DC_E_DEVICE;
+    return call_failed(c);
   }
 }
 
@@ -1059,7 +1131,7 @@ void for_each_buf(dc_ctx* c, F&& f) {
                   &c->rk1, &c->rv1, &c->rpart, &c->npart, &c->ch_key, &c->ch_op, &c->ch_w,
                   &c->ch_dk, &c->cnet, &c->cptr, &c->new_deg, &c->deg_part, &c->tile_row, &c->ins_pos, &c->ins_keys, &c->src_flag,
                   &c->src_pos, &c->src_list, &c->dflag, &c->dpos, &c->dlist, &c->R, &c->cflag,
-                  &c->rflag, &c->rpos2, &c->Rlist, &c->seg_beg, &c->seg_end, &c->chsrc,
+                  &c->rflag, &c->rpos2, &c->Rlist, &c->seg_beg, &c->seg_end, &c->chsrc, &c->R_before,
                   &c->accflag, &c->cascand, &c->clist, &c->uflag, &c->ulist, &c->pre, &c->sink_g, &c->best_j,
                   &c->best_g, &c->ds_items, &c->sub_cnt, &c->sub_off, &c->sub_adj,
                   &c->par, &c->first,

@@ -10,6 +10,21 @@
 
 using namespace dc;
 
+// A time step between its first change and its last: OPEN from the first change
+// on (step_undo takes it back), FINAL once the new labels are being written.
+enum StepState : int { STEP_NONE = 0, STEP_OPEN, STEP_FINAL };
+
+// What a step replaces beside the buffers it leaves alone until it is final
+// (the CSR of G_{t-1}, C_{t-1}).
+struct StepStart {
+  int cur = 0;
+  int64_t nnz = 0, two_m = 0, R_count = 0;
+  bool have_R_all = true;
+  bool R_kept = false;  // dc_ctx.R_before holds the bytes of R
+  dc_step_stats stats{};
+  std::vector<dc_sweep_rec> trace;
+};
+
 struct dc_ctx {
   int32_t n = 0;
   dc_options opt{};
@@ -64,6 +79,10 @@ struct dc_ctx {
   bool R_open = false;           // R holds R_t but for the members of the communities that
   const uint8_t* R_cflag = nullptr;  // R_cflag flags (null: none); level 0 completes it
   bool have_R_all = true;
+  bool singletons = false;       // level 0 starts from singletons (its next start only)
+  StepState step = STEP_NONE;
+  StepStart before;              // of the step that is OPEN
+  DBuf R_before;                 // R_{t-1} during a step that screens
   // graph of communities kept across steps (incremental level-0 compaction)
   IncCoarsen inc;
   int64_t nch_last = 0;     // change records of the current batch
@@ -109,6 +128,8 @@ dc_status apply_front(dc_ctx* c, const dc_edges* add, const dc_edges* del, const
 void levels_begin(dc_ctx* c, const int32_t* active, int64_t n_active, LevelRun& L);
 void levels_finish(dc_ctx* c, LevelRun& L, long long level0_gain);
 void apply_output(dc_ctx* c, int32_t* C_out, int32_t out_on_device);
+// The status of a call on c that threw; called in the handler that caught it.
+dc_status call_failed(dc_ctx* c);
 // All levels of one step (Louvain or SLM per the options), level 0 over
 // `active` (null = every vertex); for graphs that do not merge level 0.
 void run_levels(dc_ctx* c, const int32_t* active, int64_t n_active);

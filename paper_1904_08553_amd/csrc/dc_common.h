@@ -18,6 +18,7 @@
 #include <cstdint>
 #include <stdexcept>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "dc.h"
@@ -93,6 +94,11 @@ struct DBuf {
     return static_cast<T*>(p);
   }
 };
+
+inline void swap_buf(DBuf& x, DBuf& y) {
+  std::swap(x.p, y.p);
+  std::swap(x.bytes, y.bytes);
+}
 
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
