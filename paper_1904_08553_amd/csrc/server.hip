@@ -256,8 +256,8 @@ void dc_server::run() {
         }
         if (c->opt.algorithm == DC_ALGO_SLM) {
           // SLM refines level 0 after its local moving: its levels run whole
-          run_levels(c, act, nact);
           r->C.resize(size_t(c->n));
+          run_levels(c, act, nact);
           apply_output(c, r->C.data(), 0);
           c->stats.ms_total = std::chrono::duration<double, std::milli>(
                                   std::chrono::steady_clock::now().time_since_epoch())
@@ -272,9 +272,8 @@ void dc_server::run() {
         cs.push_back(c);
         Ls.push_back(L);
         swept.push_back(r);
-      } catch (const DeviceError&) {
-        c->poisoned = true;
-        finish(r, DC_E_DEVICE);
+      } catch (...) {
+        finish(r, call_failed(c));
       }
     }
     if (!swept.empty()) {
@@ -282,7 +281,7 @@ void dc_server::run() {
       bool ok = true;
       try {
         level0_merged(cs.data(), Ls.data(), gains.data(), int(swept.size()), X);
-      } catch (const std::exception&) {
+      } catch (...) {
         ok = false;
       }
       for (size_t j = 0; j < swept.size(); ++j) {
@@ -294,8 +293,8 @@ void dc_server::run() {
           continue;
         }
         try {
-          levels_finish(c, Ls[j], gains[j]);
           r->C.resize(size_t(c->n));
+          levels_finish(c, Ls[j], gains[j]);
           apply_output(c, r->C.data(), 0);
           const double now = std::chrono::duration<double, std::milli>(
                                  std::chrono::steady_clock::now().time_since_epoch())
@@ -303,9 +302,8 @@ void dc_server::run() {
           c->stats.ms_total = now - r->t0_ms;
           r->stats = c->stats;
           finish(r, DC_OK);
-        } catch (const DeviceError&) {
-          c->poisoned = true;
-          finish(r, DC_E_DEVICE);
+        } catch (...) {
+          finish(r, call_failed(c));
         }
       }
       for (size_t j = 0; j < swept.size(); ++j) all[size_t(swept[j]->gid)]->edges = cs[j]->nnz / 2;

@@ -5,6 +5,8 @@ import os
 import sys
 
 SHIM = ct.CDLL(sys.argv[1], mode=ct.RTLD_GLOBAL) if __name__ == "__main__" else None
+if SHIM:
+    SHIM.shim_launches.restype = ct.c_long
 sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
 
 import numpy as np  # noqa: E402
@@ -80,6 +82,53 @@ def out_of_memory(case):
     assert allowed > 20
 
 
+def server(_):
+    """A batch whose memory runs out, one whose kernels never run and one whose
+    last sweep never runs: each fails alone, and the server goes on."""
+    n = 1500
+    edges, batches = W.DCSBM(n=n, m=6 * n, blocks=15, dmax=300, seed=5).stream(2, frac=0.05)
+    batches = [(b.add_u, b.add_v, b.add_w, b.del_u, b.del_v) for b in batches]
+    ref = dc.DynamicCommunities(n, *edges)
+    want = [ref.apply_batch(*b).copy() for b in batches]
+    ref.close()
+    srv = dc.Server(max_inflight=4)
+    oom, front, finish, twin = [srv.add_graph(n, *edges) for _ in range(4)]
+
+    def run(gid, t):
+        ticket = srv.submit(gid, *batches[t])
+        try:
+            return srv.poll(ticket, gid)[0]
+        except dc.DCError as e:
+            return e.status
+
+    dc.load().dc_trim_device_cache()
+    SHIM.shim_allow(ct.c_long(2))
+    assert run(oom, 0) == -8
+    SHIM.shim_allow(ct.c_long(-1))
+    assert np.array_equal(run(oom, 0), want[0])
+    print("out of memory: reported, then as if nothing had been", flush=True)
+
+    SHIM.shim_drop_from(ct.c_long(SHIM.shim_launches()))
+    assert run(front, 0) == -9
+    SHIM.shim_drop_from(ct.c_long(-1))
+    assert run(front, 0) == -10
+    print("no kernel ran: the graph is out of use", flush=True)
+
+    first = SHIM.shim_launches()
+    assert np.array_equal(run(twin, 0), want[0])
+    steps = SHIM.shim_launches() - first
+    # the last six launches: a sweep's four and the final labels' two
+    SHIM.shim_drop_from(ct.c_long(SHIM.shim_launches() + steps - 6))
+    assert run(finish, 0) == -9
+    SHIM.shim_drop_from(ct.c_long(-1))
+    assert run(finish, 0) == -10
+    print("the last sweep did not run: the graph is out of use", flush=True)
+
+    for gid in (oom, twin):
+        assert np.array_equal(run(gid, 1), want[1])
+    srv.close()
+
+
 if __name__ == "__main__":
     kind, _, arg = sys.argv[2].partition(":")
-    {"oom": out_of_memory}[kind](arg)
+    {"oom": out_of_memory, "server": server}[kind](arg)

@@ -32,3 +32,7 @@ def _run(shim, case):
 @pytest.mark.parametrize("case", sorted(OPTIONS))
 def test_batch_out_of_memory(shim, case):
     _run(shim, f"oom:{case}")
+
+
+def test_server_goes_on_after_failed_batches(shim):
+    _run(shim, "server")
