@@ -237,9 +237,9 @@ __device__ __forceinline__ void host_store(T* p, T v) {
 
 // A kernel's publication to the host: a word of pinned host memory that the
 // kernel sets to the launch's own value once the data before it is there.
-// The host spins on the word (wait_tag), which returns some microseconds
-// before a wait on the stream would, and launches queued behind the kernel
-// run meanwhile.
+// The host spins on the word for a while (wait_tag), which returns some
+// microseconds before a wait on the stream would, and launches queued behind the
+// kernel run meanwhile.
 struct HostTag {
   uint32_t* host = nullptr;
   uint32_t* dev = nullptr;

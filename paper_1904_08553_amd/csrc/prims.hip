@@ -1,6 +1,7 @@
 // prims.hip -- scan, stable LSD radix sort, fills.  Hand-written for gfx950:
 // 256-thread blocks of four 64-wide waves, wave prefix sums by shuffles,
 // radix ranking by one 64-bit ballot per digit bit, running digit counts per wave.
+#include <chrono>
 #include <cstdlib>
 
 #include "dc_scan.h"
@@ -15,20 +16,29 @@ bool sync_check_enabled() {
   return on;
 }
 
+// Most publications come within some tens of microseconds, for which the host
+// spins; after SPIN_US it waits on the stream instead, asleep if the device's
+// scheduling flag says so, so that a long kernel does not cost the process a
+// core.  A stream that failed, or that ended without the publication, ends the
+// wait there.
+constexpr int SPIN_US = 300;
 void wait_tag(const HostTag& t, hipStream_t st) {
+  using clock = std::chrono::steady_clock;
+  clock::time_point until{};
   for (uint32_t spin = 1;; ++spin) {
     if (__atomic_load_n(t.host, __ATOMIC_ACQUIRE) == t.value) return;
-    if (spin % 4096 == 0) {
-      // about every 100 us: a stream that failed, or that ended without
-      // the publication, ends the wait
-      const hipError_t e = hipStreamQuery(st);
-      if (e == hipErrorNotReady) continue;
-      DC_HIP(e);
-      if (__atomic_load_n(t.host, __ATOMIC_ACQUIRE) == t.value) return;
-      throw std::runtime_error("a kernel ended without its publication");
+    if (spin % 64 == 0) {
+      const clock::time_point now = clock::now();
+      if (spin == 64)
+        until = now + std::chrono::microseconds(SPIN_US);
+      else if (now >= until)
+        break;
     }
     __builtin_ia32_pause();
   }
+  DC_HIP(hipStreamSynchronize(st));
+  if (__atomic_load_n(t.host, __ATOMIC_ACQUIRE) != t.value)
+    throw std::runtime_error("a kernel ended without its publication");
 }
 
 PrimScratch& prim_scratch() {
