@@ -3,6 +3,7 @@
 // radix ranking by one 64-bit ballot per digit bit, running digit counts per wave.
 #include <chrono>
 #include <cstdlib>
+#include <thread>
 
 #include "dc_scan.h"
 
@@ -17,24 +18,27 @@ bool sync_check_enabled() {
 }
 
 // Most publications come within some tens of microseconds, for which the host
-// spins; after SPIN_US it waits on the stream instead, asleep if the device's
-// scheduling flag says so, so that a long kernel does not cost the process a
-// core.  A stream that failed, or that ended without the publication, ends the
-// wait there.
-constexpr int SPIN_US = 300;
+// spins.  After SPIN_US it offers its core to other threads between two looks,
+// and after YIELD_US it waits on the stream, asleep if the device's scheduling
+// flag says so, so that a long kernel does not cost the process a core.  A
+// stream that failed, or that ended without the publication, ends the wait
+// there.
+constexpr int SPIN_US = 300, YIELD_US = 2000;
 void wait_tag(const HostTag& t, hipStream_t st) {
   using clock = std::chrono::steady_clock;
-  clock::time_point until{};
+  clock::time_point start{};
+  bool yield = false;
   for (uint32_t spin = 1;; ++spin) {
     if (__atomic_load_n(t.host, __ATOMIC_ACQUIRE) == t.value) return;
-    if (spin % 64 == 0) {
-      const clock::time_point now = clock::now();
-      if (spin == 64)
-        until = now + std::chrono::microseconds(SPIN_US);
-      else if (now >= until)
-        break;
-    }
-    __builtin_ia32_pause();
+    if (yield)
+      std::this_thread::yield();
+    else
+      __builtin_ia32_pause();
+    if (spin % 64 != 0) continue;
+    const clock::time_point now = clock::now();
+    if (spin == 64) start = now;
+    if (now - start >= std::chrono::microseconds(YIELD_US)) break;
+    yield = now - start >= std::chrono::microseconds(SPIN_US);
   }
   DC_HIP(hipStreamSynchronize(st));
   if (__atomic_load_n(t.host, __ATOMIC_ACQUIRE) != t.value)

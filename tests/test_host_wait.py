@@ -115,7 +115,7 @@ int main() {
 
 def _source():
     text = open(SRC).read()
-    m = re.search(r"^(constexpr int SPIN_US = \d+;\n)?void wait_tag\(.*?\n\}\n", text, re.S | re.M)
+    m = re.search(r"^(constexpr int SPIN_US = [^;]*;\n)?void wait_tag\(.*?\n\}\n", text, re.S | re.M)
     assert m, "wait_tag not found in prims.hip"
     return m.group(0)
 
