@@ -37,10 +37,15 @@ __device__ __forceinline__ void touch_label(int X, long long v, long long* dpack
 // labels are loaded first, the block reserves its movers' places in the mover
 // list with one atomic, then lists them and applies their label changes.
 // The reservations of all blocks queue at one counter (about 30 ns each), and
-// a block is one chain of dependent loads and barriers: 1024 threads and as
-// many rounds as keep the grid near 500 blocks.  Blocks of 2,048 entries
-// took 162 us for 8M active vertices (4,000 reservations) and 35 for 300K
-// (147 blocks on 256 CUs), these 108 and 25.
+// a block is one chain of dependent loads and barriers: 1024 threads, and more
+// rounds for longer lists (sweep_apply).  With few movers, blocks of 2,048
+// entries took 162 us for 8M active vertices (4,000 reservations), these 108.
+// The label changes are summed in an LDS table, for all rounds together as long
+// as it has room for their labels; it is emptied after a round that leaves it
+// more than half full (first sweeps from singletons), since labels past it go
+// one by one to the counter of touched labels.  A first sweep of 1.06M / 2.1M /
+// 4.3M vertices takes 160 / 277 / 575 us that way, and took 390 / 753 / 1,542 in
+// blocks of eight rounds with one table for all of them.
 constexpr int AM_TPB = 1024;
 constexpr int AM_NW = AM_TPB / WAVE;
 template <int ROUNDS>
@@ -75,8 +80,30 @@ __global__ void __launch_bounds__(AM_TPB)
   // one update per block (see agg_try)
   agg_init(agg);
   auto* const counters = reinterpret_cast<unsigned long long*>(stat);
-  if (reserve_places<ROUNDS * AM_NW>(&wc[0][0], counters + ST_MOVES) == 0)
-    return;  // uniform: nothing moved in this block's tiles
+  const int total = reserve_places<ROUNDS * AM_NW>(&wc[0][0], counters + ST_MOVES);
+  if (total == 0) return;  // uniform: nothing moved in this block's tiles
+  // every label in the table gets one global update; the labels that this
+  // sweep touches first are appended to tlist with one counter update for the
+  // block
+  static_assert(AGG_SLOTS == AM_TPB, "a slot per thread");
+  __shared__ int fcount[AM_NW];
+  auto flush = [&]() {
+    const int X = agg.keys[threadIdx.x];
+    bool first = false;
+    if (X != EMPTY_KEY) {
+      const long long v = agg.vals[threadIdx.x];
+      if (v != 0) {
+        atomicAdd((unsigned long long*)&dpack[X], (unsigned long long)v);
+        first = atomicExch(&tflag[X], 1) == 0;
+      }
+    }
+    const uint64_t gm = __ballot(first);
+    if (lane == 0) fcount[wid] = __popcll(gm);
+    agg_init(agg);  // each thread its own slot
+    (void)reserve_places<AM_NW>(fcount, counters + ST_TOUCHED);
+    if (first) tlist[fcount[wid] + __popcll(gm & lt)] = X;
+  };
+  const bool many = total > AGG_SLOTS / 2;  // two labels each
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     if (from[r] != to[r]) {
@@ -87,34 +114,11 @@ __global__ void __launch_bounds__(AM_TPB)
       if (!agg_try(agg, to[r], pack2(ku, 1)))
         touch_label(to[r], pack2(ku, 1), dpack, tflag, tlist, stat);
     }
+    if (many || r == ROUNDS - 1) __syncthreads();
+    if (r == ROUNDS - 1 ||
+        (many && __syncthreads_count(agg.keys[threadIdx.x] != EMPTY_KEY) > AGG_SLOTS / 2))
+      flush();
   }
-  // every label left in the table gets one global update; the labels that
-  // this sweep touches first are appended to tlist with one counter update
-  // for the block
-  constexpr int FR = AGG_SLOTS / AM_TPB;
-  __shared__ int fcount[FR][AM_NW];
-  __syncthreads();
-  int fx[FR];
-  uint64_t gm[FR];
-#pragma unroll
-  for (int r = 0; r < FR; ++r) {
-    const int X = agg.keys[r * AM_TPB + threadIdx.x];
-    bool first = false;
-    if (X != EMPTY_KEY) {
-      const long long v = agg.vals[r * AM_TPB + threadIdx.x];
-      if (v != 0) {
-        atomicAdd((unsigned long long*)&dpack[X], (unsigned long long)v);
-        first = atomicExch(&tflag[X], 1) == 0;
-      }
-    }
-    fx[r] = first ? X : -1;
-    gm[r] = __ballot(first);
-    if (lane == 0) fcount[r][wid] = __popcll(gm[r]);
-  }
-  (void)reserve_places<FR * AM_NW>(&fcount[0][0], counters + ST_TOUCHED);
-#pragma unroll
-  for (int r = 0; r < FR; ++r)
-    if (fx[r] >= 0) tlist[fcount[r][wid] + __popcll(gm[r] & lt)] = fx[r];
 }
 
 
@@ -286,10 +290,14 @@ void sweep_apply(const LevelView& g, const int32_t* active, int64_t n_active, in
     k_apply_moves<R><<<int(ceil_div(cnt, R * AM_TPB)), AM_TPB, 0, st>>>(
         active, n_active, C, Cn, g.k, dpack, tflag, tlist, movers, stat);
   };
+  // at most 512 blocks up to 4M active vertices, and never fewer than 256 (a
+  // block per CU) once there is more than one round
   if (cnt <= 512 * AM_TPB)
     apply(std::integral_constant<int, 1>());
   else if (cnt <= 2 * 512 * AM_TPB)
     apply(std::integral_constant<int, 2>());
+  else if (cnt <= 4 * 512 * AM_TPB)
+    apply(std::integral_constant<int, 4>());
   else
     apply(std::integral_constant<int, 8>());
   DC_LAUNCH_CHECK();

@@ -211,3 +211,23 @@ def test_hub_tables_past_one_round(hubs):
     w = ((u.astype(np.int64) * 7 + v * 13) % 5 + 1).astype(np.int32)
     o, g = make_pair(hubs + leaves, u, v, w, max_levels=1, max_sweeps=1)
     compare(o, g, f"hubs={hubs}")
+
+
+@pytest.mark.parametrize("n", [1 << 19, (1 << 19) + 1, (1 << 20) + 1, (1 << 21) + 1])
+def test_movers_at_block_rounds(n):
+    """Triangles with random edges between them, from singletons: most vertices
+    of a block move, to more labels than its table holds; then a batch that moves
+    few.  Vertex counts around those at which a block takes more of the list."""
+    print(f"case: movers of {n} vertices", flush=True)
+    rng = np.random.default_rng(n)
+    i = np.arange(n // 3) * 3
+    u = np.concatenate([i, i, i + 1, rng.integers(0, n, n // 8)])
+    v = np.concatenate([i + 1, i + 2, i + 2, rng.integers(0, n, n // 8)])
+    u, v = u[u != v].astype(np.int32), v[u != v].astype(np.int32)
+    w = (1 + u % 3).astype(np.int32)
+    o, g = make_pair(n, u, v, w)
+    compare(o, g, "init")
+    add_u = rng.integers(0, n, 500).astype(np.int32)
+    add_v = ((add_u + 1 + rng.integers(0, n - 1, 500)) % n).astype(np.int32)
+    step_pair(o, g, W.Batch(add_u, add_v, np.full(500, 9, np.int32), u[:200], v[:200]))
+    compare(o, g, "step")
