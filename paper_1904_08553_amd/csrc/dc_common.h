@@ -418,13 +418,8 @@ __device__ __forceinline__ int table_get(const int* keys, const int* vals,
 // primitives (prims.hip)
 
 // out[i] = sum_{j<i} in[j]; *total (device, may be null) = sum of all.
-// host_total (may be null): a device-visible address of pinned host memory
-// that the last kernel also writes the sum to, for the host to read after
-// its next wait on the stream (no copy).
-void scan_excl_i32(const int32_t* in, int32_t* out, int64_t n,
-                   int32_t* total, hipStream_t st, int32_t* host_total = nullptr);
-void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n,
-                   int64_t* total, hipStream_t st, int64_t* host_total = nullptr);
+void scan_excl_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* total, hipStream_t st);
+void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* total, hipStream_t st);
 
 // scan_excl_i32 whose tile totals the caller's kernel has already written to
 // part (one per SCAN_TILE elements of dc_scan.h; overwritten).

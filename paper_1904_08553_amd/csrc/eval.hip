@@ -156,78 +156,40 @@ __device__ __forceinline__ int group_sum(int v) {
     return group_sum<GS, S + 1>(v + xchg<S>(v));
 }
 
-// The value of the lane of each lane's own group whose flag is set (at most
-// one per group), 0 when none is: one ballot and a readlane per group.
-template <int GS>
-__device__ __forceinline__ int group_pick(bool flag, int v) {
-  constexpr int GPW = WAVE / GS;
+// The value of the wave's lane whose flag is set (at most one), 0 when none is.
+__device__ __forceinline__ int wave_pick(bool flag, int v) {
   const uint64_t m = __ballot(flag);
-  int out = 0;
-#pragma unroll
-  for (int g = 0; g < GPW; ++g) {
-    uint64_t sub;
-    if constexpr (GPW == 1)
-      sub = m;
-    else
-      sub = (m >> (g * GS)) & ((uint64_t(1) << GS) - 1);
-    const int x = sub ? __builtin_amdgcn_readlane(v, g * GS + __builtin_ctzll(sub)) : 0;
-    if (int(lane_id()) / GS == g) out = x;
-  }
-  return out;
+  return m ? __builtin_amdgcn_readlane(v, __builtin_ctzll(m)) : 0;
 }
 
-// Per group: lane r of the group (r < returned count) receives the r-th
-// distinct label of the group's valid lanes (order of first appearance)
-// and its weight sum.  Each iteration takes, for every group of the wave at
-// once, the label of the lowest lane not yet matched (scalar readlanes) and
-// matches it with one ballot; afterwards every valid lane adds its weight
-// into the LDS slot of its label's rank.  lsum: the wave's 64 ints, zero on
-// entry and on return.
-// probe / prank (may be null): each lane's rank of label `probe` among its
-// group's distinct labels, -1 when absent (found as the labels are taken).
-template <int GS>
-__device__ __forceinline__ int group_collect(bool valid, int key, int w, int* lsum, int& ck,
-                                             int& cs, int* iters = nullptr, int probe = 0,
-                                             int* prank = nullptr) {
-  constexpr int GPW = WAVE / GS;
+// Lane r of the wave (r < returned count) receives the r-th distinct label of
+// the valid lanes (order of first appearance) and its weight sum.  Each
+// iteration takes the label of the lowest lane not yet matched (a scalar
+// readlane) and matches it with one ballot; afterwards every valid lane adds
+// its weight into the LDS slot of its label's rank.  lsum: the wave's 64 ints,
+// zero on entry and on return.
+// probe / prank (may be null): each lane's rank of label `probe` among the
+// distinct labels, -1 when absent (found as the labels are taken).
+__device__ __forceinline__ int wave_collect(bool valid, int key, int w, int* lsum, int& ck, int& cs,
+                                            int probe = 0, int* prank = nullptr) {
   const int lane = lane_id();
-  const int gl = lane & (GS - 1);
-  const int grp = lane / GS;
   uint64_t rem = __ballot(valid);
-  int r = 0, myr = 0, it = 0, pr = -1;
+  int r = 0, myr = 0, pr = -1;
   while (rem) {
-    ++it;
-    int kl = 0;
-    bool act = false;
-#pragma unroll
-    for (int g = 0; g < GPW; ++g) {
-      uint64_t sub;
-      if constexpr (GPW == 1)
-        sub = rem;
-      else
-        sub = (rem >> (g * GS)) & ((uint64_t(1) << GS) - 1);
-      if (sub) {
-        const int kg = __builtin_amdgcn_readlane(key, g * GS + __builtin_ctzll(sub));
-        if (grp == g) {
-          kl = kg;
-          act = true;
-        }
-      }
-    }
-    const bool mine = act && valid && key == kl;
+    const int kl = __builtin_amdgcn_readlane(key, __builtin_ctzll(rem));
+    const bool mine = valid && key == kl;
     rem &= ~__ballot(mine);
     if (mine) myr = r;
-    if (act && gl == r) ck = kl;
-    if (prank && act && probe == kl) pr = r;
-    r += act ? 1 : 0;
+    if (lane == r) ck = kl;
+    if (prank && probe == kl) pr = r;
+    ++r;
   }
   if (prank) *prank = pr;
-  if (valid) atomicAdd(&lsum[lane - gl + myr], w);
+  if (valid) atomicAdd(&lsum[myr], w);
   wave_sync();
-  cs = gl < r ? lsum[lane] : 0;
+  cs = lane < r ? lsum[lane] : 0;
   lsum[lane] = 0;
   wave_sync();
-  if (iters) *iters = it;  // wave-uniform: the largest count of any group
   return r;
 }
 
@@ -235,8 +197,8 @@ __device__ __forceinline__ int group_collect(bool valid, int key, int w, int* ls
 // label c (own).  A lane for which it returns true holds a label (ck) and that
 // label's sum (cs).  In groups of at most 32 lanes every lane compares its own
 // label with all the others', so several lanes may hold one label: straight-line
-// DPP code of two exchanges and three operations per peer, where the loop of
-// group_collect takes one label of each group per turn (a readlane and selects
+// DPP code of two exchanges and three operations per peer, where a loop like
+// wave_collect's takes one label of each group per turn (a readlane and selects
 // per group) and ends in LDS atomics.  Its turns are as many as the distinct
 // labels of the wave's worst group: sweeps of the 316K planted graph took
 // 14.5 us with it and take 7.8, those of an 8M-vertex temporal graph 414 and
@@ -256,9 +218,9 @@ __device__ __forceinline__ bool group_labels(bool valid, int y, int w, int c, in
     it = GS;
     return valid;
   } else {
-    const int nd = group_collect<GS>(valid, key, w, lsum, ck, cs, &it);
-    const bool has = (lane_id() & (GS - 1)) < nd;
-    own = group_pick<GS>(has && ck == c, cs);
+    it = wave_collect(valid, key, w, lsum, ck, cs);
+    const bool has = lane_id() < it;
+    own = wave_pick(has && ck == c, cs);
     return has;
   }
 }
@@ -282,14 +244,12 @@ __device__ __forceinline__ bool group_labels(bool valid, int y, int w, int c, in
     }
     return has;
   } else {
-    const int lane = lane_id(), gl = lane & (GS - 1);
     int xr = -1;
-    const int nd = group_collect<GS>(valid, valid ? y : EMPTY_KEY, w, lsum, ck, cs, &it,
-                                     sink ? X : EMPTY_KEY, &xr);
-    const int sv = __shfl(cs, lane - gl + (xr < 0 ? 0 : xr), WAVE);
+    it = wave_collect(valid, valid ? y : EMPTY_KEY, w, lsum, ck, cs, sink ? X : EMPTY_KEY, &xr);
+    const int sv = __shfl(cs, xr < 0 ? 0 : xr, WAVE);
     if (xr >= 0) sx = sv;
-    const bool has = gl < nd;
-    own = group_pick<GS>(has && ck == c, cs);
+    const bool has = lane_id() < it;
+    own = wave_pick(has && ck == c, cs);
     return has;
   }
 }
@@ -373,8 +333,8 @@ __device__ __forceinline__ void pre_commit(const EvalArgs& A, int i, bool move, 
 // for a deletion endpoint (the conservative-rule path runs the two tests in
 // separate passes).  Returns the deletion tests accepted (0 or ACC_DEL).
 template <int MODE, int GS>
-__device__ __forceinline__ long long group_item(const EvalArgs& A, int i, bool have, int lane,
-                                                int gl, int gbase, int* lsum) {
+__device__ __forceinline__ long long group_item(const EvalArgs& A, int i, bool have, int gl,
+                                                int* lsum) {
   static_assert(MODE == EV_SWEEP || MODE == EV_DSADD || MODE == EV_DSDEL,
                 "the paired kernels take the other modes");
   long long accepted = 0;
@@ -647,7 +607,6 @@ __device__ __forceinline__ void eval_group_body(const EvalArgs& A, const BinList
   constexpr int GPW = WAVE / GS;  // groups per wave
   const int lane = lane_id();
   const int gl = lane & (GS - 1);
-  const int gbase = lane - gl;
   const int64_t cnt = *L.count;
   const int64_t ngroups = nblocks * NW * GPW;
   long long accepted = 0;
@@ -675,7 +634,7 @@ __device__ __forceinline__ void eval_group_body(const EvalArgs& A, const BinList
       const int64_t idx = wb + lane / GS;
       const bool have = idx < cnt;
       const int i = have ? L.list[idx] : 0;
-      accepted += group_item<MODE, GS>(A, i, have, lane, gl, gbase, ls);
+      accepted += group_item<MODE, GS>(A, i, have, gl, ls);
     }
   }
   if constexpr (MODE != EV_SWEEP && MODE != EV_FEAT) {
@@ -804,27 +763,27 @@ __device__ __forceinline__ uint32_t table_cap(int deg, uint32_t max_slots) {
 constexpr int GTPB = 1024;  // threads of a bin-G block (one hub row per block)
 constexpr int GT_UI = 8;     // bin G: row chunks per load round
 constexpr int WTAB_UI = WTAB_MAX / WAVE;   // bin W: the whole row in one load round
-constexpr int WTAB_US = 8;                 // and its table in rounds of 8 slots
+constexpr int TAB_US = 8;    // a block's table: slots of a thread taken together
 
 // This thread's best (score, label) over its slots of the table, skipping
-// label `skip`; the community totals of US slots are gathered together.
-template <int G, int US>
+// label `skip`; the community totals of TAB_US slots are gathered together.
+template <int G>
 __device__ __forceinline__ Best table_best(const EvalArgs& A, const int* keys, const int* vals,
                                            uint32_t mask, long long ki, int skip, int t) {
   Best b = {NO_SCORE, NO_LABEL};
-  for (uint32_t s0 = t; s0 <= mask; s0 += US * G) {
-    int X[US], V[US], AX[US];
+  for (uint32_t s0 = t; s0 <= mask; s0 += TAB_US * G) {
+    int X[TAB_US], V[TAB_US], AX[TAB_US];
 #pragma unroll
-    for (int u = 0; u < US; ++u) {
+    for (int u = 0; u < TAB_US; ++u) {
       const uint32_t s = s0 + uint32_t(u * G);
       X[u] = s <= mask ? keys[s] : EMPTY_KEY;
       V[u] = s <= mask ? vals[s] : 0;
       if (X[u] == skip) X[u] = EMPTY_KEY;
     }
 #pragma unroll
-    for (int u = 0; u < US; ++u) AX[u] = X[u] != EMPTY_KEY ? A.a[X[u]] : 0;
+    for (int u = 0; u < TAB_US; ++u) AX[u] = X[u] != EMPTY_KEY ? A.a[X[u]] : 0;
 #pragma unroll
-    for (int u = 0; u < US; ++u) {
+    for (int u = 0; u < TAB_US; ++u) {
       if (X[u] == EMPTY_KEY) continue;
       // 2m < 2^31: 32x32->64 products
       const long long sc = (long long)int(A.two_m) * V[u] - (long long)int(ki) * AX[u];
@@ -865,7 +824,7 @@ __device__ __forceinline__ Best table_best_listed(const EvalArgs& A, const int* 
 // 38 and 104 (L1 misses queueing for the label gathers bound it: its requests
 // come at the short-row kernel's rate).
 constexpr long long TABLE_FULL = -1;
-template <int MODE, int G, int UI, int US, bool BOUNDED = false>
+template <int MODE, int G, int UI, bool BOUNDED = false>
 __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, uint32_t mask,
                                 GroupLds<G>& L, int* tstate = nullptr,
                                 uint16_t* used = nullptr, int used_cap = 0) {
@@ -1008,7 +967,7 @@ __device__ long long eval_table(const EvalArgs& A, int i, int* keys, int* vals, 
     if constexpr (LISTED)
       return table_best_listed<G>(A, keys, vals, used, taken, ki, skip, t);
     else
-      return table_best<G, US>(A, keys, vals, mask, ki, skip, t);
+      return table_best<G>(A, keys, vals, mask, ki, skip, t);
   };
   Best b = best_label(EMPTY_KEY);
   b = group_best<G>(b, L);
@@ -1076,7 +1035,7 @@ __global__ void __launch_bounds__(TPB, MODE == EV_SWEEP ? 8 : 7) k_eval_wtab(Eva
   long long accepted = 0;
   for (int64_t idx = int64_t(blockIdx.x) * NW + wid; idx < cnt; idx += nwaves) {
     const int i = uniform(A.list[idx]);
-    const long long acc = eval_table<MODE, WAVE, WTAB_UI, WTAB_US, true>(
+    const long long acc = eval_table<MODE, WAVE, WTAB_UI, true>(
         A, i, keys[wid], vals[wid], WT_SLOTS - 1, L[wid], tst[wid], used[wid], WT_SLOTS / 2);
     if (acc == TABLE_FULL) {
       if (lane_id() == 0) A.ovf_list[atomicAdd(A.ovf_count, 1)] = i;
@@ -1099,7 +1058,7 @@ __global__ void __launch_bounds__(TPB) k_eval_btab(EvalArgs A) {
   const int i = A.list[idx];
   const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], BT_SLOTS);
   const long long acc =
-      eval_table<MODE, TPB, 4, 8, true>(A, i, keys, vals, cap - 1, L, tst);
+      eval_table<MODE, TPB, 4, true>(A, i, keys, vals, cap - 1, L, tst);
   if (threadIdx.x != 0) return;
   if (acc == TABLE_FULL)
     A.ovf_list[atomicAdd(A.ovf_count, 1)] = i;
@@ -1125,7 +1084,7 @@ __global__ void __launch_bounds__(TPB) k_eval_ovf(EvalArgs A) {
   for (int64_t idx = blockIdx.x; idx < cnt; idx += gridDim.x) {
     const int i = A.ovf_list[idx];
     const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], BTAB_SLOTS);
-    accepted += eval_table<MODE, TPB, 4, 8>(A, i, keys, vals, cap - 1, L);
+    accepted += eval_table<MODE, TPB, 4>(A, i, keys, vals, cap - 1, L);
   }
   if (MODE != EV_SWEEP && threadIdx.x == 0 && accepted) add_accepted(A.stat, accepted);
 }
@@ -1144,7 +1103,7 @@ __global__ void __launch_bounds__(GTPB) k_eval_gtab(EvalArgs A) {
   const int64_t idx = blockIdx.x;
   if (idx >= *A.count) return;
   const int i = A.list[idx];
-  long long acc = eval_table<MODE, GTPB, GT_UI, 8, true>(A, i, keys, vals, BTAB_SLOTS - 1, L,
+  long long acc = eval_table<MODE, GTPB, GT_UI, true>(A, i, keys, vals, BTAB_SLOTS - 1, L,
                                                          tstate);
   if (acc == TABLE_FULL) {
     const long long o0 = A.tab_off[idx], o1 = A.tab_off[idx + 1];
@@ -1153,7 +1112,7 @@ __global__ void __launch_bounds__(GTPB) k_eval_gtab(EvalArgs A) {
       if (threadIdx.x == 0) atomicOr((unsigned long long*)&A.stat[ST_ERR], 1ull);
       return;
     }
-    acc = eval_table<MODE, GTPB, 4, 8>(A, i, A.gkeys + o0, A.gvals + o0, uint32_t(o1 - o0) - 1,
+    acc = eval_table<MODE, GTPB, 4>(A, i, A.gkeys + o0, A.gvals + o0, uint32_t(o1 - o0) - 1,
                                        L);
   }
   if (MODE != EV_SWEEP && threadIdx.x == 0 && acc) add_accepted(A.stat, acc);
@@ -1177,7 +1136,6 @@ __global__ void __launch_bounds__(TPB) k_sweep_group_multi(MultiArgs M) {
   constexpr int GPW = WAVE / GS;
   const int lane = lane_id();
   const int gl = lane & (GS - 1);
-  const int gbase = lane - gl;
   __shared__ int lsum_all[NW][WAVE];
   int* ls = lsum_all[threadIdx.x / WAVE];
   ls[lane] = 0;
@@ -1189,7 +1147,7 @@ __global__ void __launch_bounds__(TPB) k_sweep_group_multi(MultiArgs M) {
     if (M.done[g]) continue;  // uniform: this graph's level has converged
     const EvalArgs A = M.descs[g];
     const int i = M.list[wb + lane / GS];
-    (void)group_item<EV_SWEEP, GS>(A, i < 0 ? 0 : i, i >= 0, lane, gl, gbase, ls);
+    (void)group_item<EV_SWEEP, GS>(A, i < 0 ? 0 : i, i >= 0, gl, ls);
   }
 }
 
@@ -1209,7 +1167,7 @@ __global__ void __launch_bounds__(TPB) k_sweep_wtab_multi(MultiArgs M) {
     if (M.done[g]) continue;
     const EvalArgs A = M.descs[g];
     const int i = uniform(M.list[idx]);
-    (void)eval_table<EV_SWEEP, WAVE, WTAB_UI, WTAB_US, true>(
+    (void)eval_table<EV_SWEEP, WAVE, WTAB_UI, true>(
         A, i, keys[wid], vals[wid], WT_SLOTS - 1, L[wid], tst[wid], used[wid], WT_SLOTS);
   }
 }
@@ -1224,7 +1182,7 @@ __global__ void __launch_bounds__(TPB) k_sweep_btab_multi(MultiArgs M) {
     const EvalArgs A = M.descs[g];
     const int i = M.list[idx];
     const uint32_t cap = table_cap(A.off[i + 1] - A.off[i], BTAB_SLOTS);
-    (void)eval_table<EV_SWEEP, TPB, 4, 8>(A, i, keys, vals, cap - 1, L);
+    (void)eval_table<EV_SWEEP, TPB, 4>(A, i, keys, vals, cap - 1, L);
   }
 }
 
@@ -1243,7 +1201,7 @@ __global__ void __launch_bounds__(GTPB)
   const EvalArgs A = M.descs[g];
   const int i = M.list[idx];
   const int64_t q = lidx[idx];
-  const long long acc = eval_table<EV_SWEEP, GTPB, GT_UI, 8, true>(A, i, keys, vals,
+  const long long acc = eval_table<EV_SWEEP, GTPB, GT_UI, true>(A, i, keys, vals,
                                                                     BTAB_SLOTS - 1, L, tstate);
   if (acc == TABLE_FULL) {
     const long long o0 = A.tab_off[q], o1 = A.tab_off[q + 1];
@@ -1251,7 +1209,7 @@ __global__ void __launch_bounds__(GTPB)
       if (threadIdx.x == 0) atomicOr((unsigned long long*)&A.stat[ST_ERR], 1ull);
       return;
     }
-    (void)eval_table<EV_SWEEP, GTPB, 4, 8>(A, i, A.gkeys + o0, A.gvals + o0,
+    (void)eval_table<EV_SWEEP, GTPB, 4>(A, i, A.gkeys + o0, A.gvals + o0,
                                            uint32_t(o1 - o0) - 1, L);
   }
 }
@@ -1554,12 +1512,6 @@ __global__ void __launch_bounds__(TO_TPB)
     at += tot;
   }
   if (threadIdx.x == 0) tab_off[cnt] = at;
-}
-
-inline int grid_for(int64_t n, int cap = 4096) {
-  int64_t g = ceil_div(n, TPB);
-  if (g > cap) g = cap;
-  return int(g < 1 ? 1 : g);
 }
 
 inline int wave_grid(int64_t items) {

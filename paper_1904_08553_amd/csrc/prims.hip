@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(SCAN_THREADS)
 template <class T>
 __global__ void __launch_bounds__(SCAN_THREADS)
     k_tile_scan(const T* in, T* out, int64_t n, const T* __restrict__ part, int raw,
-                T* total, int64_t nblocks, T* htotal) {
+                T* total, int64_t nblocks) {
   __shared__ T lds[SCAN_THREADS / WAVE];
   // the tile's items and the partials before it are loaded first, at
   // clamped indexes (n >= 1, nblocks >= 1), so they are in flight together
@@ -103,31 +103,27 @@ __global__ void __launch_bounds__(SCAN_THREADS)
     if (idx < n) out[idx] = run;
     run += v[i];
   }
-  if (blockIdx.x == nblocks - 1 && threadIdx.x == 0) {
-    if (total) *total = off + tot;
-    if (htotal) host_store(htotal, off + tot);
-  }
+  if (total && blockIdx.x == nblocks - 1 && threadIdx.x == 0) *total = off + tot;
 }
 
 template <class T>
-__global__ void k_set_scalar(T* p, T v, T* hp) {
-  if (p) *p = v;
-  if (hp) host_store(hp, v);
+__global__ void k_set_scalar(T* p, T v) {
+  *p = v;
 }
 
 template <class T>
 void scan_excl_impl(const T* in, T* out, int64_t n, T* total, hipStream_t st,
-                    T* tmp, size_t tmp_elems, T* htotal) {
+                    T* tmp, size_t tmp_elems) {
   if (n <= 0) {
-    if (total || htotal) {
-      k_set_scalar<T><<<1, 1, 0, st>>>(total, T(0), htotal);
+    if (total) {
+      k_set_scalar<T><<<1, 1, 0, st>>>(total, T(0));
       DC_LAUNCH_CHECK();
     }
     return;
   }
   int64_t nb = ceil_div(n, SCAN_TILE);
   if (nb == 1) {
-    k_tile_scan<T><<<1, SCAN_THREADS, 0, st>>>(in, out, n, nullptr, 0, total, 1, htotal);
+    k_tile_scan<T><<<1, SCAN_THREADS, 0, st>>>(in, out, n, nullptr, 0, total, 1);
     DC_LAUNCH_CHECK();
     return;
   }
@@ -137,24 +133,24 @@ void scan_excl_impl(const T* in, T* out, int64_t n, T* total, hipStream_t st,
   DC_LAUNCH_CHECK();
   if (nb <= SCAN_RAW_MAX) {
     // each tile sums the totals before it (at most SCAN_RAW_MAX reads)
-    k_tile_scan<T><<<nb, SCAN_THREADS, 0, st>>>(in, out, n, part, 1, total, nb, htotal);
+    k_tile_scan<T><<<nb, SCAN_THREADS, 0, st>>>(in, out, n, part, 1, total, nb);
     DC_LAUNCH_CHECK();
     return;
   }
   // exclusive scan of the block partials in place (recursion on the tail)
-  scan_excl_impl<T>(part, part, nb, nullptr, st, tmp + nb, tmp_elems - size_t(nb), nullptr);
-  k_tile_scan<T><<<nb, SCAN_THREADS, 0, st>>>(in, out, n, part, 0, total, nb, htotal);
+  scan_excl_impl<T>(part, part, nb, nullptr, st, tmp + nb, tmp_elems - size_t(nb));
+  k_tile_scan<T><<<nb, SCAN_THREADS, 0, st>>>(in, out, n, part, 0, total, nb);
   DC_LAUNCH_CHECK();
 }
 
 template <class T>
-void scan_excl(const T* in, T* out, int64_t n, T* total, hipStream_t st, T* htotal) {
+void scan_excl(const T* in, T* out, int64_t n, T* total, hipStream_t st) {
   // partial sums need ~ n/2048 + n/2048^2 + ... elements
   size_t need = size_t(ceil_div(n, SCAN_TILE)) + 64;
   need += need / SCAN_TILE + 64;
   DBuf& b = prim_scratch().scan_tmp;
   b.ensure(need * sizeof(T));
-  scan_excl_impl<T>(in, out, n, total, st, b.as<T>(), b.bytes / sizeof(T), htotal);
+  scan_excl_impl<T>(in, out, n, total, st, b.as<T>(), b.bytes / sizeof(T));
 }
 
 // ---------------------------------------------------------------------------
@@ -642,8 +638,8 @@ inline int grid_for(int64_t n, int threads = 256) {
 }  // namespace
 
 void scan_excl_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* total,
-                   hipStream_t st, int32_t* host_total) {
-  scan_excl<int32_t>(in, out, n, total, st, host_total);
+                   hipStream_t st) {
+  scan_excl<int32_t>(in, out, n, total, st);
 }
 
 void scan_tiles_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* part, int32_t* total,
@@ -652,13 +648,13 @@ void scan_tiles_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* part, i
   const int64_t nb = ceil_div(n, SCAN_TILE);
   const int raw = nb <= SCAN_RAW_MAX;
   if (!raw) scan_excl_i32(part, part, nb, nullptr, st);
-  k_tile_scan<int32_t><<<nb, SCAN_THREADS, 0, st>>>(in, out, n, part, raw, total, nb, nullptr);
+  k_tile_scan<int32_t><<<nb, SCAN_THREADS, 0, st>>>(in, out, n, part, raw, total, nb);
   DC_LAUNCH_CHECK();
 }
 
 void scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* total,
-                   hipStream_t st, int64_t* host_total) {
-  scan_excl<int64_t>(in, out, n, total, st, host_total);
+                   hipStream_t st) {
+  scan_excl<int64_t>(in, out, n, total, st);
 }
 
 void radix_sort_pairs(uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1,
