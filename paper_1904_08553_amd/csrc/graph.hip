@@ -392,6 +392,15 @@ __device__ __forceinline__ int32_t wave_lower_bound(const uint64_t* __restrict__
 constexpr int RC_TPB = 1024;
 constexpr int RC_BLOCKS = 256;
 constexpr int RC_ROWS = SCAN_TILE / RC_TPB;  // rows of a thread
+// LONG (slices of more than two rounds on average, where there are fewer tiles
+// than blocks: a large batch of a dense graph of few rows): RC_LONG rounds' loads in flight together,
+// and where a wave holds at most RC_RUNS rows their lanes counted by ballots,
+// since their atomics would queue at few words: 400K changes of 2,000 rows 311
+// us, without 496.  The others keep the short form, which this code beside it
+// slows down by its registers (8,000 changes of 20K rows 13.7 us, with it 15).
+constexpr int RC_LONG = 4;
+constexpr int RC_RUNS = 8;
+template <bool LONG>
 __global__ void __launch_bounds__(RC_TPB)
     k_row_changes(const uint64_t* __restrict__ ch_key, const int32_t* __restrict__ ch_op,
                   const int32_t* __restrict__ ch_dk, const int32_t* __restrict__ ins_pos,
@@ -402,7 +411,7 @@ __global__ void __launch_bounds__(RC_TPB)
   __shared__ int32_t s_del[SCAN_TILE];
   __shared__ unsigned long long l64[RC_TPB / WAVE];
   __shared__ int32_t s_lo, s_hi, s_ub, s_cb;
-  const int t = threadIdx.x, wid = t / WAVE;
+  const int t = threadIdx.x, wid = t / WAVE, lane = lane_id();
   agg_init(agg);
   const int32_t nnz = off[n];
   const int64_t ntiles = ceil_div(n, SCAN_TILE);
@@ -433,7 +442,61 @@ __global__ void __launch_bounds__(RC_TPB)
     }
     __syncthreads();
     const int32_t lo = s_lo, hi = s_hi;
-    for (int32_t q0 = lo; q0 < hi; q0 += RC_TPB) {  // block-uniform
+    int32_t q0 = lo;  // block-uniform
+    if constexpr (LONG) {
+      for (; hi - q0 > 2 * RC_TPB; q0 += RC_LONG * RC_TPB) {
+        uint64_t key[RC_LONG];
+        int32_t op[RC_LONG], dk[RC_LONG];
+  #pragma unroll
+        for (int j = 0; j < RC_LONG; ++j) {
+          const int32_t q = q0 + j * RC_TPB + t, qc = q < hi ? q : hi - 1;
+          key[j] = ch_key[qc];
+          op[j] = q < hi ? ch_op[qc] : 0;  // 0: no change here
+          dk[j] = q < hi ? ch_dk[qc] : 0;
+        }
+        if (o.uflag) {
+          int32_t cd[RC_LONG], cs[RC_LONG];
+  #pragma unroll
+          for (int j = 0; j < RC_LONG; ++j) {
+            const bool gone = op[j] == OP_DELETE || op[j] == OP_REPLACE;
+            cd[j] = gone ? C[int32_t(key_col(key[j], kb))] : -1;
+            cs[j] = gone ? C[int32_t(key_row(key[j], kb))] : -2;
+          }
+  #pragma unroll
+          for (int j = 0; j < RC_LONG; ++j) op[j] |= cd[j] == cs[j] ? 8 : 0;  // inside one community
+        }
+  #pragma unroll
+        for (int j = 0; j < RC_LONG; ++j) {
+          const int32_t x = int32_t(int64_t(key_row(key[j], kb)) - r0), p = op[j] & 7;
+          const int32_t before = __shfl_up(x, 1, WAVE);
+          const uint64_t heads = __ballot(lane == 0 || x != before);  // of the wave's rows
+          if (__popcll(heads) <= RC_RUNS) {
+            const uint64_t b_in = __ballot(p != 0), b_new = __ballot(p == OP_NEW);
+            const uint64_t b_gone = __ballot(p == OP_DELETE), b_del = __ballot(op[j] >= 8);
+            for (uint64_t h = heads; h; h &= h - 1) {
+              const int l = __ffsll((unsigned long long)h) - 1;
+              const uint64_t next = h & (h - 1);  // the row's lanes end before its lowest bit
+              const uint64_t m = ((next & -next) - 1) & ~((uint64_t(1) << l) - 1);
+              const int32_t d = wave_sum(m >> lane & 1 ? dk[j] : 0);
+              if (lane == l) {
+                atomicAdd(&s_cnt[x], int32_t(__popcll(b_in & m)));
+                atomicAdd(&s_ins[x], int32_t(__popcll(b_in & m & ~b_gone)));
+                atomicAdd(&s_net[x], int32_t(__popcll(b_new & m)) - int32_t(__popcll(b_gone & m)));
+                atomicAdd(&s_dk[x], d);
+                if (b_del & m) s_del[x] = 1;
+              }
+            }
+          } else if (p) {
+            atomicAdd(&s_cnt[x], 1);
+            if (p != OP_DELETE) atomicAdd(&s_ins[x], 1);
+            if (p == OP_NEW || p == OP_DELETE) atomicAdd(&s_net[x], p == OP_NEW ? 1 : -1);
+            if (dk[j]) atomicAdd(&s_dk[x], dk[j]);
+            if (op[j] >= 8) s_del[x] = 1;
+          }
+        }
+      }
+    }
+    for (; q0 < hi; q0 += RC_TPB) {
       const int32_t q = q0 + t;
       const bool in = q < hi;
       const int32_t qc = in ? q : hi - 1;
@@ -874,8 +937,14 @@ void row_changes(const uint64_t* ch_key, const int32_t* ch_op, const int32_t* ch
                  const int32_t* C, int32_t n, const RowOut& o, hipStream_t st) {
   if (n <= 0) return;
   const int64_t tiles = ceil_div(n, SCAN_TILE);
-  k_row_changes<<<int(tiles < RC_BLOCKS ? tiles : RC_BLOCKS), RC_TPB, 0, st>>>(
-      ch_key, ch_op, ch_dk, ins_pos, int32_t(nch), int32_t(n_ins), key_bits(n), off, C, n, o);
+  auto launch = [&](auto kernel) {
+    kernel<<<int(tiles < RC_BLOCKS ? tiles : RC_BLOCKS), RC_TPB, 0, st>>>(
+        ch_key, ch_op, ch_dk, ins_pos, int32_t(nch), int32_t(n_ins), key_bits(n), off, C, n, o);
+  };
+  if (tiles < RC_BLOCKS && nch > 2 * RC_TPB * tiles)
+    launch(k_row_changes<true>);
+  else
+    launch(k_row_changes<false>);
   DC_LAUNCH_CHECK();
 }
 

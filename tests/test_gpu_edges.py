@@ -231,3 +231,34 @@ def test_movers_at_block_rounds(n):
     add_v = ((add_u + 1 + rng.integers(0, n - 1, 500)) % n).astype(np.int32)
     step_pair(o, g, W.Batch(add_u, add_v, np.full(500, 9, np.int32), u[:200], v[:200]))
     compare(o, g, "step")
+
+
+@pytest.mark.parametrize("n,edges,changes", [(100, 3_000, 1_500), (700, 60_000, 30_000),
+                                             (2_048, 30_000, 2_100), (4_097, 60_000, 20_000)])
+def test_long_change_slices(n, edges, changes):
+    """Batches with more than two rounds of changes a tile of rows: hundreds of
+    changes a row and a few, a last tile of one row; insertions, additions to
+    pairs that are there, replacements and deletions, in both screening forms."""
+    print(f"case: {changes} changes of {n} vertices", flush=True)
+    rng = np.random.default_rng(n)
+    key = rng.choice(n * (n - 1) // 2, edges, replace=False)
+    hi = ((1 + np.sqrt(1 + 8 * key.astype(np.float64))) / 2).astype(np.int64)
+    hi -= key < hi * (hi - 1) // 2
+    hi += key >= hi * (hi + 1) // 2
+    u, v = (key - hi * (hi - 1) // 2).astype(np.int32), hi.astype(np.int32)
+    w = rng.integers(1, 5, edges).astype(np.int32)
+    kept = edges - changes // 2  # the rest come in as new pairs
+    for mode in ("delta", "all"):
+        o, g = make_pair(n, u[:kept], v[:kept], w[:kept], mode=mode)
+        gone = rng.choice(kept, changes // 2, replace=False)
+        again = gone[: changes // 4]  # replaced, and others added to
+        more = rng.choice(kept, changes // 4, replace=False)
+        more = np.setdiff1d(more, gone)
+        add = np.concatenate([np.arange(kept, edges), again, more])
+        rng.shuffle(add)
+        first = W.Batch(u[add], v[add], w[add], u[gone], v[gone])
+        back = gone[changes // 4:]
+        second = W.Batch(u[back], v[back], w[back], u[kept:], v[kept:])
+        for t, b in enumerate((first, second)):
+            step_pair(o, g, b)
+            compare(o, g, f"n={n} {mode} step {t}")
