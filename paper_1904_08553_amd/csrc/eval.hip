@@ -7,20 +7,17 @@
 //     score(X) = 2m * e_{i->X} - k_i * a_X^{(-i)}
 // (the gain of Sec. 3.1 scaled by (2m)^2/2; a^{(-i)} takes i out of c).
 //
-// Grouping equal labels is the hot operation.  Most neighbours of a vertex
-// share one or a few communities, so a hash insert per entry would pile
-// atomics onto the same slot.  Instead a wave loads 64 entries, picks the
-// label of the first unprocessed lane, finds all lanes holding it with one
-// ballot and parks the label in the lane numbered by the iteration: one
-// register-only iteration per distinct label.  Each lane then adds its
-// weight into a per-wave LDS slot of its label's rank.  The community totals are then gathered (or the table
-// inserts issued) by all pair-holding lanes at once, so no chain of
-// dependent memory accesses remains.  Rows of up to 64 entries finish this
-// way (bin S, one wave per vertex).  Longer rows collect per 64-entry chunk
-// and add the chunk's pairs to a hash table: wave-private LDS for rows up
-// to 512 entries (bin W), a block-shared LDS table up to 4096 (bin B),
-// global memory beyond (bin G).  A sweep writes only the next label;
-// movers are collected afterwards.
+// Grouping equal labels is the hot operation.  Rows of at most 64 entries are
+// grouped in registers, a row to a group of 8, 16, 32 or 64 lanes (bins 8 to
+// 64): up to 32 lanes every lane compares its label with all the others', 64
+// lanes take one distinct label a turn.  Longer rows go entry by entry into a
+// hash table of the foreign labels (the own community, usually most of the
+// row, is summed in registers): an LDS table per wave for rows up to 512
+// entries (bin W), one per block up to 4096 (bin B) and beyond (bin G), with
+// a larger table for the rows that overflow it.  Small levels above 0 have a
+// table slot per label instead.  The community totals of a row's labels are
+// gathered together, so no chain of dependent memory accesses remains.  A
+// sweep writes only the next label; movers are collected afterwards.
 #include "dc_louvain.h"
 #include "dc_scan.h"
 

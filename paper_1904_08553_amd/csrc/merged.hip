@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(TPB)
 }
 
 // Change of the intra-community weight over the movers' rows, one wave per
-// mover (k_delta_intra).
+// mover and an entry a lane (k_delta_terms' first blocks take four).
 __global__ void __launch_bounds__(TPB)
     k_mg_intra(const MergedGraph* __restrict__ G, const int32_t* __restrict__ state) {
   const int j = blockIdx.y;
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(TPB)
   block_add(s, &g.stat[ST_DI]);
 }
 
-// Change of sum a^2 over the touched labels (k_delta_squares).
+// Change of sum a^2 over the touched labels (k_delta_terms' other blocks).
 __global__ void __launch_bounds__(TPB)
     k_mg_squares(const MergedGraph* __restrict__ G, const int32_t* __restrict__ state) {
   const int j = blockIdx.y;

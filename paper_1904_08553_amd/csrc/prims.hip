@@ -1,6 +1,7 @@
-// prims.hip -- scan, stable LSD radix sort, fills.  Hand-written for gfx950:
-// 256-thread blocks of four 64-wide waves, wave prefix sums by shuffles,
-// radix ranking by one 64-bit ballot per digit bit, running digit counts per wave.
+// prims.hip -- scan, stable LSD radix sort, fills, and the host's wait for a
+// kernel's publication.  Hand-written for gfx950: scans in blocks of 256
+// threads, wave prefix sums by shuffles; the sort in blocks of 1,024, ranking by
+// one 64-bit ballot per digit bit, running digit counts per wave.
 #include <chrono>
 #include <cstdlib>
 #include <thread>

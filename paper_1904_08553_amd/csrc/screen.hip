@@ -82,8 +82,10 @@ __global__ void k_mark_neighbourhoods(const int32_t* __restrict__ list,
 // R[v] |= cflag[C[v]] (cflag may be null), and the vertices of R appended
 // to list: a block takes ROUNDS tiles of RL_TPB vertices and reserves its
 // places with one atomic on *count (ascending within the block, blocks in any
-// order).  The reservations queue at the counter (about 25 ns each): blocks
-// of 2,048 vertices took 11.7 us for 1M and 55 for 8M, these 6.9 and 25.
+// order).  The reservations queue at the counter (about 25 ns each) and a small
+// grid leaves CUs idle: one round up to 256K vertices, two up to 512K, eight
+// beyond.  530K / 1.06M / 2.1M / 4.3M vertices take 5.6 / 7.6 / 10.8 / 17.6 us,
+// in blocks of 2,048 vertices 8.8 / 13.7 / 19.2 / 33.6.
 constexpr int RL_TPB = 1024;
 constexpr int RL_NW = RL_TPB / WAVE;
 template <int RL_ROUNDS>

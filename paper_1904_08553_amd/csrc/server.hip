@@ -70,14 +70,17 @@ void copy_edges(const dc_edges* e, bool weights, std::vector<int32_t>& u,
   if (weights) DC_HIP(hipMemcpy(w.data(), e->w, m * 4, kind));
 }
 
-// Upper estimate of a context's device bytes (grow-only buffers, 25%
-// headroom each) after a call that leaves `edges` undirected edges and sorted
-// a batch of `changes` changes: per-vertex state, bins and labels (about 150
-// B per vertex), the CSR double buffer and the coarsening and screening
-// scratch sized by the entries (about 170 B per edge), the batch's records
-// (about 240 B per change).  dc_init's own sort buffers are released before
-// it returns.  Admission reserves these; after each round the reservations
-// are replaced by the measured footprints.
+// Estimate of a context's device bytes (grow-only buffers, 25% headroom each)
+// after a call that leaves `edges` undirected edges and sorted a batch of
+// `changes` changes: per-vertex state, bins and labels (about 150 B per
+// vertex), the CSR double buffer and the coarsening and screening scratch
+// sized by the entries (about 170 B per edge), the batch's records (about 240 B
+// per change).  It takes steps whose movers hold a small part of the entries:
+// the restricted compaction keeps 56 B for each of the four slots of an entry
+// in a mover's row, 45 B per edge when a tenth of the entries move, and a step
+// that moves more takes more than this.  dc_init's own sort buffers are released
+// before it returns.  Admission reserves these; after each round the
+// reservations are replaced by the measured footprints.
 int64_t est_step_bytes(int64_t n, int64_t edges, int64_t changes) {
   return 160 * n + 192 * edges + 256 * changes + (int64_t(1) << 18);
 }
