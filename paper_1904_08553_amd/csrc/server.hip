@@ -223,6 +223,7 @@ void dc_server::run() {
     std::vector<Request*> swept;
     cs.reserve(run_now.size());
     Ls.reserve(run_now.size());
+    swept.reserve(run_now.size());  // the three grow together, or not at all
     for (Request* r : run_now) {
       Graph& g = *all[size_t(r->gid)];
       if (r->init) {
